@@ -314,12 +314,12 @@ __device__ __forceinline__ void gemv_epilogue(const GemvArgs &a, int unit, float
     }
 }
 
-// ------------------------------------------------------------------ single-query attention
+// ------------------------------------------------------------------ attention item (persistent kernel)
 // One work item = (key/value head g, context chunk s) handled by a block of NT threads.  The
 // query heads [hq0, hq1) of those sharing head g are served from the chunk, one after another.  Chunks are merged by whichever block
 // finishes last for a head, walking the partial results in chunk order (deterministic).
 // LDS: sc[a.chunk], red[NT/64], dyn[NT * VEC] floats, one int.
-// COH: outputs are written through; partial results of other chunks are re-read coherently.
+// Outputs are written through; partial results of other chunks are re-read coherently.
 // Sum over groups of LPP consecutive lanes (LPP a power of two), complete in the LAST lane of
 // each group: lane-crossing moves of the vector unit instead of LDS permutes.
 __device__ __forceinline__ float group_sum_last(float v, int lpp) {
@@ -368,18 +368,18 @@ __device__ __forceinline__ void group_sums_last(float (&v)[N], int lpp) {
 // coherently until no word reads ACT_UNSET; bounded, the error word is raised past the limit)
 // -- after the cached rows of the earlier positions have been requested, so that the wait and
 // that fetch overlap.  The newest position is handled by the first lanes of wave 0.
-// ROWS: cached rows a lane keeps in flight per batch of loads (0: 10); every row of a batch costs
+// ROWS: cached rows a lane keeps in flight per batch of loads; every row of a batch costs
 // its arithmetic whether the chunk reaches it or not.
-template <typename KT, int NT, bool COH = false, int ROWS = 0>
+template <typename KT, int NT, int ROWS>
 __device__ __forceinline__ void attn_item(const AttnArgs &a, int g, int s, int n_ctx, float *sc, float *red,
-                                          float *dyn, int *s_last, int hq0 = 0, int hq1 = INT_MAX, int *err = nullptr) {
+                                          float *dyn, int *s_last, int hq0, int hq1, int *err) {
     constexpr int VEC = Store<KT>::VEC;
     constexpr int NWAVE = NT / WAVE;
     int tid = threadIdx.x;
-    // (the persistent kernel calls this once per layer: without this the compiler computes every
+    // (called once per layer: without this the compiler computes every
     // thread-dependent address below once, before the layer loop, and keeps some thirty vector
     // registers occupied through all the other phases)
-    if (COH) asm volatile("" : "+v"(tid));
+    asm volatile("" : "+v"(tid));
     const int lane = tid & (WAVE - 1), wid = tid / WAVE;
     const int dh = a.d_head;
     const int LPP = dh / VEC;             // lanes per cached position
@@ -388,7 +388,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, int g, int s, int n
     const int sub = lane / LPP, li = lane % LPP;
     const int t0 = s * a.chunk;
     const int t1 = min(n_ctx, t0 + a.chunk);
-    const bool awaited = COH && a.k_new != nullptr;              // q (and the newest k, v) are awaited as data
+    const bool awaited = a.k_new != nullptr;              // q (and the newest k, v) are awaited as data
     const bool has_new = awaited && t1 == n_ctx && t1 > t0;      // this chunk ends with the newest position
     const int t1c = has_new ? t1 - 1 : t1;                       // cached rows: [t0, t1c)
     const bool new_lanes = has_new && wid == 0 && sub == 0;      // the lanes that handle the newest position
@@ -402,7 +402,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, int g, int s, int n
     // 160 positions, which is what contexts up to 1280 give on 256 blocks and 32 heads; 12 spills
     // registers in the persistent kernel), and the first batch of value
     // rows together with the keys: this phase is a chain of memory latencies, not bandwidth.
-    constexpr int ATTN_BATCH = ROWS ? ROWS : 10;
+    constexpr int ATTN_BATCH = ROWS;
     const int tbase = t0 + wid * PPW + sub;
     // query heads [hq0, hq1) of the group that shares key/value head g
     for (int hq = hq0; hq < min(hq1, group); ++hq) {
@@ -585,15 +585,14 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, int g, int s, int n
         }
         if (n_splits == 1) {
             if (tid < dh) {
-                act_store<COH>(a.out + (size_t)h * dh + tid, o / l);
-                if (COH && a.out_twin) twin_unset(a.out + (size_t)h * dh + tid, a.out_twin);
+                act_store<true>(a.out + (size_t)h * dh + tid, o / l);
+                if (a.out_twin) twin_unset(a.out + (size_t)h * dh + tid, a.out_twin);
             }
         } else {
             float *pp = a.part + ((size_t)h * a.max_splits + s) * (dh + 2);
-            if (tid < dh) act_store<COH>(pp + 2 + tid, o);
-            if (tid == 0) { act_store<COH>(pp, m); act_store<COH>(pp + 1, l); }
-            if (COH) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // write-through stores acknowledged
-            else __threadfence();
+            if (tid < dh) act_store<true>(pp + 2 + tid, o);
+            if (tid == 0) { act_store<true>(pp, m); act_store<true>(pp + 1, l); }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // write-through stores acknowledged
             __syncthreads();
             if (tid == 0) {
                 const int old = __hip_atomic_fetch_add(as_global(a.counters) + (size_t)h * ATTN_COUNTER_STRIDE, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -601,7 +600,6 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, int g, int s, int n
             }
             __syncthreads();
             if (*s_last) {
-                if (!COH) __threadfence();
                 const float *ph = a.part + (size_t)h * a.max_splits * (dh + 2);
                 float L = 0.f, O = 0.f;
                 if (n_splits <= min(a.chunk, NT)) {
@@ -642,8 +640,8 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, int g, int s, int n
                     }
                 }
                 if (tid < dh) {
-                    act_store<COH>(a.out + (size_t)h * dh + tid, O / L);
-                    if (COH && a.out_twin) twin_unset(a.out + (size_t)h * dh + tid, a.out_twin);
+                    act_store<true>(a.out + (size_t)h * dh + tid, O / L);
+                    if (a.out_twin) twin_unset(a.out + (size_t)h * dh + tid, a.out_twin);
                 }
                 // (written through: the next user of this counter may sit behind another L2)
                 if (tid == 0) __hip_atomic_store(as_global(a.counters) + (size_t)h * ATTN_COUNTER_STRIDE, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

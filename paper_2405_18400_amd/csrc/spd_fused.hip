@@ -787,16 +787,16 @@ __global__ __launch_bounds__(NT) void fused_forward_kernel(const FusedArgs a) {
                 constexpr int R4 = TIGHT ? 8 : 10, R8_ONE = TIGHT ? 6 : FUSED_HALF_ROWS_ONE, R8_CUT = TIGHT ? 5 : FUSED_HALF_ROWS_CUT;
                 if constexpr (sizeof(KT) == 2) {
                     if (n_ctx <= 16 * R4)   // one batch of 8-byte pieces
-                        attn_item<half4_t, NT, true, R4>(t, h / group, item % n_splits, n_ctx, sh.sc, sh.red, dyn, &sh.s_last,
+                        attn_item<half4_t, NT, R4>(t, h / group, item % n_splits, n_ctx, sh.sc, sh.red, dyn, &sh.s_last,
                                                          h % group, h % group + 1, err);
                     else if (n_splits == 1)
-                        attn_item<half_t, NT, true, R8_ONE>(t, h / group, item % n_splits, n_ctx, sh.sc, sh.red, dyn, &sh.s_last,
+                        attn_item<half_t, NT, R8_ONE>(t, h / group, item % n_splits, n_ctx, sh.sc, sh.red, dyn, &sh.s_last,
                                                             h % group, h % group + 1, err);
                     else
-                        attn_item<half_t, NT, true, R8_CUT>(t, h / group, item % n_splits, n_ctx, sh.sc, sh.red, dyn, &sh.s_last,
+                        attn_item<half_t, NT, R8_CUT>(t, h / group, item % n_splits, n_ctx, sh.sc, sh.red, dyn, &sh.s_last,
                                                             h % group, h % group + 1, err);
                 } else {
-                    attn_item<KT, NT, true, R4>(t, h / group, item % n_splits, n_ctx, sh.sc, sh.red, dyn, &sh.s_last,
+                    attn_item<KT, NT, R4>(t, h / group, item % n_splits, n_ctx, sh.sc, sh.red, dyn, &sh.s_last,
                                                 h % group, h % group + 1, err);
                 }
             }

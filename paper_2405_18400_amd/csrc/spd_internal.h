@@ -236,7 +236,7 @@ constexpr int FUSED_MAX_BLOCKS = 1024;                      // largest grid of t
 constexpr int SYNC_LAUNCH_WORD = 0;                         // launches of the fused kernel since the last reset (its parity picks the arena)
 constexpr int SYNC_WORDS = 64;
 constexpr int TOPK_PART_MAX = 128;
-constexpr int ATTN_CHUNK = 128;        // cached positions per attention item (one kernel per operator; short contexts)
+constexpr int ATTN_CHUNK = 128;        // stand-alone attention: its scratch has room for chunks of this many positions
 constexpr int ATTN_CHUNK_MIN = 64;    // the fused kernel picks the chunk per step within these bounds
 constexpr int ATTN_CHUNK_MAX = 512;
 

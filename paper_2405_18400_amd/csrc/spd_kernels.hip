@@ -133,18 +133,6 @@ __global__ __launch_bounds__(BLOCK) void gemv_kernel(const GemvArgs a) {
     }
 }
 
-// ------------------------------------------------------------------ single-query attention
-template <typename KT>
-__global__ __launch_bounds__(BLOCK) void attn_kernel(const AttnArgs a) {
-    __shared__ float sc[ATTN_CHUNK];
-    __shared__ float red[NWAVE];
-    __shared__ int s_last;
-    extern __shared__ __align__(16) float dyn[];   // [BLOCK / LPP][dh] partial outputs
-    const int n_ctx = a.st ? a.st->pos + 1 : a.n_ctx;
-    if ((int)blockIdx.y * a.chunk >= n_ctx) return;
-    attn_item<KT, BLOCK>(a, blockIdx.x, blockIdx.y, n_ctx, sc, red, dyn, &s_last);
-}
-
 // ------------------------------------------------------------------ superposed embedding
 // Section 3.1: gamma_i = p_i / sum_j p_j (from log p_i), x~ = sum_i gamma_i z_i.
 // mode 0 feeds a prefix token's own embedding (gamma = 1) during the prefix pass.
@@ -490,17 +478,6 @@ hipError_t gemv(hipStream_t s, int dtype, int epi, const GemvArgs &a, int num_cu
     const size_t lds = gemv_lds_bytes(dtype, a.cols);
     if (dtype == SPD_DTYPE_BF16) return gemv_dispatch<bf16_t>(s, epi, a, blocks, lds);
     return gemv_dispatch<float>(s, epi, a, blocks, lds);
-}
-
-hipError_t attention(hipStream_t s, int dtype, const AttnArgs &a) {
-    const dim3 grid(a.n_kv_heads, (a.cap_ctx + a.chunk - 1) / a.chunk);
-    const int vec = dtype == SPD_DTYPE_FP32 ? 4 : 8;
-    const int lpp = a.d_head / vec;
-    const size_t lds = (size_t)(BLOCK / lpp) * a.d_head * sizeof(float);
-    if (dtype == SPD_DTYPE_BF16) hipLaunchKernelGGL(attn_kernel<bf16_t>, grid, dim3(BLOCK), lds, s, a);
-    else if (dtype == SPD_DTYPE_FP16) hipLaunchKernelGGL(attn_kernel<half_t>, grid, dim3(BLOCK), lds, s, a);
-    else hipLaunchKernelGGL(attn_kernel<float>, grid, dim3(BLOCK), lds, s, a);
-    return hipGetLastError();
 }
 
 hipError_t superpose(hipStream_t s, int dtype, const SuperposeArgs &a) {

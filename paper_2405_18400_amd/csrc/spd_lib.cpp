@@ -254,8 +254,8 @@ hipError_t enqueue_forward(spd_ctx *c, int mode, int k, bool head) {
         g.kv_half = m.kv_dtype == SPD_DTYPE_FP16;
         e = launch(c, KC_QKV, [&] { return spdk::gemv(c->stream, m.dtype, EPI_QKV, g, c->num_cu); });
         if (e != hipSuccess) return e;
-        AttnArgs a{q, c->kcache(l), c->vcache(l), att, c->at<float>(c->L.part), c->at<int32_t>(c->L.counters),
-                   c->st(), 0, m.n_heads, m.n_kv_heads, dh, m.max_ctx, ATTN_CHUNK, c->L.max_splits};
+        AttnArgs a{q, c->kcache(l), c->vcache(l), att, c->at<float>(c->L.part), nullptr,
+                   c->st(), 0, m.n_heads, m.n_kv_heads, dh, m.max_ctx, 0, c->L.max_splits};
         e = launch(c, KC_ATTN, [&] { return spdk::attention(c->stream, m.kv_dtype, a); });
         if (e != hipSuccess) return e;
         GemvArgs o{};
@@ -376,14 +376,12 @@ int attention_args_status(int dtype, const float *q, const void *K, const void *
     return SPD_OK;
 }
 
-// `scratch`: DEVICE, 256-byte aligned, spd_op_attention_scratch_bytes() bytes: the heads'
-// arrival counters (cleared here, by a fill kernel) followed by the chunks' partial results.
+// `scratch`: DEVICE, 256-byte aligned, spd_op_attention_scratch_bytes() bytes: one line per head
+// (not used) followed by the chunks' partial results.
 int attention_on_scratch(hipStream_t s, int dtype, const float *q, const void *K, const void *V, float *out,
                          void *scratch, int n_heads, int n_kv_heads, int d_head, int n_ctx, int cap_ctx) {
-    int32_t *counters = (int32_t *)scratch;
     float *part = (float *)((char *)scratch + up((size_t)n_heads * ATTN_COUNTER_STRIDE * 4));
-    if (fill_i32(s, counters, 0, n_heads * ATTN_COUNTER_STRIDE) != hipSuccess) return SPD_EHIP;
-    AttnArgs a{q, K, V, out, part, counters, nullptr, n_ctx, n_heads, n_kv_heads, d_head, cap_ctx, ATTN_CHUNK,
+    AttnArgs a{q, K, V, out, part, nullptr, nullptr, n_ctx, n_heads, n_kv_heads, d_head, cap_ctx, 0,
                (cap_ctx + ATTN_CHUNK - 1) / ATTN_CHUNK};
     return attention(s, dtype, a) == hipSuccess ? SPD_OK : SPD_EHIP;
 }

@@ -1,14 +1,14 @@
 // spd_op_attention_static: the stand-alone single-query attention for callers that cannot
 // allocate device memory (code under HIP graph capture, tight serving loops, harnesses that
-// forbid hipMalloc).  Same kernels as spd_op_attention; the scratch they need (one arrival
-// counter line per head and the per-chunk partial results that the last block of a head
-// merges) lives in a file-scope device array instead of a caller-supplied buffer.
+// forbid hipMalloc).  Same kernels as spd_op_attention; the scratch they need (the per-chunk
+// partial results that a second kernel merges) lives in a file-scope device array instead of a
+// caller-supplied buffer.
 //
 // Every GPU the library runs on holds its own copy of that array, at its own address, until
 // the process ends.  The array's name is only a host-side handle: its device address is looked
-// up once per device with hipGetSymbolAddress and that pointer is what kernels and fills get.
+// up once per device with hipGetSymbolAddress and that pointer is what the kernels get.
 // All calls on one GPU share the array: calls that overlap on one GPU (different streams or
-// threads) race; calls on one stream are ordered and each clears the counters it needs.
+// threads) race; calls on one stream are ordered.
 #include "spd_internal.h"
 
 #include <mutex>

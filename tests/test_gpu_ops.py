@@ -86,3 +86,27 @@ def test_attention(dtype, dh, heads, kv, n_ctx, cap):
     out2 = torch.zeros(heads, dh, device="cuda")
     P().spd_op_attention(dtype, torch.from_numpy(q).cuda(), dev(Kst, dtype).view(kv, cap, dh), dev(Vst, dtype).view(kv, cap, dh), out2, n_ctx)
     assert torch.equal(out, out2)
+
+
+# Where the kernels change hands: the vector path (up to two query heads per key/value head, or a
+# head size the matrix-core path has no tile for) and the matrix-core path (tiles of 16 query heads,
+# turns of 128 positions), one chunk (128 KB of keys per head, 64 KB for larger groups) or several.
+# The rows behind the context hold NaN: nothing may read them into a result.
+@pytest.mark.parametrize("dtype,dh,heads,kv,n_ctx,cap", [
+    ("fp32", 128, 8, 8, 256, 260), ("fp32", 128, 8, 8, 257, 700), ("fp16", 128, 4, 4, 512, 520), ("fp16", 128, 4, 4, 513, 520),
+    ("bf16", 8, 6, 3, 77, 90), ("bf16", 256, 4, 2, 300, 400), ("fp32", 256, 3, 3, 1500, 1500), ("fp16", 64, 300, 300, 2100, 2100),
+    ("fp32", 128, 6, 2, 127, 130), ("fp32", 128, 6, 2, 128, 130), ("fp32", 128, 6, 2, 129, 400), ("fp16", 64, 34, 2, 16, 20),
+    ("fp16", 64, 34, 2, 1025, 1030), ("bf16", 256, 16, 4, 1, 3), ("bf16", 256, 16, 4, 2049, 2049), ("fp16", 128, 16, 1, 5000, 5000)])
+def test_attention_where_its_kernels_change_hands(dtype, dh, heads, kv, n_ctx, cap):
+    g = torch.Generator(device="cuda").manual_seed(n_ctx + heads)
+    tdt = {"fp32": torch.float32, "bf16": torch.bfloat16, "fp16": torch.float16}[dtype]
+    K, V = (torch.randn(kv, cap, dh, generator=g, device="cuda").to(tdt) for _ in range(2))
+    K[:, n_ctx:], V[:, n_ctx:] = float("nan"), float("nan")
+    q = torch.randn(heads, dh, generator=g, device="cuda")
+    out = torch.full((heads, dh), float("nan"), device="cuda")
+    print(f"attention {dtype} d_head={dh} heads={heads}/{kv} n_ctx={n_ctx} cap={cap}", flush=True)
+    P().spd_op_attention(dtype, q, K, V, out, n_ctx)
+    Kd, Vd = K[:, :n_ctx].double(), V[:, :n_ctx].double()
+    want = torch.stack([((Kd[h * kv // heads] @ q[h].double()) / dh ** 0.5).softmax(-1) @ Vd[h * kv // heads] for h in range(heads)])
+    # fp32 sums of at most 5000 terms: about sqrt(5000) 2^-24 = 4e-6 of the scale
+    assert_close_scaled(out.cpu().numpy(), want.cpu().numpy(), 1e-5, "attention")
