@@ -118,6 +118,14 @@ __device__ __forceinline__ u32x4 buffer_load16(__amdgpu_buffer_rsrc_t rsrc, uint
     return __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)lane_offset, 0, 0);
 }
 
+// 16 bytes per lane from memory straight into LDS: lane l's land at `to` + 16 l (`to` is wave-uniform).  The compiler
+// does not wait for these: the reader waits for vmcnt itself.  (The host pass knows no 16-byte form of the builtin.)
+template <int AUX = 0> __device__ __forceinline__ void load16_to_lds(__amdgpu_buffer_rsrc_t rsrc, char *to, uint32_t lane_offset, uint32_t offset) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void *)to, 16, (int)lane_offset, (int)offset, 0, AUX);
+#endif
+}
+
 typedef const char __attribute__((address_space(1))) *global_char_ptr;
 
 __device__ __forceinline__ u32x4 stream_load16(const void *p) {

@@ -10,10 +10,10 @@
 //
 // Operands need no transposition: with W row-major [rows, d] and activations [tokens, d], both
 // MFMA operands are "row index in the lane, 8 consecutive k in the register", i.e. plain
-// 16-byte pieces.  The k-index assignment inside a 64-wide k step is permuted (each half of the
-// wave owns 32 consecutive k) so that a lane's four weight loads of a step are 64 contiguous
-// bytes.
+// 16-byte pieces.
 #include "spd_device.h"
+
+#include <algorithm>
 
 using namespace spdd;
 
@@ -28,8 +28,6 @@ __device__ __forceinline__ void kv_put(void *cache, int kv_half, size_t at, floa
     else as_global((float *)cache)[at] = v;
 }
 
-constexpr int KSTEP = 64;         // k per pipeline step (4 MFMAs of k = 16)
-
 __device__ __forceinline__ uint16_t bf16_rn(float v) {
     uint32_t u = __float_as_uint(v);
     u += 0x7FFFu + ((u >> 16) & 1u);
@@ -43,66 +41,92 @@ __device__ __forceinline__ void split_store(uint16_t *hi, uint16_t *lo, size_t a
     as_global(lo)[at] = bf16_rn(x - bf16_f(h));
 }
 
-// Where element (token t, feature k) of a [T, K] activation operand lives.  Row-major for the
-// LDS-tiled GEMM; for the split-k GEMM of short chunks the operand is stored the way the matrix
-// cores take it, so that every load of a wave is 1 KB contiguous: 32-token tile, then 64-wide
-// k step, then the step's four 16-wide products j, then the lane (token t % 32 in lanes
-// 0..31 for the step's first 32 k, in lanes 32..63 for the other 32), then 8 consecutive k.
-__device__ __forceinline__ size_t act_at(bool tiled, int t, int k, int K) {
-    if (!tiled) return (size_t)t * K + k;
-    const int kk = k % KSTEP;
-    return ((((size_t)(t / 32) * (K / KSTEP) + k / KSTEP) * 4 + (kk % 32) / 8) * WAVE + (t % 32) + 32 * (kk / 32)) * 8 + k % 8;
+// Eight consecutive elements, one 16-byte store per half.
+__device__ __forceinline__ void split_store8(uint16_t *hi, uint16_t *lo, size_t at, const float (&y)[8]) {
+    uint32_t h[4], l[4];
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+        const uint16_t h0 = bf16_rn(y[e]), h1 = bf16_rn(y[e + 1]);
+        h[e / 2] = (uint32_t)h0 | ((uint32_t)h1 << 16);
+        l[e / 2] = (uint32_t)bf16_rn(y[e] - bf16_f(h0)) | ((uint32_t)bf16_rn(y[e + 1] - bf16_f(h1)) << 16);
+    }
+    *(u32x4 __attribute__((address_space(1))) *)(hi + at) = u32x4{h[0], h[1], h[2], h[3]};
+    *(u32x4 __attribute__((address_space(1))) *)(lo + at) = u32x4{l[0], l[1], l[2], l[3]};
 }
 
-// ------------------------------------------------------------------ token rows, norms, rotary table
-__global__ __launch_bounds__(256) void embed_rows_kernel(const uint16_t *embed, const int32_t *prefix, int p0, int T,
-                                                         int d, float *H) {
-    const int t = blockIdx.x;
-    const int tok = as_global(prefix)[p0 + t];
-    for (int c = threadIdx.x; c < d; c += 256) as_global(H)[(size_t)t * d + c] = bf16_f(as_global(embed)[(size_t)tok * d + c]);
-}
-
-// xn = x * rsqrt(mean x^2 + eps) * gain, written as the (hi, lo) pair.  One block per token; a
-// thread keeps its runs of 8 consecutive features in registers (one read of the row) and
-// writes each run as one 16-byte store per half (8 consecutive k are contiguous in both layouts).
+// ------------------------------------------------------------------ residual stream, norms, rotary table
+// The residual stream between two products, one block per token: h = embedding of the token (EMBED), or
+// h = residual + the partial sums of the product before it, added in split order; then
+// xn = h * rsqrt(mean h^2 + eps) * gain as the (hi, lo) pair.  A thread keeps its runs of 8 consecutive
+// features in registers (one read of the row) and writes each run as one 16-byte store per half.
 constexpr int NORM_RUNS = 4;      // runs per thread: d_model <= 256 * 8 * NORM_RUNS
 
-__global__ __launch_bounds__(256) void rmsnorm_split_kernel(const float *H, const uint16_t *gain, float eps, int d,
-                                                            uint16_t *hi, uint16_t *lo, bool tiled) {
+struct PrefillNormArgs {
+    const uint16_t *embed;       // EMBED: [vocab, d]
+    const int32_t *tokens;       // EMBED: token ids of the chunk
+    const float *resid, *part;   // [T, d]; [splits, T, d]
+    float *h;                    // [T, d]
+    const uint16_t *gain;        // null: only h is wanted
+    uint16_t *hi, *lo;           // [T, d]
+    int32_t T, d, splits, first_row;
+    float eps;
+};
+
+template <bool EMBED>
+__global__ __launch_bounds__(256) void prefill_norm_kernel(const PrefillNormArgs a) {
     __shared__ float red[256 / WAVE];
-    const int t = blockIdx.x;
-    const float *x = H + (size_t)t * d;
+    const int t = a.first_row + blockIdx.x, d = a.d;
+    const size_t row = (size_t)t * d;
+    const size_t from = EMBED ? (size_t)as_global(a.tokens)[t] * d : row;
     float v[NORM_RUNS][8];
     float ss = 0.f;
 #pragma unroll
     for (int i = 0; i < NORM_RUNS; ++i) {
         const int c = 8 * (threadIdx.x + 256 * i);
         if (c < d) {
-            const float4 a = global_load_float4(x + c), b = global_load_float4(x + c + 4);
-            v[i][0] = a.x; v[i][1] = a.y; v[i][2] = a.z; v[i][3] = a.w; v[i][4] = b.x; v[i][5] = b.y; v[i][6] = b.z; v[i][7] = b.w;
+            if (EMBED) {
+                const u32x4 g = global_load16(a.embed + from + c);
+                const uint32_t gw[4] = {g.x, g.y, g.z, g.w};
+#pragma unroll
+                for (int e = 0; e < 8; e += 2) { v[i][e] = __uint_as_float(gw[e / 2] << 16); v[i][e + 1] = __uint_as_float(gw[e / 2] & 0xFFFF0000u); }
+            } else {
+                auto take = [&](const float *x, float (&y)[8]) {
+                    const float4 p = global_load_float4(x), q = global_load_float4(x + 4);
+                    y[0] = p.x; y[1] = p.y; y[2] = p.z; y[3] = p.w; y[4] = q.x; y[5] = q.y; y[6] = q.z; y[7] = q.w;
+                };
+                take(a.resid + row + c, v[i]);
+                float sum[8], more[8];
+                take(a.part + row + c, sum);
+                for (int s = 1; s < a.splits; ++s) {
+                    take(a.part + (size_t)s * a.T * d + row + c, more);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) sum[e] += more[e];
+                }
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[i][e] += sum[e];
+            }
+            *(f32x4 __attribute__((address_space(1))) *)(a.h + row + c) = f32x4{v[i][0], v[i][1], v[i][2], v[i][3]};
+            *(f32x4 __attribute__((address_space(1))) *)(a.h + row + c + 4) = f32x4{v[i][4], v[i][5], v[i][6], v[i][7]};
 #pragma unroll
             for (int e = 0; e < 8; ++e) ss += v[i][e] * v[i][e];
         }
     }
+    if (a.gain == nullptr) return;
     const float tot = block_sum<256>(ss, red);
-    const float rs = 1.0f / sqrtf(tot / (float)d + eps);
+    const float rs = 1.0f / sqrtf(tot / (float)d + a.eps);
 #pragma unroll
     for (int i = 0; i < NORM_RUNS; ++i) {
         const int c = 8 * (threadIdx.x + 256 * i);
         if (c < d) {
-            const u32x4 g = global_load16(gain + c);
-            uint32_t h[4], l[4];
+            const u32x4 g = global_load16(a.gain + c);
+            float y[8];
 #pragma unroll
             for (int e = 0; e < 8; e += 2) {
                 const uint32_t gw = e < 2 ? g.x : e < 4 ? g.y : e < 6 ? g.z : g.w;
-                const float y0 = v[i][e] * rs * __uint_as_float(gw << 16), y1 = v[i][e + 1] * rs * __uint_as_float(gw & 0xFFFF0000u);
-                const uint16_t h0 = bf16_rn(y0), h1 = bf16_rn(y1);
-                h[e / 2] = (uint32_t)h0 | ((uint32_t)h1 << 16);
-                l[e / 2] = (uint32_t)bf16_rn(y0 - bf16_f(h0)) | ((uint32_t)bf16_rn(y1 - bf16_f(h1)) << 16);
+                y[e] = v[i][e] * rs * __uint_as_float(gw << 16);
+                y[e + 1] = v[i][e + 1] * rs * __uint_as_float(gw & 0xFFFF0000u);
             }
-            const size_t at = act_at(tiled, t, c, d);
-            *(u32x4 __attribute__((address_space(1))) *)(hi + at) = u32x4{h[0], h[1], h[2], h[3]};
-            *(u32x4 __attribute__((address_space(1))) *)(lo + at) = u32x4{l[0], l[1], l[2], l[3]};
+            split_store8(a.hi, a.lo, row + c, y);
         }
     }
 }
@@ -116,382 +140,219 @@ __global__ void rope_table_kernel(const double *inv_freq, int p0, int T, int hal
 }
 
 // ------------------------------------------------------------------ GEMM on the matrix cores
-enum { PE_RESID = 0, PE_QKV = 1, PE_SWIGLU = 2 };
+// PE_PART: partial sums over this block's share of k, to `part`; the consumer adds the splits.
+enum { PE_PART = 0, PE_QKV = 1, PE_SWIGLU = 2 };
 
 struct PrefillGemmArgs {
-    const uint16_t *xhi, *xlo;   // [T_pad, K] bf16 pair
-    const uint16_t *W, *W2;      // [N, K] bf16; W2: the "up" matrix (PE_SWIGLU)
+    const uint16_t *xhi, *xlo;   // [T, K] bf16 pair
+    const uint16_t *W, *W2;      // [N, K] bf16; W2: the "up" matrix (PE_SWIGLU), or columns N .. 2 N - 1 (PE_PART; N a multiple of the tile), or null
     int32_t T, N, K;
-    // PE_RESID
-    const float *resid;          // [T, N]
-    float *out;                  // [T, N]
+    int32_t t_tiles, n_tiles;    // token tiles; column tiles of W (and W2)
+    int32_t splits, split_steps; // blocks that share a tile's k range, and steps per block
+    float *part;                 // PE_PART: [splits, T, N (2 N with W2)]
     // PE_QKV
     float *q;                    // [T, n_q_rows]
     void *kcache, *vcache;       // [n_kv_heads, cap_ctx, d_head] fp32, or fp16 (kv_half)
     int32_t kv_half;
     const float2 *rope;          // [T, d_head / 2]
     int32_t n_q_rows, n_kv_rows, d_head, cap_ctx, p0;
-    // PE_SWIGLU
-    uint16_t *uhi, *ulo;         // [T_pad, N]
-    bool tiled;                  // layout of xhi / xlo and of uhi / ulo: see act_at
-    int32_t t_tiles, n_tiles;    // tiled kernel: token tiles and column tiles of the launch
-    float *ks_part;              // split-k kernel, k range halved between two blocks: their partial tiles
-    int32_t *ks_count;           //   and one arrival count per tile (zero between launches)
+    uint16_t *uhi, *ulo;         // PE_SWIGLU: [T, N]
 };
 
-// Block: one token tile (32 * TT tokens) and one column tile (32 * NWV columns);
-// wave w owns columns [32 w, 32 w + 32) of it, all TT token tiles.  Per k step of 64:
-//   * the activation tile (hi and lo, 32 TT rows x 64 k) is brought in ONCE per block through
-//     LDS (every wave needs all of it; fetched per wave it saturates the L2),
-//   * each wave fetches its 32 weight rows' 64 k coalesced (one load = 8 rows x 128 bytes) and turns
-//     them into the operand layout (row in the lane) through a wave-private LDS tile; fetched in
-//     that layout directly, every load touches 32 cache lines and the address path saturates,
-//   * 8 TT (x 2 for gate and up) matrix-core products per wave.
-// Both are double-buffered: the loads of step s + 1 are in flight during the products of
-// step s.  Token rows past T are computed and dropped.
-constexpr int A_ROW = KSTEP * 2 + 16;    // bytes per LDS row: 64 bf16 + 16 (rows 4 banks apart: conflict-free)
+// Token t's value v of row nc of the fused QKV product, `other` its rotary partner's (row nc ^ 1): rotated, to q or
+// the cache.
+__device__ __forceinline__ void qkv_put(const PrefillGemmArgs &a, int t, int nc, float v, float other) {
+    const bool rotates = nc < a.n_q_rows + a.n_kv_rows;
+    if (rotates) {
+        const size_t ri = 2 * ((size_t)t * (a.d_head / 2) + (nc % a.d_head) / 2);
+        const float cs_x = as_global((const float *)a.rope)[ri], cs_y = as_global((const float *)a.rope)[ri + 1];
+        v = (nc & 1) ? __fadd_rn(__fmul_rn(other, cs_y), __fmul_rn(v, cs_x)) : __fsub_rn(__fmul_rn(v, cs_x), __fmul_rn(other, cs_y));
+    }
+    if (nc < a.n_q_rows) {
+        as_global(a.q)[(size_t)t * a.n_q_rows + nc] = v;
+        return;
+    }
+    const int rr = rotates ? nc - a.n_q_rows : nc - a.n_q_rows - a.n_kv_rows;
+    kv_put(rotates ? a.kcache : a.vcache, a.kv_half, ((size_t)(rr / a.d_head) * a.cap_ctx + a.p0 + t) * a.d_head + rr % a.d_head, v);
+}
 
-template <int EPI, int TT, int NWV>
-__global__ __launch_bounds__(64 * NWV) void prefill_gemm_kernel(const PrefillGemmArgs a) {
-    constexpr int NMAT = EPI == PE_SWIGLU ? 2 : 1;
-    constexpr int NTH = 64 * NWV;
-    constexpr int ROWS = 32 * TT;
-    constexpr int PIECES = ROWS * 8;                       // 16-byte pieces of one (hi or lo) tile
-    constexpr int PER_THREAD = (PIECES + NTH - 1) / NTH;   // staged per thread, per half
-    extern __shared__ __align__(16) char a_lds[];          // [2 buffers][hi, lo][ROWS][A_ROW]
-    const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE;
-    // Workgroups go to the 8 XCDs round-robin and each XCD has its own L2: all token tiles of a
-    // column tile are placed on one XCD, so a weight tile is fetched into one L2 only (the
-    // activations, an order of magnitude smaller, are what every L2 holds).
-    const int xcd = blockIdx.x % 8, slot_in_xcd = blockIdx.x / 8;
-    const int tile_y = (slot_in_xcd / a.t_tiles) * 8 + xcd, tile_x = slot_in_xcd % a.t_tiles;
-    if (tile_y >= a.n_tiles) return;
-    const int t0 = tile_x * ROWS;
-    f32x16 acc[NMAT][TT];
+// A block of WM x WN waves makes a tile of BM = 32 TT WM tokens x BN = 32 NT WN columns; a wave's share is
+// TT x NT accumulators of 32 x 32.  Per step of KS k the tile's operands (x hi, x lo, W: rows of KS elements)
+// go from memory straight into LDS (no registers in between), ST steps deep: while step s is multiplied, steps
+// s + 1 .. s + ST - 1 are on their way, and one barrier per step says both "step s has arrived" and "the buffer
+// of step s - 1 may be overwritten".  A load instruction fills 1 KB of LDS in lane order, so the rows lie
+// unpadded; the 16-byte pieces of a row are permuted by the row number (`swz`: the lane picks which piece of
+// the row it fetches), which spreads any 8 and any 16 consecutive rows' reads of one piece over all banks.
+// What bounds it: with 128-token tiles the matrix cores at the clock they hold under such products; with few tokens
+// the weight stream (HBM) and each launch's ramp.  A kernel of 64-token tiles whose waves each turned their own 32 weight
+// rows round in LDS (160 bytes of LDS traffic per cycle wanted, 128 there) and, up to 96 tokens, one whose
+// waves split k, did it before; before -> after, us: 1024 tokens, 12288 x 4096: 290 -> 168 (200 with the rotary
+// epilogue); gate and up 2 x 11008 x 4096: 410 -> 335; 4096 x 11008: 248 -> 160; 256 tokens, 5120 x 13824: 214 -> 77;
+// 64 tokens, 12288 x 4096: 50 -> 24 (4.3 TB/s); gate and up: 73 -> 43; 4096 x 11008: 62 -> 25.  Weights go past
+// the L2's keep list (STREAM_W) where few token tiles read them: 5 % at 64 tokens; at 1024 it costs 2 %.
+template <int KS> __device__ __forceinline__ int swz(int row) {
+    static_assert(KS == 64, "rows of 128 bytes");
+    return (row & 7) ^ ((row >> 3) & 1);
+}
+
+template <int EPI, int WM, int WN, int TT, int NT, int KS, int ST, bool STREAM_W>
+__global__ __launch_bounds__(64 * WM * WN, WM * WN / 4) void prefill_gemm_kernel(const PrefillGemmArgs a) {
+    constexpr int NWV = WM * WN, BM = 32 * TT * WM, BN = 32 * NT * WN;
+    constexpr int ROWB = KS * 2, RPL = 1024 / ROWB;        // bytes per row; rows one load instruction of a wave brings
+    constexpr int ROWS = 2 * BM + BN;                      // rows of a stage: x hi, x lo, W
+    constexpr int PER = ROWS / (RPL * NWV);                // load instructions per wave and stage
+    constexpr int STAGE = ROWS * ROWB;
+    constexpr int NG = EPI == PE_SWIGLU ? NT / 2 : NT;     // column tiles of a wave per matrix (PE_SWIGLU: gate, then the same units of up)
+    static_assert(ROWS % (RPL * NWV) == 0 && BM % RPL == 0 && BN % (2 * RPL) == 0, "whole load instructions");
+    extern __shared__ __align__(16) char stages[];         // [ST][STAGE]
+    const int lane = threadIdx.x & (WAVE - 1), w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    // Workgroups go to the 8 XCDs round-robin and each XCD has its own L2: all token tiles of a column tile run on
+    // one XCD, one after the other, so that a weight tile enters one L2 only.
+    const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
+    const int n_mats = EPI == PE_PART && a.W2 != nullptr ? 2 : 1;
+    const int col = (slot / a.t_tiles) * 8 + xcd, tile_x = slot % a.t_tiles;
+    if (col >= a.n_tiles * n_mats * a.splits) return;
+    const int split = col / (a.n_tiles * n_mats), tile_y = col % (a.n_tiles * n_mats);
+    const bool second = EPI == PE_PART && tile_y >= a.n_tiles;
+    const int t0 = tile_x * BM;
+    const int n0 = (second ? tile_y - a.n_tiles : tile_y) * (EPI == PE_SWIGLU ? BN / 2 : BN);   // first row of the weight matrix
+    const int s0 = split * a.split_steps, n_steps = min(a.split_steps, a.K / KS - s0);
+
+    // This wave's loads of a stage: load i brings rows RPL (w + NWV i) ..; lane -> row l / (64 / RPL), piece l % (64 / RPL).
+    // A row past the end re-reads the last one (its products are dropped).
+    __amdgpu_buffer_rsrc_t rsrc[PER];
+    uint32_t off[PER];
 #pragma unroll
-    for (int mt = 0; mt < NMAT; ++mt)
+    for (int i = 0; i < PER; ++i) {
+        const int q = RPL * (w + NWV * i), r = lane / (WAVE / RPL);           // (q is uniform; a load lies within one operand)
+        const char *base;
+        int row, rows;
+        if (q < 2 * BM) {
+            base = (const char *)(q < BM ? a.xhi : a.xlo);
+            row = t0 + (q < BM ? q : q - BM) + r;
+            rows = a.T;
+        } else {
+            const int c = q - 2 * BM;
+            const bool up = EPI == PE_SWIGLU ? c >= BN / 2 : second;
+            base = (const char *)(up ? a.W2 : a.W);
+            row = n0 + (EPI == PE_SWIGLU && up ? c - BN / 2 : c) + r;
+            rows = a.N;
+        }
+        rsrc[i] = row_resource(base, (uint32_t)rows * (uint32_t)a.K * 2u);
+        off[i] = ((uint32_t)min(row, rows - 1) * (uint32_t)a.K + (uint32_t)s0 * KS) * 2u + 16u * (uint32_t)((lane % (WAVE / RPL)) ^ swz<KS>(q + r));
+    }
+    auto fetch = [&](int s) {
+        char *to = stages + (s % ST) * STAGE;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            if (STREAM_W && RPL * NWV * i >= 2 * BM) load16_to_lds<2>(rsrc[i], to + (w + NWV * i) * 1024, off[i], s * ROWB);
+            else load16_to_lds<0>(rsrc[i], to + (w + NWV * i) * 1024, off[i], s * ROWB);
+        }
+    };
+
+    const int wm = w / WN, wn = w % WN;
+    const int x_row = 32 * TT * wm + lane % 32;
+    auto w_row = [&](int nt) {
+        return 2 * BM + lane % 32 + (nt / NG) * (BN / 2) + 32 * (NG * wn + nt % NG);
+    };
+    f32x16 acc[NT][TT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[mt][tt][r] = 0.f;
-
-    // pieces on their way to LDS: two steps are in flight (one step's products are shorter than a
-    // trip to memory), in two register slots
-    u32x4 stage_hi[2][PER_THREAD], stage_lo[2][PER_THREAD], ws[2][NMAT][4];
-    // weights, fetch side: load i of a step takes rows 8 i + lane / 8 of the wave's 32, piece lane % 8.
-    // Addresses are a wave-uniform base (matrix + k offset, scalar registers) plus a 32-bit byte
-    // offset per lane, computed once.
-    uint32_t w_off[4], x_off[PER_THREAD];
+            for (int r = 0; r < 16; ++r) acc[nt][tt][r] = 0.f;
+    auto multiply = [&](int s) {
+        const char *from = stages + (s % ST) * STAGE;
+        auto piece = [&](int row, int j) { return __builtin_bit_cast(bf16x8, *(const u32x4 *)(from + row * ROWB + 16 * ((2 * j + lane / 32) ^ swz<KS>(row)))); };
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-        w_off[i] = ((uint32_t)min(tile_y * (32 * NWV) + 32 * w + 8 * i + lane / 8, a.N - 1) * (uint32_t)a.K + 8 * (lane % 8)) * 2u;   // (ragged last tile: re-reads the last row)
+        for (int j = 0; j < KS / 16; ++j) {
+            bf16x8 wv[NT], xh[TT], xl[TT];
 #pragma unroll
-    for (int i = 0; i < PER_THREAD; ++i) {
-        const int p = min(tid + NTH * i, PIECES - 1);
-        x_off[i] = ((uint32_t)(t0 + p / 8) * (uint32_t)a.K + 8 * (p % 8)) * 2u;
-    }
-    char *w_tile = a_lds + (size_t)2 * 2 * ROWS * A_ROW + (size_t)w * (NMAT * 32 * A_ROW);   // wave-private
-    const int w_put = (lane / 8) * A_ROW + (lane % 8) * 16;           // + (mt * 32 + 8 i) * A_ROW
-    const int w_get = (lane % 32) * A_ROW + (lane / 32) * 64;         // + mt * 32 * A_ROW + 16 j
-    auto lds_at = [&](int buf, int half, int row, int piece) -> char * {
-        return a_lds + (size_t)((buf * 2 + half) * ROWS + row) * A_ROW + piece * 16;
+            for (int nt = 0; nt < NT; ++nt) wv[nt] = piece(w_row(nt), j);
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt) { xh[tt] = piece(x_row + 32 * tt, j); xl[tt] = piece(BM + x_row + 32 * tt, j); }
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) acc[nt][tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xh[tt], wv[nt], acc[nt][tt], 0, 0, 0);
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) acc[nt][tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xl[tt], wv[nt], acc[nt][tt], 0, 0, 0);
+        }
     };
-#define FETCH_A(slot, k0)                                                                                      \
-    _Pragma("unroll") for (int i = 0; i < PER_THREAD; ++i) {                                              \
-        stage_hi[slot][i] = global_load16(a.xhi + (k0), x_off[i]);                                        \
-        stage_lo[slot][i] = global_load16(a.xlo + (k0), x_off[i]);                                        \
+    // The compiler does not count loads into LDS: the waits are written out.  Before the barrier every wave has
+    // its own loads of step s in LDS (all but the (ST - 2) PER youngest have arrived: loads arrive in order) and
+    // its reads of step s - 1 behind it.
+    for (int s = 0; s < ST - 1 && s < n_steps; ++s) fetch(s);
+    int s = 0;
+    for (; s + ST - 1 < n_steps; ++s) {
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((ST - 2) * PER) : "memory");
+        fetch(s + ST - 1);
+        multiply(s);
     }
-#define FETCH_W(slot, k0)                                                                                      \
-    _Pragma("unroll") for (int i = 0; i < 4; ++i) {                                                       \
-        ws[slot][0][i] = stream_load16(a.W + (k0), w_off[i]);                                             \
-        if (NMAT == 2) ws[slot][1][i] = stream_load16(a.W2 + (k0), w_off[i]);                             \
-    }
-#define STORE_A(buf, slot)                                                                                   \
-    _Pragma("unroll") for (int i = 0; i < PER_THREAD; ++i) {                                              \
-        const int p = tid + NTH * i;                                                                      \
-        if (PIECES % NTH == 0 || p < PIECES) {                                                            \
-            *(u32x4 *)lds_at(buf, 0, p / 8, p % 8) = stage_hi[slot][i];                                     \
-            *(u32x4 *)lds_at(buf, 1, p / 8, p % 8) = stage_lo[slot][i];                                     \
-        }                                                                                                 \
-    }
-#define STORE_W(slot)                                                                                  \
-    _Pragma("unroll") for (int mt = 0; mt < NMAT; ++mt)                                                   \
-        _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                     \
-            *(u32x4 *)(w_tile + w_put + (mt * 32 + 8 * i) * A_ROW) = ws[slot][mt][i];
-#define PRODUCTS(buf)                                                                                    \
-    _Pragma("unroll") for (int j = 0; j < 4; ++j) {                                                       \
-        bf16x8 wv[NMAT];                                                                                  \
-        _Pragma("unroll") for (int mt = 0; mt < NMAT; ++mt)                                               \
-            wv[mt] = __builtin_bit_cast(bf16x8, *(const u32x4 *)(w_tile + w_get + mt * 32 * A_ROW + 16 * j)); \
-        _Pragma("unroll") for (int tt = 0; tt < TT; ++tt) {                                               \
-            const bf16x8 xh = __builtin_bit_cast(bf16x8, *(const u32x4 *)lds_at(buf, 0, 32 * tt + lane % 32, 4 * (lane / 32) + j)); \
-            const bf16x8 xl = __builtin_bit_cast(bf16x8, *(const u32x4 *)lds_at(buf, 1, 32 * tt + lane % 32, 4 * (lane / 32) + j)); \
-            _Pragma("unroll") for (int mt = 0; mt < NMAT; ++mt) {                                         \
-                acc[mt][tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xh, wv[mt], acc[mt][tt], 0, 0, 0); \
-                acc[mt][tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xl, wv[mt], acc[mt][tt], 0, 0, 0); \
-            }                                                                                             \
-        }                                                                                                 \
+    for (; s < n_steps; ++s) {
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        multiply(s);
     }
 
-    // K is a multiple of two steps (the host checks): the loop body has no branch, and the
-    // scheduling barriers keep the compiler from sinking a step's loads down to their first use.
-    // The weight tile is private to its wave and the LDS serves a wave's accesses in order: the
-    // tile of the next step is written behind the reads of this one without a barrier.
-    const int k_last = a.K - KSTEP;
-    FETCH_A(0, 0) FETCH_W(0, 0)
-    FETCH_A(1, KSTEP) FETCH_W(1, KSTEP)
-    STORE_A(0, 0) STORE_W(0)
-    __syncthreads();
-    for (int k0 = 0; k0 < a.K; k0 += 2 * KSTEP) {
-        // LDS buffer 0 holds step k0, slot 1 (in flight) step k0 + 1; slot 0 is free
-        FETCH_A(0, min(k0 + 2 * KSTEP, k_last)) FETCH_W(0, min(k0 + 2 * KSTEP, k_last))
-        __builtin_amdgcn_sched_barrier(0);
-        PRODUCTS(0)
-        __builtin_amdgcn_sched_barrier(0);
-        STORE_A(1, 1) STORE_W(1)
-        __syncthreads();
-        FETCH_A(1, min(k0 + 3 * KSTEP, k_last)) FETCH_W(1, min(k0 + 3 * KSTEP, k_last))
-        __builtin_amdgcn_sched_barrier(0);
-        PRODUCTS(1)
-        __builtin_amdgcn_sched_barrier(0);
-        STORE_A(0, 0) STORE_W(0)
-        __syncthreads();
-    }
-#undef STORE_W
-#undef FETCH_A
-#undef FETCH_W
-#undef STORE_A
-#undef PRODUCTS
-
-    // C layout: lane -> column nc = tile + lane % 32; register r -> token 8 (r / 4) + 4 (lane / 32) + r % 4
-    const int nc = tile_y * (32 * NWV) + 32 * w + lane % 32;
+    // C layout: lane -> column, register r -> token 8 (r / 4) + 4 (lane / 32) + r % 4
 #pragma unroll
-    for (int tt = 0; tt < TT; ++tt)
+    for (int nt = 0; nt < NG; ++nt)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int t = t0 + 32 * tt + 8 * (r / 4) + 4 * (lane / 32) + (r % 4);
-            const float v = acc[0][tt][r];
-            if (EPI == PE_QKV) {
-                // rotary on (even, odd) column pairs: the partner sits in the neighbouring lane
-                const float other = dpp_move<0xB1, 0xF>(v, 0.f);
-                if (t < a.T && nc < a.N) {
-                    if (nc < a.n_q_rows + a.n_kv_rows) {
-                        const size_t ri = 2 * ((size_t)t * (a.d_head / 2) + (nc % a.d_head) / 2);
-                        const float2 cs = make_float2(as_global((const float *)a.rope)[ri], as_global((const float *)a.rope)[ri + 1]);
-                        const float rot = (nc & 1) ? __fadd_rn(__fmul_rn(other, cs.y), __fmul_rn(v, cs.x))
-                                                   : __fsub_rn(__fmul_rn(v, cs.x), __fmul_rn(other, cs.y));
-                        if (nc < a.n_q_rows) as_global(a.q)[(size_t)t * a.n_q_rows + nc] = rot;
-                        else {
-                            const int rr = nc - a.n_q_rows;
-                            kv_put(a.kcache, a.kv_half, ((size_t)(rr / a.d_head) * a.cap_ctx + a.p0 + t) * a.d_head + rr % a.d_head, rot);
-                        }
-                    } else {
-                        const int rr = nc - a.n_q_rows - a.n_kv_rows;
-                        kv_put(a.vcache, a.kv_half, ((size_t)(rr / a.d_head) * a.cap_ctx + a.p0 + t) * a.d_head + rr % a.d_head, v);
-                    }
-                }
-            } else if (t < a.T && nc < a.N) {
-                if (EPI == PE_RESID) {
-                    as_global(a.out)[(size_t)t * a.N + nc] = as_global(a.resid)[(size_t)t * a.N + nc] + v;
-                } else {   // PE_SWIGLU: gate in acc[0], up in acc[1]
-                    const float up = acc[NMAT - 1][tt][r];
+        for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int t = t0 + 32 * (TT * wm + tt) + 8 * (r / 4) + 4 * (lane / 32) + (r % 4);
+                const int nc = n0 + 32 * (NG * wn + nt) + lane % 32;
+                const float v = acc[nt][tt][r];
+                const bool exists = t < a.T && nc < a.N;
+                if (EPI == PE_QKV) {
+                    const float other = dpp_move<0xB1, 0xF>(v, 0.f);   // the rotary partner's column sits in the neighbouring lane
+                    if (exists) qkv_put(a, t, nc, v, other);
+                } else if (EPI == PE_PART) {
+                    const size_t ld = (size_t)a.N * n_mats;
+                    if (exists) as_global(a.part)[((size_t)split * a.T + t) * ld + (second ? a.N : 0) + nc] = v;
+                } else if (exists) {
+                    const float up = acc[(nt + NG) % NT][tt][r];
                     split_store(a.uhi, a.ulo, (size_t)t * a.N + nc, v / (1.0f + expf(-v)) * up);
                 }
             }
-        }
 }
 
-// ------------------------------------------------------------------ few tokens: split-k GEMM
-// With at most a few dozen tokens the product is bound by streaming the weights, and the tiling
-// above leaves most of the chip idle (few blocks, one k sweep each).  Here a block owns 32
-// weight rows and one 32-token tile, and its NWV waves split the k range between them: wave w
-// takes the 64-wide k steps w, w + NWV, ...  No operand is shared between the waves:
-//   * the weights are fetched coalesced (a wave's load = 8 rows x 128 bytes) and turned into
-//     the matrix-core layout (row in the lane) through a wave-private LDS tile -- fetched in
-//     that layout directly, every load touches 32 cache lines and the address path, not the
-//     HBM, is the bound;
-//   * the activations are stored in the matrix-core layout by their producers (act_at) and go
-//     straight into registers, 1 KB contiguous per load, out of the L2.
-// The waves' partial accumulators are summed through LDS in wave order (a fixed order: results
-// do not vary from run to run), and the epilogue runs on the sums: wave w finishes accumulator
-// registers w, w + NWV, ...
-constexpr int W_ROW = KSTEP * 2 + 16;    // bytes per LDS row of the weight tile (as A_ROW)
-
-// KS = 2: two blocks share a tile, each with half of the k steps (twice the blocks: the 128
-// column tiles of a 4096-row matrix then fill 256 compute units, and 344 tiles spread more
-// evenly); the block that finishes second adds the other's partial tile (a sum of two terms:
-// the same whichever is second) and runs the epilogue.
-template <int EPI, int NWV, int KS>
-__global__ __launch_bounds__(64 * NWV) void prefill_skinny_kernel(const PrefillGemmArgs a) {
-    constexpr int NMAT = EPI == PE_SWIGLU ? 2 : 1;
-    constexpr int TILE = NMAT * 32 * W_ROW;                // one wave's weight tile(s)
-    constexpr int NWE = NWV * KS;                          // waves that share the tile's k range
-    constexpr int RPW = 16 / NWV;                          // accumulator registers a wave finishes
-    extern __shared__ __align__(16) char a_lds[];          // weight tiles [NWV][TILE]; then float [NWV][NMAT][16][64]
-    __shared__ int ks_second;
-    float *red = (float *)a_lds;
-    const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE;
-    // Block order (KS = 1, several token tiles): workgroups go to the 8 XCDs round-robin, so the
-    // token tiles of a column tile are 8 apart in the linear index: same XCD, started together,
-    // and the second one finds the weight tile in that XCD's L2.
-    const int n_col = (a.N + 31) / 32;
-    const int grp = blockIdx.x / (8 * a.t_tiles), rem = blockIdx.x % (8 * a.t_tiles);
-    const int ty = KS == 1 ? rem / 8 : 0;
-    const int col_tile = KS == 1 ? grp * 8 + rem % 8 : (int)blockIdx.x / KS;
-    const int half = KS == 1 ? 0 : (int)blockIdx.x % KS, we = w + NWV * half;
-    if (col_tile >= n_col) return;
-    const int t0 = ty * 32;
-    const int S = a.K / KSTEP;
-    const int n_w = we < S ? (S - we + NWE - 1) / NWE : 0;           // k steps of this wave
-    f32x16 acc[NMAT];
-#pragma unroll
-    for (int mt = 0; mt < NMAT; ++mt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[mt][r] = 0.f;
-
-    // fetch side: load i of a step takes rows 8 i + lane / 8, 16-byte piece lane % 8
-    size_t w_row[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-        w_row[i] = (size_t)min(col_tile * 32 + 8 * i + lane / 8, a.N - 1) * a.K + 8 * (lane % 8);   // (ragged last tile: re-reads the last row)
-    char *tile = a_lds + (size_t)w * TILE;
-    const int put = (lane / 8) * W_ROW + (lane % 8) * 16;            // + (mt * 32 + 8 i) * W_ROW
-    const int get = (lane % 32) * W_ROW + (lane / 32) * 64;          // + mt * 32 * W_ROW + 16 j
-    // Activations: one descriptor per half over this token tile's region (act_at order: step, j,
-    // lane, 8 k).  Lanes whose token does not exist get an offset past the extent: zeros come
-    // back and nothing is fetched, so a tile with few tokens costs few cache lines per load.
-    const uint32_t tile_bytes = (uint32_t)S * (4 * WAVE * 8) * 2u;
-    const __amdgpu_buffer_rsrc_t xh_rsrc = row_resource(a.xhi + (size_t)ty * S * (4 * WAVE * 8), tile_bytes);
-    const __amdgpu_buffer_rsrc_t xl_rsrc = row_resource(a.xlo + (size_t)ty * S * (4 * WAVE * 8), tile_bytes);
-    const bool token_exists = t0 + lane % 32 < a.T;
-    const uint32_t x_lane = token_exists ? (uint32_t)lane * 16u : 0xFFFFFFF0u - 4u * (WAVE * 16u);   // (+ 3 j pieces stays past the extent, no wrap)
-
-    u32x4 stage[2][NMAT][4], xh[2][4], xl[2][4];
-#define FETCH_W(slot, i_)                                                                                \
-    {                                                                                                     \
-        const int k0 = KSTEP * min(we + NWE * (i_), S - 1);                                               \
-        _Pragma("unroll") for (int i = 0; i < 4; ++i) {                                                   \
-            stage[slot][0][i] = stream_load16(a.W + w_row[i] + k0);                                       \
-            if (NMAT == 2) stage[slot][1][i] = stream_load16(a.W2 + w_row[i] + k0);                       \
-        }                                                                                                 \
+// The partial sums of a split QKV product, added in split order, through its epilogue.  A thread has a rotary pair.
+__global__ __launch_bounds__(256) void prefill_qkv_sum_kernel(const PrefillGemmArgs a) {
+    const int t = blockIdx.y, nc = 2 * (blockIdx.x * 256 + threadIdx.x);
+    if (nc >= a.N) return;
+    float v0 = 0.f, v1 = 0.f;
+    for (int s = 0; s < a.splits; ++s) {
+        const size_t at = ((size_t)s * a.T + t) * a.N + nc;
+        v0 += as_global(a.part)[at]; v1 += as_global(a.part)[at + 1];
     }
-#define FETCH_X(slot, i_)                                                                                \
-    {                                                                                                     \
-        const uint32_t at = (token_exists ? (uint32_t)min(we + NWE * (i_), S - 1) * (4 * WAVE * 16u) : 0u) + x_lane; \
-        _Pragma("unroll") for (int j = 0; j < 4; ++j) {                                                   \
-            xh[slot][j] = buffer_load16(xh_rsrc, at + j * (WAVE * 16u));                                  \
-            xl[slot][j] = buffer_load16(xl_rsrc, at + j * (WAVE * 16u));                                  \
-        }                                                                                                 \
-    }
-    // Step i: its weights (asked for two steps ago) go through the LDS tile; then the requests
-    // of the coming steps -- activations of step i + 1 first, weights of step i + 2 behind them,
-    // since a wave's loads complete in the order they were issued and the next step must not
-    // have to wait for weights it does not need yet -- and the products of step i.
-#define STEP(slot, i_)                                                                                   \
-    {                                                                                                     \
-        _Pragma("unroll") for (int mt = 0; mt < NMAT; ++mt)                                               \
-            _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                 \
-                *(u32x4 *)(tile + put + (mt * 32 + 8 * i) * W_ROW) = stage[slot][mt][i];                  \
-        __builtin_amdgcn_sched_barrier(0);                                                                \
-        FETCH_X(1 - slot, (i_) + 1)                                                                       \
-        FETCH_W(slot, (i_) + 2)                                                                           \
-        __builtin_amdgcn_sched_barrier(0);                                                                \
-        _Pragma("unroll") for (int j = 0; j < 4; ++j)                                                     \
-            _Pragma("unroll") for (int mt = 0; mt < NMAT; ++mt) {                                         \
-                const bf16x8 wv = __builtin_bit_cast(bf16x8, *(const u32x4 *)(tile + get + mt * 32 * W_ROW + 16 * j)); \
-                acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, xh[slot][j]), wv, acc[mt], 0, 0, 0); \
-                acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, xl[slot][j]), wv, acc[mt], 0, 0, 0); \
-            }                                                                                             \
-        __builtin_amdgcn_sched_barrier(0);                                                                \
-    }
-    // The tile is private to the wave and the LDS serves a wave's accesses in order: no barrier
-    // inside the loop.  Loads are unconditional (clamped to the last step); a step past the
-    // wave's share is skipped as a whole on a wave-uniform condition.
-    FETCH_W(0, 0)
-    FETCH_X(0, 0)
-    FETCH_W(1, 1)
-    for (int i = 0; i < n_w; i += 2) {
-        STEP(0, i)
-        if (i + 1 < n_w) STEP(1, i + 1)
-    }
-#undef FETCH_W
-#undef FETCH_X
-#undef STEP
+    qkv_put(a, t, nc, v0, v1);
+    qkv_put(a, t, nc + 1, v1, v0);
+}
 
-    __syncthreads();                                       // every wave is done with its weight tile
+// The same for gate and up: SiLU(gate) * up as the (hi, lo) pair.  A thread has 8 units.
+__global__ __launch_bounds__(256) void prefill_swiglu_sum_kernel(const PrefillGemmArgs a) {
+    const int t = blockIdx.y, nc = 8 * (blockIdx.x * 256 + threadIdx.x);
+    if (nc >= a.N) return;
+    float g[8], u[8];
 #pragma unroll
-    for (int mt = 0; mt < NMAT; ++mt)
+    for (int e = 0; e < 8; ++e) g[e] = u[e] = 0.f;
+    for (int s = 0; s < a.splits; ++s) {
+        const float *p = a.part + ((size_t)s * a.T + t) * 2 * a.N + nc;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) red[((w * NMAT + mt) * 16 + r) * WAVE + lane] = acc[mt][r];
-    __syncthreads();
-
-    // C layout: lane -> column nc = tile + lane % 32; register r -> token 8 (r / 4) + 4 (lane / 32) + r % 4
-    const int nc = col_tile * 32 + lane % 32;
-    float sums[RPW][NMAT];
-#pragma unroll
-    for (int ri = 0; ri < RPW; ++ri)
-#pragma unroll
-        for (int mt = 0; mt < NMAT; ++mt) {
-            sums[ri][mt] = 0.f;
-            for (int ww = 0; ww < NWV; ++ww) sums[ri][mt] += red[((ww * NMAT + mt) * 16 + w + NWV * ri) * WAVE + lane];
-        }
-    if (KS == 2) {
-        const size_t tile_lin = (size_t)col_tile;   // (KS = 2 runs with one token tile)
-        float *mine = a.ks_part + ((tile_lin * 2 + half) * NMAT) * (16 * WAVE);
-        const float *other = a.ks_part + ((tile_lin * 2 + (1 - half)) * NMAT) * (16 * WAVE);
-#pragma unroll
-        for (int ri = 0; ri < RPW; ++ri)
-#pragma unroll
-            for (int mt = 0; mt < NMAT; ++mt) act_store<true>(mine + (mt * 16 + w + NWV * ri) * WAVE + lane, sums[ri][mt]);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // write-through stores acknowledged
-        __syncthreads();
-        if (tid == 0) {
-            const int old = __hip_atomic_fetch_add(as_global(a.ks_count) + tile_lin, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            ks_second = old;
-            if (old == 1) __hip_atomic_store(as_global(a.ks_count) + tile_lin, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        __syncthreads();
-        if (!ks_second) return;
-#pragma unroll
-        for (int ri = 0; ri < RPW; ++ri)
-#pragma unroll
-            for (int mt = 0; mt < NMAT; ++mt) sums[ri][mt] += coherent_load(other + (mt * 16 + w + NWV * ri) * WAVE + lane);
-    }
-#pragma unroll
-    for (int ri = 0; ri < RPW; ++ri) {
-        const int r = w + NWV * ri;
-        float sum[NMAT];
-#pragma unroll
-        for (int mt = 0; mt < NMAT; ++mt) sum[mt] = sums[ri][mt];
-        const int t = t0 + 8 * (r / 4) + 4 * (lane / 32) + (r % 4);
-        const float v = sum[0];
-        if (EPI == PE_QKV) {
-            const float other = dpp_move<0xB1, 0xF>(v, 0.f);   // rotary partner: the neighbouring column
-            if (t < a.T && nc < a.N) {
-                if (nc < a.n_q_rows + a.n_kv_rows) {
-                    const size_t ri = 2 * ((size_t)t * (a.d_head / 2) + (nc % a.d_head) / 2);
-                    const float cs_x = as_global((const float *)a.rope)[ri], cs_y = as_global((const float *)a.rope)[ri + 1];
-                    const float rot = (nc & 1) ? __fadd_rn(__fmul_rn(other, cs_y), __fmul_rn(v, cs_x))
-                                               : __fsub_rn(__fmul_rn(v, cs_x), __fmul_rn(other, cs_y));
-                    if (nc < a.n_q_rows) as_global(a.q)[(size_t)t * a.n_q_rows + nc] = rot;
-                    else {
-                        const int rr = nc - a.n_q_rows;
-                        kv_put(a.kcache, a.kv_half, ((size_t)(rr / a.d_head) * a.cap_ctx + a.p0 + t) * a.d_head + rr % a.d_head, rot);
-                    }
-                } else {
-                    const int rr = nc - a.n_q_rows - a.n_kv_rows;
-                    kv_put(a.vcache, a.kv_half, ((size_t)(rr / a.d_head) * a.cap_ctx + a.p0 + t) * a.d_head + rr % a.d_head, v);
-                }
-            }
-        } else if (t < a.T && nc < a.N) {
-            if (EPI == PE_RESID) {
-                as_global(a.out)[(size_t)t * a.N + nc] = as_global(a.resid)[(size_t)t * a.N + nc] + v;
-            } else {   // PE_SWIGLU: gate in sum[0], up in sum[1]
-                const float up = sum[NMAT - 1];
-                split_store(a.uhi, a.ulo, act_at(true, t, nc, a.N), v / (1.0f + expf(-v)) * up);
-            }
+        for (int e = 0; e < 8; e += 4) {
+            const float4 x = global_load_float4(p + e), y = global_load_float4(p + a.N + e);
+            g[e] += x.x; g[e + 1] += x.y; g[e + 2] += x.z; g[e + 3] += x.w;
+            u[e] += y.x; u[e + 1] += y.y; u[e + 2] += y.z; u[e + 3] += y.w;
         }
     }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) g[e] = g[e] / (1.0f + expf(-g[e])) * u[e];
+    split_store8(a.uhi, a.ulo, (size_t)t * a.N + nc, g);
 }
 
 // ------------------------------------------------------------------ causal attention over the chunk
@@ -525,7 +386,6 @@ struct PrefillAttnArgs {
     const void *kcache, *vcache;  // [n_kv_heads, cap_ctx, d_head] in the kernel's KT
     uint16_t *ohi, *olo;          // [T_pad, n_heads * d_head]
     int32_t T, p0, n_heads, n_kv_heads, d_head, cap_ctx;
-    bool tiled;                   // layout of ohi / olo: see act_at
 };
 
 template <typename KT>
@@ -626,7 +486,7 @@ __global__ __launch_bounds__(ANT) void prefill_attn_kernel(const PrefillAttnArgs
 #pragma unroll
         for (int g4 = 0; g4 < 4; ++g4)
             if (4 * (sub + 8 * g4) < dh) {
-                const size_t at = act_at(a.tiled, t, h * dh + 4 * (sub + 8 * g4), nqd);   // 4 consecutive k share a run of 8
+                const size_t at = (size_t)t * nqd + h * dh + 4 * (sub + 8 * g4);
                 split_store(a.ohi, a.olo, at, acc[g4].x / l); split_store(a.ohi, a.olo, at + 1, acc[g4].y / l);
                 split_store(a.ohi, a.olo, at + 2, acc[g4].z / l); split_store(a.ohi, a.olo, at + 3, acc[g4].w / l);
             }
@@ -781,7 +641,7 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_mfma_kernel(const Prefill
         const float inv = 1.0f / lsum;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {                       // row rho of product tile dt is feature NT rho + dt
-            const size_t at = act_at(a.tiled, t, head * DH + NT * (8 * (r / 4) + 4 * h + r % 4), nqd);
+            const size_t at = (size_t)t * nqd + head * DH + NT * (8 * (r / 4) + 4 * h + r % 4);
 #pragma unroll
             for (int dt = 0; dt < NT; ++dt) split_store(a.ohi, a.olo, at + dt, o[dt][r] * inv);
         }
@@ -794,79 +654,105 @@ namespace spdk {
 
 size_t prefill_attn_lds(int d_head) { return (size_t)(AQ * (d_head + 4) + AK * (d_head + 4) + AK * d_head + AQ * (AK + 1)) * sizeof(float); }
 
-// Launch with the widest column tile that still gives every compute unit a block.
-constexpr int GEMM_TT = 2;
-constexpr int SWIGLU_TT = 2;  // the same for gate and up side by side
+// The tile shapes: one block of 8 waves per compute unit, k steps of 64.  `step_us` is what a step takes a block when
+// all compute units have one (sweeps over tiles of 64 .. 512 columns, k steps of 32 / 64 / 128, 2 .. 10 stages, 4, 8 and
+// 16 waves; at 128 tokens the products bound it -- 1130 .. 1230 TFLOP/s over the chip, a large library product reaches
+// 1220 -- and at 32 what one compute unit pulls of the weights).
+constexpr int KS = 64;
+struct Tile { int bm, bn, stages; double step_us; };
+constexpr Tile TILES[] = {{32, 256, 4, 0.78}, {64, 256, 3, 0.95}, {64, 384, 2, 1.40}, {128, 256, 2, 1.86}, {128, 384, 2, 2.62}};
+constexpr int N_TILES = 5;
+constexpr int tile_lds(int i) { return TILES[i].stages * (2 * TILES[i].bm + TILES[i].bn) * KS * 2; }
 
-static size_t skinny_lds(int nmat, int nwv) {
-    const size_t tiles = (size_t)nwv * nmat * 32 * W_ROW, red = (size_t)nwv * nmat * 16 * 64 * sizeof(float);
-    return tiles > red ? tiles : red;
-}
-constexpr int SKINNY_MAX_T = 96;      // up to here the split-k kernel is the faster one
-
-template <int EPI, int TT>
-static void launch_gemm(hipStream_t s, const PrefillGemmArgs &g, int num_cu) {
-    if (g.tiled) {
-        // one 32-token tile: halve the k range between two blocks (more, smaller blocks balance better)
-        PrefillGemmArgs a = g;
-        a.t_tiles = (g.T + 31) / 32;
-        const int n_col = (g.N + 31) / 32;
-        if (a.t_tiles == 1 && g.ks_part != nullptr)
-            hipLaunchKernelGGL((prefill_skinny_kernel<EPI, 8, 2>), dim3(2 * n_col), dim3(512), skinny_lds(EPI == PE_SWIGLU ? 2 : 1, 8), s, a);
-        else
-            hipLaunchKernelGGL((prefill_skinny_kernel<EPI, 8, 1>), dim3(((n_col + 7) / 8) * 8 * a.t_tiles), dim3(512), skinny_lds(EPI == PE_SWIGLU ? 2 : 1, 8), s, a);
-        return;
+typedef void (*GemmFn)(PrefillGemmArgs);
+template <int EPI> static GemmFn gemm_kernel(int tile) {
+    constexpr bool GU = EPI == PE_SWIGLU;    // gate and up side by side take an even number of column tiles per wave
+    switch (tile) {
+        case 0: return GU ? nullptr : prefill_gemm_kernel<GU ? (int)PE_PART : EPI, 1, 8, 1, 1, KS, 4, true>;
+        case 1: return prefill_gemm_kernel<EPI, 2, 4, 1, 2, KS, 3, true>;
+        case 2: return GU ? nullptr : prefill_gemm_kernel<GU ? (int)PE_PART : EPI, 2, 4, 1, 3, KS, 2, true>;
+        case 3: return prefill_gemm_kernel<EPI, 2, 4, 2, 2, KS, 2, false>;
+        default: return GU ? nullptr : prefill_gemm_kernel<GU ? (int)PE_PART : EPI, 2, 4, 2, 3, KS, 2, false>;
     }
-    const int t_tiles = (g.T + 32 * TT - 1) / (32 * TT);
-    const int nmat = EPI == PE_SWIGLU ? 2 : 1;
-    auto lds_of = [&](int nwv) { return (size_t)(2 * 2 * (32 * TT) + nwv * nmat * 32) * A_ROW; };
-    auto blocks = [&](int nwv) { return t_tiles * ((g.N + 32 * nwv - 1) / (32 * nwv)); };
-    PrefillGemmArgs a = g;
-    a.t_tiles = t_tiles;
-    auto launch = [&](auto kernel, int nwv) {
-        a.n_tiles = (g.N + 32 * nwv - 1) / (32 * nwv);
-        hipLaunchKernelGGL(kernel, dim3(t_tiles * ((a.n_tiles + 7) / 8) * 8), dim3(64 * nwv), lds_of(nwv), s, a);
-    };
-    if (blocks(4) >= num_cu) launch(prefill_gemm_kernel<EPI, TT, 4>, 4);
-    else if (blocks(2) >= num_cu) launch(prefill_gemm_kernel<EPI, TT, 2>, 2);
-    else launch(prefill_gemm_kernel<EPI, TT, 1>, 1);
+}
+
+// How one product of the chunk is cut up.
+struct Cut { int tile, t_tiles, n_tiles, splits, split_steps; bool fused; };
+
+// The tile shape and the number of blocks that share a tile's k range: the cheapest by estimate.  A block's steps take
+// step_us each, blocks beyond the compute units queue; the weights come at 5.5 TB/s at best; partial sums are written
+// and read at 4 TB/s and, where the product has an epilogue, cost one more launch.
+static Cut cut_product(const PrefillChunk &c, int T, int N, int mats, int K, int epi) {
+    Cut best{};
+    double best_us = 1e30;
+    for (int tile = 0; tile < N_TILES; ++tile) {
+        const Tile &t = TILES[tile];
+        const int t_tiles = (T + t.bm - 1) / t.bm, steps = K / KS;
+        const bool can_fuse = epi == PE_QKV || (epi == PE_SWIGLU && gemm_kernel<PE_SWIGLU>(tile) != nullptr);
+        for (int want = 1; want <= 16; ++want) {
+            const int split_steps = (steps + want - 1) / want, splits = (steps + split_steps - 1) / split_steps;
+            const bool fused = can_fuse && splits == 1;
+            if (want > 1 && split_steps < 4) break;
+            if (!fused && (size_t)splits * T * N * mats > c.part_floats) continue;
+            const int n_tiles = fused && epi == PE_SWIGLU ? (2 * N + t.bn - 1) / t.bn : (N + t.bn - 1) / t.bn;
+            const int blocks = t_tiles * n_tiles * splits * (fused ? 1 : mats);
+            double us = std::max(t.step_us * split_steps * ((blocks + c.num_cu - 1) / c.num_cu), (double)N * K * mats * 2 / 5.5e6);
+            if (!fused) us += (double)splits * T * N * mats * 8 / 4e6 + (epi == PE_PART ? 0.0 : 4.0);
+            if (us < best_us) { best_us = us; best = Cut{tile, t_tiles, n_tiles, splits, split_steps, fused}; }
+        }
+    }
+    return best;
+}
+
+static void launch_gemm(hipStream_t s, GemmFn kernel, PrefillGemmArgs &a, const Cut &cut, int mats) {
+    a.t_tiles = cut.t_tiles; a.n_tiles = cut.n_tiles; a.splits = cut.splits; a.split_steps = cut.split_steps;
+    const int cols = cut.n_tiles * mats * cut.splits;
+    hipLaunchKernelGGL(kernel, dim3((cols + 7) / 8 * 8 * cut.t_tiles), dim3(512), tile_lds(cut.tile), s, a);
 }
 
 hipError_t prefill_init() {
     hipError_t e = hipFuncSetAttribute((const void *)prefill_attn_kernel<float>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)prefill_attn_lds(128));
     if (e == hipSuccess) e = hipFuncSetAttribute((const void *)prefill_attn_kernel<half_t>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)prefill_attn_lds(128));
-    const int big = (2 * 2 * 128 + 4 * 2 * 32) * A_ROW;     // at least what any instantiation asks for
-#define SPD_LDS(K, B) if (e == hipSuccess) e = hipFuncSetAttribute((const void *)(K), hipFuncAttributeMaxDynamicSharedMemorySize, B)
-    SPD_LDS((prefill_gemm_kernel<PE_QKV, GEMM_TT, 4>), big); SPD_LDS((prefill_gemm_kernel<PE_QKV, GEMM_TT, 2>), big); SPD_LDS((prefill_gemm_kernel<PE_QKV, GEMM_TT, 1>), big);
-    SPD_LDS((prefill_gemm_kernel<PE_RESID, GEMM_TT, 4>), big); SPD_LDS((prefill_gemm_kernel<PE_RESID, GEMM_TT, 2>), big); SPD_LDS((prefill_gemm_kernel<PE_RESID, GEMM_TT, 1>), big);
-    SPD_LDS((prefill_gemm_kernel<PE_SWIGLU, SWIGLU_TT, 4>), big); SPD_LDS((prefill_gemm_kernel<PE_SWIGLU, SWIGLU_TT, 2>), big); SPD_LDS((prefill_gemm_kernel<PE_SWIGLU, SWIGLU_TT, 1>), big);
-    SPD_LDS((prefill_skinny_kernel<PE_QKV, 8, 1>), (int)skinny_lds(1, 8)); SPD_LDS((prefill_skinny_kernel<PE_QKV, 8, 2>), (int)skinny_lds(1, 8));
-    SPD_LDS((prefill_skinny_kernel<PE_RESID, 8, 1>), (int)skinny_lds(1, 8)); SPD_LDS((prefill_skinny_kernel<PE_RESID, 8, 2>), (int)skinny_lds(1, 8));
-    SPD_LDS((prefill_skinny_kernel<PE_SWIGLU, 8, 1>), (int)skinny_lds(2, 8)); SPD_LDS((prefill_skinny_kernel<PE_SWIGLU, 8, 2>), (int)skinny_lds(2, 8));
-#undef SPD_LDS
+    for (int tile = 0; tile < N_TILES; ++tile)
+        for (GemmFn k : {gemm_kernel<PE_PART>(tile), gemm_kernel<PE_QKV>(tile), gemm_kernel<PE_SWIGLU>(tile)})
+            if (e == hipSuccess && k != nullptr) e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, tile_lds(tile));
     return e;
 }
 
+size_t prefill_part_floats(int d_model, int qkv_rows, int d_ffn) {
+    const size_t resid = (size_t)3 * PREFILL_CHUNK * d_model, wide = (size_t)4 * 64 * std::max(qkv_rows, 2 * d_ffn);
+    return std::max(resid, wide);
+}
+
 // One chunk of T prefix tokens at positions p0 .. p0 + T - 1 through the whole stack.  On
-// return (stream order) A.h holds the residual stream after the last layer and the caches are
-// extended; the caller finishes the last token (final norm + LM head).
+// return (stream order) c.h holds the last token's residual stream after the last layer in row T - 1 and the
+// caches are extended; the caller finishes that token (final norm + LM head).
 hipError_t prefill_chunk(hipStream_t s, const PrefillChunk &c) {
     const int T = c.T, d = c.d_model, dh = d / c.n_heads, nq = c.n_heads * dh, nkv = c.n_kv_heads * dh;
-    hipLaunchKernelGGL(embed_rows_kernel, dim3(T), dim3(256), 0, s, (const uint16_t *)c.embed, c.prefix, c.p0, T, d, c.h);
     hipLaunchKernelGGL(rope_table_kernel, dim3((T * (dh / 2) + 255) / 256), dim3(256), 0, s, c.inv_freq, c.p0, T, dh / 2, c.rope);
+    const Cut cut_qkv = cut_product(c, T, nq + 2 * nkv, 1, d, PE_QKV), cut_o = cut_product(c, T, d, 1, nq, PE_PART);
+    const Cut cut_gu = cut_product(c, T, c.d_ffn, 2, d, PE_SWIGLU), cut_down = cut_product(c, T, d, 1, c.d_ffn, PE_PART);
     float *h = c.h, *h1 = c.h1;
-    const bool tiled = T <= SKINNY_MAX_T;      // short chunk: split-k GEMMs, operands in their layout
     for (int l = 0; l < c.n_layers; ++l) {
         const spd_layer_weights &w = c.layers[l];
-        hipLaunchKernelGGL(rmsnorm_split_kernel, dim3(T), dim3(256), 0, s, h, (const uint16_t *)w.attn_norm, c.eps, d, c.xhi, c.xlo, tiled);
+        PrefillNormArgs n{};
+        n.h = h; n.gain = (const uint16_t *)w.attn_norm; n.hi = c.xhi; n.lo = c.xlo; n.T = T; n.d = d; n.eps = c.eps; n.part = c.part;
+        if (l == 0) {
+            n.embed = (const uint16_t *)c.embed; n.tokens = c.prefix + c.p0;
+            hipLaunchKernelGGL((prefill_norm_kernel<true>), dim3(T), dim3(256), 0, s, n);
+        } else {
+            n.resid = h1; n.splits = cut_down.splits;
+            hipLaunchKernelGGL((prefill_norm_kernel<false>), dim3(T), dim3(256), 0, s, n);
+        }
         PrefillGemmArgs g{};
-        g.xhi = c.xhi; g.xlo = c.xlo; g.W = (const uint16_t *)w.wqkv; g.T = T; g.N = nq + 2 * nkv; g.K = d;
+        g.xhi = c.xhi; g.xlo = c.xlo; g.W = (const uint16_t *)w.wqkv; g.T = T; g.N = nq + 2 * nkv; g.K = d; g.part = c.part;
         g.q = c.q; g.kcache = c.kv + (size_t)(2 * l) * c.kv_layer_bytes;
         g.vcache = c.kv + (size_t)(2 * l + 1) * c.kv_layer_bytes; g.kv_half = c.kv_half;
-        g.tiled = tiled; g.ks_part = c.ks_part; g.ks_count = c.ks_count; g.rope = c.rope; g.n_q_rows = nq; g.n_kv_rows = nkv; g.d_head = dh; g.cap_ctx = c.cap_ctx; g.p0 = c.p0;
-        launch_gemm<PE_QKV, GEMM_TT>(s, g, c.num_cu);
+        g.rope = c.rope; g.n_q_rows = nq; g.n_kv_rows = nkv; g.d_head = dh; g.cap_ctx = c.cap_ctx; g.p0 = c.p0;
+        launch_gemm(s, cut_qkv.fused ? gemm_kernel<PE_QKV>(cut_qkv.tile) : gemm_kernel<PE_PART>(cut_qkv.tile), g, cut_qkv, 1);
+        if (!cut_qkv.fused) hipLaunchKernelGGL(prefill_qkv_sum_kernel, dim3((g.N / 2 + 255) / 256, T), dim3(256), 0, s, g);
 
-        PrefillAttnArgs at{c.q, g.kcache, g.vcache, c.xhi, c.xlo, T, c.p0, c.n_heads, c.n_kv_heads, dh, c.cap_ctx, tiled};
+        PrefillAttnArgs at{c.q, g.kcache, g.vcache, c.xhi, c.xlo, T, c.p0, c.n_heads, c.n_kv_heads, dh, c.cap_ctx};
         const dim3 mfma_grid(((T + 31) / 32) * ((c.n_heads + 7) / 8) * 8), plain_grid((T + AQ - 1) / AQ, c.n_heads);
         if (c.kv_half) {
             if (dh == 128) hipLaunchKernelGGL((prefill_attn_mfma_kernel<128, half_t>), mfma_grid, dim3(256), 0, s, at);
@@ -879,19 +765,25 @@ hipError_t prefill_chunk(hipStream_t s, const PrefillChunk &c) {
         }
 
         PrefillGemmArgs o{};
-        o.xhi = c.xhi; o.xlo = c.xlo; o.W = (const uint16_t *)w.wo; o.T = T; o.N = d; o.K = nq; o.resid = h; o.out = h1; o.tiled = tiled; o.ks_part = c.ks_part; o.ks_count = c.ks_count;
-        launch_gemm<PE_RESID, GEMM_TT>(s, o, c.num_cu);
+        o.xhi = c.xhi; o.xlo = c.xlo; o.W = (const uint16_t *)w.wo; o.T = T; o.N = d; o.K = nq; o.part = c.part;
+        launch_gemm(s, gemm_kernel<PE_PART>(cut_o.tile), o, cut_o, 1);
+        n.h = h1; n.resid = h; n.splits = cut_o.splits; n.gain = (const uint16_t *)w.ffn_norm;
+        hipLaunchKernelGGL((prefill_norm_kernel<false>), dim3(T), dim3(256), 0, s, n);
 
-        hipLaunchKernelGGL(rmsnorm_split_kernel, dim3(T), dim3(256), 0, s, h1, (const uint16_t *)w.ffn_norm, c.eps, d, c.xhi, c.xlo, tiled);
         PrefillGemmArgs f{};
-        f.xhi = c.xhi; f.xlo = c.xlo; f.W = (const uint16_t *)w.w_gate; f.W2 = (const uint16_t *)w.w_up; f.T = T; f.N = c.d_ffn; f.K = d;
-        f.uhi = c.uhi; f.ulo = c.ulo; f.tiled = tiled; f.ks_part = c.ks_part; f.ks_count = c.ks_count;
-        launch_gemm<PE_SWIGLU, SWIGLU_TT>(s, f, c.num_cu);
+        f.xhi = c.xhi; f.xlo = c.xlo; f.W = (const uint16_t *)w.w_gate; f.W2 = (const uint16_t *)w.w_up; f.T = T; f.N = c.d_ffn; f.K = d; f.part = c.part;
+        f.uhi = c.uhi; f.ulo = c.ulo;
+        launch_gemm(s, cut_gu.fused ? gemm_kernel<PE_SWIGLU>(cut_gu.tile) : gemm_kernel<PE_PART>(cut_gu.tile), f, cut_gu, cut_gu.fused ? 1 : 2);
+        if (!cut_gu.fused) hipLaunchKernelGGL(prefill_swiglu_sum_kernel, dim3((f.N / 8 + 255) / 256, T), dim3(256), 0, s, f);
 
         PrefillGemmArgs dn{};
-        dn.xhi = c.uhi; dn.xlo = c.ulo; dn.W = (const uint16_t *)w.w_down; dn.T = T; dn.N = d; dn.K = c.d_ffn; dn.resid = h1; dn.out = h; dn.tiled = tiled; dn.ks_part = c.ks_part; dn.ks_count = c.ks_count;
-        launch_gemm<PE_RESID, GEMM_TT>(s, dn, c.num_cu);
+        dn.xhi = c.uhi; dn.xlo = c.ulo; dn.W = (const uint16_t *)w.w_down; dn.T = T; dn.N = d; dn.K = c.d_ffn; dn.part = c.part;
+        launch_gemm(s, gemm_kernel<PE_PART>(cut_down.tile), dn, cut_down, 1);
     }
+    // after the last layer only the last token's row is wanted
+    PrefillNormArgs n{};
+    n.h = h; n.resid = h1; n.part = c.part; n.T = T; n.d = d; n.splits = cut_down.splits; n.first_row = T - 1;
+    hipLaunchKernelGGL((prefill_norm_kernel<false>), dim3(1), dim3(256), 0, s, n);
     return hipGetLastError();
 }
 

@@ -284,6 +284,15 @@ def test_dense_prefix_pass_matches_the_oracle_and_the_token_by_token_pass(m):
     assert np.max(np.abs(logits[True] - logits[False])) <= 1e-4 * np.max(np.abs(logits[False]))
 
 
+@pytest.mark.timeout(600)
+@pytest.mark.parametrize("m", [66, 531])
+def test_prefix_products_of_every_tile_shape(m):
+    """7B widths, one layer: together with the other prefix lengths tested, every tile shape of the prefix
+    products runs, fused and as partial sums (66: 64 tokens x 384 columns, split; 531: 128 x 256 with both
+    epilogues, 64 x 384 in five splits; 1030: 128 x 384; up to 64: 32 x 256 and 64 x 256)."""
+    _layer_truncated(synth.LLAMA7B, 1, m, 2, 2, 31, "fused")
+
+
 # ---- the fp16 key/value cache a bf16 model may ask for (spd_model_cfg.kv_dtype): every kernel that
 # writes or reads the cache, against the same oracle (which keeps its keys and values unrounded), to
 # the bf16 tolerance; the rounding of the cache is the only difference to the fp32-cache cases above,
