@@ -221,13 +221,14 @@ struct PrefillChunk {
     char *kv;
     size_t kv_layer_bytes;
     int32_t kv_half;                   // the cache holds fp16, not fp32
-    float *h, *h1;                     // [PREFILL_CHUNK, d_model] residual stream (in / out) and after attention
+    float *h;                          // [PREFILL_CHUNK, d_model] residual stream
+    // Partial sums of split products.  They lie in what the product neither reads nor writes: QKV's in (uhi, ulo);
+    // those of the others in `part`, [PREFILL_CHUNK, d_model], and q behind it, which nothing reads after attention.
+    float *part;
     float *q;                          // [PREFILL_CHUNK, n_heads * d_head]
     uint16_t *xhi, *xlo;               // [PREFILL_CHUNK, max(d_model, n_heads * d_head)] bf16 pair
-    uint16_t *uhi, *ulo;               // [PREFILL_CHUNK, d_ffn] bf16 pair
+    uint16_t *uhi, *ulo;               // [PREFILL_CHUNK, d_ffn] bf16 pair (lo behind hi)
     float2 *rope;                      // [PREFILL_CHUNK, d_head / 2]
-    float *part;                       // [part_floats] partial sums of split products
-    size_t part_floats;
 };
 
 constexpr int FUSED_MAX_EPI = 512;     // residual values one block of the fused kernel stages per phase
@@ -250,7 +251,6 @@ hipError_t expand_prune(hipStream_t s, const ExpandArgs &a);
 hipError_t nucleus(hipStream_t s, const NucleusArgs &a);
 hipError_t prefill_chunk(hipStream_t s, const PrefillChunk &c);
 hipError_t prefill_init();
-size_t prefill_part_floats(int d_model, int qkv_rows, int d_ffn);   // room for every product's partial sums at the splits it may take
 hipError_t advance(hipStream_t s, DevState *st);
 hipError_t renorm(hipStream_t s, DevState *st, int k);
 hipError_t fill_i32(hipStream_t s, int32_t *p, int32_t v, int n);

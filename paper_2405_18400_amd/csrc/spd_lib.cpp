@@ -21,8 +21,7 @@ const char *const KC_NAMES[KC_N] = {"superpose", "gemv_qkv", "attention", "gemv_
                                     "gemv_down", "gemv_head", "topk_partial", "expand_prune", "fused_forward", "nucleus"};
 
 struct Layout {
-    size_t pf_h, pf_h1, pf_q, pf_xhi, pf_xlo, pf_uhi, pf_ulo, pf_rope;   // dense prefix pass arena (0 = none)
-    size_t pf_part, pf_part_floats;
+    size_t pf_h, pf_part, pf_q, pf_xhi, pf_xlo, pf_uhi, pf_ulo, pf_rope;   // dense prefix pass arena (0 = none)
     bool dense;
     size_t state, sync, layers_dev, prof, act, logits, part, counters, inv_freq, prefix, hist_tok, hist_par, pv, pi, pm, ps, pn, nuc_pb, nuc_count, nuc_hist, nuc_bk, kv, total;
     size_t kv_layer_bytes;   // K (or V) of one layer
@@ -105,15 +104,13 @@ Layout make_layout(const spd_model_cfg &c) {
     if (L.dense) {
         const size_t nq = (size_t)c.n_heads * dh, wide = nq > (size_t)c.d_model ? nq : (size_t)c.d_model;
         L.pf_h = take((size_t)PREFILL_CHUNK * c.d_model * 4);
-        L.pf_h1 = take((size_t)PREFILL_CHUNK * c.d_model * 4);
+        L.pf_part = take((size_t)PREFILL_CHUNK * c.d_model * 4);   // goes on into the queries, see PrefillChunk
         L.pf_q = take((size_t)PREFILL_CHUNK * nq * 4);
         L.pf_xhi = take((size_t)PREFILL_CHUNK * wide * 2);
         L.pf_xlo = take((size_t)PREFILL_CHUNK * wide * 2);
         L.pf_uhi = take((size_t)PREFILL_CHUNK * c.d_ffn * 2);
         L.pf_ulo = take((size_t)PREFILL_CHUNK * c.d_ffn * 2);
         L.pf_rope = take((size_t)PREFILL_CHUNK * (dh / 2) * 8);
-        L.pf_part_floats = spdk::prefill_part_floats(c.d_model, (int)nq + 2 * c.n_kv_heads * dh, c.d_ffn);
-        L.pf_part = take(L.pf_part_floats * 4);
     }
     L.kv_layer_bytes = up((size_t)c.n_kv_heads * c.max_ctx * dh * (c.kv_dtype == SPD_DTYPE_FP16 ? 2 : 4));
     L.kv = take(L.kv_layer_bytes * 2 * (size_t)c.n_layers);
@@ -558,11 +555,10 @@ static int run_prefix_pass(spd_ctx *c, int p0, int m) {
         pc.n_layers = mc.n_layers; pc.d_model = mc.d_model; pc.n_heads = mc.n_heads; pc.n_kv_heads = mc.n_kv_heads;
         pc.d_ffn = mc.d_ffn; pc.cap_ctx = mc.max_ctx; pc.eps = mc.rms_eps; pc.num_cu = c->num_cu;
         pc.inv_freq = c->at<double>(c->L.inv_freq); pc.kv = c->ws + c->L.kv; pc.kv_layer_bytes = c->L.kv_layer_bytes; pc.kv_half = mc.kv_dtype == SPD_DTYPE_FP16;
-        pc.h = c->at<float>(c->L.pf_h); pc.h1 = c->at<float>(c->L.pf_h1); pc.q = c->at<float>(c->L.pf_q);
+        pc.h = c->at<float>(c->L.pf_h); pc.part = c->at<float>(c->L.pf_part); pc.q = c->at<float>(c->L.pf_q);
         pc.xhi = c->at<uint16_t>(c->L.pf_xhi); pc.xlo = c->at<uint16_t>(c->L.pf_xlo);
         pc.uhi = c->at<uint16_t>(c->L.pf_uhi); pc.ulo = c->at<uint16_t>(c->L.pf_ulo);
         pc.rope = c->at<float2>(c->L.pf_rope);
-        pc.part = c->at<float>(c->L.pf_part); pc.part_floats = c->L.pf_part_floats;
         int last_T = 0;
         for (int at = p0; at < m; at += PREFILL_CHUNK) {
             pc.p0 = at; pc.T = last_T = (m - at < PREFILL_CHUNK) ? m - at : PREFILL_CHUNK;

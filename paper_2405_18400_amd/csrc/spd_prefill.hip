@@ -64,8 +64,8 @@ constexpr int NORM_RUNS = 4;      // runs per thread: d_model <= 256 * 8 * NORM_
 struct PrefillNormArgs {
     const uint16_t *embed;       // EMBED: [vocab, d]
     const int32_t *tokens;       // EMBED: token ids of the chunk
-    const float *resid, *part;   // [T, d]; [splits, T, d]
-    float *h;                    // [T, d]
+    const float *part;           // [splits, T, d]
+    float *h;                    // [T, d]: the residual, updated in place
     const uint16_t *gain;        // null: only h is wanted
     uint16_t *hi, *lo;           // [T, d]
     int32_t T, d, splits, first_row;
@@ -94,7 +94,7 @@ __global__ __launch_bounds__(256) void prefill_norm_kernel(const PrefillNormArgs
                     const float4 p = global_load_float4(x), q = global_load_float4(x + 4);
                     y[0] = p.x; y[1] = p.y; y[2] = p.z; y[3] = p.w; y[4] = q.x; y[5] = q.y; y[6] = q.z; y[7] = q.w;
                 };
-                take(a.resid + row + c, v[i]);
+                take(a.h + row + c, v[i]);
                 float sum[8], more[8];
                 take(a.part + row + c, sum);
                 for (int s = 1; s < a.splits; ++s) {
@@ -682,7 +682,7 @@ struct Cut { int tile, t_tiles, n_tiles, splits, split_steps; bool fused; };
 // The tile shape and the number of blocks that share a tile's k range: the cheapest by estimate.  A block's steps take
 // step_us each, blocks beyond the compute units queue; the weights come at 5.5 TB/s at best; partial sums are written
 // and read at 4 TB/s and, where the product has an epilogue, cost one more launch.
-static Cut cut_product(const PrefillChunk &c, int T, int N, int mats, int K, int epi) {
+static Cut cut_product(const PrefillChunk &c, int T, int N, int mats, int K, int epi, size_t part_floats) {
     Cut best{};
     double best_us = 1e30;
     for (int tile = 0; tile < N_TILES; ++tile) {
@@ -693,7 +693,7 @@ static Cut cut_product(const PrefillChunk &c, int T, int N, int mats, int K, int
             const int split_steps = (steps + want - 1) / want, splits = (steps + split_steps - 1) / split_steps;
             const bool fused = can_fuse && splits == 1;
             if (want > 1 && split_steps < 4) break;
-            if (!fused && (size_t)splits * T * N * mats > c.part_floats) continue;
+            if (!fused && (size_t)splits * T * N * mats > part_floats) continue;
             const int n_tiles = fused && epi == PE_SWIGLU ? (2 * N + t.bn - 1) / t.bn : (N + t.bn - 1) / t.bn;
             const int blocks = t_tiles * n_tiles * splits * (fused ? 1 : mats);
             double us = std::max(t.step_us * split_steps * ((blocks + c.num_cu - 1) / c.num_cu), (double)N * K * mats * 2 / 5.5e6);
@@ -719,33 +719,28 @@ hipError_t prefill_init() {
     return e;
 }
 
-size_t prefill_part_floats(int d_model, int qkv_rows, int d_ffn) {
-    const size_t resid = (size_t)3 * PREFILL_CHUNK * d_model, wide = (size_t)4 * 64 * std::max(qkv_rows, 2 * d_ffn);
-    return std::max(resid, wide);
-}
-
 // One chunk of T prefix tokens at positions p0 .. p0 + T - 1 through the whole stack.  On
 // return (stream order) c.h holds the last token's residual stream after the last layer in row T - 1 and the
 // caches are extended; the caller finishes that token (final norm + LM head).
 hipError_t prefill_chunk(hipStream_t s, const PrefillChunk &c) {
     const int T = c.T, d = c.d_model, dh = d / c.n_heads, nq = c.n_heads * dh, nkv = c.n_kv_heads * dh;
     hipLaunchKernelGGL(rope_table_kernel, dim3((T * (dh / 2) + 255) / 256), dim3(256), 0, s, c.inv_freq, c.p0, T, dh / 2, c.rope);
-    const Cut cut_qkv = cut_product(c, T, nq + 2 * nkv, 1, d, PE_QKV), cut_o = cut_product(c, T, d, 1, nq, PE_PART);
-    const Cut cut_gu = cut_product(c, T, c.d_ffn, 2, d, PE_SWIGLU), cut_down = cut_product(c, T, d, 1, c.d_ffn, PE_PART);
-    float *h = c.h, *h1 = c.h1;
+    const size_t room = (size_t)PREFILL_CHUNK * (d + nq);
+    const Cut cut_qkv = cut_product(c, T, nq + 2 * nkv, 1, d, PE_QKV, (size_t)PREFILL_CHUNK * c.d_ffn), cut_o = cut_product(c, T, d, 1, nq, PE_PART, room);
+    const Cut cut_gu = cut_product(c, T, c.d_ffn, 2, d, PE_SWIGLU, room), cut_down = cut_product(c, T, d, 1, c.d_ffn, PE_PART, room);
     for (int l = 0; l < c.n_layers; ++l) {
         const spd_layer_weights &w = c.layers[l];
         PrefillNormArgs n{};
-        n.h = h; n.gain = (const uint16_t *)w.attn_norm; n.hi = c.xhi; n.lo = c.xlo; n.T = T; n.d = d; n.eps = c.eps; n.part = c.part;
+        n.h = c.h; n.gain = (const uint16_t *)w.attn_norm; n.hi = c.xhi; n.lo = c.xlo; n.T = T; n.d = d; n.eps = c.eps; n.part = c.part;
         if (l == 0) {
             n.embed = (const uint16_t *)c.embed; n.tokens = c.prefix + c.p0;
             hipLaunchKernelGGL((prefill_norm_kernel<true>), dim3(T), dim3(256), 0, s, n);
         } else {
-            n.resid = h1; n.splits = cut_down.splits;
+            n.splits = cut_down.splits;
             hipLaunchKernelGGL((prefill_norm_kernel<false>), dim3(T), dim3(256), 0, s, n);
         }
         PrefillGemmArgs g{};
-        g.xhi = c.xhi; g.xlo = c.xlo; g.W = (const uint16_t *)w.wqkv; g.T = T; g.N = nq + 2 * nkv; g.K = d; g.part = c.part;
+        g.xhi = c.xhi; g.xlo = c.xlo; g.W = (const uint16_t *)w.wqkv; g.T = T; g.N = nq + 2 * nkv; g.K = d; g.part = (float *)c.uhi;
         g.q = c.q; g.kcache = c.kv + (size_t)(2 * l) * c.kv_layer_bytes;
         g.vcache = c.kv + (size_t)(2 * l + 1) * c.kv_layer_bytes; g.kv_half = c.kv_half;
         g.rope = c.rope; g.n_q_rows = nq; g.n_kv_rows = nkv; g.d_head = dh; g.cap_ctx = c.cap_ctx; g.p0 = c.p0;
@@ -767,7 +762,7 @@ hipError_t prefill_chunk(hipStream_t s, const PrefillChunk &c) {
         PrefillGemmArgs o{};
         o.xhi = c.xhi; o.xlo = c.xlo; o.W = (const uint16_t *)w.wo; o.T = T; o.N = d; o.K = nq; o.part = c.part;
         launch_gemm(s, gemm_kernel<PE_PART>(cut_o.tile), o, cut_o, 1);
-        n.h = h1; n.resid = h; n.splits = cut_o.splits; n.gain = (const uint16_t *)w.ffn_norm;
+        n.splits = cut_o.splits; n.gain = (const uint16_t *)w.ffn_norm;
         hipLaunchKernelGGL((prefill_norm_kernel<false>), dim3(T), dim3(256), 0, s, n);
 
         PrefillGemmArgs f{};
@@ -782,7 +777,7 @@ hipError_t prefill_chunk(hipStream_t s, const PrefillChunk &c) {
     }
     // after the last layer only the last token's row is wanted
     PrefillNormArgs n{};
-    n.h = h; n.resid = h1; n.part = c.part; n.T = T; n.d = d; n.splits = cut_down.splits; n.first_row = T - 1;
+    n.h = c.h; n.part = c.part; n.T = T; n.d = d; n.splits = cut_down.splits; n.first_row = T - 1;
     hipLaunchKernelGGL((prefill_norm_kernel<false>), dim3(1), dim3(256), 0, s, n);
     return hipGetLastError();
 }
