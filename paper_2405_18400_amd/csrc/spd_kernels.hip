@@ -14,7 +14,7 @@ constexpr int BLOCK = 256;
 constexpr int NWAVE = BLOCK / WAVE;
 
 // ------------------------------------------------------------------ matrix-vector product
-// One wave owns two output rows at a time (EPI_SWIGLU: row r of the gate and of the up
+// For rows and operands gemv_stream_kernel below does not take.  One wave owns two output rows at a time (EPI_SWIGLU: row r of the gate and of the up
 // matrix) and walks the columns 64 lanes x 16 bytes at a time; x lives in LDS as fp32.
 // Loads of the next 4-iteration chunk are issued before the current chunk is consumed, and
 // the very first chunk is issued before x is staged, so HBM latency overlaps the prologue.
@@ -130,6 +130,105 @@ __global__ __launch_bounds__(BLOCK) void gemv_kernel(const GemvArgs a) {
         acc1 = wave_sum(acc1);
         if (lane == 0) gemv_epilogue<WT, EPI>(a, unit, acc0, acc1, EPI == EPI_QKV ? a.st->pos : 0);
         unit = next_unit;
+    }
+}
+
+// The same product for rows of up to 64 pieces of 64 x 16 bytes (32768 bf16 columns): nothing but the weight stream between
+// memory and registers.  A wave owns a segment of NI pieces of a row's columns, the same one for every row, so its
+// part of x stays in registers (normalised once); `wpr` waves side by side make up a row, and finish through LDS.
+// A group of wpr waves takes two rows (EPI_SWIGLU: gate and up) at a time: each of the 2 NI registers in flight is
+// re-requested for the group's next two rows as soon as it has been consumed, so that 2 NI KB per wave are always on
+// their way.  Past the last row the descriptor is empty: the request costs no traffic and needs no branch.
+// Bound: HBM.  us per call with the weights out of cache, the kernel above -> this one: gate and up 2 x 13824 x 5120
+// 62.9 -> 41.4 (6.8 TB/s), 32000 x 4096 63 -> 42, 4096 x 4096 8.8 -> 5.9.
+// waves per SIMD by the registers an instantiation needs
+constexpr int gemv_waves(int ni) { return ni <= 2 ? 8 : ni == 3 ? 6 : ni == 4 ? 5 : ni <= 6 ? 4 : 3; }
+
+template <typename WT, int EPI, int NI, int NW>
+__global__ __launch_bounds__(NW * WAVE, gemv_waves(NI)) void gemv_stream_kernel(const GemvArgs a, const int wpr) {
+    constexpr int VEC = Store<WT>::VEC, PIECE = WAVE * 16;
+    __shared__ float red[NW];
+    __shared__ float2 part[2][NW];
+    const int lane = threadIdx.x & (WAVE - 1), w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const int seg = w % wpr, n_groups = (int)gridDim.x * (NW / wpr);
+    const int n_units = EPI == EPI_SWIGLU ? a.rows : a.rows / 2;
+    const uint32_t row_bytes = (uint32_t)a.cols * sizeof(WT);
+    int unit = (int)blockIdx.x * (NW / wpr) + w / wpr;
+    const uint32_t at = (uint32_t)(seg * NI * PIECE + lane * 16);
+    auto row0 = [&](int un) {
+        return row_resource((const char *)a.W + (size_t)min(un, n_units - 1) * row_bytes * (EPI == EPI_SWIGLU ? 1 : 2), un < n_units ? row_bytes : 0u);
+    };
+    auto row1 = [&](int un) {
+        const char *p = EPI == EPI_SWIGLU ? (const char *)a.W2 + (size_t)min(un, n_units - 1) * row_bytes
+                                          : (const char *)a.W + (size_t)min(un, n_units - 1) * row_bytes * 2 + row_bytes;
+        return row_resource(p, un < n_units ? row_bytes : 0u);
+    };
+    u32x4 A[NI], B[NI];
+    {
+        const __amdgpu_buffer_rsrc_t r0 = row0(unit), r1 = row1(unit);
+#pragma unroll
+        for (int i = 0; i < NI; ++i) { A[i] = stream_load16(r0, at + i * PIECE); B[i] = stream_load16(r1, at + i * PIECE); }
+    }
+    // this lane's part of x (zero past the row's end), normalised where a gain is given
+    float x[NI][VEC];
+    const __amdgpu_buffer_rsrc_t xr = row_resource(a.x, (uint32_t)a.cols * 4u);
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int v = 0; v < VEC; v += 4) {
+            const u32x4 t = buffer_load16(xr, (at + i * PIECE) * (4 / sizeof(WT)) + v * 4);
+            x[i][v] = __uint_as_float(t.x); x[i][v + 1] = __uint_as_float(t.y); x[i][v + 2] = __uint_as_float(t.z); x[i][v + 3] = __uint_as_float(t.w);
+        }
+    if (a.gain != nullptr) {
+        const __amdgpu_buffer_rsrc_t gr = row_resource(a.gain, row_bytes);
+        u32x4 g[NI];
+#pragma unroll
+        for (int i = 0; i < NI; ++i) g[i] = buffer_load16(gr, at + i * PIECE);
+        float ss = 0.f;
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) ss += x[i][v] * x[i][v];
+        ss = wave_sum_last(ss);
+        if (lane == WAVE - 1) red[w] = ss;
+        __syncthreads();
+        float tot = 0.f;
+        for (int q = 0; q < wpr; ++q) tot += red[q];
+        const float rs = 1.0f / sqrtf(tot / (float)a.cols + a.eps);
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            float gf[VEC];
+            Store<WT>::unpack(g[i], gf);
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) x[i][v] = x[i][v] * rs * gf[v];
+        }
+    }
+    const int rounds = (n_units + n_groups - 1) / n_groups;
+    for (int r = 0; r < rounds; ++r, unit += n_groups) {
+        const __amdgpu_buffer_rsrc_t r0 = row0(unit + n_groups), r1 = row1(unit + n_groups);
+        float acc0 = 0.f, acc1 = 0.f;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            float f0[VEC], f1[VEC];
+            Store<WT>::unpack(A[i], f0);
+            Store<WT>::unpack(B[i], f1);
+            A[i] = stream_load16(r0, at + i * PIECE);
+            B[i] = stream_load16(r1, at + i * PIECE);
+            __builtin_amdgcn_sched_barrier(0);   // (the compiler would first wait for half of the pieces)
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) { acc0 = fmaf(f0[v], x[i][v], acc0); acc1 = fmaf(f1[v], x[i][v], acc1); }
+        }
+        acc0 = wave_sum_last(acc0);
+        acc1 = wave_sum_last(acc1);
+        if (wpr > 1) {     // (two buffers: the waves of a group are at most one barrier apart)
+            if (lane == WAVE - 1) part[r & 1][w] = make_float2(acc0, acc1);
+            __syncthreads();
+            if (seg == 0) {
+                acc0 = acc1 = 0.f;
+                for (int q = 0; q < wpr; ++q) { acc0 += part[r & 1][w + q].x; acc1 += part[r & 1][w + q].y; }
+            }
+        }
+        if (seg == 0 && lane == WAVE - 1 && unit < n_units) gemv_epilogue<WT, EPI>(a, unit, acc0, acc1, EPI == EPI_QKV ? a.st->pos : 0);
     }
 }
 
@@ -447,16 +546,54 @@ __global__ void fill_i32_kernel(int32_t *p, int32_t v, int n) {
     if (i < n) p[i] = v;
 }
 
+template <typename WT, int EPI>
+hipError_t gemv_launch(hipStream_t s, const GemvArgs &a, int num_cu, size_t lds) {
+    const int units = EPI == EPI_SWIGLU ? a.rows : a.rows / 2;
+    const int pieces = (int)(((size_t)a.cols * sizeof(WT) + WAVE * 16 - 1) / (WAVE * 16));
+    const uintptr_t all = (uintptr_t)a.W | (uintptr_t)a.W2 | (uintptr_t)a.gain | (uintptr_t)a.x;
+    if (pieces > 64 || (all & 15)) {   // wider rows, operands off the 16-byte grid: x through LDS
+        const int blocks = std::max(1, std::min((units + NWAVE - 1) / NWAVE, num_cu * 8));
+        hipLaunchKernelGGL((gemv_kernel<WT, EPI>), dim3(blocks), dim3(BLOCK), lds, s, a);
+        return hipGetLastError();
+    }
+    // Waves per row: as few as hold the row in 8 pieces each, more while the units do not give every SIMD two waves
+    // (256 rows of 4096: 128 units, each split four ways).
+    int wpr = 1;
+    while ((pieces + wpr - 1) / wpr > 8) wpr *= 2;
+    while (wpr < 4 && (pieces + wpr - 1) / wpr > 1 && units * wpr < num_cu * 8) wpr *= 2;
+    const int nw = wpr == 8 ? 8 : 4, ni = (pieces + wpr - 1) / wpr;
+    // as many blocks as fit the chip, each with the same number of rounds
+    const int need = (units * wpr + nw - 1) / nw, cap = num_cu * (nw == 8 ? 1 : gemv_waves(ni));
+    const int rounds = (need + cap - 1) / cap, blocks = (need + rounds - 1) / rounds;
+#define SPD_GEMV(NI, NW) hipLaunchKernelGGL((gemv_stream_kernel<WT, EPI, NI, NW>), dim3(blocks), dim3(NW * WAVE), 0, s, a, wpr)
+    if (nw == 8) {
+        if (ni <= 6) SPD_GEMV(6, 8);
+        else SPD_GEMV(8, 8);
+    } else {
+        switch (ni) {
+            case 1: SPD_GEMV(1, 4); break;
+            case 2: SPD_GEMV(2, 4); break;
+            case 3: SPD_GEMV(3, 4); break;
+            case 4: SPD_GEMV(4, 4); break;
+            case 5: SPD_GEMV(5, 4); break;
+            case 6: SPD_GEMV(6, 4); break;
+            case 7: SPD_GEMV(7, 4); break;
+            default: SPD_GEMV(8, 4); break;
+        }
+    }
+#undef SPD_GEMV
+    return hipGetLastError();
+}
+
 template <typename WT>
-hipError_t gemv_dispatch(hipStream_t s, int epi, const GemvArgs &a, int blocks, size_t lds) {
+hipError_t gemv_dispatch(hipStream_t s, int epi, const GemvArgs &a, int num_cu, size_t lds) {
     switch (epi) {
-        case EPI_PLAIN: hipLaunchKernelGGL((gemv_kernel<WT, EPI_PLAIN>), dim3(blocks), dim3(BLOCK), lds, s, a); break;
-        case EPI_RESID: hipLaunchKernelGGL((gemv_kernel<WT, EPI_RESID>), dim3(blocks), dim3(BLOCK), lds, s, a); break;
-        case EPI_QKV: hipLaunchKernelGGL((gemv_kernel<WT, EPI_QKV>), dim3(blocks), dim3(BLOCK), lds, s, a); break;
-        case EPI_SWIGLU: hipLaunchKernelGGL((gemv_kernel<WT, EPI_SWIGLU>), dim3(blocks), dim3(BLOCK), lds, s, a); break;
+        case EPI_PLAIN: return gemv_launch<WT, EPI_PLAIN>(s, a, num_cu, lds);
+        case EPI_RESID: return gemv_launch<WT, EPI_RESID>(s, a, num_cu, lds);
+        case EPI_QKV: return gemv_launch<WT, EPI_QKV>(s, a, num_cu, lds);
+        case EPI_SWIGLU: return gemv_launch<WT, EPI_SWIGLU>(s, a, num_cu, lds);
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 }  // namespace
@@ -470,14 +607,9 @@ size_t gemv_lds_bytes(int dtype, int cols) {
 }
 
 hipError_t gemv(hipStream_t s, int dtype, int epi, const GemvArgs &a, int num_cu) {
-    const int units = epi == EPI_SWIGLU ? a.rows : a.rows / 2;
-    int blocks = (units + NWAVE - 1) / NWAVE;
-    const int cap = num_cu * 8;
-    if (blocks > cap) blocks = cap;
-    if (blocks < 1) blocks = 1;
     const size_t lds = gemv_lds_bytes(dtype, a.cols);
-    if (dtype == SPD_DTYPE_BF16) return gemv_dispatch<bf16_t>(s, epi, a, blocks, lds);
-    return gemv_dispatch<float>(s, epi, a, blocks, lds);
+    if (dtype == SPD_DTYPE_BF16) return gemv_dispatch<bf16_t>(s, epi, a, num_cu, lds);
+    return gemv_dispatch<float>(s, epi, a, num_cu, lds);
 }
 
 hipError_t superpose(hipStream_t s, int dtype, const SuperposeArgs &a) {

@@ -52,6 +52,29 @@ def test_gemv(dtype, rows, cols, norm, resid):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("rows,cols,shift", [(2, 8, 0), (130, 512, 0), (4098, 520, 0), (8192, 4096, 0), (66, 4104, 0), (4100, 8200, 0),
+                                             (40, 16384, 0), (38, 16392, 0), (20, 32768, 0), (6, 32776, 0), (34, 520, 1), (34, 4096, 1)])
+def test_gemv_pieces_and_waves_per_row(dtype, rows, cols, shift):
+    """Rows that end at, before and past a whole number of 1 KB pieces, one to eight waves per row, more rows
+    than one round takes; rows too wide for registers and operands off the 16-byte grid (`shift` floats)."""
+    rng = np.random.default_rng(rows + cols)
+    Wst, W = mat(rows, cols, dtype, 31)
+    gst, g = mat(1, cols, dtype, 32, std=1.0)
+    x, r = rng.standard_normal(cols, dtype=np.float32), rng.standard_normal(rows, dtype=np.float32)
+    xin = O.rmsnorm(x, g[0], 1e-5).astype(np.float64)
+    xd = torch.zeros(cols + 8, device="cuda")[shift:shift + cols]
+    xd.copy_(torch.from_numpy(x))
+    Wd, gd, y, u = dev(Wst, dtype), dev(gst.reshape(-1), dtype), torch.empty(rows, device="cuda"), torch.empty(rows, device="cuda")
+    P().spd_op_gemv(dtype, Wd, xd, y, gain=gd, eps=1e-5, residual=torch.from_numpy(r).cuda())
+    P().spd_op_swiglu(dtype, Wd, Wd, xd, u, eps=1e-5)
+    torch.cuda.synchronize()
+    W64 = W.astype(np.float64)
+    assert_close_scaled(y.cpu().numpy(), W64 @ xin + r, 2e-5, "gemv")      # fp32 accumulation of exact products
+    z = W64 @ x.astype(np.float64)
+    assert_close_scaled(u.cpu().numpy(), z / (1 + np.exp(-z)) * z, 2e-5, "swiglu")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
 @pytest.mark.parametrize("rows,cols", [(11008, 4096), (7, 24), (1025, 264)])
 def test_swiglu(dtype, rows, cols):
     Gst, G = mat(rows, cols, dtype, 4, std=0.05)
