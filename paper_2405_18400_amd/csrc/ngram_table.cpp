@@ -4,7 +4,9 @@
 // p_{n-gram}(x | context) = count(context, x) / sum_x' count(context, x').
 #include "spd_internal.h"
 
+#include <algorithm>
 #include <cstring>
+#include <utility>
 
 uint64_t ngram_capacity_for(const spd_ngram_host_tables *t) {
     uint64_t n = 0;
@@ -21,17 +23,38 @@ struct Builder {
     // Finds the slot of `key`, or the empty slot where it belongs.
     NgramSlot *locate(const int32_t *key, bool &found) {
         uint64_t at = ngram_home(ngram_hash(key), cap);
-        for (int32_t p = 0;; ++p, at = (at + 1 == cap) ? 0 : at + 1) {
+        for (;; at = (at + 1 == cap) ? 0 : at + 1) {
             NgramSlot &s = tab.slots[at];
             if (s.tok[0] == NG_EMPTY) {
                 found = false;
-                if (p > tab.max_probe) tab.max_probe = p;
                 return &s;
             }
             if (std::memcmp(s.tok, key, sizeof(s.tok)) == 0) {
                 found = true;
                 return &s;
             }
+        }
+    }
+
+    // Which slots are taken does not depend on the order of insertion; who sits where does.  Within every run of taken
+    // slots the entries are put in the order of their home slots, which makes the longest displacement the least there
+    // is.  It bounds the device's walk for a key that is not stored, and a walk is a chain of trips to memory.
+    void settle() {
+        uint64_t first = 0;
+        while (tab.slots[first].tok[0] != NG_EMPTY) ++first;      // (there is one: the load factor is below 1)
+        std::vector<std::pair<uint64_t, NgramSlot>> run;          // distance of the home slot from the start of the run; entry
+        auto wrap = [&](uint64_t at) { return at >= cap ? at - cap : at; };
+        for (uint64_t done = 0; done < cap;) {
+            const uint64_t start = wrap(first + done);
+            run.clear();
+            for (uint64_t at = start; tab.slots[at].tok[0] != NG_EMPTY; at = wrap(at + 1))
+                run.emplace_back(wrap(ngram_home(ngram_hash(tab.slots[at].tok), cap) + cap - start), tab.slots[at]);
+            std::stable_sort(run.begin(), run.end(), [](const auto &a, const auto &b) { return a.first < b.first; });
+            for (uint64_t i = 0; i < run.size(); ++i) {
+                tab.slots[wrap(start + i)] = run[i].second;
+                tab.max_probe = std::max(tab.max_probe, (int32_t)(i - run[i].first));
+            }
+            done += run.size() + 1;                               // (and the empty slot behind the run)
         }
     }
 };
@@ -86,5 +109,6 @@ int ngram_build(const spd_ngram_host_tables *t, int32_t vocab, uint64_t capacity
             s->cnt_hi = (uint32_t)(tot >> 32);
         }
     }
+    b.settle();
     return SPD_OK;
 }

@@ -6,6 +6,9 @@
 // (no float atomics), so results are bit-reproducible run to run.
 #include "spd_device.h"
 
+#include <algorithm>
+#include <type_traits>
+
 using namespace spdd;
 
 namespace {
@@ -245,180 +248,292 @@ __global__ __launch_bounds__(BLOCK) void superpose_kernel(const SuperposeArgs a)
 __device__ __forceinline__ bool better(float va, int ia, float vb, int ib) {
     return va > vb || (va == vb && ia < ib);
 }
-// Block-wide arg-best; every thread gets the winner.  sv / si have NWAVE entries.
-__device__ __forceinline__ void block_best(float &v, int &i, float *sv, int *si) {
+// The order as unsigned integers: a value's key rises with it and is 0 for an absent entry and for a NaN, which is never
+// better than anything; -0 and 0 are equal.  With the inverted id below it an entry is one 64-bit word.
+__device__ __forceinline__ uint32_t value_key(float v) {
+    const uint32_t u = __float_as_uint(v + 0.f);
+    return v != v ? 0u : (u & 0x80000000u) ? ~u : u | 0x80000000u;
+}
+__device__ __forceinline__ float key_value(uint32_t key) { return key == 0u ? -INFINITY : __uint_as_float((key & 0x80000000u) ? key & 0x7FFFFFFFu : ~key); }
+__device__ __forceinline__ unsigned long long entry_key(float v, int id) { return ((unsigned long long)value_key(v) << 32) | (uint32_t)~id; }
+__device__ __forceinline__ float read_lane(float v, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); }
+
+template <int CTRL, int ROW_MASK> __device__ __forceinline__ uint32_t dpp_max(uint32_t v) {
+    return max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROW_MASK, 0xF, false));
+}
+__device__ __forceinline__ uint32_t wave_max_key(uint32_t v) {
+    v = dpp_max<0xB1, 0xF>(v); v = dpp_max<0x4E, 0xF>(v); v = dpp_max<0x141, 0xF>(v);
+    v = dpp_max<0x140, 0xF>(v); v = dpp_max<0x142, 0xA>(v); v = dpp_max<0x143, 0xC>(v);
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, WAVE - 1);
+}
+// The k best of the NR entries per lane (keys; id(q) rises with q) end up one per lane, best first, in lanes 0 .. k - 1.
+// No LDS, no barrier, no branch on a lane's data: a round takes 0.1 us where one over a block with its two barriers took
+// 0.75, and so did one whose lanes compared (value, id) pairs under branches.
+template <int NR, typename ID> __device__ __forceinline__ void wave_top_k(int k, uint32_t (&key)[NR], ID id, float &kv, int &ki) {
+    const int lane = threadIdx.x & (WAVE - 1);
+    kv = -INFINITY; ki = INT_MAX;
+    for (int r = 0; r < k; ++r) {
+        uint32_t best = key[0];
+        int at = id(0);
 #pragma unroll
-    for (int o = WAVE / 2; o > 0; o >>= 1) {
-        const float ov = __shfl_xor(v, o, WAVE);
-        const int oi = __shfl_xor(i, o, WAVE);
-        if (better(ov, oi, v, i)) { v = ov; i = oi; }
+        for (int q = 1; q < NR; ++q) {
+            at = key[q] > best ? id(q) : at;
+            best = max(best, key[q]);
+        }
+        const uint32_t m = wave_max_key(best);
+        if (m == 0u) return;                    // (the wave as a whole: nothing is left)
+        unsigned long long who = __ballot(best == m);
+        if (__popcll(who) != 1) {               // a tie: the lowest id
+            int lowest = best == m ? at : INT_MAX;
+#pragma unroll
+            for (int o = WAVE / 2; o > 0; o >>= 1) lowest = min(lowest, __shfl_xor(lowest, o, WAVE));
+            who = __ballot(best == m && at == lowest);
+        }
+        const int won = __builtin_amdgcn_readlane(at, __builtin_amdgcn_readfirstlane(__ffsll((long long)who) - 1));
+        if (lane == r) { kv = key_value(m); ki = won; }
+#pragma unroll
+        for (int q = 0; q < NR; ++q) key[q] = id(q) == won ? 0u : key[q];
     }
-    __syncthreads();
-    if ((threadIdx.x & (WAVE - 1)) == 0) { sv[threadIdx.x / WAVE] = v; si[threadIdx.x / WAVE] = i; }
-    __syncthreads();
-    v = sv[0]; i = si[0];
+}
+// Where entry tid / PARTS of n stands in the order; equal words (absent entries) in the order they lie in.  PARTS lanes
+// (a power of two up to 16) compare with every PARTS-th entry each: one thread walking all of 64 took 2.4 us.
+template <int PARTS> __device__ __forceinline__ int rank_among(const unsigned long long *e, int n) {
+    const int t = threadIdx.x / PARTS, part = threadIdx.x % PARTS;
+    int rank = 0;
+    if (t < n) {
+        const unsigned long long mine = e[t];
+        for (int c = part; c < n; c += PARTS) {
+            const unsigned long long other = e[c];
+            rank += (int)(other > mine) + (int)((other == mine) & (c < t));
+        }
+    }
 #pragma unroll
-    for (int w = 1; w < NWAVE; ++w)
-        if (better(sv[w], si[w], v, i)) { v = sv[w]; i = si[w]; }
+    for (int o = PARTS / 2; o > 0; o >>= 1) rank += __shfl_xor(rank, o, WAVE);
+    return rank;
 }
 
-// Each block scans a contiguous slice of the logits: its k best entries, its max and its
-// sum of exp((z - max)) with z = logit / tau.
+// Each block scans a contiguous slice of the logits: its k best entries, its max and min and its sum of
+// exp(z - max) with z = logit / tau.  Every wave does so for its share, then the waves' results are merged: one
+// barrier.  A chain of latencies (launch, one trip to memory, k rounds): 9.2 -> 5.3 us at k = 8 against the kernel whose
+// rounds went over the block.
+// NR: entries of the slice per thread (4 up to vocabularies of 131072).
+template <int NR>
 __global__ __launch_bounds__(BLOCK) void topk_partial_kernel(const TopkArgs a) {
-    __shared__ float sv[NWAVE];
-    __shared__ int si[NWAVE];
-    __shared__ float red[NWAVE];
-    const int tid = threadIdx.x, b = blockIdx.x;
+    __shared__ unsigned long long entry[NWAVE * SPD_K_MAX];
+    __shared__ float sv[NWAVE * SPD_K_MAX], wave_max[NWAVE], wave_exp[NWAVE], wave_min[NWAVE];
+    __shared__ int si[NWAVE * SPD_K_MAX];
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE, b = blockIdx.x, k = a.k;
     const int lo = b * a.per_part, hi = min(a.vocab, lo + a.per_part);
-    // A thread's first NR entries of the slice stay in registers (all of them for slices of up
-    // to NR * BLOCK entries); the kernel is a chain of block-wide reductions, so it reads its
-    // logits once and takes the maximum from the first arg-best round (x -> x / tau is
-    // monotonic for tau > 0: the largest logit gives the largest z).
-    constexpr int NR = 4;
     float rv[NR];
+    uint32_t key[NR];
 #pragma unroll
     for (int q = 0; q < NR; ++q) {
         const int i = lo + tid + q * BLOCK;
-        rv[q] = i < hi ? a.logits[i] : -INFINITY;
+        rv[q] = i < hi ? as_global(a.logits)[i] : -INFINITY;
     }
-    float pv = INFINITY;   // previous winner: everything "after" it in the total order is eligible
-    int pi = -1;
-    for (int r = 0; r < a.k; ++r) {
-        float bv = -INFINITY;
-        int bi = INT_MAX;
 #pragma unroll
-        for (int q = 0; q < NR; ++q) {
-            const int i = lo + tid + q * BLOCK;
-            if (i < hi && better(pv, pi, rv[q], i) && better(rv[q], i, bv, bi)) { bv = rv[q]; bi = i; }
-        }
-        for (int i = lo + tid + NR * BLOCK; i < hi; i += BLOCK) {
-            const float v = a.logits[i];
-            if (better(pv, pi, v, i) && better(v, i, bv, bi)) { bv = v; bi = i; }
-        }
-        block_best(bv, bi, sv, si);
-        if (tid == 0) { a.pv[b * SPD_K_MAX + r] = bv; a.pi[b * SPD_K_MAX + r] = bi; }
-        pv = bv; pi = bi;
-        if (r == 0) {
-            const float mx = lo < hi ? __fdiv_rn(bv, a.tau) : -INFINITY;
-            float sm = 0.f;
+    for (int q = 0; q < NR; ++q) key[q] = lo + tid + q * BLOCK < hi ? value_key(rv[q]) : 0u;
+    float kv;
+    int ki;
+    wave_top_k(k, key, [&](int q) { return lo + tid + q * BLOCK; }, kv, ki);
+    if (lane < k) { sv[w * k + lane] = kv; si[w * k + lane] = ki; entry[w * k + lane] = ki == INT_MAX ? 0ull : entry_key(kv, ki); }
+    // x -> x / tau is monotonic for tau > 0: the largest logit gives the largest z
+    const float mx = __fdiv_rn(read_lane(kv, 0), a.tau), ref = mx == -INFINITY ? 0.f : mx;   // (a share without entries, or of -inf alone: every term is 0)
+    float sm = 0.f, lowest = INFINITY;
 #pragma unroll
-            for (int q = 0; q < NR; ++q)
-                if (lo + tid + q * BLOCK < hi) sm += expf(__fdiv_rn(rv[q], a.tau) - mx);
-            for (int i = lo + tid + NR * BLOCK; i < hi; i += BLOCK) sm += expf(__fdiv_rn(a.logits[i], a.tau) - mx);
-            sm = block_sum<BLOCK>(sm, red);
-            float lowest = INFINITY;   // of the logits: x -> x / tau is monotonic
+    for (int q = 0; q < NR; ++q)
+        if (lo + tid + q * BLOCK < hi) { sm += expf(__fdiv_rn(rv[q], a.tau) - ref); lowest = fminf(lowest, rv[q]); }
+    sm = wave_sum_last(sm);
+    lowest = -wave_max_last(-lowest);
+    if (lane == WAVE - 1) { wave_max[w] = mx; wave_exp[w] = sm; wave_min[w] = lowest; }
+    __syncthreads();
+    constexpr int PARTS = BLOCK / (NWAVE * SPD_K_MAX);
+    const int rank = rank_among<PARTS>(entry, NWAVE * k), t = tid / PARTS;
+    if (t < NWAVE * k && rank < k && tid % PARTS == 0) { a.pv[b * SPD_K_MAX + rank] = sv[t]; a.pi[b * SPD_K_MAX + rank] = si[t]; }
+    if (tid == BLOCK - 1) {
+        float m = -INFINITY, s = 0.f, l = INFINITY;
 #pragma unroll
-            for (int q = 0; q < NR; ++q)
-                if (lo + tid + q * BLOCK < hi) lowest = fminf(lowest, rv[q]);
-            for (int i = lo + tid + NR * BLOCK; i < hi; i += BLOCK) lowest = fminf(lowest, a.logits[i]);
-            lowest = -block_max<BLOCK>(-lowest, red);
-            if (tid == 0) { a.pm[b] = mx; a.ps[b] = sm; a.pn[b] = lo < hi ? __fdiv_rn(lowest, a.tau) : INFINITY; }
-        }
+        for (int q = 0; q < NWAVE; ++q) { m = fmaxf(m, wave_max[q]); l = fminf(l, wave_min[q]); }
+#pragma unroll
+        for (int q = 0; q < NWAVE; ++q) s += wave_max[q] == -INFINITY ? wave_exp[q] : wave_exp[q] * expf(wave_max[q] - m);
+        a.pm[b] = m; a.ps[b] = s; a.pn[b] = lo < hi ? __fdiv_rn(l, a.tau) : INFINITY;
     }
 }
 
 // ------------------------------------------------------------------ expand, interpolate, prune
-// Linear probing, NG_PROBE_BATCH consecutive slots per trip to memory (32-byte slots: a batch
-// is two or three cache lines; every trip is a random access into a table far larger than any
-// cache, and the kernel waits for the longest chain of all its probes: at a load factor of 0.7
-// some of a step's 60..360 probes walk past four slots, few past eight).  The slots are then
-// examined in probing order, so the result is that of a slot-by-slot walk.
-constexpr int NG_PROBE_BATCH = 8;
-__device__ __forceinline__ unsigned long long ngram_probe(const NgramDev &ng, const int32_t *key) {
-    uint64_t at = ngram_home(ngram_hash(key), ng.capacity);
-    for (int p = 0; p <= ng.max_probe; p += NG_PROBE_BATCH) {
-        u32x4 lo[NG_PROBE_BATCH], hi[NG_PROBE_BATCH];
+// Linear probing.  The eight lanes of a group look at eight consecutive slots (256 bytes) of one probe's walk at a time, N
+// probes of a group side by side: every trip is a random access into a table far larger than any cache, so what
+// counts is the number of trips (at a load factor of 0.7 some of a step's 60 .. 360 probes walk past four slots, few past
+// eight) and of cache lines a load instruction touches (with a probe per lane every one of its 16 loads touched 64
+// lines); 360 probes 6 .. 15 -> 5.5 us, with the table in order of home slots.
+// The slots are examined in probing order, so the result is that of a slot-by-slot walk; all lanes of a group get it.
+constexpr int PROBE_LANES = 8;
+// `home`: the key's home slot, NO_HOME: not wanted (its 64-bit multiplications are dear: one lane's work, not eight's).
+constexpr uint64_t NO_HOME = ~0ull;
+template <int N>
+__device__ __forceinline__ void ngram_probes(const NgramDev &ng, const int32_t (&key)[N][6], const uint64_t (&home)[N], unsigned long long (&count)[N]) {
+    const int lane = threadIdx.x & (WAVE - 1), j = lane % PROBE_LANES, first = lane - j;
+    uint64_t at[N];
+    bool open[N];
 #pragma unroll
-        for (int j = 0; j < NG_PROBE_BATCH; ++j) {
-            uint64_t idx = at + (uint64_t)j;
-            while (idx >= ng.capacity) idx -= ng.capacity;
-            const NgramSlot *sl = ng.slots + idx;
-            lo[j] = *(const u32x4 *)sl;
-            hi[j] = *((const u32x4 *)sl + 1);
-        }
-#pragma unroll
-        for (int j = 0; j < NG_PROBE_BATCH; ++j) {
-            if (p + j > ng.max_probe || (int32_t)lo[j].x == NG_EMPTY) return 0ull;
-            if ((int32_t)lo[j].x == key[0] && (int32_t)lo[j].y == key[1] && (int32_t)lo[j].z == key[2] &&
-                (int32_t)lo[j].w == key[3] && (int32_t)hi[j].x == key[4] && (int32_t)hi[j].y == key[5])
-                return ((unsigned long long)hi[j].w << 32) | hi[j].z;
-        }
-        at += NG_PROBE_BATCH;
-        while (at >= ng.capacity) at -= ng.capacity;
+    for (int u = 0; u < N; ++u) {
+        count[u] = 0ull;
+        open[u] = home[u] != NO_HOME;
+        at[u] = home[u] + (uint64_t)j;
+        while (open[u] && at[u] >= ng.capacity) at[u] -= ng.capacity;
     }
-    return 0ull;
+    for (int p = 0; p <= ng.max_probe; p += PROBE_LANES) {
+        u32x4 lo[N], hi[N];
+        bool more = false;
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+            if (open[u]) {
+                const NgramSlot *sl = ng.slots + at[u];
+                lo[u] = global_load16(sl);
+                hi[u] = global_load16((const char *)sl + 16);
+            }
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            bool hit = false, end = false;
+            uint32_t c0 = 0, c1 = 0;
+            if (open[u]) {
+                const bool past = p + j > ng.max_probe;
+                end = past || (int32_t)lo[u].x == NG_EMPTY;
+                hit = !past && (int32_t)lo[u].x == key[u][0] && (int32_t)lo[u].y == key[u][1] && (int32_t)lo[u].z == key[u][2] &&
+                      (int32_t)lo[u].w == key[u][3] && (int32_t)hi[u].x == key[u][4] && (int32_t)hi[u].y == key[u][5];
+                c0 = hi[u].z; c1 = hi[u].w;
+            }
+            const uint32_t hits = (uint32_t)(__ballot(hit) >> first) & 0xFFu, ends = (uint32_t)(__ballot(end) >> first) & 0xFFu;
+            const int at_hit = hits ? __ffs((int)hits) - 1 : PROBE_LANES, at_end = ends ? __ffs((int)ends) - 1 : PROBE_LANES;
+            const int from = first + (at_hit & (PROBE_LANES - 1));
+            const uint32_t r0 = __shfl(c0, from, WAVE), r1 = __shfl(c1, from, WAVE);
+            if (open[u] && at_hit < at_end) count[u] = ((unsigned long long)r1 << 32) | r0;
+            open[u] = open[u] && !hits && !ends;
+            at[u] += PROBE_LANES;
+            while (open[u] && at[u] >= ng.capacity) at[u] -= ng.capacity;
+            more = more || open[u];
+        }
+        if (!__any(more)) break;
+    }
 }
 
 // One block.  Merges the per-slice top-k into the global KeepTopK and log-softmax, builds the
 // k x k options, probes the n-gram store for every (draft, kept token, order), applies the
 // mixture (Eq. 3), the interpolation (Eq. 4) or the penalty form (Eq. 5), keeps the k best
 // options and rewrites the draft state.
-__global__ __launch_bounds__(BLOCK) void expand_prune_kernel(const ExpandArgs a) {
-    __shared__ float sv[NWAVE];
-    __shared__ int si[NWAVE];
+// A chain of latencies.  Whatever does not depend on the kept tokens is asked for at the start: the first MERGE threads
+// select among the slices' candidates, wave by wave, while the others look up the drafts' context totals.
+// k = 8, five orders, 1.6 M slots: 28 -> 13 us (merge 2.9, ranks 0.6, hashes 0.8, probes 5.5, mixture and scores 1.1, prune and state 1.5).
+constexpr int ENT = 1024, MERGE = 256, MERGE_WAVES = MERGE / WAVE;
+
+__global__ __launch_bounds__(ENT) void expand_prune_kernel(const ExpandArgs a) {
+    __shared__ unsigned long long entry[MERGE_WAVES * SPD_K_MAX], option[SPD_KK];
+    __shared__ float sv[MERGE_WAVES * SPD_K_MAX];
+    __shared__ int si[MERGE_WAVES * SPD_K_MAX];
     __shared__ int s_top[SPD_K_MAX];
     __shared__ float s_logp[SPD_K_MAX];
     __shared__ float s_lse;
-    __shared__ float s_red[NWAVE];
     __shared__ float s_new[SPD_K_MAX];
     __shared__ int s_tails[SPD_K_MAX][SPD_TAIL];
     __shared__ float s_old[SPD_K_MAX];
     __shared__ unsigned long long s_cnt[SPD_KK * SPD_N_ORDERS];
+    __shared__ uint64_t s_home[SPD_KK * SPD_N_ORDERS];
     __shared__ unsigned long long s_tot[SPD_K_MAX * SPD_N_ORDERS];
     __shared__ float s_png[SPD_KK];
     __shared__ int s_any[SPD_K_MAX];
     __shared__ float s_score[SPD_KK];
     __shared__ int s_valid[SPD_KK];
-    const int tid = threadIdx.x, k = a.k;
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1), k = a.k;
     DevState *st = a.st;
+    const int gen = st->n_gen, pos = st->pos;
 
-    // Everything this kernel reads from memory before the probes is requested at once: the
-    // slices' candidates (a thread's first one stays in registers for all k rounds), the
-    // slices' (max, sum-exp) pairs, the drafts' state.
-    const int n_cand = a.n_part * k;
-    float c0v = -INFINITY;
-    int c0i = INT_MAX;
-    if (tid < n_cand) {
-        const int at = (tid / k) * SPD_K_MAX + (tid % k);
-        c0v = a.pv[at];
-        c0i = a.pi[at];
-    }
-    float my_m = -INFINITY;
-    for (int b = tid; b < a.n_part; b += BLOCK) my_m = fmaxf(my_m, a.pm[b]);
-    if (tid < SPD_K_MAX) {
-        s_old[tid] = st->logscore[tid];
-        s_any[tid] = 0;
-        for (int q = 0; q < SPD_TAIL; ++q)
-            s_tails[tid][q] = a.first ? st->prefix_tail[q] : st->tails[tid][q];
-    }
-    // log-sum-exp over the slices: M = max of the maxima, S = sum of sum-exp * exp(max - M)
-    const float M = block_max<BLOCK>(my_m, s_red);
-    float my_s = 0.f;
-    for (int b = tid; b < a.n_part; b += BLOCK) my_s += a.ps[b] * expf(a.pm[b] - M);
-    const float S = block_sum<BLOCK>(my_s, s_red);
-    if (tid == 0) s_lse = M + logf(S);
-    // global top-k of the slices' candidates
-    float pv = INFINITY;
-    int pi = -1;
-    for (int r = 0; r < k; ++r) {
-        float bv = -INFINITY;
-        int bi = INT_MAX;
-        if (better(pv, pi, c0v, c0i) && better(c0v, c0i, bv, bi)) { bv = c0v; bi = c0i; }
-        for (int c = tid + BLOCK; c < n_cand; c += BLOCK) {
-            const int at = (c / k) * SPD_K_MAX + (c % k);
-            const float v = a.pv[at];
-            const int i = a.pi[at];
-            if (better(pv, pi, v, i) && better(v, i, bv, bi)) { bv = v; bi = i; }
+    // The n-gram (the last n - 1 tokens of a draft, token) as a key (token NG_TOTAL: its context's total); false: it cannot
+    // be in the store (no table of that order; the last n - 1 tokens of the history must all exist).
+    auto make_key = [&](const int (&tail)[SPD_TAIL], int n, int token, int32_t (&key)[6]) {
+#pragma unroll
+        for (int q = 0; q < 6; ++q) key[q] = NG_PAD;
+#pragma unroll
+        for (int q = 0; q < SPD_TAIL; ++q) {     // (constant indices: the key stays in registers)
+#pragma unroll
+            for (int m = SPD_MIN_ORDER; m < SPD_MIN_ORDER + SPD_N_ORDERS; ++m)
+                if (m == n) {
+                    if (q < m - 1) key[q] = tail[SPD_TAIL - (m - 1) + q];
+                    if (q == m - 2) key[q + 1] = token;
+                }
         }
-        block_best(bv, bi, sv, si);
-        if (tid == 0) { s_top[r] = bi; s_logp[r] = bv; }
-        pv = bv; pi = bi;
+        return a.ng.slots != nullptr && a.ng.present[n - SPD_MIN_ORDER] && key[0] >= 0;
+    };
+    const bool use_ng = !a.first && a.alpha != 0.0f;
+    if (tid < MERGE) {
+        const int n_cand = a.n_part * k;
+        constexpr int NR = TOPK_PART_MAX * SPD_K_MAX / MERGE;
+        auto candidate = [&](int q, float &v, int &i) {
+            const int c = tid + q * MERGE, at = (c / k) * SPD_K_MAX + (c % k);
+            v = c < n_cand ? as_global(a.pv)[at] : -INFINITY;
+            i = c < n_cand ? as_global(a.pi)[at] : INT_MAX;
+        };
+        float cv[NR];
+        int ci[NR];
+        candidate(0, cv[0], ci[0]);
+        if (n_cand > MERGE) {
+#pragma unroll
+            for (int q = 1; q < NR; ++q) candidate(q, cv[q], ci[q]);
+        }
+        if (tid < WAVE) {   // log-sum-exp over the slices: M = max of the maxima, S = sum of sum-exp * exp(max - M)
+            float m = -INFINITY, sum = 0.f;
+            for (int b = lane; b < a.n_part; b += WAVE) m = fmaxf(m, a.pm[b]);
+            const float M = read_lane(wave_max_last(m), WAVE - 1);
+            for (int b = lane; b < a.n_part; b += WAVE) sum += a.ps[b] * expf(a.pm[b] - M);
+            const float S = read_lane(wave_sum_last(sum), WAVE - 1);
+            if (lane == 0) s_lse = M + logf(S);
+        }
+        float kv;
+        int ki;
+        auto select = [&](auto count) {
+            constexpr int N = decltype(count)::value;
+            uint32_t key[N];
+#pragma unroll
+            for (int q = 0; q < N; ++q) key[q] = ci[q] == INT_MAX ? 0u : value_key(cv[q]);
+            wave_top_k(k, key, [&](int q) { return ci[q]; }, kv, ki);
+        };
+        if (n_cand > MERGE) select(std::integral_constant<int, NR>());
+        else select(std::integral_constant<int, 1>());
+        if (lane < k) {
+            const int at = (tid / WAVE) * k + lane;
+            sv[at] = kv; si[at] = ki; entry[at] = ki == INT_MAX ? 0ull : entry_key(kv, ki);
+        }
+    } else {
+        const int u = tid - MERGE;
+        if (u < SPD_K_MAX) {
+            s_old[u] = st->logscore[u];
+            s_any[u] = 0;
+            for (int q = 0; q < SPD_TAIL; ++q) s_tails[u][q] = a.first ? st->prefix_tail[q] : st->tails[u][q];
+        }
+        const int e = u / PROBE_LANES;
+        static_assert((ENT - MERGE) / PROBE_LANES >= SPD_K_MAX * SPD_N_ORDERS, "a group of lanes per context");
+        if (use_ng && e < (k * SPD_N_ORDERS + PROBE_LANES - 1) / PROBE_LANES * PROBE_LANES) {   // (whole waves)
+            int tail[SPD_TAIL];
+            int32_t key[1][6];
+            unsigned long long total[1];
+#pragma unroll
+            for (int q = 0; q < SPD_TAIL; ++q) tail[q] = st->tails[min(e / SPD_N_ORDERS, SPD_K_MAX - 1)][q];
+            const bool known = make_key(tail, SPD_MIN_ORDER + e % SPD_N_ORDERS, NG_TOTAL, key[0]);
+            const uint64_t home[1] = {known && e < k * SPD_N_ORDERS ? ngram_home(ngram_hash(key[0]), a.ng.capacity) : NO_HOME};
+            ngram_probes<1>(a.ng, key, home, total);
+            if (e < k * SPD_N_ORDERS && u % PROBE_LANES == 0) s_tot[e] = total[0];
+        }
     }
     __syncthreads();
-    if (tid < k) {
-        s_logp[tid] = __fdiv_rn(s_logp[tid], a.tau) - s_lse;
-        st->top_ids[tid] = s_top[tid];
-        st->top_logp[tid] = s_logp[tid];
+    {
+        constexpr int PARTS = 16;
+        const int rank = rank_among<PARTS>(entry, MERGE_WAVES * k), t = tid / PARTS;
+        if (t < MERGE_WAVES * k && rank < k && tid % PARTS == 0) {
+            const float logp = __fdiv_rn(sv[t], a.tau) - s_lse;
+            s_top[rank] = si[t];
+            s_logp[rank] = logp;
+            st->top_ids[rank] = si[t];
+            st->top_logp[rank] = logp;
+        }
     }
     __syncthreads();
 
@@ -433,35 +548,42 @@ __global__ __launch_bounds__(BLOCK) void expand_prune_kernel(const ExpandArgs a)
             a.hist_tok[tid] = s_top[tid];
             a.hist_par[tid] = -1;
         }
-        for (int c = tid; c < k * k; c += BLOCK) {
+        for (int c = tid; c < k * k; c += ENT) {
             st->cand_score[c] = (c < k) ? s_logp[c] : -INFINITY;
             st->cand_valid[c] = (c < k);
             st->cand_png[c] = 0.f;
         }
     } else {
-        const bool use_ng = a.alpha != 0.0f;
         if (use_ng) {
-            const int n_probe = k * SPD_N_ORDERS + k * k * SPD_N_ORDERS;
-            for (int e = tid; e < n_probe; e += BLOCK) {
-                int i, j, n;
-                const bool total = e < k * SPD_N_ORDERS;
-                if (total) { i = e / SPD_N_ORDERS; j = 0; n = SPD_MIN_ORDER + e % SPD_N_ORDERS; }
-                else {
-                    const int f = e - k * SPD_N_ORDERS;
-                    i = f / (k * SPD_N_ORDERS); j = (f / SPD_N_ORDERS) % k; n = SPD_MIN_ORDER + f % SPD_N_ORDERS;
-                }
-                unsigned long long res = 0ull;
-                // the last n-1 tokens of the history must all exist
-                if (a.ng.slots != nullptr && a.ng.present[n - SPD_MIN_ORDER] && s_tails[i][SPD_TAIL - (n - 1)] >= 0) {
-                    int32_t key[6];
+            constexpr int GROUPS = ENT / PROBE_LANES, N = 4;       // up to k = 10 in one go
+            const int n_probe = k * k * SPD_N_ORDERS;
+            auto key_of = [&](int e, int32_t (&key)[6]) {          // probe e: draft, kept token, order
+                int tail[SPD_TAIL];
 #pragma unroll
-                    for (int q = 0; q < 6; ++q) key[q] = NG_PAD;
-                    for (int q = 0; q < n - 1; ++q) key[q] = s_tails[i][SPD_TAIL - (n - 1) + q];
-                    key[n - 1] = total ? NG_TOTAL : s_top[j];
-                    res = ngram_probe(a.ng, key);
+                for (int q = 0; q < SPD_TAIL; ++q) tail[q] = s_tails[e / (k * SPD_N_ORDERS)][q];
+                return make_key(tail, SPD_MIN_ORDER + e % SPD_N_ORDERS, s_top[(e / SPD_N_ORDERS) % k], key);
+            };
+            for (int e = tid; e < n_probe; e += ENT) {
+                int32_t key[6];
+                s_home[e] = key_of(e, key) ? ngram_home(ngram_hash(key), a.ng.capacity) : NO_HOME;
+            }
+            __syncthreads();
+            for (int e0 = 0; e0 < n_probe; e0 += N * GROUPS) {
+                int32_t key[N][6];
+                uint64_t home[N];
+                unsigned long long count[N];
+#pragma unroll
+                for (int u = 0; u < N; ++u) {
+                    const int e = e0 + u * GROUPS + tid / PROBE_LANES, f = min(e, n_probe - 1);
+                    (void)key_of(f, key[u]);
+                    home[u] = e < n_probe ? s_home[f] : NO_HOME;
                 }
-                if (total) s_tot[i * SPD_N_ORDERS + (n - SPD_MIN_ORDER)] = res;
-                else s_cnt[(i * k + j) * SPD_N_ORDERS + (n - SPD_MIN_ORDER)] = res;
+                ngram_probes<N>(a.ng, key, home, count);
+#pragma unroll
+                for (int u = 0; u < N; ++u) {
+                    const int e = e0 + u * GROUPS + tid / PROBE_LANES;
+                    if (e < n_probe && tid % PROBE_LANES == 0) s_cnt[e] = count[u];
+                }
             }
             __syncthreads();
             if (tid < k * k) {  // Eq. 3
@@ -493,22 +615,22 @@ __global__ __launch_bounds__(BLOCK) void expand_prune_kernel(const ExpandArgs a)
             }
             s_score[tid] = valid ? score : -INFINITY;
             s_valid[tid] = valid;
+            option[tid] = valid ? entry_key(score, tid) : 0ull;   // score desc, then parent asc, then token rank asc
             st->cand_score[tid] = s_score[tid];
             st->cand_valid[tid] = valid;
             st->cand_png[tid] = use_ng ? s_png[tid] : 0.f;
         }
         __syncthreads();
-        if (tid < k * k && s_valid[tid]) {
-            // rank among valid options: score desc, then parent asc, then token rank asc
-            int rank = 0;
-            for (int c = 0; c < k * k; ++c)
-                if (s_valid[c] && better(s_score[c], c, s_score[tid], tid)) ++rank;
+        // the options' ranks: 16 lanes for each of up to 64, 4 for each of up to 256
+        const bool few = k * k <= ENT / 16;
+        const int rank = few ? rank_among<16>(option, k * k) : rank_among<4>(option, k * k), c = few ? tid / 16 : tid / 4;
+        if (c < k * k && s_valid[c] && (few ? tid % 16 : tid % 4) == 0) {
             if (rank < k) {
-                const int i = tid / k, j = tid % k, gen = st->n_gen;
+                const int i = c / k, j = c % k;
                 for (int q = 0; q < SPD_TAIL - 1; ++q) st->tails[rank][q] = s_tails[i][q + 1];
                 st->tails[rank][SPD_TAIL - 1] = s_top[j];
-                st->logscore[rank] = s_score[tid];
-                s_new[rank] = s_score[tid];
+                st->logscore[rank] = s_score[c];
+                s_new[rank] = s_score[c];
                 st->new_tok[rank] = s_top[j];
                 st->new_parent[rank] = i;
                 if (gen < a.max_gen) {
@@ -519,15 +641,16 @@ __global__ __launch_bounds__(BLOCK) void expand_prune_kernel(const ExpandArgs a)
         }
     }
     __syncthreads();
-    __threadfence_block();
-    if (tid == 0) {  // Eq. 2 on the new scores
-        float mx = -INFINITY, sum = 0.f, g[SPD_K_MAX];
+    if (tid < k) {  // Eq. 2 on the new scores
+        float mx = -INFINITY, sum = 0.f;
         for (int i = 0; i < k; ++i) mx = fmaxf(mx, s_new[i]);
-        for (int i = 0; i < k; ++i) { g[i] = expf(s_new[i] - mx); sum += g[i]; }
-        for (int i = 0; i < k; ++i) st->gamma[i] = g[i] / sum;
-        st->k = k;
-        st->n_gen = a.first ? 1 : st->n_gen + 1;
-        if (a.advance) st->pos += 1;
+        for (int i = 0; i < k; ++i) sum += expf(s_new[i] - mx);
+        st->gamma[tid] = expf(s_new[tid] - mx) / sum;
+        if (tid == 0) {
+            st->k = k;
+            st->n_gen = a.first ? 1 : gen + 1;
+            if (a.advance) st->pos = pos + 1;
+        }
     }
 }
 
@@ -620,12 +743,14 @@ hipError_t superpose(hipStream_t s, int dtype, const SuperposeArgs &a) {
 }
 
 hipError_t topk_partial(hipStream_t s, const TopkArgs &a) {
-    hipLaunchKernelGGL(topk_partial_kernel, dim3(a.n_part), dim3(BLOCK), 0, s, a);
+    if (a.per_part <= 4 * BLOCK) hipLaunchKernelGGL(topk_partial_kernel<4>, dim3(a.n_part), dim3(BLOCK), 0, s, a);
+    else if (a.per_part <= 32 * BLOCK) hipLaunchKernelGGL(topk_partial_kernel<32>, dim3(a.n_part), dim3(BLOCK), 0, s, a);
+    else return hipErrorInvalidValue;   // (vocabularies stay below 2^20)
     return hipGetLastError();
 }
 
 hipError_t expand_prune(hipStream_t s, const ExpandArgs &a) {
-    hipLaunchKernelGGL(expand_prune_kernel, dim3(1), dim3(BLOCK), 0, s, a);
+    hipLaunchKernelGGL(expand_prune_kernel, dim3(1), dim3(ENT), 0, s, a);
     return hipGetLastError();
 }
 

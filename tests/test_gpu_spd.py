@@ -489,6 +489,35 @@ def test_k1_is_greedy_on_the_gpu(tiny):
         sess.close()
 
 
+@pytest.mark.parametrize("vocab,k", [(64, 16), (1026, 16), (4098, 7), (32000, 1), (32000, 16), (140000, 16)])
+def test_kept_tokens_and_log_softmax_of_masked_logits(vocab, k):
+    """KeepTopK and the log-softmax from given logits: whole slices masked with -inf, whole slices equal, +0 and -0
+    tied, more candidates than one pass of the merge takes (k = 16 of 32000 and more), slices of more than 1024."""
+    pkg = P()
+    shape = synth.ModelShape("select", 1, 128, 2, 2, 256, vocab, "fp32")
+    rng = np.random.default_rng(vocab + k)
+    z = np.round(rng.standard_normal(vocab) * 2, 2).astype(np.float32)      # many exact ties
+    if vocab > 2048:
+        z[1000:2100] = -np.inf
+        z[2100:3300] = 1.25
+    z[:40] = np.where(np.arange(40) % 2, np.float32(-0.0), np.float32(0.0))
+    cases = [z, np.where(np.arange(vocab) % 40 == 3, z, -np.inf).astype(np.float32) if vocab >= 40 * k else z,
+             np.where(np.abs(z) > 0, -1.0, z).astype(np.float32)]           # only the zeros stand out
+    sess = pkg.Session(shape, synth.make_weights(shape, seed=1), max_ctx=16, k_max=16)
+    try:
+        sess.spd_prefill(np.zeros(2, np.int32))
+        for x in cases:
+            sess.spd_expand_prune(pkg.SpdDecodeCfg(k, 0.0, 1.0, 0.1), torch.from_numpy(x).cuda(), True)
+            ids, logp, _, _, _ = sess.spd_get_step_info(k)
+            want = np.lexsort((np.arange(vocab), -x.astype(np.float64)))[:k]
+            assert ids.tolist() == want.tolist()
+            x64 = x.astype(np.float64)
+            lse = x64.max() + np.log(np.exp(x64 - x64.max()).sum())
+            np.testing.assert_allclose(logp, x64[want] - lse, atol=4e-6)   # a few fp32 roundings of numbers below 16
+    finally:
+        sess.close()
+
+
 def test_expand_prune_on_scripted_logits_with_ties(tiny):
     """Decision logic alone: crafted logits (exact ties included) fed straight to the
     post-forward kernels; everything here is integer- or fp32-exact, so results are compared
