@@ -148,6 +148,7 @@ struct NucleusArgs {
     unsigned long long *sc_hist; // scratch, [2048]: entry count above probability mass per first-level bucket; zero between calls
     uint16_t *sc_bk;             // scratch, [32768]: first-level bucket per entry, 0xFFFF past the vocabulary (vocab <= 32768 only)
     float top_p, tau;
+    float u;                     // the draw, or negative: it is in the state (a captured launch's arguments are fixed)
     int32_t first, advance;
     int32_t *hist_tok, *hist_par;
     int32_t max_gen;

@@ -293,8 +293,9 @@ hipError_t enqueue_decide(spd_ctx *c, const spd_decode_cfg &dc, const float *log
     return launch(c, KC_EXPAND, [&] { return spdk::expand_prune(c->stream, x); });
 }
 
-// Post-forward part of one nucleus-sampling step: slice statistics, then the sampler.
-hipError_t enqueue_sample(spd_ctx *c, const spd_sample_cfg &sc, const float *logits, int first, int advance) {
+// Post-forward part of one nucleus-sampling step: slice statistics, then the sampler
+// (u negative: the draw is in the state).
+hipError_t enqueue_sample(spd_ctx *c, const spd_sample_cfg &sc, float u, const float *logits, int first, int advance) {
     TopkArgs t{logits, c->cfg.vocab, 1, c->L.n_part, c->L.per_part, sc.tau,
                c->at<float>(c->L.pv), c->at<int32_t>(c->L.pi), c->at<float>(c->L.pm), c->at<float>(c->L.ps), c->at<float>(c->L.pn)};
     hipError_t e = launch(c, KC_TOPK, [&] { return spdk::topk_partial(c->stream, t); });
@@ -306,7 +307,7 @@ hipError_t enqueue_sample(spd_ctx *c, const spd_sample_cfg &sc, const float *log
     n.sc_count = c->at<unsigned>(c->L.nuc_count);
     n.sc_hist = c->at<unsigned long long>(c->L.nuc_hist);
     n.sc_bk = c->at<uint16_t>(c->L.nuc_bk);
-    n.top_p = sc.top_p; n.tau = sc.tau; n.first = first; n.advance = advance;
+    n.top_p = sc.top_p; n.tau = sc.tau; n.u = u; n.first = first; n.advance = advance;
     n.hist_tok = c->at<int32_t>(c->L.hist_tok); n.hist_par = c->at<int32_t>(c->L.hist_par);
     n.max_gen = c->cfg.max_ctx;
     return launch(c, KC_NUCLEUS, [&] { return spdk::nucleus(c->stream, n); });
@@ -708,23 +709,24 @@ int spd_nucleus_step(spd_ctx *c, const spd_sample_cfg *sc, float u, int32_t *out
     if (const char *why = check_sample(sc, u)) return fail(c, SPD_EINVAL, why);
     if (c->state == ST_CREATED) return fail(c, SPD_ESTATE, "spd_nucleus_step before spd_prefill");
     if (c->state == ST_STEPPING && c->k != 1) return fail(c, SPD_ESTATE, "a generation with k > 1 drafts is in progress");
-    uint32_t bits;
-    std::memcpy(&bits, &u, 4);
-    HIPCHK(c, hipMemsetD32Async((hipDeviceptr_t)&c->st()->sample_u, (int)bits, 1, c->stream));
     if (c->state == ST_PREFILLED) {
-        HIPCHK(c, enqueue_sample(c, *sc, c->at<float>(c->L.logits), 1, 0));
+        HIPCHK(c, enqueue_sample(c, *sc, u, c->at<float>(c->L.logits), 1, 0));
         c->state = ST_STEPPING;
         c->k = 1;
         c->n_gen = 1;
     } else {
         if (c->pos + 1 > c->cfg.max_ctx) return fail(c, SPD_ECTX_OVERFLOW, "KV cache is full");
         if (c->n_gen >= c->cfg.max_ctx) return fail(c, SPD_ECTX_OVERFLOW, "token history is full");
+        const bool graph = graphs_usable(c);
         auto body = [&]() -> hipError_t {
             hipError_t e = enqueue_forward(c, 1, 1, true);
-            if (e == hipSuccess) e = enqueue_sample(c, *sc, c->at<float>(c->L.logits), 0, 1);
+            if (e == hipSuccess) e = enqueue_sample(c, *sc, graph ? -1.f : u, c->at<float>(c->L.logits), 0, 1);
             return e;
         };
-        if (graphs_usable(c)) {
+        if (graph) {
+            uint32_t bits;
+            std::memcpy(&bits, &u, 4);
+            HIPCHK(c, hipMemsetD32Async((hipDeviceptr_t)&c->st()->sample_u, (int)bits, 1, c->stream));
             if (c->nucleus_exec && std::memcmp(&c->nucleus_sc, sc, sizeof(*sc)) != 0) drop_graph(c->nucleus_exec);
             if (!c->nucleus_exec) {
                 const int rc = capture(c, &c->nucleus_exec, body);
@@ -764,10 +766,7 @@ int spd_nucleus_sample(spd_ctx *c, const spd_sample_cfg *sc, float u, const floa
     if (c->state == ST_CREATED) return fail(c, SPD_ESTATE, "spd_nucleus_sample before spd_prefill");
     if (!first && (c->state != ST_STEPPING || c->k != 1)) return fail(c, SPD_ESTATE, "no nucleus pass is in progress");
     if (!first && c->n_gen >= c->cfg.max_ctx) return fail(c, SPD_ECTX_OVERFLOW, "token history is full");
-    uint32_t bits;
-    std::memcpy(&bits, &u, 4);
-    HIPCHK(c, hipMemsetD32Async((hipDeviceptr_t)&c->st()->sample_u, (int)bits, 1, c->stream));
-    HIPCHK(c, enqueue_sample(c, *sc, dev_logits, first ? 1 : 0, 0));
+    HIPCHK(c, enqueue_sample(c, *sc, u, dev_logits, first ? 1 : 0, 0));
     if (first) { c->state = ST_STEPPING; c->k = 1; c->n_gen = 1; }
     else c->n_gen += 1;
     return SPD_OK;

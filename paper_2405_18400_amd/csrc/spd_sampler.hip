@@ -352,6 +352,12 @@ __global__ __launch_bounds__(SNT) void nucleus_kernel(const NucleusArgs a) {
     if (!s.is_last) return;
 
     // ---- stage B: first-level histogram
+    // (the state it ends with is asked for now: at the end it would be one more trip to memory)
+    const float u = a.u >= 0.f ? a.u : st->sample_u, old_score = a.first ? 0.f : st->logscore[0];
+    const int gen = a.first ? 0 : st->n_gen, pos = st->pos;
+    int tail[SPD_TAIL];
+#pragma unroll
+    for (int q = 0; q < SPD_TAIL; ++q) tail[q] = a.first ? st->prefix_tail[q] : st->tails[0][q];
     Entries<CACHED> en;
     en.pb = a.sc_pb; en.vocab = a.vocab;
     if constexpr (CACHED) {
@@ -381,7 +387,7 @@ __global__ __launch_bounds__(SNT) void nucleus_kernel(const NucleusArgs a) {
     const int id_T = s.r_id;
     __syncthreads();
     // 2. the draw: the first entry whose cumulative probability exceeds u * mass (within the nucleus)
-    const unsigned long long x_u = (unsigned long long)((double)st->sample_u * (double)mass_fx);
+    const unsigned long long x_u = (unsigned long long)((double)u * (double)mass_fx);
     search<true, CACHED>(s, en, x_u);
     int tok = s.r_id;
     if (s.r_key > key_T) tok = id_T;   // (only rounding could take it past the nucleus)
@@ -392,23 +398,21 @@ __global__ __launch_bounds__(SNT) void nucleus_kernel(const NucleusArgs a) {
     }
     if (tid == 0) {   // the pass's state: one draft (k = 1, gamma = 1)
         const float logp = __fdiv_rn(as_global(a.logits)[tok], a.tau) - lse;
-        int tail[SPD_TAIL];
-        for (int q = 0; q < SPD_TAIL; ++q) tail[q] = a.first ? st->prefix_tail[q] : st->tails[0][q];
+#pragma unroll
         for (int q = 0; q < SPD_TAIL - 1; ++q) st->tails[0][q] = tail[q + 1];
         st->tails[0][SPD_TAIL - 1] = tok;
-        st->logscore[0] = a.first ? logp : st->logscore[0] + logp;
+        st->logscore[0] = a.first ? logp : old_score + logp;
         st->gamma[0] = 1.f;
         st->new_tok[0] = tok;
         st->new_parent[0] = a.first ? -1 : 0;
         st->top_ids[0] = tok;
         st->top_logp[0] = logp;
-        const int gen = a.first ? 0 : st->n_gen;
         if (gen < a.max_gen) { as_global(a.hist_tok)[(size_t)gen * SPD_K_MAX] = tok; as_global(a.hist_par)[(size_t)gen * SPD_K_MAX] = a.first ? -1 : 0; }
         st->nucleus_size = (int)size;
         st->nucleus_mass = (float)((double)mass_fx / (double)FX_ONE);
         st->k = 1;
         st->n_gen = gen + 1;
-        if (a.advance) st->pos += 1;
+        if (a.advance) st->pos = pos + 1;
         __hip_atomic_store(as_global(a.sc_count), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next call
     }
 }
