@@ -95,12 +95,15 @@ __global__ __launch_bounds__(256) void prefill_norm_kernel(const PrefillNormArgs
                     y[0] = p.x; y[1] = p.y; y[2] = p.z; y[3] = p.w; y[4] = q.x; y[5] = q.y; y[6] = q.z; y[7] = q.w;
                 };
                 take(a.h + row + c, v[i]);
-                float sum[8], more[8];
+                float sum[8], more[4][8];
                 take(a.part + row + c, sum);
-                for (int s = 1; s < a.splits; ++s) {
-                    take(a.part + (size_t)s * a.T * d + row + c, more);
+                for (int s = 1; s < a.splits; s += 4) {   // four at a time: each is a trip to memory (a split past the last re-reads it with weight 0)
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) sum[e] += more[e];
+                    for (int q = 0; q < 4; ++q) take(a.part + (size_t)min(s + q, a.splits - 1) * a.T * d + row + c, more[q]);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) sum[e] += s + q < a.splits ? more[q][e] : 0.f;
                 }
 #pragma unroll
                 for (int e = 0; e < 8; ++e) v[i][e] += sum[e];
@@ -196,7 +199,7 @@ template <int KS> __device__ __forceinline__ int swz(int row) {
 }
 
 template <int EPI, int WM, int WN, int TT, int NT, int KS, int ST, bool STREAM_W>
-__global__ __launch_bounds__(64 * WM * WN, WM * WN / 4) void prefill_gemm_kernel(const PrefillGemmArgs a) {
+__global__ __launch_bounds__(64 * WM * WN, WM * WN >= 4 ? WM * WN / 4 : 1) void prefill_gemm_kernel(const PrefillGemmArgs a) {
     constexpr int NWV = WM * WN, BM = 32 * TT * WM, BN = 32 * NT * WN;
     constexpr int ROWB = KS * 2, RPL = 1024 / ROWB;        // bytes per row; rows one load instruction of a wave brings
     constexpr int ROWS = 2 * BM + BN;                      // rows of a stage: x hi, x lo, W
@@ -326,9 +329,16 @@ __global__ __launch_bounds__(256) void prefill_qkv_sum_kernel(const PrefillGemmA
     const int t = blockIdx.y, nc = 2 * (blockIdx.x * 256 + threadIdx.x);
     if (nc >= a.N) return;
     float v0 = 0.f, v1 = 0.f;
-    for (int s = 0; s < a.splits; ++s) {
-        const size_t at = ((size_t)s * a.T + t) * a.N + nc;
-        v0 += as_global(a.part)[at]; v1 += as_global(a.part)[at + 1];
+    for (int s = 0; s < a.splits; s += 4) {
+        float p0[4], p1[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const size_t at = ((size_t)min(s + q, a.splits - 1) * a.T + t) * a.N + nc;
+            p0[q] = as_global(a.part)[at]; p1[q] = as_global(a.part)[at + 1];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (s + q < a.splits) { v0 += p0[q]; v1 += p1[q]; }
     }
     qkv_put(a, t, nc, v0, v1);
     qkv_put(a, t, nc + 1, v1, v0);
@@ -648,20 +658,244 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_mfma_kernel(const Prefill
     }
 }
 
+// The same over an fp16 cache, for d_head 64 and 128, through v_mfma_f32_32x32x16_f16: sixteen times the rate of the fp32
+// products.  The cached keys and values are fp16 and enter as they are; what multiplies them is split in two: a query's
+// row, scaled by a power of two that puts its largest element into [2^14, 2^15), and the probabilities times 2^14 go in as
+// hi = fp16(x) and lo = fp16(x - hi): 22 bits and an absolute floor 2^-38 below the largest, two products into one fp32
+// accumulator.  The error against 64 bits is that of the fp32 products, whose longer chains of roundings weigh more.
+// Layouts as above (a query stays in its lane); contraction index (step j, lane half h, element i) stands for feature
+// (d_head / 2) h + 8 j + i in the first product and for key 8 ((8 j + i) / 4) + 4 h + i % 4 in the second, which are the eight
+// registers 8 j .. 8 j + 7 of S^T.  A wave brings its 32-key tiles of K and of V into LDS of its own (16-byte pieces of a
+// key's row permuted by the row, as in the GEMM), each tile as soon as the one before has been read: no barrier, and the
+// waits are counted by hand.  What bounds it now is the vector unit (16 exponentials and 32 splits per lane and tile).
+// us per chunk and layer, heads of 128, the fp32 products -> this: 1024 tokens of 32 heads 143 -> 51, 512 of 64 (8 cached) 98 -> 45,
+// 64 of 32 16 -> 8.6.
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+constexpr float P_SCALE = 16384.f;
+
+__device__ __forceinline__ void split_f16(float x, _Float16 &hi, _Float16 &lo) {
+    hi = (_Float16)x;
+    lo = (_Float16)(x - (float)hi);
+}
+
+template <int DH>
+__global__ __launch_bounds__(256, 2) void prefill_attn_f16_kernel(const PrefillAttnArgs a) {
+    constexpr int NT = DH / 32, NJ = DH / 16, NWV = 4;
+    constexpr int ROWB = DH * 2, PIECES = ROWB / 16, TILE = 32 * ROWB, LOADS = TILE / 1024;
+    constexpr int SLOT = (2 + 16 * NT) * WAVE * 4;           // one wave's partial result: m, sum, O^T
+    static_assert(2 * SLOT <= NWV * 2 * TILE + 32 * DH * 4, "the partial results take the place of the tiles and of Q");
+    extern __shared__ __align__(16) char tiles[];            // [NWV][K, V][TILE], then Q: 32 rows of fp32, pieces permuted by the row
+    const int lane = threadIdx.x & (WAVE - 1), w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE), h = lane / 32, c = lane % 32;
+    const int q_tiles = (a.T + 31) / 32;
+    const int xcd = blockIdx.x % 8, slot_in_xcd = blockIdx.x / 8;   // (placement as above)
+    const int head = (slot_in_xcd / q_tiles) * 8 + xcd;
+    if (head >= a.n_heads) return;
+    const int kvh = head / (a.n_heads / a.n_kv_heads);
+    const int q0 = (q_tiles - 1 - slot_in_xcd % q_tiles) * 32;
+    const int nqd = a.n_heads * DH;
+    const int qpos = a.p0 + q0 + c;                          // cached positions 0 .. qpos are visible to this lane's query
+    const int last_key = a.p0 + min(q0 + 31, a.T - 1);       // last position any query of the tile sees
+
+    // one head's rows 0 .. last_key; a row past the last re-reads it (its scores are masked)
+    const size_t head_at = (size_t)kvh * a.cap_ctx * DH;
+    const __amdgpu_buffer_rsrc_t k_rsrc = row_resource((const uint16_t *)a.kcache + head_at, (uint32_t)(last_key + 1) * ROWB);
+    const __amdgpu_buffer_rsrc_t v_rsrc = row_resource((const uint16_t *)a.vcache + head_at, (uint32_t)(last_key + 1) * ROWB);
+    char *k_tile = tiles + (2 * w) * TILE, *v_tile = k_tile + TILE;
+    auto swizzle = [](int row) { return DH == 128 ? row & 15 : (row & 7) ^ ((row >> 3) & 1); };
+    auto fetch = [&](__amdgpu_buffer_rsrc_t rsrc, char *to, int k0) {
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) {
+            const int row = (lane + WAVE * i) / PIECES;
+            load16_to_lds(rsrc, to + 1024 * i, (uint32_t)min(k0 + row, last_key) * ROWB + 16u * (uint32_t)((lane % PIECES) ^ swizzle(row)), 0);
+        }
+    };
+    int k0 = 32 * w;
+    if (k0 <= last_key) { fetch(k_rsrc, k_tile, k0); fetch(v_rsrc, v_tile, k0); }
+
+    // Q through LDS: fetched by the row (a lane's own row fetched directly makes every load touch 64 cache lines)
+    char *q_tile = tiles + NWV * 2 * TILE;
+    constexpr int Q_PIECES = DH / 4;
+#pragma unroll
+    for (int i = 0; i < 32 * Q_PIECES / 256; ++i) {
+        const int row = (threadIdx.x + 256 * i) / Q_PIECES, piece = threadIdx.x % Q_PIECES;
+        const float4 v = global_load_float4(a.q + (size_t)min(q0 + row, a.T - 1) * nqd + (size_t)head * DH + 4 * piece);
+        *(float4 *)(q_tile + row * (DH * 4) + 16 * (piece ^ (row & 15))) = v;
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");           // (the tiles stay under way)
+    // this lane's operand values of Q: query q0 + c, features (DH / 2) h + 8 j + i
+    f16x8 qh[NJ], ql[NJ];
+    float unscale;
+    {
+        float q[NJ][8], top = 0.f;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int e = 0; e < 8; e += 4) {
+                const float4 v = *(const float4 *)(q_tile + c * (DH * 4) + 16 * (((DH / 8) * h + 2 * j + e / 4) ^ (c & 15)));
+                q[j][e] = v.x; q[j][e + 1] = v.y; q[j][e + 2] = v.z; q[j][e + 3] = v.w;
+            }
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) top = fmaxf(top, fabsf(q[j][e]));
+        top = fmaxf(top, __shfl_xor(top, 32));
+        int ex = 15;
+        if (top > 0.f && top < INFINITY) (void)frexpf(top, &ex);
+        ex = max(ex, -100);
+        const float up = ldexpf(1.f, 15 - ex);
+        unscale = ldexpf(1.f, ex - 15) * (1.0f / sqrtf((float)DH));
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                _Float16 hi, lo;
+                split_f16(q[j][e] * up, hi, lo);
+                qh[j][e] = hi; ql[j][e] = lo;
+            }
+    }
+    float m = -INFINITY, lsum = 0.f;
+    f32x16 o[NT];
+#pragma unroll
+    for (int dt = 0; dt < NT; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
+
+    for (; k0 <= last_key; k0 += 32 * NWV) {
+        const int next = k0 + 32 * NWV;
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS) : "memory");          // K of this tile is in LDS (V's loads are younger)
+        f32x16 st;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) st[r] = 0.f;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const f16x8 k = __builtin_bit_cast(f16x8, *(const u32x4 *)(k_tile + c * ROWB + 16 * (((PIECES / 2) * h + j) ^ swizzle(c))));
+            st = __builtin_amdgcn_mfma_f32_32x32x16_f16(k, qh[j], st, 0, 0, 0);
+            st = __builtin_amdgcn_mfma_f32_32x32x16_f16(k, ql[j], st, 0, 0, 0);
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                    // and has been read
+        if (next <= last_key) fetch(k_rsrc, k_tile, next);
+        float mx = m;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int key = k0 + 8 * (r / 4) + 4 * h + r % 4;
+            st[r] = key <= qpos ? st[r] * unscale : -INFINITY;
+            mx = fmaxf(mx, st[r]);
+        }
+        mx = fmaxf(mx, __shfl_xor(mx, 32));                  // the other half of the keys
+        // a query that sees none of this tile's keys and none before it: keep exp() away from inf - inf
+        const float ref = mx == -INFINITY ? 0.f : mx;
+        const float alpha = expf(m - ref);
+        float psum = 0.f;
+        f16x8 ph[2], pl[2];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const float p = expf(st[r] - ref);
+            psum += p;
+            _Float16 hi, lo;
+            split_f16(p * P_SCALE, hi, lo);
+            ph[r / 8][r % 8] = hi; pl[r / 8][r % 8] = lo;
+        }
+        lsum = lsum * alpha + psum;
+        m = mx;
+        if (__any(alpha != 1.f)) {
+#pragma unroll
+            for (int dt = 0; dt < NT; ++dt)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o[dt][r] *= alpha;
+        }
+        if (next <= last_key) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS) : "memory");   // V of this tile is in LDS (the next K's loads are younger)
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        // features NT c .. NT c + NT - 1 of eight keys, then turned round: eight keys of each feature
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            _Float16 v[8][NT];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int row = 8 * ((8 * j + i) / 4) + 4 * h + i % 4, byte = 2 * NT * c;
+                const char *from = v_tile + row * ROWB + 16 * ((byte / 16) ^ swizzle(row)) + byte % 16;
+                typedef _Float16 f16xn __attribute__((ext_vector_type(NT)));
+                const f16xn x = *(const f16xn *)from;
+#pragma unroll
+                for (int dt = 0; dt < NT; ++dt) v[i][dt] = x[dt];
+            }
+#pragma unroll
+            for (int dt = 0; dt < NT; ++dt) {
+                f16x8 vt;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) vt[i] = v[i][dt];
+                o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vt, ph[j], o[dt], 0, 0, 0);
+                o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vt, pl[j], o[dt], 0, 0, 0);
+            }
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (next <= last_key) fetch(v_rsrc, v_tile, next);
+    }
+
+    // merge: waves 2, 3 -> waves 0, 1; then all threads put those two together (over the tiles, which nobody needs any
+    // more).  Wave 0 holds key 0, visible to every query, so the merged maximum is finite.
+    auto put = [&](int slot) {
+        float *b = (float *)(tiles + slot * SLOT);
+        b[lane] = m; b[WAVE + lane] = lsum;
+#pragma unroll
+        for (int dt = 0; dt < NT; ++dt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) b[(2 + 16 * dt + r) * WAVE + lane] = o[dt][r];
+    };
+    auto take = [&](int slot) {
+        const float *b = (const float *)(tiles + slot * SLOT);
+        const float m2 = b[lane], mt = fmaxf(m, m2);
+        const float ref = mt == -INFINITY ? 0.f : mt;
+        const float f1 = expf(m - ref), f2 = expf(m2 - ref);
+        lsum = lsum * f1 + b[WAVE + lane] * f2;
+#pragma unroll
+        for (int dt = 0; dt < NT; ++dt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[dt][r] = o[dt][r] * f1 + b[(2 + 16 * dt + r) * WAVE + lane] * f2;
+        m = mt;
+    };
+    __syncthreads();
+    if (w >= 2) put(w - 2);
+    __syncthreads();
+    if (w < 2) take(w);
+    __syncthreads();
+    if (w < 2) put(w);
+    __syncthreads();
+    // thread -> query c, features F (tid / 32) .. + F - 1; row rho of product tile dt is feature NT rho + dt
+    constexpr int F = DH / 8;
+    const float *b0 = (const float *)tiles, *b1 = (const float *)(tiles + SLOT);
+    const int qc = threadIdx.x % 32, f0 = F * (threadIdx.x / 32), t = q0 + qc;
+    const float mt = fmaxf(b0[qc], b1[qc]);
+    const float f1 = expf(b0[qc] - mt), f2 = expf(b1[qc] - mt);
+    const float inv = 1.0f / (((b0[WAVE + qc] + b0[WAVE + 32 + qc]) * f1 + (b1[WAVE + qc] + b1[WAVE + 32 + qc]) * f2) * P_SCALE);
+#pragma unroll
+    for (int e0 = 0; e0 < F; e0 += 8) {
+        float y[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int f = f0 + e0 + e, dt = f % NT, rho = f / NT, r = 4 * (rho / 8) + rho % 4, at = (2 + 16 * dt + r) * WAVE + 32 * ((rho / 4) % 2) + qc;
+            y[e] = (b0[at] * f1 + b1[at] * f2) * inv;
+        }
+        if (t < a.T) split_store8(a.ohi, a.olo, (size_t)t * nqd + head * DH + f0 + e0, y);
+    }
+}
+
+template <int DH> constexpr int attn_f16_lds() { return 4 * 2 * 32 * DH * 2 + 32 * DH * 4; }
+
 }  // namespace
 
 namespace spdk {
 
 size_t prefill_attn_lds(int d_head) { return (size_t)(AQ * (d_head + 4) + AK * (d_head + 4) + AK * d_head + AQ * (AK + 1)) * sizeof(float); }
 
-// The tile shapes: one block of 8 waves per compute unit, k steps of 64.  `step_us` is what a step takes a block when
+// The tile shapes: one block per compute unit, k steps of 64.  `step_us` is what a step takes a block when
 // all compute units have one (sweeps over tiles of 64 .. 512 columns, k steps of 32 / 64 / 128, 2 .. 10 stages, 4, 8 and
 // 16 waves; at 128 tokens the products bound it -- 1130 .. 1230 TFLOP/s over the chip, a large library product reaches
 // 1220 -- and at 32 what one compute unit pulls of the weights).
 constexpr int KS = 64;
-struct Tile { int bm, bn, stages; double step_us; };
-constexpr Tile TILES[] = {{32, 256, 4, 0.78}, {64, 256, 3, 0.95}, {64, 384, 2, 1.40}, {128, 256, 2, 1.86}, {128, 384, 2, 2.62}};
-constexpr int N_TILES = 5;
+struct Tile { int bm, bn, stages, waves; double step_us; };
+constexpr Tile TILES[] = {{32, 256, 4, 8, 0.78}, {64, 256, 3, 8, 0.95}, {64, 384, 2, 8, 1.40}, {128, 256, 2, 8, 1.86},
+                          {128, 384, 2, 8, 2.62}, {64, 128, 4, 4, 0.72}, {32, 128, 5, 2, 0.60}};
+constexpr int N_TILES = 7;
 constexpr int tile_lds(int i) { return TILES[i].stages * (2 * TILES[i].bm + TILES[i].bn) * KS * 2; }
 
 typedef void (*GemmFn)(PrefillGemmArgs);
@@ -672,7 +906,9 @@ template <int EPI> static GemmFn gemm_kernel(int tile) {
         case 1: return prefill_gemm_kernel<EPI, 2, 4, 1, 2, KS, 3, true>;
         case 2: return GU ? nullptr : prefill_gemm_kernel<GU ? (int)PE_PART : EPI, 2, 4, 1, 3, KS, 2, true>;
         case 3: return prefill_gemm_kernel<EPI, 2, 4, 2, 2, KS, 2, false>;
-        default: return GU ? nullptr : prefill_gemm_kernel<GU ? (int)PE_PART : EPI, 2, 4, 2, 3, KS, 2, false>;
+        case 4: return GU ? nullptr : prefill_gemm_kernel<GU ? (int)PE_PART : EPI, 2, 4, 2, 3, KS, 2, false>;
+        case 5: return prefill_gemm_kernel<EPI, 2, 2, 1, 2, KS, 4, true>;
+        default: return prefill_gemm_kernel<EPI, 1, 2, 1, 2, KS, 5, true>;
     }
 }
 
@@ -697,7 +933,7 @@ static Cut cut_product(const PrefillChunk &c, int T, int N, int mats, int K, int
             const int n_tiles = fused && epi == PE_SWIGLU ? (2 * N + t.bn - 1) / t.bn : (N + t.bn - 1) / t.bn;
             const int blocks = t_tiles * n_tiles * splits * (fused ? 1 : mats);
             double us = std::max(t.step_us * split_steps * ((blocks + c.num_cu - 1) / c.num_cu), (double)N * K * mats * 2 / 5.5e6);
-            if (!fused) us += (double)splits * T * N * mats * 8 / 4e6 + (epi == PE_PART ? 0.0 : 4.0);
+            if (!fused) us += (double)splits * T * N * mats * 8 / 4e6 + (epi == PE_PART ? 0.0 : 6.0);
             if (us < best_us) { best_us = us; best = Cut{tile, t_tiles, n_tiles, splits, split_steps, fused}; }
         }
     }
@@ -707,12 +943,13 @@ static Cut cut_product(const PrefillChunk &c, int T, int N, int mats, int K, int
 static void launch_gemm(hipStream_t s, GemmFn kernel, PrefillGemmArgs &a, const Cut &cut, int mats) {
     a.t_tiles = cut.t_tiles; a.n_tiles = cut.n_tiles; a.splits = cut.splits; a.split_steps = cut.split_steps;
     const int cols = cut.n_tiles * mats * cut.splits;
-    hipLaunchKernelGGL(kernel, dim3((cols + 7) / 8 * 8 * cut.t_tiles), dim3(512), tile_lds(cut.tile), s, a);
+    hipLaunchKernelGGL(kernel, dim3((cols + 7) / 8 * 8 * cut.t_tiles), dim3(TILES[cut.tile].waves * WAVE), tile_lds(cut.tile), s, a);
 }
 
 hipError_t prefill_init() {
     hipError_t e = hipFuncSetAttribute((const void *)prefill_attn_kernel<float>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)prefill_attn_lds(128));
     if (e == hipSuccess) e = hipFuncSetAttribute((const void *)prefill_attn_kernel<half_t>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)prefill_attn_lds(128));
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void *)prefill_attn_f16_kernel<128>, hipFuncAttributeMaxDynamicSharedMemorySize, attn_f16_lds<128>());
     for (int tile = 0; tile < N_TILES; ++tile)
         for (GemmFn k : {gemm_kernel<PE_PART>(tile), gemm_kernel<PE_QKV>(tile), gemm_kernel<PE_SWIGLU>(tile)})
             if (e == hipSuccess && k != nullptr) e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, tile_lds(tile));
@@ -750,8 +987,8 @@ hipError_t prefill_chunk(hipStream_t s, const PrefillChunk &c) {
         PrefillAttnArgs at{c.q, g.kcache, g.vcache, c.xhi, c.xlo, T, c.p0, c.n_heads, c.n_kv_heads, dh, c.cap_ctx};
         const dim3 mfma_grid(((T + 31) / 32) * ((c.n_heads + 7) / 8) * 8), plain_grid((T + AQ - 1) / AQ, c.n_heads);
         if (c.kv_half) {
-            if (dh == 128) hipLaunchKernelGGL((prefill_attn_mfma_kernel<128, half_t>), mfma_grid, dim3(256), 0, s, at);
-            else if (dh == 64) hipLaunchKernelGGL((prefill_attn_mfma_kernel<64, half_t>), mfma_grid, dim3(256), 0, s, at);
+            if (dh == 128) hipLaunchKernelGGL(prefill_attn_f16_kernel<128>, mfma_grid, dim3(256), attn_f16_lds<128>(), s, at);
+            else if (dh == 64) hipLaunchKernelGGL(prefill_attn_f16_kernel<64>, mfma_grid, dim3(256), attn_f16_lds<64>(), s, at);
             else hipLaunchKernelGGL(prefill_attn_kernel<half_t>, plain_grid, dim3(ANT), prefill_attn_lds(dh), s, at);
         } else {
             if (dh == 128) hipLaunchKernelGGL((prefill_attn_mfma_kernel<128, float>), mfma_grid, dim3(256), 0, s, at);

@@ -358,6 +358,31 @@ def test_fp16_cache_dense_prefix_pass(m):
     assert np.max(np.abs(logits[True] - logits[False])) <= 1e-3 * np.max(np.abs(logits[False]))
 
 
+@pytest.mark.parametrize("heads,m", [(4, 65), (8, 131)])
+def test_fp16_cache_prefix_attention_does_not_depend_on_the_scale_of_queries(heads, m):
+    """The prefix pass's attention over the fp16 cache splits a query's row into two fp16 numbers after scaling it by
+    a power of two.  Queries 2^-8 and 2^4 times as large against keys scaled the other way leave the scores as they are,
+    up to the fp16 rounding of keys that become subnormal (6e-8 in a few of them)."""
+    pkg = P()
+    shape = synth.ModelShape("small-bf16-dense", 2, 512, heads, heads, 1408, 1024, "bf16")
+    prefix = synth.make_prefix_zipf(shape.vocab, m, seed=m)
+    logits = []
+    for q_scale, k_scale in ((0, 0), (-8, 8), (4, -4)):
+        w = synth.make_weights(shape, seed=3)
+        for l in range(shape.n_layers):
+            for name, scale in (("wq", q_scale), ("wk", k_scale)):
+                key = f"layers.{l}.{name}"
+                w[key] = synth.bf16_bits(synth.bf16_widen(w[key]) * np.float32(2.0 ** scale)).reshape(w[key].shape)
+        sess = session(shape, w, max_ctx=m + 4, kv_dtype="fp16")
+        try:
+            sess.spd_prefill(prefix)
+            logits.append(sess.spd_read_logits())
+        finally:
+            sess.close()
+    for z in logits[1:]:
+        assert np.max(np.abs(z - logits[0])) <= 1e-5 * np.max(np.abs(logits[0]))
+
+
 def test_fp16_cache_head_width_32_plain_prefix_attention():
     """d_head 32: the prefix pass uses its plain (not matrix-core) attention kernel."""
     shape = synth.ModelShape("small-bf16-dh32", 2, 256, 8, 4, 512, 1024, "bf16")
