@@ -242,6 +242,9 @@ constexpr int ATTN_CHUNK = 128;        // stand-alone attention: its scratch has
 constexpr int ATTN_CHUNK_MIN = 64;    // the fused kernel picks the chunk per step within these bounds
 constexpr int ATTN_CHUNK_MAX = 512;
 
+// p[0 .. n) = v
+struct FillRange { int32_t *p; int32_t v, n; };
+
 namespace spdk {
 hipError_t gemv(hipStream_t s, int dtype, int epi, const GemvArgs &a, int num_cu);
 size_t gemv_lds_bytes(int dtype, int cols);
@@ -255,6 +258,7 @@ hipError_t prefill_init();
 hipError_t advance(hipStream_t s, DevState *st);
 hipError_t renorm(hipStream_t s, DevState *st, int k);
 hipError_t fill_i32(hipStream_t s, int32_t *p, int32_t v, int n);
+hipError_t fill3_i32(hipStream_t s, const FillRange &a, const FillRange &b, const FillRange &c);   // one launch
 // Fused forward: 0 if no instantiation serves this shape, else resident blocks per CU.
 int fused_max_blocks_per_cu(int dtype, int kv_half, int d_model, int d_ffn);
 hipError_t fused_forward(hipStream_t s, int dtype, const FusedArgsHost &a, int blocks);

@@ -669,6 +669,13 @@ __global__ void fill_i32_kernel(int32_t *p, int32_t v, int n) {
     if (i < n) p[i] = v;
 }
 
+__global__ void fill3_i32_kernel(FillRange a, FillRange b, FillRange c) {
+    const int at = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
+    for (int i = at; i < a.n; i += step) a.p[i] = a.v;
+    for (int i = at; i < b.n; i += step) b.p[i] = b.v;
+    for (int i = at; i < c.n; i += step) c.p[i] = c.v;
+}
+
 template <typename WT, int EPI>
 hipError_t gemv_launch(hipStream_t s, const GemvArgs &a, int num_cu, size_t lds) {
     const int units = EPI == EPI_SWIGLU ? a.rows : a.rows / 2;
@@ -766,6 +773,12 @@ hipError_t renorm(hipStream_t s, DevState *st, int k) {
 
 hipError_t fill_i32(hipStream_t s, int32_t *p, int32_t v, int n) {
     hipLaunchKernelGGL(fill_i32_kernel, dim3((n + 255) / 256), dim3(256), 0, s, p, v, n);
+    return hipGetLastError();
+}
+
+hipError_t fill3_i32(hipStream_t s, const FillRange &a, const FillRange &b, const FillRange &c) {
+    const int most = std::max(a.n, std::max(b.n, c.n));
+    hipLaunchKernelGGL(fill3_i32_kernel, dim3(std::max(1, std::min((most + 255) / 256, 2048))), dim3(256), 0, s, a, b, c);
     return hipGetLastError();
 }
 

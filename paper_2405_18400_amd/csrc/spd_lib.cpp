@@ -318,10 +318,9 @@ hipError_t enqueue_sample(spd_ctx *c, const spd_sample_cfg &sc, float u, const f
 // counters of the attention merge, which a launch that gave up on a wait may have left short
 // of the count that resets them).
 hipError_t reset_fused_state(spd_ctx *c) {
-    hipError_t e = spdk::fill_i32(c->stream, c->at<int32_t>(c->L.sync), 0, SYNC_WORDS);
-    if (e == hipSuccess) e = spdk::fill_i32(c->stream, c->at<int32_t>(c->L.counters), 0, c->cfg.n_heads * ATTN_COUNTER_STRIDE);
-    if (e == hipSuccess) e = spdk::fill_i32(c->stream, c->at<int32_t>(c->L.act), (int32_t)ACT_UNSET, (int)(2 * c->L.arena_bytes / 4));
-    return e;
+    return spdk::fill3_i32(c->stream, FillRange{c->at<int32_t>(c->L.sync), 0, SYNC_WORDS},
+                           FillRange{c->at<int32_t>(c->L.counters), 0, c->cfg.n_heads * ATTN_COUNTER_STRIDE},
+                           FillRange{c->at<int32_t>(c->L.act), (int32_t)ACT_UNSET, (int)(2 * c->L.arena_bytes / 4)});
 }
 
 void drop_graph(hipGraphExec_t &g) {
@@ -531,7 +530,9 @@ static int run_prefix_pass(spd_ctx *c, int p0, int m) {
     HIPCHK(c, hipStreamSynchronize(c->stream));   // the pinned staging area may still be in flight
     DevState *hs = (DevState *)c->pinned;
     std::memset(hs, 0, sizeof(DevState));
-    hs->pos = p0;
+    const int n = m - p0;
+    const bool dense = c->use_dense && n >= DENSE_PREFILL_MIN;
+    hs->pos = dense ? m : p0;      // (the dense pass takes its positions from the host)
     for (int q = 0; q < SPD_TAIL; ++q) {
         const int src = m - SPD_TAIL + q;
         hs->prefix_tail[q] = src >= 0 ? c->text[src] : NG_PAD;
@@ -545,9 +546,8 @@ static int run_prefix_pass(spd_ctx *c, int p0, int m) {
     HIPCHK(c, hipMemcpyAsync(c->ws + c->L.prefix + (size_t)p0 * 4, hp, (size_t)(m - p0) * 4, hipMemcpyHostToDevice, c->stream));
     c->state = ST_CREATED;
     c->pos = p0; c->n_gen = 0; c->k = 0;
-    const int n = m - p0;
 
-    if (c->use_dense && n >= DENSE_PREFILL_MIN) {
+    if (dense) {
         // whole chunks of prefix tokens on the matrix cores; the last token's final norm and
         // LM head go through the matrix-vector kernel
         const spd_model_cfg &mc = c->cfg;
@@ -569,7 +569,6 @@ static int run_prefix_pass(spd_ctx *c, int p0, int m) {
         g.W = c->lm_head; g.gain = c->final_norm; g.eps = mc.rms_eps; g.x = pc.h + (size_t)(last_T - 1) * mc.d_model;
         g.y = c->at<float>(c->L.logits); g.rows = mc.vocab; g.cols = mc.d_model;
         HIPCHK(c, spdk::gemv(c->stream, mc.dtype, EPI_PLAIN, g, c->num_cu));
-        HIPCHK(c, spdk::fill_i32(c->stream, &c->st()->pos, m, 1));
         c->pos = m;
         c->state = ST_PREFILLED;
         return SPD_OK;

@@ -22,12 +22,6 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 namespace {
 
-// One element of the key/value cache (fp32, or fp16 rounded to nearest even).
-__device__ __forceinline__ void kv_put(void *cache, int kv_half, size_t at, float v) {
-    if (kv_half) Store<half_t>::store1(cache, at, v);
-    else as_global((float *)cache)[at] = v;
-}
-
 __device__ __forceinline__ uint16_t bf16_rn(float v) {
     uint32_t u = __float_as_uint(v);
     u += 0x7FFFu + ((u >> 16) & 1u);
@@ -162,22 +156,37 @@ struct PrefillGemmArgs {
     uint16_t *uhi, *ulo;         // PE_SWIGLU: [T, N]
 };
 
-// Token t's value v of row nc of the fused QKV product, `other` its rotary partner's (row nc ^ 1): rotated, to q or
-// the cache.
-__device__ __forceinline__ void qkv_put(const PrefillGemmArgs &a, int t, int nc, float v, float other) {
-    const bool rotates = nc < a.n_q_rows + a.n_kv_rows;
-    if (rotates) {
-        const size_t ri = 2 * ((size_t)t * (a.d_head / 2) + (nc % a.d_head) / 2);
-        const float cs_x = as_global((const float *)a.rope)[ri], cs_y = as_global((const float *)a.rope)[ri + 1];
-        v = (nc & 1) ? __fadd_rn(__fmul_rn(other, cs_y), __fmul_rn(v, cs_x)) : __fsub_rn(__fmul_rn(v, cs_x), __fmul_rn(other, cs_y));
+// Row nc of the fused QKV product: what its values become, and where they go.  `other` is the value of the rotary
+// partner (row nc ^ 1).
+struct QkvRow {
+    bool rotates, odd, is_q;
+    int pair;                    // of the head's rotary pairs
+    char *to;                    // token 0's element
+    size_t stride;               // elements from token to token
+    __device__ __forceinline__ QkvRow(const PrefillGemmArgs &a, int nc) {
+        rotates = nc < a.n_q_rows + a.n_kv_rows; odd = nc & 1; is_q = nc < a.n_q_rows;
+        const int rr = is_q ? nc : rotates ? nc - a.n_q_rows : nc - a.n_q_rows - a.n_kv_rows;
+        const int head = rr / a.d_head, f = rr % a.d_head;
+        pair = f / 2;
+        if (is_q) {
+            to = (char *)(a.q + nc);
+            stride = (size_t)a.n_q_rows;
+        } else {
+            to = (char *)(rotates ? a.kcache : a.vcache) + (((size_t)head * a.cap_ctx + a.p0) * a.d_head + f) * (a.kv_half ? 2 : 4);
+            stride = (size_t)a.d_head;
+        }
     }
-    if (nc < a.n_q_rows) {
-        as_global(a.q)[(size_t)t * a.n_q_rows + nc] = v;
-        return;
+    __device__ __forceinline__ float2 angle(const PrefillGemmArgs &a, int t) const {     // (cos, sin); only asked for where it rotates
+        typedef float f32x2 __attribute__((ext_vector_type(2)));
+        const f32x2 cs = *(const f32x2 __attribute__((address_space(1))) *)(a.rope + (size_t)t * (a.d_head / 2) + pair);
+        return make_float2(cs.x, cs.y);
     }
-    const int rr = rotates ? nc - a.n_q_rows : nc - a.n_q_rows - a.n_kv_rows;
-    kv_put(rotates ? a.kcache : a.vcache, a.kv_half, ((size_t)(rr / a.d_head) * a.cap_ctx + a.p0 + t) * a.d_head + rr % a.d_head, v);
-}
+    __device__ __forceinline__ void put(const PrefillGemmArgs &a, int t, float v, float other, float2 cs) const {
+        if (rotates) v = odd ? __fadd_rn(__fmul_rn(other, cs.y), __fmul_rn(v, cs.x)) : __fsub_rn(__fmul_rn(v, cs.x), __fmul_rn(other, cs.y));
+        if (is_q || !a.kv_half) as_global((float *)to)[(size_t)t * stride] = v;
+        else Store<half_t>::store1(to, (size_t)t * stride, v);
+    }
+};
 
 // A block of WM x WN waves makes a tile of BM = 32 TT WM tokens x BN = 32 NT WN columns; a wave's share is
 // TT x NT accumulators of 32 x 32.  Per step of KS k the tile's operands (x hi, x lo, W: rows of KS elements)
@@ -189,7 +198,7 @@ __device__ __forceinline__ void qkv_put(const PrefillGemmArgs &a, int t, int nc,
 // What bounds it: with 128-token tiles the matrix cores at the clock they hold under such products; with few tokens
 // the weight stream (HBM) and each launch's ramp.  A kernel of 64-token tiles whose waves each turned their own 32 weight
 // rows round in LDS (160 bytes of LDS traffic per cycle wanted, 128 there) and, up to 96 tokens, one whose
-// waves split k, did it before; before -> after, us: 1024 tokens, 12288 x 4096: 290 -> 168 (200 with the rotary
+// waves split k, did it before; before -> after, us: 1024 tokens, 12288 x 4096: 290 -> 168 (187 with the rotary
 // epilogue); gate and up 2 x 11008 x 4096: 410 -> 335; 4096 x 11008: 248 -> 160; 256 tokens, 5120 x 13824: 214 -> 77;
 // 64 tokens, 12288 x 4096: 50 -> 24 (4.3 TB/s); gate and up: 73 -> 43; 4096 x 11008: 62 -> 25.  Weights go past
 // the L2's keep list (STREAM_W) where few token tiles read them: 5 % at 64 tokens; at 1024 it costs 2 %.
@@ -302,18 +311,25 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN >= 4 ? WM * WN / 4 : 1) void 
 
     // C layout: lane -> column, register r -> token 8 (r / 4) + 4 (lane / 32) + r % 4
 #pragma unroll
-    for (int nt = 0; nt < NG; ++nt)
+    for (int nt = 0; nt < NG; ++nt) {
+        const int nc = n0 + 32 * (NG * wn + nt) + lane % 32;
+        const QkvRow row(a, EPI == PE_QKV ? nc : 0);
 #pragma unroll
-        for (int tt = 0; tt < TT; ++tt)
+        for (int tt = 0; tt < TT; ++tt) {
+            const int tb = t0 + 32 * (TT * wm + tt) + 4 * (lane / 32);
+            float2 cs[16];
+            if (EPI == PE_QKV && row.rotates) {    // (one trip for all sixteen)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) cs[r] = row.angle(a, min(tb + 8 * (r / 4) + r % 4, a.T - 1));
+            }
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int t = t0 + 32 * (TT * wm + tt) + 8 * (r / 4) + 4 * (lane / 32) + (r % 4);
-                const int nc = n0 + 32 * (NG * wn + nt) + lane % 32;
+                const int t = tb + 8 * (r / 4) + (r % 4);
                 const float v = acc[nt][tt][r];
                 const bool exists = t < a.T && nc < a.N;
                 if (EPI == PE_QKV) {
                     const float other = dpp_move<0xB1, 0xF>(v, 0.f);   // the rotary partner's column sits in the neighbouring lane
-                    if (exists) qkv_put(a, t, nc, v, other);
+                    if (exists) row.put(a, t, v, other, cs[r]);
                 } else if (EPI == PE_PART) {
                     const size_t ld = (size_t)a.N * n_mats;
                     if (exists) as_global(a.part)[((size_t)split * a.T + t) * ld + (second ? a.N : 0) + nc] = v;
@@ -322,6 +338,8 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN >= 4 ? WM * WN / 4 : 1) void 
                     split_store(a.uhi, a.ulo, (size_t)t * a.N + nc, v / (1.0f + expf(-v)) * up);
                 }
             }
+        }
+    }
 }
 
 // The partial sums of a split QKV product, added in split order, through its epilogue.  A thread has a rotary pair.
@@ -340,8 +358,10 @@ __global__ __launch_bounds__(256) void prefill_qkv_sum_kernel(const PrefillGemmA
         for (int q = 0; q < 4; ++q)
             if (s + q < a.splits) { v0 += p0[q]; v1 += p1[q]; }
     }
-    qkv_put(a, t, nc, v0, v1);
-    qkv_put(a, t, nc + 1, v1, v0);
+    const QkvRow even(a, nc), odd(a, nc + 1);
+    const float2 cs = even.rotates ? even.angle(a, t) : make_float2(1.f, 0.f);
+    even.put(a, t, v0, v1, cs);
+    odd.put(a, t, v1, v0, cs);
 }
 
 // The same for gate and up: SiLU(gate) * up as the (hi, lo) pair.  A thread has 8 units.
@@ -894,7 +914,7 @@ size_t prefill_attn_lds(int d_head) { return (size_t)(AQ * (d_head + 4) + AK * (
 constexpr int KS = 64;
 struct Tile { int bm, bn, stages, waves; double step_us; };
 constexpr Tile TILES[] = {{32, 256, 4, 8, 0.78}, {64, 256, 3, 8, 0.95}, {64, 384, 2, 8, 1.40}, {128, 256, 2, 8, 1.86},
-                          {128, 384, 2, 8, 2.62}, {64, 128, 4, 4, 0.72}, {32, 128, 5, 2, 0.60}};
+                          {128, 384, 2, 8, 2.62}, {64, 128, 4, 4, 0.76}, {32, 128, 5, 2, 0.60}};
 constexpr int N_TILES = 7;
 constexpr int tile_lds(int i) { return TILES[i].stages * (2 * TILES[i].bm + TILES[i].bn) * KS * 2; }
 
