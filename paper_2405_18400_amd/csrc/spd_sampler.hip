@@ -25,6 +25,8 @@
 //   The first-level histogram serves both questions.
 #include "spd_device.h"
 
+#include <type_traits>
+
 using namespace spdd;
 
 namespace {
@@ -58,7 +60,11 @@ struct Stage {                                  // LDS of stage B
     int r_id;                                   // result of a search: the entry, its cumulative mass, its position in the order
     unsigned long long r_mass, r_key;
     unsigned r_index;
+    float r_logit;
     int is_last;
+    int q_bucket[2];                            // the two questions' crossings in the first-level histogram: the bucket (or -1),
+    unsigned long long q_from[2], q_to[2];      // and the prefix sums before and behind it
+    float ll[LC];                               // the list's logits
 };
 
 // A histogram word: entry count (20 bits: vocab <= 2^20... the sums of all masses stay below
@@ -68,10 +74,10 @@ constexpr unsigned long long ONE_ENTRY = 1ull << CNT_SHIFT;
 __device__ __forceinline__ unsigned long long mass_of(unsigned long long w) { return w & (ONE_ENTRY - 1ull); }
 __device__ __forceinline__ unsigned count_of(unsigned long long w) { return (unsigned)(w >> CNT_SHIFT); }
 
-// In place: hm (NB values) -> exclusive prefix sums, totals at index NB.
-__device__ __forceinline__ void prefix_sums(Stage &s, int lv) {
+// hm (NB values, this thread's two given) -> exclusive prefix sums, totals at index NB; this thread's three come back in
+// registers, everybody's are in LDS after the next barrier.
+__device__ __forceinline__ void prefix_sums(Stage &s, int lv, unsigned long long a0, unsigned long long a1, unsigned long long (&out)[3]) {
     const int t = threadIdx.x, lane = t & (WAVE - 1), w = t / WAVE;
-    const unsigned long long a0 = s.hm[lv][2 * t], a1 = s.hm[lv][2 * t + 1];
     unsigned long long m = a0 + a1;
 #pragma unroll
     for (int o = 1; o < WAVE; o <<= 1) {        // inclusive scan over the wave
@@ -85,7 +91,7 @@ __device__ __forceinline__ void prefix_sums(Stage &s, int lv) {
     const unsigned long long em = pm + m - (a0 + a1);
     s.hm[lv][2 * t] = em; s.hm[lv][2 * t + 1] = em + a0;
     if (t == SNT - 1) s.hm[lv][NB] = em + a0 + a1;
-    __syncthreads();
+    out[0] = em; out[1] = em + a0; out[2] = em + a0 + a1;
 }
 
 // The bucket in which the cumulative mass first reaches x (STRICT: exceeds x), or, if the
@@ -246,7 +252,9 @@ __device__ __forceinline__ void search(Stage &s, Entries<CACHED> &en, unsigned l
             }
         });
         __syncthreads();
-        prefix_sums(s, 1);
+        unsigned long long sums[3];
+        prefix_sums(s, 1, s.hm[1][2 * t], s.hm[1][2 * t + 1], sums);
+        __syncthreads();
         const int b2 = crossing<STRICT>(s, 1, x - base_m);          // (x >= base_m: the crossing lies in this range or beyond everything)
         base_m += mass_of(s.hm[1][b2]);
         base_c += count_of(s.hm[1][b2]);
@@ -299,6 +307,61 @@ __device__ __forceinline__ void search(Stage &s, Entries<CACHED> &en, unsigned l
         s.r_mass = base_m + s.lcum[t];
         s.r_index = base_c + (unsigned)pick;
     }
+    __syncthreads();
+}
+
+// The same question where the crossing bucket of the first-level histogram fits the list (nearly always): three barriers
+// instead of nine.  w[0 .. 2]: the prefix sums around this thread's two buckets, still in its registers; the bucket's
+// entry whose cumulative mass crosses x is the one that reaches it while the entry before does not, which each entry
+// knows by itself once it has its rank and mass.  Slots of Stage are per question, cleared beforehand.  32000 entries, the kernel:
+// 15.2 -> 13.2 us.
+template <bool STRICT, bool CACHED>
+__device__ __forceinline__ void ask(Stage &s, Entries<CACHED> &en, const float *logits, int which, unsigned long long x, const unsigned long long (&w)[3]) {
+    const int t = threadIdx.x;
+    auto reaches = [&](unsigned long long m) { return STRICT ? m > x : m >= x; };
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+        if (!reaches(mass_of(w[q])) && reaches(mass_of(w[q + 1]))) { s.q_bucket[which] = 2 * t + q; s.q_from[which] = w[q]; s.q_to[which] = w[q + 1]; }
+    __syncthreads();
+    const int b1 = s.q_bucket[which];
+    const unsigned long long from = s.q_from[which];
+    const unsigned base_c = count_of(from);
+    if (b1 < 0 || count_of(s.q_to[which]) - base_c > (unsigned)LC) {   // (the same for every thread)
+        search<STRICT, CACHED>(s, en, x);
+        if (t == 0) s.r_logit = as_global(logits)[s.r_id];
+        __syncthreads();
+        return;
+    }
+    en.walk_bucket(b1, [&](int i, unsigned long long pf) {
+        const float l = as_global(logits)[i];
+        const int at = atomicAdd(&s.n_list, 1);
+        s.lk[at] = sort_key(pf, i); s.lp[at] = pf; s.lid[at] = i; s.ll[at] = l;
+    });
+    __syncthreads();
+    const int nl = s.n_list;
+    auto rank = [&](auto parts) {      // PARTS lanes side by side compare an entry with every PARTS-th one each
+        constexpr int PARTS = decltype(parts)::value;
+        const int i = t / PARTS, part = t % PARTS;
+        unsigned cnt = 0u;
+        unsigned long long mass = 0ull;
+        if (i < nl) {
+            const unsigned long long ki = s.lk[i];
+            for (int j = part; j < nl; j += PARTS)
+                if (s.lk[j] < ki) { ++cnt; mass += s.lp[j]; }
+        }
+#pragma unroll
+        for (int o = PARTS / 2; o > 0; o >>= 1) { cnt += __shfl_xor(cnt, o, WAVE); mass += __shfl_xor(mass, o, WAVE); }
+        if (i < nl && part == 0) {
+            const unsigned long long before = mass_of(from) + mass, tot = before + s.lp[i];
+            const bool crosses = reaches(tot) && (cnt == 0u || !reaches(before));
+            if (crosses || (cnt == (unsigned)nl - 1u && !reaches(tot))) {   // (nothing reaches x: the last entry)
+                s.r_id = s.lid[i]; s.r_key = s.lk[i]; s.r_logit = s.ll[i];
+                s.r_mass = tot; s.r_index = base_c + cnt;
+            }
+        }
+    };
+    if (nl <= 64) rank(std::integral_constant<int, 16>());
+    else rank(std::integral_constant<int, 4>());
     __syncthreads();
 }
 
@@ -360,44 +423,47 @@ __global__ __launch_bounds__(SNT) void nucleus_kernel(const NucleusArgs a) {
     for (int q = 0; q < SPD_TAIL; ++q) tail[q] = a.first ? st->prefix_tail[q] : st->tails[0][q];
     Entries<CACHED> en;
     en.pb = a.sc_pb; en.vocab = a.vocab;
+    if (tid == 0) { s.q_bucket[0] = s.q_bucket[1] = -1; s.n_list = 0; }
+    unsigned long long h0, h1, sums[3];
     if constexpr (CACHED) {
         // the histogram all blocks have added to (left at zero for the next call), and this thread's bucket numbers
-        {   // one 16-byte piece: this thread's two words
-            const __amdgpu_buffer_rsrc_t hrs = __builtin_amdgcn_make_buffer_rsrc(a.sc_hist, 0, NB * 8, 0x00020000);
-            const u32x4 v = coherent_load16(hrs, 16u * (unsigned)tid);
-            en.load_buckets(a.sc_bk);
-            s.hm[0][2 * tid] = ((unsigned long long)v.y << 32) | v.x;
-            s.hm[0][2 * tid + 1] = ((unsigned long long)v.w << 32) | v.z;
-        }
+        const __amdgpu_buffer_rsrc_t hrs = __builtin_amdgcn_make_buffer_rsrc(a.sc_hist, 0, NB * 8, 0x00020000);
+        const u32x4 v = coherent_load16(hrs, 16u * (unsigned)tid);   // one 16-byte piece: this thread's two words
+        en.load_buckets(a.sc_bk);
+        h0 = ((unsigned long long)v.y << 32) | v.x;
+        h1 = ((unsigned long long)v.w << 32) | v.z;
     } else {
         s.hm[0][2 * tid] = 0ull; s.hm[0][2 * tid + 1] = 0ull;
         __syncthreads();
         en.first_walk([&](int, int b, unsigned long long pf) {
             atomicAdd(&s.hm[0][b], pf + ONE_ENTRY);
         });
+        __syncthreads();
+        h0 = s.hm[0][2 * tid]; h1 = s.hm[0][2 * tid + 1];
     }
-    __syncthreads();
-    prefix_sums(s, 0);
+    prefix_sums(s, 0, h0, h1, sums);
 
     // 1. the nucleus: the first entry whose cumulative probability reaches top_p, and all before it
     const unsigned long long x_p = (unsigned long long)((double)a.top_p * (double)FX_ONE);
-    search<false, CACHED>(s, en, x_p);
+    ask<false, CACHED>(s, en, a.logits, 0, x_p, sums);
     const unsigned long long mass_fx = s.r_mass, key_T = s.r_key;
     const unsigned size = s.r_index + 1u;
     const int id_T = s.r_id;
-    __syncthreads();
+    const float logit_T = s.r_logit;
+    if (tid == 0) s.n_list = 0;     // (everybody has read it; the next barrier stands before its next use)
     // 2. the draw: the first entry whose cumulative probability exceeds u * mass (within the nucleus)
     const unsigned long long x_u = (unsigned long long)((double)u * (double)mass_fx);
-    search<true, CACHED>(s, en, x_u);
+    ask<true, CACHED>(s, en, a.logits, 1, x_u, sums);
     int tok = s.r_id;
-    if (s.r_key > key_T) tok = id_T;   // (only rounding could take it past the nucleus)
+    float logit = s.r_logit;
+    if (s.r_key > key_T) { tok = id_T; logit = logit_T; }   // (only rounding could take it past the nucleus)
 
     if (CACHED) {
         __hip_atomic_store(as_global(a.sc_hist) + 2 * tid, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(as_global(a.sc_hist) + 2 * tid + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (tid == 0) {   // the pass's state: one draft (k = 1, gamma = 1)
-        const float logp = __fdiv_rn(as_global(a.logits)[tok], a.tau) - lse;
+        const float logp = __fdiv_rn(logit, a.tau) - lse;
 #pragma unroll
         for (int q = 0; q < SPD_TAIL - 1; ++q) st->tails[0][q] = tail[q + 1];
         st->tails[0][SPD_TAIL - 1] = tok;
