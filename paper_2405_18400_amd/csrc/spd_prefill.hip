@@ -14,6 +14,7 @@
 #include "spd_device.h"
 
 #include <algorithm>
+#include <cmath>
 
 using namespace spdd;
 
@@ -903,7 +904,7 @@ size_t prefill_attn_lds(int d_head) { return (size_t)(AQ * (d_head + 4) + AK * (
 // 1220 -- and at 32 what one compute unit pulls of the weights).
 constexpr int KS = 64;
 struct Tile { int bm, bn, stages, waves; double step_us; };
-constexpr Tile TILES[] = {{32, 256, 4, 8, 0.78}, {64, 256, 3, 8, 0.95}, {64, 384, 2, 8, 1.40}, {128, 256, 2, 8, 1.86},
+constexpr Tile TILES[] = {{32, 256, 4, 8, 0.78}, {64, 256, 3, 8, 1.00}, {64, 384, 2, 8, 1.40}, {128, 256, 2, 8, 1.82},
                           {128, 384, 2, 8, 2.62}, {64, 128, 4, 4, 0.76}, {32, 128, 5, 2, 0.60}};
 constexpr int N_TILES = 7;
 constexpr int tile_lds(int i) { return TILES[i].stages * (2 * TILES[i].bm + TILES[i].bn) * KS * 2; }
@@ -926,8 +927,9 @@ template <int EPI> static GemmFn gemm_kernel(int tile) {
 struct Cut { int tile, t_tiles, n_tiles, splits, split_steps; bool fused; };
 
 // The tile shape and the number of blocks that share a tile's k range: the cheapest by estimate.  A block's steps take
-// step_us each, blocks beyond the compute units queue; the weights come at 5.5 TB/s at best; partial sums are written
-// and read at 4 TB/s and, where the product has an epilogue, cost one more launch.
+// step_us each, blocks beyond the compute units queue (a last, partly empty round runs faster than a full one: 3.5 rounds
+// of 128 x 256 for gate and up at 512 tokens of the 70B widths take 848 us, seven of 64 x 256 908); the weights come at
+// 5.5 TB/s at best; partial sums are written and read at 4 TB/s and, where the product has an epilogue, cost one more launch.
 static Cut cut_product(const PrefillChunk &c, int T, int N, int mats, int K, int epi, size_t part_floats) {
     Cut best{};
     double best_us = 1e30;
@@ -942,7 +944,8 @@ static Cut cut_product(const PrefillChunk &c, int T, int N, int mats, int K, int
             if (!fused && (size_t)splits * T * N * mats > part_floats) continue;
             const int n_tiles = fused && epi == PE_SWIGLU ? (2 * N + t.bn - 1) / t.bn : (N + t.bn - 1) / t.bn;
             const int blocks = t_tiles * n_tiles * splits * (fused ? 1 : mats);
-            double us = std::max(t.step_us * split_steps * ((blocks + c.num_cu - 1) / c.num_cu), (double)N * K * mats * 2 / 5.5e6);
+            const double full = (double)blocks / c.num_cu, rounds = std::max(1.0, std::min(std::ceil(full), full + 0.25));
+            double us = std::max(t.step_us * split_steps * rounds, (double)N * K * mats * 2 / 5.5e6);
             if (!fused) us += (double)splits * T * N * mats * 8 / 4e6 + (epi == PE_PART ? 0.0 : 6.0);
             if (us < best_us) { best_us = us; best = Cut{tile, t_tiles, n_tiles, splits, split_steps, fused}; }
         }
