@@ -321,6 +321,12 @@ int spd_test_state_layout(size_t *out_words, size_t *out_err_word);
 int spd_test_state_status(const int32_t *state_words, size_t n_words);
 int spd_test_poke_err(spd_ctx *ctx, int32_t value);
 
+/* ---- test hook of the dense prefix pass ----
+ * How a product (0: QKV, 1: attention output, 2: gate and up, 3: down) of a chunk of n_tokens is cut up on a GPU of num_cu
+ * compute units (host only, no GPU): out[4] = tokens and columns of a tile, blocks that share a tile's k range, 1 where the
+ * product runs its epilogue itself.  SPD_EINVAL for models without a dense pass. */
+int spd_test_prefill_cut(const spd_model_cfg *cfg, int32_t num_cu, int32_t n_tokens, int32_t product, int32_t *out);
+
 const char *spd_last_error(const spd_ctx *ctx);
 const char *spd_strerror(int status);
 

@@ -93,6 +93,7 @@ def lib():
             "spd_test_state_layout": [C.POINTER(sz), C.POINTER(sz)],
             "spd_test_state_status": [vp, sz],
             "spd_test_poke_err": [vp, i32],
+            "spd_test_prefill_cut": [C.POINTER(SpdModelCfg), i32, i32, i32, vp],
             "spd_op_gemv": [i32, vp, vp, f32, vp, vp, vp, i32, i32, vp],
             "spd_op_swiglu": [i32, vp, vp, vp, f32, vp, vp, i32, i32, vp],
             "spd_op_attention": [i32, vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, vp],
@@ -415,3 +416,12 @@ def spd_test_state_layout():
 def spd_test_state_status(state_words) -> int:
     a = np.ascontiguousarray(state_words, dtype=np.int32)
     return lib().spd_test_state_status(_np_ptr(a), a.size)
+
+
+def spd_test_prefill_cut(cfg: SpdModelCfg, num_cu: int, n_tokens: int, product: int):
+    """-> (tokens and columns of a tile, blocks that share a tile's k range, epilogue in the product)."""
+    out = np.zeros(4, np.int32)
+    rc = lib().spd_test_prefill_cut(C.byref(cfg), num_cu, n_tokens, product, _np_ptr(out))
+    if rc:
+        raise SpdError(rc, "spd_test_prefill_cut")
+    return int(out[0]), int(out[1]), int(out[2]), bool(out[3])

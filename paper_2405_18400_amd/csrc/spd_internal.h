@@ -232,6 +232,10 @@ struct PrefillChunk {
     float2 *rope;                      // [PREFILL_CHUNK, d_head / 2]
 };
 
+// How one product of a chunk is cut up: tile shape, token and column tiles, blocks that share a tile's k range and the steps
+// of each, and whether the epilogue runs in the product (else partial sums are left and added by another kernel).
+struct PrefillCut { int tile, t_tiles, n_tiles, splits, split_steps; bool fused; };
+
 constexpr int FUSED_MAX_EPI = 512;     // residual values one block of the fused kernel stages per phase
 constexpr int FUSED_PROF_BLOCKS = 512;  // blocks of the fused kernel whose phase clocks are kept
 constexpr int FUSED_MAX_BLOCKS = 1024;                      // largest grid of the fused kernel
@@ -255,6 +259,8 @@ hipError_t expand_prune(hipStream_t s, const ExpandArgs &a);
 hipError_t nucleus(hipStream_t s, const NucleusArgs &a);
 hipError_t prefill_chunk(hipStream_t s, const PrefillChunk &c);
 hipError_t prefill_init();
+void prefill_cuts(const PrefillChunk &c, int T, PrefillCut (&cut)[4]);   // QKV, attention output, gate and up, down
+void prefill_tile(int tile, int &tokens, int &columns);
 hipError_t advance(hipStream_t s, DevState *st);
 hipError_t renorm(hipStream_t s, DevState *st, int k);
 hipError_t fill_i32(hipStream_t s, int32_t *p, int32_t v, int n);

@@ -930,6 +930,19 @@ int spd_test_poke_err(spd_ctx *c, int32_t value) {
     return SPD_OK;
 }
 
+int spd_test_prefill_cut(const spd_model_cfg *cfg, int32_t num_cu, int32_t n_tokens, int32_t product, int32_t *out) {
+    if (!out || check_cfg(cfg) || num_cu < 1 || n_tokens < 1 || n_tokens > PREFILL_CHUNK || product < 0 || product > 3) return SPD_EINVAL;
+    if (!make_layout(*cfg).dense) return SPD_EINVAL;
+    PrefillChunk pc{};
+    pc.d_model = cfg->d_model; pc.n_heads = cfg->n_heads; pc.n_kv_heads = cfg->n_kv_heads; pc.d_ffn = cfg->d_ffn; pc.num_cu = num_cu;
+    PrefillCut cut[4];
+    spdk::prefill_cuts(pc, n_tokens, cut);
+    int tokens, columns;
+    spdk::prefill_tile(cut[product].tile, tokens, columns);
+    out[0] = tokens; out[1] = columns; out[2] = cut[product].splits; out[3] = cut[product].fused ? 1 : 0;
+    return SPD_OK;
+}
+
 int spd_position(const spd_ctx *c, int32_t *out_pos) {
     if (!c || !out_pos) return SPD_EINVAL;
     *out_pos = c->pos;

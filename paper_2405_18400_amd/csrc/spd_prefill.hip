@@ -898,14 +898,14 @@ namespace spdk {
 
 size_t prefill_attn_lds(int d_head) { return (size_t)(AQ * (d_head + 4) + AK * (d_head + 4) + AK * d_head + AQ * (AK + 1)) * sizeof(float); }
 
-// The tile shapes: one block per compute unit, k steps of 64.  `step_us` is what a step takes a block when
-// all compute units have one (sweeps over tiles of 64 .. 512 columns, k steps of 32 / 64 / 128, 2 .. 10 stages, 4, 8 and
+// The tile shapes: one block per compute unit, k steps of 64.  What a step takes a block: `step_us` when all compute units
+// have one, `alone_us` when few do (sweeps over tiles of 64 .. 512 columns, k steps of 32 / 64 / 128, 2 .. 10 stages, 4, 8 and
 // 16 waves; at 128 tokens the products bound it -- 1130 .. 1230 TFLOP/s over the chip, a large library product reaches
 // 1220 -- and at 32 what one compute unit pulls of the weights).
 constexpr int KS = 64;
-struct Tile { int bm, bn, stages, waves; double step_us; };
-constexpr Tile TILES[] = {{32, 256, 4, 8, 0.78}, {64, 256, 3, 8, 1.00}, {64, 384, 2, 8, 1.40}, {128, 256, 2, 8, 1.82},
-                          {128, 384, 2, 8, 2.62}, {64, 128, 4, 4, 0.76}, {32, 128, 5, 2, 0.60}};
+struct Tile { int bm, bn, stages, waves; double step_us, alone_us; };
+constexpr Tile TILES[] = {{32, 256, 4, 8, 0.68, 0.68}, {64, 256, 3, 8, 1.02, 0.81}, {64, 384, 2, 8, 1.50, 1.40}, {128, 256, 2, 8, 1.70, 1.18},
+                          {128, 384, 2, 8, 2.40, 1.70}, {64, 128, 4, 4, 0.63, 0.48}, {32, 128, 5, 2, 0.53, 0.46}};
 constexpr int N_TILES = 7;
 constexpr int tile_lds(int i) { return TILES[i].stages * (2 * TILES[i].bm + TILES[i].bn) * KS * 2; }
 
@@ -923,15 +923,17 @@ template <int EPI> static GemmFn gemm_kernel(int tile) {
     }
 }
 
-// How one product of the chunk is cut up.
-struct Cut { int tile, t_tiles, n_tiles, splits, split_steps; bool fused; };
-
 // The tile shape and the number of blocks that share a tile's k range: the cheapest by estimate.  A block's steps take
-// step_us each, blocks beyond the compute units queue (a last, partly empty round runs faster than a full one: 3.5 rounds
-// of 128 x 256 for gate and up at 512 tokens of the 70B widths take 848 us, seven of 64 x 256 908); the weights come at
-// 5.5 TB/s at best; partial sums are written and read at 4 TB/s and, where the product has an epilogue, cost one more launch.
-static Cut cut_product(const PrefillChunk &c, int T, int N, int mats, int K, int epi, size_t part_floats) {
-    Cut best{};
+// step_us each.  All token tiles of a column run on one of the 8 XCDs, so the busiest XCD's blocks count, in rounds over its
+// compute units: counted over the whole chip 22 columns x 11 token tiles seem to fit 256 compute units once, and take two
+// rounds (7B output projection, 700 tokens, 64 x 384 in two splits: 114 us; 128 x 256: 63).  A last, partly empty round takes
+// between alone_us and step_us a step (128 x 256 at 1.25 and 1.75 rounds: 3.2 and 3.5 us).  The weights come at
+// 6.4 TB/s at best; partial sums are written and read at 4.3 TB/s and, where the product has an epilogue, cost one more launch.
+// Held against every shape and split, products of the 1B, 7B, 13B and 70B widths: the four products of a layer take 1.6 % longer
+// than with the best choice for each at the 33 lengths the constants were fitted to and 1.3 % at 26 others (at most 10 %);
+// with the chip's blocks counted and partial rounds priced as their share + 0.25, 7.7 and 8.4 % (at most 38 %).
+static PrefillCut cut_product(const PrefillChunk &c, int T, int N, int mats, int K, int epi, size_t part_floats) {
+    PrefillCut best{};
     double best_us = 1e30;
     for (int tile = 0; tile < N_TILES; ++tile) {
         const Tile &t = TILES[tile];
@@ -943,17 +945,29 @@ static Cut cut_product(const PrefillChunk &c, int T, int N, int mats, int K, int
             if (want > 1 && split_steps < 4) break;
             if (!fused && (size_t)splits * T * N * mats > part_floats) continue;
             const int n_tiles = fused && epi == PE_SWIGLU ? (2 * N + t.bn - 1) / t.bn : (N + t.bn - 1) / t.bn;
-            const int blocks = t_tiles * n_tiles * splits * (fused ? 1 : mats);
-            const double full = (double)blocks / c.num_cu, rounds = std::max(1.0, std::min(std::ceil(full), full + 0.25));
-            double us = std::max(t.step_us * split_steps * rounds, (double)N * K * mats * 2 / 5.5e6);
-            if (!fused) us += (double)splits * T * N * mats * 8 / 4e6 + (epi == PE_PART ? 0.0 : 6.0);
-            if (us < best_us) { best_us = us; best = Cut{tile, t_tiles, n_tiles, splits, split_steps, fused}; }
+            const int cols = n_tiles * splits * (fused ? 1 : mats);
+            const double rounds = (double)((cols + 7) / 8) * t_tiles / (c.num_cu / 8.0), whole = std::floor(rounds), rest = rounds - whole;
+            const double step = whole * t.step_us + (rest > 0.0 ? t.alone_us + (t.step_us - t.alone_us) * rest : 0.0);
+            double us = std::max(step * split_steps, (double)N * K * mats * 2 / 6.4e6);
+            if (!fused) us += (double)splits * T * N * mats * 8 / 4.3e6 + (epi == PE_PART ? 0.0 : 3.7);
+            if (us < best_us) { best_us = us; best = PrefillCut{tile, t_tiles, n_tiles, splits, split_steps, fused}; }
         }
     }
     return best;
 }
 
-static void launch_gemm(hipStream_t s, GemmFn kernel, PrefillGemmArgs &a, const Cut &cut, int mats) {
+void prefill_cuts(const PrefillChunk &c, int T, PrefillCut (&cut)[4]) {
+    const int d = c.d_model, dh = d / c.n_heads, nq = c.n_heads * dh, nkv = c.n_kv_heads * dh;
+    const size_t room = (size_t)PREFILL_CHUNK * (d + nq);
+    cut[0] = cut_product(c, T, nq + 2 * nkv, 1, d, PE_QKV, (size_t)PREFILL_CHUNK * c.d_ffn);
+    cut[1] = cut_product(c, T, d, 1, nq, PE_PART, room);
+    cut[2] = cut_product(c, T, c.d_ffn, 2, d, PE_SWIGLU, room);
+    cut[3] = cut_product(c, T, d, 1, c.d_ffn, PE_PART, room);
+}
+
+void prefill_tile(int tile, int &tokens, int &columns) { tokens = TILES[tile].bm; columns = TILES[tile].bn; }
+
+static void launch_gemm(hipStream_t s, GemmFn kernel, PrefillGemmArgs &a, const PrefillCut &cut, int mats) {
     a.t_tiles = cut.t_tiles; a.n_tiles = cut.n_tiles; a.splits = cut.splits; a.split_steps = cut.split_steps;
     const int cols = cut.n_tiles * mats * cut.splits;
     hipLaunchKernelGGL(kernel, dim3((cols + 7) / 8 * 8 * cut.t_tiles), dim3(TILES[cut.tile].waves * WAVE), tile_lds(cut.tile), s, a);
@@ -975,9 +989,9 @@ hipError_t prefill_init() {
 hipError_t prefill_chunk(hipStream_t s, const PrefillChunk &c) {
     const int T = c.T, d = c.d_model, dh = d / c.n_heads, nq = c.n_heads * dh, nkv = c.n_kv_heads * dh;
     hipLaunchKernelGGL(rope_table_kernel, dim3((T * (dh / 2) + 255) / 256), dim3(256), 0, s, c.inv_freq, c.p0, T, dh / 2, c.rope);
-    const size_t room = (size_t)PREFILL_CHUNK * (d + nq);
-    const Cut cut_qkv = cut_product(c, T, nq + 2 * nkv, 1, d, PE_QKV, (size_t)PREFILL_CHUNK * c.d_ffn), cut_o = cut_product(c, T, d, 1, nq, PE_PART, room);
-    const Cut cut_gu = cut_product(c, T, c.d_ffn, 2, d, PE_SWIGLU, room), cut_down = cut_product(c, T, d, 1, c.d_ffn, PE_PART, room);
+    PrefillCut cut[4];
+    prefill_cuts(c, T, cut);
+    const PrefillCut &cut_qkv = cut[0], &cut_o = cut[1], &cut_gu = cut[2], &cut_down = cut[3];
     for (int l = 0; l < c.n_layers; ++l) {
         const spd_layer_weights &w = c.layers[l];
         PrefillNormArgs n{};

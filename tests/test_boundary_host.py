@@ -140,3 +140,32 @@ def test_static_scratch_variant_refuses_oversized_shapes_before_any_gpu_work(pkg
     assert L.spd_op_attention_static(1, dummy, dummy, dummy, dummy, 8, 3, 128, 10, 64, None) == -1
     assert L.spd_op_attention_static(1, dummy, dummy, dummy, dummy, 8, 8, 128, 65, 64, None) == -1
     assert L.spd_op_attention_static(5, dummy, dummy, dummy, dummy, 8, 8, 128, 10, 64, None) == -1
+
+
+W1B = synth.ModelShape("1b-shape", 16, 2048, 32, 8, 5504, 32000, "bf16")
+
+
+@pytest.mark.parametrize("shape,n_tokens,product,near_best", [
+    # (tokens and columns of a tile, blocks per k range, epilogue inside) that measured within 6 % of the best of all shapes
+    # and splits on 256 compute units; us of the best, and of 64 x 384 or narrow tiles there
+    (synth.LLAMA13B, 384, 3, {(64, 256, 2, False), (128, 256, 4, False)}),       # 113; 225
+    (synth.LLAMA70B, 700, 3, {(64, 256, 2, False), (128, 256, 1, False)}),       # 665; 1329
+    (synth.LLAMA13B, 768, 1, {(128, 256, 2, False)}),                            # 85; 165
+    (synth.LLAMA7B, 700, 1, {(128, 256, 2, False)}),                             # 63; 114
+    (synth.LLAMA70B, 513, 0, {(64, 256, 2, False), (128, 256, 1, True), (64, 384, 2, False)}),   # 205; 356
+    (synth.LLAMA13B, 129, 3, {(64, 256, 4, False)}),                             # 65; 118
+    (synth.LLAMA70B, 129, 0, {(64, 256, 2, False)}),                             # 68; 122
+    (synth.LLAMA13B, 800, 0, {(128, 256, 1, True)}),                             # 275; 370
+    (W1B, 96, 2, {(64, 128, 1, True)}),                                          # 23; 39
+])
+def test_prefix_products_are_cut_as_measured_best(pkg, shape, n_tokens, product, near_best):
+    """Lengths at which a shape whose blocks do not fit the XCDs evenly takes another round and up to twice the time."""
+    cfg = pkg.binding.model_cfg(shape, 1100, 8)
+    assert pkg.spd_test_prefill_cut(cfg, 256, n_tokens, product) in near_best
+
+
+def test_prefix_cut_refuses_what_has_no_dense_pass(pkg):
+    for cfg, n_tokens, product in [(pkg.binding.model_cfg(synth.TINY, 64, 8), 16, 0), (pkg.binding.model_cfg(synth.LLAMA7B, 64, 8), 0, 0),
+                                   (pkg.binding.model_cfg(synth.LLAMA7B, 64, 8), 16, 4)]:
+        with pytest.raises(pkg.SpdError):
+            pkg.spd_test_prefill_cut(cfg, 256, n_tokens, product)
