@@ -422,9 +422,11 @@ __device__ __forceinline__ void ngram_probes(const NgramDev &ng, const int32_t (
 // mixture (Eq. 3), the interpolation (Eq. 4) or the penalty form (Eq. 5), keeps the k best
 // options and rewrites the draft state.
 // A chain of latencies.  Whatever does not depend on the kept tokens is asked for at the start: the first MERGE threads
-// select among the slices' candidates, wave by wave, while the others look up the drafts' context totals.
+// select among the slices' candidates, wave by wave, while the others look up the drafts' context totals -- where that
+// selection takes as long as a lookup.  With few drafts it does not, and the totals are looked up together with the counts, a
+// group of lanes for each probe (`one_go`: the kernel at k = 1 .. 4, five orders, 9.1 .. 10.0 -> 5.9 .. 7.4 us).
 // k = 8, five orders, 1.6 M slots: 28 -> 13 us (merge 2.9, ranks 0.6, hashes 0.8, probes 5.5, mixture and scores 1.1, prune and state 1.5).
-constexpr int ENT = 1024, MERGE = 256, MERGE_WAVES = MERGE / WAVE;
+constexpr int ENT = 1024, MERGE = 256, MERGE_WAVES = MERGE / WAVE, GROUPS = ENT / PROBE_LANES;
 
 __global__ __launch_bounds__(ENT) void expand_prune_kernel(const ExpandArgs a) {
     __shared__ unsigned long long entry[MERGE_WAVES * SPD_K_MAX], option[SPD_KK];
@@ -464,6 +466,8 @@ __global__ __launch_bounds__(ENT) void expand_prune_kernel(const ExpandArgs a) {
         return a.ng.slots != nullptr && a.ng.present[n - SPD_MIN_ORDER] && key[0] >= 0;
     };
     const bool use_ng = !a.first && a.alpha != 0.0f;
+    const int n_count = k * k * SPD_N_ORDERS, n_total = k * SPD_N_ORDERS;
+    const bool one_go = n_count + n_total <= GROUPS;
     if (tid < MERGE) {
         const int n_cand = a.n_part * k;
         constexpr int NR = TOPK_PART_MAX * SPD_K_MAX / MERGE;
@@ -511,16 +515,16 @@ __global__ __launch_bounds__(ENT) void expand_prune_kernel(const ExpandArgs a) {
         }
         const int e = u / PROBE_LANES;
         static_assert((ENT - MERGE) / PROBE_LANES >= SPD_K_MAX * SPD_N_ORDERS, "a group of lanes per context");
-        if (use_ng && e < (k * SPD_N_ORDERS + PROBE_LANES - 1) / PROBE_LANES * PROBE_LANES) {   // (whole waves)
+        if (use_ng && !one_go && e < (n_total + PROBE_LANES - 1) / PROBE_LANES * PROBE_LANES) {   // (whole waves)
             int tail[SPD_TAIL];
             int32_t key[1][6];
             unsigned long long total[1];
 #pragma unroll
             for (int q = 0; q < SPD_TAIL; ++q) tail[q] = st->tails[min(e / SPD_N_ORDERS, SPD_K_MAX - 1)][q];
             const bool known = make_key(tail, SPD_MIN_ORDER + e % SPD_N_ORDERS, NG_TOTAL, key[0]);
-            const uint64_t home[1] = {known && e < k * SPD_N_ORDERS ? ngram_home(ngram_hash(key[0]), a.ng.capacity) : NO_HOME};
+            const uint64_t home[1] = {known && e < n_total ? ngram_home(ngram_hash(key[0]), a.ng.capacity) : NO_HOME};
             ngram_probes<1>(a.ng, key, home, total);
-            if (e < k * SPD_N_ORDERS && u % PROBE_LANES == 0) s_tot[e] = total[0];
+            if (e < n_total && u % PROBE_LANES == 0) s_tot[e] = total[0];
         }
     }
     __syncthreads();
@@ -555,34 +559,47 @@ __global__ __launch_bounds__(ENT) void expand_prune_kernel(const ExpandArgs a) {
         }
     } else {
         if (use_ng) {
-            constexpr int GROUPS = ENT / PROBE_LANES, N = 4;       // up to k = 10 in one go
-            const int n_probe = k * k * SPD_N_ORDERS;
-            auto key_of = [&](int e, int32_t (&key)[6]) {          // probe e: draft, kept token, order
+            auto key_of = [&](int e, int32_t (&key)[6]) {          // probe e: draft, kept token, order; behind the counts: draft, order of a total
+                const bool total = e >= n_count;
+                const int i = total ? (e - n_count) / SPD_N_ORDERS : e / n_total;
                 int tail[SPD_TAIL];
 #pragma unroll
-                for (int q = 0; q < SPD_TAIL; ++q) tail[q] = s_tails[e / (k * SPD_N_ORDERS)][q];
-                return make_key(tail, SPD_MIN_ORDER + e % SPD_N_ORDERS, s_top[(e / SPD_N_ORDERS) % k], key);
+                for (int q = 0; q < SPD_TAIL; ++q) tail[q] = s_tails[i][q];
+                return make_key(tail, SPD_MIN_ORDER + e % SPD_N_ORDERS, total ? NG_TOTAL : s_top[(e / SPD_N_ORDERS) % k], key);
             };
-            for (int e = tid; e < n_probe; e += ENT) {
-                int32_t key[6];
-                s_home[e] = key_of(e, key) ? ngram_home(ngram_hash(key), a.ng.capacity) : NO_HOME;
-            }
-            __syncthreads();
-            for (int e0 = 0; e0 < n_probe; e0 += N * GROUPS) {
-                int32_t key[N][6];
-                uint64_t home[N];
-                unsigned long long count[N];
-#pragma unroll
-                for (int u = 0; u < N; ++u) {
-                    const int e = e0 + u * GROUPS + tid / PROBE_LANES, f = min(e, n_probe - 1);
-                    (void)key_of(f, key[u]);
-                    home[u] = e < n_probe ? s_home[f] : NO_HOME;
+            if (one_go) {
+                const int n_probe = n_count + n_total, e = tid / PROBE_LANES;
+                if (tid / WAVE * (WAVE / PROBE_LANES) < n_probe) {     // (whole waves)
+                    int32_t key[1][6];
+                    unsigned long long count[1];
+                    const bool known = key_of(min(e, n_probe - 1), key[0]);
+                    const uint64_t home[1] = {known && e < n_probe ? ngram_home(ngram_hash(key[0]), a.ng.capacity) : NO_HOME};
+                    ngram_probes<1>(a.ng, key, home, count);
+                    if (e < n_probe && tid % PROBE_LANES == 0) (e < n_count ? s_cnt[e] : s_tot[e - n_count]) = count[0];
                 }
-                ngram_probes<N>(a.ng, key, home, count);
+            } else {
+                constexpr int N = 4;                               // up to k = 10 in one go
+                for (int e = tid; e < n_count; e += ENT) {
+                    int32_t key[6];
+                    s_home[e] = key_of(e, key) ? ngram_home(ngram_hash(key), a.ng.capacity) : NO_HOME;
+                }
+                __syncthreads();
+                for (int e0 = 0; e0 < n_count; e0 += N * GROUPS) {
+                    int32_t key[N][6];
+                    uint64_t home[N];
+                    unsigned long long count[N];
 #pragma unroll
-                for (int u = 0; u < N; ++u) {
-                    const int e = e0 + u * GROUPS + tid / PROBE_LANES;
-                    if (e < n_probe && tid % PROBE_LANES == 0) s_cnt[e] = count[u];
+                    for (int u = 0; u < N; ++u) {
+                        const int e = e0 + u * GROUPS + tid / PROBE_LANES, f = min(e, n_count - 1);
+                        (void)key_of(f, key[u]);
+                        home[u] = e < n_count ? s_home[f] : NO_HOME;
+                    }
+                    ngram_probes<N>(a.ng, key, home, count);
+#pragma unroll
+                    for (int u = 0; u < N; ++u) {
+                        const int e = e0 + u * GROUPS + tid / PROBE_LANES;
+                        if (e < n_count && tid % PROBE_LANES == 0) s_cnt[e] = count[u];
+                    }
                 }
             }
             __syncthreads();

@@ -54,6 +54,24 @@ def test_orders_2_to_4_only(tiny, k):
         sess.close()
 
 
+@pytest.mark.parametrize("k", [1, 4, 5, 16])
+def test_five_orders_over_the_numbers_of_probes(tiny, k):
+    """Up to four drafts the contexts' totals are looked up together with the counts, a group of lanes per probe; from five on
+    before them, and the counts four probes to a group; 16 drafts take three rounds of those."""
+    shape, w, prefix = tiny
+    pkg = P()
+    lam = synth.PAPER_LAMBDAS
+    tabs = synth.plant_ngrams(synth.make_ngram_tables_zipf(shape.vocab, 40_000, seed=4), visits_of(shape, w, prefix, k, 5), shape.vocab, seed=k)
+    sess = pkg.Session(shape, w, max_ctx=64, k_max=16)
+    try:
+        sess.spd_load_ngrams(tabs, lam)
+        cfg = O.DecodeCfg(k, 0.54, 1.0, 0.1, tuple(lam))
+        _, recs, _ = teacher_forced(sess, make_oracle(shape, w), tabs, lam, prefix, cfg, 5, RTOL[shape.dtype], pkg.SpdDecodeCfg(k, 0.54, 1.0, 0.1))
+        assert any(c.overlap for r in recs[1:] for c in r.candidates), "planting produced no n-gram hit"
+    finally:
+        sess.close()
+
+
 def test_tables_replaced_between_timesteps(tiny):
     """Three timesteps with five orders, then the tables are replaced by a different set with
     orders 2..4 on the live context, three more timesteps.  The oracle is driven step by step
