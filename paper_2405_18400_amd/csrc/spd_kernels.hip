@@ -316,7 +316,8 @@ template <int PARTS> __device__ __forceinline__ int rank_among(const unsigned lo
 // exp(z - max) with z = logit / tau.  Every wave does so for its share, then the waves' results are merged: one
 // barrier.  A chain of latencies (launch, one trip to memory, k rounds): 9.2 -> 5.3 us at k = 8 against the kernel whose
 // rounds went over the block.
-// NR: entries of the slice per thread (4 up to vocabularies of 131072).
+// NR: entries of the slice per thread, the least of 4, 8, 16 and 32 that hold it (4 up to vocabularies of 131072): each is looked at
+// in every round (131074 entries, the kernel: 4.1 us at k = 1 with the rounds over the block, 5.6 with 32 entries, 4.1 with 8; 262144: 5.4, 6.0, 4.4).
 template <int NR>
 __global__ __launch_bounds__(BLOCK) void topk_partial_kernel(const TopkArgs a) {
     __shared__ unsigned long long entry[NWAVE * SPD_K_MAX];
@@ -768,6 +769,8 @@ hipError_t superpose(hipStream_t s, int dtype, const SuperposeArgs &a) {
 
 hipError_t topk_partial(hipStream_t s, const TopkArgs &a) {
     if (a.per_part <= 4 * BLOCK) hipLaunchKernelGGL(topk_partial_kernel<4>, dim3(a.n_part), dim3(BLOCK), 0, s, a);
+    else if (a.per_part <= 8 * BLOCK) hipLaunchKernelGGL(topk_partial_kernel<8>, dim3(a.n_part), dim3(BLOCK), 0, s, a);
+    else if (a.per_part <= 16 * BLOCK) hipLaunchKernelGGL(topk_partial_kernel<16>, dim3(a.n_part), dim3(BLOCK), 0, s, a);
     else if (a.per_part <= 32 * BLOCK) hipLaunchKernelGGL(topk_partial_kernel<32>, dim3(a.n_part), dim3(BLOCK), 0, s, a);
     else return hipErrorInvalidValue;   // (vocabularies stay below 2^20)
     return hipGetLastError();

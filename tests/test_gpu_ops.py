@@ -133,3 +133,25 @@ def test_attention_where_its_kernels_change_hands(dtype, dh, heads, kv, n_ctx, c
     want = torch.stack([((Kd[h * kv // heads] @ q[h].double()) / dh ** 0.5).softmax(-1) @ Vd[h * kv // heads] for h in range(heads)])
     # fp32 sums of at most 5000 terms: about sqrt(5000) 2^-24 = 4e-6 of the scale
     assert_close_scaled(out.cpu().numpy(), want.cpu().numpy(), 1e-5, "attention")
+
+
+@pytest.mark.parametrize("vocab", [131072, 131074, 262144, 262146, 524290])
+def test_top_k_where_the_entries_per_thread_change(vocab):
+    """A slice's entries per thread: 4, 8, 16 and 32, the last and the first vocabulary of each; ties and the two ends included."""
+    pkg = P()
+    shape = synth.ModelShape("one-head", 1, 64, 1, 1, 128, vocab, "fp32")
+    k = 16
+    sess = pkg.Session(shape, synth.make_weights(shape, seed=1), max_ctx=32, k_max=k)
+    try:
+        sess.spd_prefill(np.arange(4))
+        z = np.random.default_rng(vocab).standard_normal(vocab).astype(np.float32)
+        z[[0, vocab - 1, 12345, 12346, vocab // 2]] = 9.0
+        sess.spd_expand_prune(pkg.SpdDecodeCfg(k, 0.0, 1.0, 0.1), torch.from_numpy(z).cuda(), True)
+        ids, logp, _, _, _ = sess.spd_get_step_info(k)
+        want = np.argsort(-z, kind="stable")[:k]
+        z64 = z.astype(np.float64)
+        lse = 9.0 + np.log(np.exp(z64 - 9.0).sum())
+        assert list(ids) == list(want)
+        np.testing.assert_allclose(logp, z64[want] - lse, atol=2e-5, rtol=0)   # fp32 sums of 131072 .. 524290 terms
+    finally:
+        sess.close()
