@@ -440,8 +440,9 @@ hipError_t launch_attention(hipStream_t s, const AttnArgs &a_in) {
     AttnArgs a = a_in;
     a.max_splits = a.max_splits < SPLITS_MAX ? a.max_splits : SPLITS_MAX;
     const int group = a.n_heads / a.n_kv_heads, row_bytes = a.d_head * (int)sizeof(KT);
-    // a position known to the device only: enough blocks for the longest context
+    // a position known to the device only: enough blocks for the longest context, and the merge unless that is one chunk
     int splits = attn_splits(group, a.n_kv_heads, a.max_splits);
+    if (a.st && attn_chunk(a.cap_ctx, group, a.n_kv_heads, row_bytes, a.max_splits) == a.cap_ctx) splits = 1;
     if (!a.st) {
         a.chunk = attn_chunk(a.n_ctx, group, a.n_kv_heads, row_bytes, a.max_splits);
         splits = (a.n_ctx + a.chunk - 1) / a.chunk;

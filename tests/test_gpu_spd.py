@@ -457,6 +457,29 @@ def test_fused_and_per_operator_forward_agree(tiny):
     np.testing.assert_allclose(out["fused"][0], out["per_operator"][0], rtol=0, atol=2e-5 * np.abs(out["fused"][0]).max())
 
 
+@pytest.mark.parametrize("max_ctx", [512, 513])
+def test_per_operator_attention_where_the_merge_begins(max_ctx):
+    """Four query heads per cached head of 64 in fp16: up to 512 positions the longest context is one chunk and attention one
+    launch, one position more and a merge follows it.  Up to the last position, against the persistent kernel."""
+    pkg = P()
+    shape = synth.ModelShape("small-bf16", 2, 512, 8, 2, 1408, 2048, "bf16")
+    w = synth.make_weights(shape, seed=5)
+    prefix = synth.make_prefix_zipf(shape.vocab, max_ctx - 2, seed=9)
+    dc = pkg.SpdDecodeCfg(3, 0.0, 1.0, 0.1)
+    sess = session(shape, w, max_ctx=max_ctx, kv_dtype="fp16")
+    try:
+        logits = []
+        for path in ("fused", "per_operator"):
+            select_path(sess, path)
+            sess.spd_prefill(prefix)
+            for _ in range(3):
+                sess.spd_step(dc)
+            logits.append(sess.spd_read_logits())
+        np.testing.assert_allclose(logits[0], logits[1], rtol=0, atol=2e-5 * np.abs(logits[1]).max())
+    finally:
+        sess.close()
+
+
 def test_generate_free_running_matches_until_first_undecided_step(tiny):
     shape, w, tabs, prefix = tiny
     pkg = P()
