@@ -321,6 +321,11 @@ int spd_test_state_layout(size_t *out_words, size_t *out_err_word);
 int spd_test_state_status(const int32_t *state_words, size_t n_words);
 int spd_test_poke_err(spd_ctx *ctx, int32_t value);
 
+/* ---- test hook of the n-gram tables ----
+ * What spd_load_ngrams would copy to the device (host only, no GPU): the slots, 32 bytes each, into HOST memory of at least
+ * spd_ngram_table_bytes() bytes, and the longest displacement of an entry from its home slot. */
+int spd_test_ngram_table(const spd_ngram_host_tables *t, int32_t vocab, void *out_slots, size_t out_bytes, int32_t *out_max_probe);
+
 /* ---- test hook of the dense prefix pass ----
  * How a product (0: QKV, 1: attention output, 2: gate and up, 3: down) of a chunk of n_tokens is cut up on a GPU of num_cu
  * compute units (host only, no GPU): out[4] = tokens and columns of a tile, blocks that share a tile's k range, 1 where the

@@ -93,6 +93,7 @@ def lib():
             "spd_test_state_layout": [C.POINTER(sz), C.POINTER(sz)],
             "spd_test_state_status": [vp, sz],
             "spd_test_poke_err": [vp, i32],
+            "spd_test_ngram_table": [C.POINTER(SpdNgramHostTables), i32, vp, sz, C.POINTER(i32)],
             "spd_test_prefill_cut": [C.POINTER(SpdModelCfg), i32, i32, i32, vp],
             "spd_op_gemv": [i32, vp, vp, f32, vp, vp, vp, i32, i32, vp],
             "spd_op_swiglu": [i32, vp, vp, vp, f32, vp, vp, i32, i32, vp],
@@ -416,6 +417,16 @@ def spd_test_state_layout():
 def spd_test_state_status(state_words) -> int:
     a = np.ascontiguousarray(state_words, dtype=np.int32)
     return lib().spd_test_state_status(_np_ptr(a), a.size)
+
+
+def spd_test_ngram_table(tables: dict, vocab: int):
+    """-> (slots [n, 8] int32: six token ids, count as two words; longest displacement)."""
+    t, _keep = ngram_struct(tables, (0, 0, 0, 0, 0))
+    slots, probe = np.zeros((spd_ngram_table_bytes(tables) // 32, 8), np.int32), C.c_int32(0)
+    rc = lib().spd_test_ngram_table(C.byref(t), vocab, _np_ptr(slots), slots.nbytes, C.byref(probe))
+    if rc:
+        raise SpdError(rc, "spd_test_ngram_table")
+    return slots, probe.value
 
 
 def spd_test_prefill_cut(cfg: SpdModelCfg, num_cu: int, n_tokens: int, product: int):

@@ -6,7 +6,6 @@
 
 #include <algorithm>
 #include <cstring>
-#include <utility>
 
 uint64_t ngram_capacity_for(const spd_ngram_host_tables *t) {
     uint64_t n = 0;
@@ -17,45 +16,47 @@ uint64_t ngram_capacity_for(const spd_ngram_host_tables *t) {
 }
 
 namespace {
+// Linear probing with the entries of every run of taken slots in the order of their home slots: the longest displacement is then
+// the least there is.  It bounds the device's walk for a key that is not stored, and a walk is a chain of trips to memory (120000
+// n-grams: 15 slots, 50 .. 70 in the order they came in).  The order is kept while inserting: displacements lie beside the slots,
+// a walk compares keys only where the home slots agree, and what has to make room moves up by one.
 struct Builder {
     NgramHostTable &tab;
     uint64_t cap;
-    // Finds the slot of `key`, or the empty slot where it belongs.
-    NgramSlot *locate(const int32_t *key, bool &found) {
-        uint64_t at = ngram_home(ngram_hash(key), cap);
-        for (;; at = (at + 1 == cap) ? 0 : at + 1) {
-            NgramSlot &s = tab.slots[at];
-            if (s.tok[0] == NG_EMPTY) {
-                found = false;
-                return &s;
-            }
-            if (std::memcmp(s.tok, key, sizeof(s.tok)) == 0) {
-                found = true;
-                return &s;
-            }
-        }
+    std::vector<int32_t> dist;      // displacement of the entry in each slot, -1: empty
+
+    Builder(NgramHostTable &t, uint64_t capacity) : tab(t), cap(capacity), dist(capacity, -1) {}
+    uint64_t next(uint64_t at) const { return at + 1 == cap ? 0 : at + 1; }
+    void prefetch(uint64_t home) const {
+        __builtin_prefetch(&dist[home], 1);
+        __builtin_prefetch(&tab.slots[home], 1);
     }
 
-    // Which slots are taken does not depend on the order of insertion; who sits where does.  Within every run of taken
-    // slots the entries are put in the order of their home slots, which makes the longest displacement the least there
-    // is.  It bounds the device's walk for a key that is not stored, and a walk is a chain of trips to memory.
-    void settle() {
-        uint64_t first = 0;
-        while (tab.slots[first].tok[0] != NG_EMPTY) ++first;      // (there is one: the load factor is below 1)
-        std::vector<std::pair<uint64_t, NgramSlot>> run;          // distance of the home slot from the start of the run; entry
-        auto wrap = [&](uint64_t at) { return at >= cap ? at - cap : at; };
-        for (uint64_t done = 0; done < cap;) {
-            const uint64_t start = wrap(first + done);
-            run.clear();
-            for (uint64_t at = start; tab.slots[at].tok[0] != NG_EMPTY; at = wrap(at + 1))
-                run.emplace_back(wrap(ngram_home(ngram_hash(tab.slots[at].tok), cap) + cap - start), tab.slots[at]);
-            std::stable_sort(run.begin(), run.end(), [](const auto &a, const auto &b) { return a.first < b.first; });
-            for (uint64_t i = 0; i < run.size(); ++i) {
-                tab.slots[wrap(start + i)] = run[i].second;
-                tab.max_probe = std::max(tab.max_probe, (int32_t)(i - run[i].first));
+    // The slot of `key`, which it gets where it has none yet (count 0).
+    NgramSlot &slot_of(const int32_t *key, uint64_t home, bool &found) {
+        uint64_t at = home;
+        int32_t p = 0;
+        for (; dist[at] >= p; at = next(at), ++p)       // (the load factor is below 1: there is an empty slot)
+            if (dist[at] == p && std::memcmp(tab.slots[at].tok, key, sizeof(tab.slots[at].tok)) == 0) {
+                found = true;
+                return tab.slots[at];
             }
-            done += run.size() + 1;                               // (and the empty slot behind the run)
+        found = false;
+        uint64_t end = at;
+        while (dist[end] >= 0) end = next(end);
+        for (uint64_t to = end; to != at;) {
+            const uint64_t from = to == 0 ? cap - 1 : to - 1;
+            tab.slots[to] = tab.slots[from];
+            dist[to] = dist[from] + 1;
+            tab.max_probe = std::max(tab.max_probe, dist[to]);
+            to = from;
         }
+        NgramSlot &s = tab.slots[at];
+        std::memcpy(s.tok, key, sizeof(s.tok));
+        s.cnt_lo = s.cnt_hi = 0;
+        dist[at] = p;
+        tab.max_probe = std::max(tab.max_probe, p);
+        return s;
     }
 };
 }  // namespace
@@ -68,47 +69,57 @@ int ngram_build(const spd_ngram_host_tables *t, int32_t vocab, uint64_t capacity
     empty.cnt_lo = empty.cnt_hi = 0;
     out.slots.assign(capacity, empty);
     out.max_probe = 0;
-    Builder b{out, capacity};
+    Builder b(out, capacity);
+    // Every entry touches two places far apart: the home slots of a batch are asked for before the first is used (2 M
+    // n-grams, the build: 340 ms one by one and unordered, 440 with a pass that ordered the runs afterwards, 270 so; 120000:
+    // 9, 16, 6.6).
+    constexpr int BATCH = 16;
+    struct { int32_t key[6]; uint64_t home, total_home; const char *bad; } batch[BATCH];
     for (int o = 0; o < SPD_N_ORDERS; ++o) {
         const int n = o + SPD_MIN_ORDER;
         const int64_t N = t->n_entries[o];
         out.present[o] = N > 0;
         if (N < 0) { err = "negative entry count"; return SPD_EINVAL; }
         if (N > 0 && (!t->keys[o] || !t->counts[o])) { err = "null keys/counts for a non-empty order"; return SPD_EINVAL; }
-        for (int64_t e = 0; e < N; ++e) {
-            const int32_t *src = t->keys[o] + e * n;
-            int32_t key[6];
-            for (int q = 0; q < 6; ++q) key[q] = NG_PAD;
-            for (int q = 0; q < n; ++q) {
-                if (src[q] < 0 || src[q] >= vocab) {
-                    err = "order " + std::to_string(n) + " entry " + std::to_string(e) + ": token id outside [0, vocab)";
+        for (int64_t e0 = 0; e0 < N; e0 += BATCH) {
+            const int m = (int)std::min<int64_t>(BATCH, N - e0);
+            for (int i = 0; i < m; ++i) {
+                auto &x = batch[i];
+                const int32_t *src = t->keys[o] + (e0 + i) * n;
+                x.bad = t->counts[o][e0 + i] == 0 ? "zero count" : nullptr;
+                for (int q = 0; q < 6; ++q) {
+                    x.key[q] = q < n ? src[q] : NG_PAD;
+                    if (q < n && (src[q] < 0 || src[q] >= vocab)) x.bad = "token id outside [0, vocab)";
+                }
+                if (x.bad) continue;
+                x.home = ngram_home(ngram_hash(x.key), capacity);
+                b.prefetch(x.home);
+                const int32_t token = x.key[n - 1];
+                x.key[n - 1] = NG_TOTAL;   // the context's running total
+                x.total_home = ngram_home(ngram_hash(x.key), capacity);
+                b.prefetch(x.total_home);
+                x.key[n - 1] = token;
+            }
+            for (int i = 0; i < m; ++i) {
+                auto &x = batch[i];
+                bool found = false;
+                const char *why = x.bad;
+                if (!why) {
+                    NgramSlot &s = b.slot_of(x.key, x.home, found);
+                    if (found) why = "duplicate key";
+                    else s.cnt_lo = t->counts[o][e0 + i];
+                }
+                if (why) {
+                    err = "order " + std::to_string(n) + " entry " + std::to_string(e0 + i) + ": " + why;
                     return SPD_ETABLE;
                 }
-                key[q] = src[q];
+                x.key[n - 1] = NG_TOTAL;
+                NgramSlot &s = b.slot_of(x.key, x.total_home, found);
+                const uint64_t tot = (((uint64_t)s.cnt_hi << 32) | s.cnt_lo) + t->counts[o][e0 + i];
+                s.cnt_lo = (uint32_t)tot;
+                s.cnt_hi = (uint32_t)(tot >> 32);
             }
-            const uint32_t c = t->counts[o][e];
-            if (c == 0) {
-                err = "order " + std::to_string(n) + " entry " + std::to_string(e) + ": zero count";
-                return SPD_ETABLE;
-            }
-            bool found;
-            NgramSlot *s = b.locate(key, found);
-            if (found) {
-                err = "order " + std::to_string(n) + " entry " + std::to_string(e) + ": duplicate key";
-                return SPD_ETABLE;
-            }
-            std::memcpy(s->tok, key, sizeof(key));
-            s->cnt_lo = c;
-            s->cnt_hi = 0;
-            key[n - 1] = NG_TOTAL;   // the context's running total
-            s = b.locate(key, found);
-            uint64_t tot = found ? (((uint64_t)s->cnt_hi << 32) | s->cnt_lo) : 0;
-            tot += c;
-            std::memcpy(s->tok, key, sizeof(key));
-            s->cnt_lo = (uint32_t)tot;
-            s->cnt_hi = (uint32_t)(tot >> 32);
         }
     }
-    b.settle();
     return SPD_OK;
 }

@@ -930,6 +930,19 @@ int spd_test_poke_err(spd_ctx *c, int32_t value) {
     return SPD_OK;
 }
 
+int spd_test_ngram_table(const spd_ngram_host_tables *t, int32_t vocab, void *out_slots, size_t out_bytes, int32_t *out_max_probe) {
+    if (!t || !out_slots || !out_max_probe) return SPD_EINVAL;
+    const uint64_t cap = ngram_capacity_for(t);
+    if (out_bytes < cap * sizeof(NgramSlot)) return SPD_EWORKSPACE;
+    NgramHostTable host;
+    std::string err;
+    const int rc = ngram_build(t, vocab, cap, host, err);
+    if (rc != SPD_OK) return rc;
+    std::memcpy(out_slots, host.slots.data(), cap * sizeof(NgramSlot));
+    *out_max_probe = host.max_probe;
+    return SPD_OK;
+}
+
 int spd_test_prefill_cut(const spd_model_cfg *cfg, int32_t num_cu, int32_t n_tokens, int32_t product, int32_t *out) {
     if (!out || check_cfg(cfg) || num_cu < 1 || n_tokens < 1 || n_tokens > PREFILL_CHUNK || product < 0 || product > 3) return SPD_EINVAL;
     if (!make_layout(*cfg).dense) return SPD_EINVAL;

@@ -169,3 +169,57 @@ def test_prefix_cut_refuses_what_has_no_dense_pass(pkg):
                                    (pkg.binding.model_cfg(synth.LLAMA7B, 64, 8), 16, 4)]:
         with pytest.raises(pkg.SpdError):
             pkg.spd_test_prefill_cut(cfg, 256, n_tokens, product)
+
+
+def home_slot(key, capacity):
+    h, mask = 0x9E3779B97F4A7C15, 2 ** 64 - 1
+    for t in key:
+        h = ((h ^ (t & 0xFFFFFFFF)) * 0xFF51AFD7ED558CCD) & mask
+        h ^= h >> 29
+    h = (h * 0xC4CEB9FE1A85EC53) & mask
+    return ((h ^ (h >> 32)) * capacity) >> 64
+
+
+@pytest.mark.parametrize("entries,vocab", [(0, 50), (1, 50), (3, 50), (15, 4), (16, 6), (17, 8), (60, 12), (400, 40), (3000, 300)])
+@pytest.mark.parametrize("seed", [0, 1, 2])
+def test_ngram_table_is_ordered_by_home_slots(pkg, entries, vocab, seed):
+    """Every n-gram and every context's total is stored once with its count, reached from its home slot without an empty slot in
+    between, the entries of a run of taken slots in the order of their home slots (runs across the table's end included),
+    and the longest displacement is what it says: it bounds the walk for a key that is not there."""
+    rng = np.random.default_rng(seed)
+    tables, want = {}, {}
+    for n in (2, 3, 6):
+        keys = np.unique(rng.integers(0, vocab, (entries, n), dtype=np.int32), axis=0) if entries else np.zeros((0, n), np.int32)
+        keys = keys[rng.permutation(len(keys))]
+        counts = rng.integers(1, 2 ** 32, len(keys), dtype=np.uint64).astype(np.uint32)
+        tables[n] = (keys, counts)
+        for key, c in zip(keys.tolist(), counts.tolist()):
+            pad = [-1] * (6 - n)
+            want[tuple(key + pad)] = c
+            total = tuple(key[:-1] + [-2] + pad)
+            want[total] = want.get(total, 0) + c
+    slots, max_probe = pkg.spd_test_ngram_table(tables, vocab)
+    cap = int(2 * sum(len(k) for k, _ in tables.values()) / 0.7) + 64      # the slots in use; the buffer is padded
+    got, displaced, taken, homes = {}, [0], slots[:cap, 0] != -3, {}
+    for at in np.nonzero(taken)[0].tolist():
+        key = tuple(slots[at, :6].tolist())
+        lo, hi = slots[at, 6:].view(np.uint32).tolist()
+        assert key not in got
+        got[key] = (hi << 32) | lo
+        homes[at] = home_slot(key, cap)
+        d = (at - homes[at]) % cap
+        displaced.append(d)
+        assert all(taken[(at - q) % cap] for q in range(d + 1))
+    assert got == want
+    assert max_probe == max(displaced)
+    for at, h in homes.items():
+        behind = (at + 1) % cap
+        if taken[behind]:
+            assert (at - h) % cap + 1 >= (behind - homes[behind]) % cap     # the next entry's home slot is not before this one's
+
+
+@pytest.mark.parametrize("keys,counts", [([[1, 2], [3, 4], [1, 2]], [1, 1, 1]), ([[1, 2], [3, 50]], [1, 1]), ([[1, 2], [-1, 4]], [1, 1]), ([[1, 2], [3, 4]], [1, 0])])
+def test_ngram_table_refuses(pkg, keys, counts):
+    with pytest.raises(pkg.SpdError) as e:
+        pkg.spd_test_ngram_table({2: (np.array(keys, np.int32), np.array(counts, np.uint32))}, 50)
+    assert e.value.code == -5
