@@ -326,11 +326,14 @@ int spd_test_poke_err(spd_ctx *ctx, int32_t value);
  * spd_ngram_table_bytes() bytes, and the longest displacement of an entry from its home slot. */
 int spd_test_ngram_table(const spd_ngram_host_tables *t, int32_t vocab, void *out_slots, size_t out_bytes, int32_t *out_max_probe);
 
-/* ---- test hook of the dense prefix pass ----
+/* ---- test hooks of the dense prefix pass ----
  * How a product (0: QKV, 1: attention output, 2: gate and up, 3: down) of a chunk of n_tokens is cut up on a GPU of num_cu
  * compute units (host only, no GPU): out[4] = tokens and columns of a tile, blocks that share a tile's k range, 1 where the
  * product runs its epilogue itself.  SPD_EINVAL for models without a dense pass. */
 int spd_test_prefill_cut(const spd_model_cfg *cfg, int32_t num_cu, int32_t n_tokens, int32_t product, int32_t *out);
+/* From now on this context cuts `product` with the tile shape `tile` (0 .. 6; -1: by estimate again) and `splits` blocks per k
+ * range, wherever partial sums of that size have room; out[4] as above, for a chunk of n_tokens. */
+int spd_test_force_prefill_cut(spd_ctx *ctx, int32_t product, int32_t tile, int32_t splits, int32_t n_tokens, int32_t *out);
 
 const char *spd_last_error(const spd_ctx *ctx);
 const char *spd_strerror(int status);

@@ -95,6 +95,7 @@ def lib():
             "spd_test_poke_err": [vp, i32],
             "spd_test_ngram_table": [C.POINTER(SpdNgramHostTables), i32, vp, sz, C.POINTER(i32)],
             "spd_test_prefill_cut": [C.POINTER(SpdModelCfg), i32, i32, i32, vp],
+            "spd_test_force_prefill_cut": [vp, i32, i32, i32, i32, vp],
             "spd_op_gemv": [i32, vp, vp, f32, vp, vp, vp, i32, i32, vp],
             "spd_op_swiglu": [i32, vp, vp, vp, f32, vp, vp, i32, i32, vp],
             "spd_op_attention": [i32, vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, vp],
@@ -323,6 +324,12 @@ class Session:
 
     def spd_test_poke_err(self, value: int):
         self._chk(self.L.spd_test_poke_err(self.ctx, int(value)), "spd_test_poke_err")
+
+    def spd_test_force_prefill_cut(self, product: int, tile: int, splits: int, n_tokens: int):
+        """-> (tokens and columns of a tile, blocks that share a tile's k range, epilogue in the product)."""
+        out = np.zeros(4, np.int32)
+        self._chk(self.L.spd_test_force_prefill_cut(self.ctx, product, tile, splits, n_tokens, _np_ptr(out)), "spd_test_force_prefill_cut")
+        return int(out[0]), int(out[1]), int(out[2]), bool(out[3])
 
     def spd_position(self) -> int:
         out = C.c_int32(0)

@@ -209,6 +209,12 @@ struct FusedArgsHost {
     float eps;
 };
 
+// How one product of a chunk is cut up: tile shape, token and column tiles, blocks that share a tile's k range and the steps
+// of each, and whether the epilogue runs in the product (else partial sums are left and added by another kernel).
+struct PrefillCut { int tile, t_tiles, n_tiles, splits, split_steps; bool fused; };
+// What a test asks for instead of the estimate (tile_1: its tile shape + 1, 0: nothing).
+struct PrefillForce { int32_t tile_1, splits; };
+
 // One chunk of the dense prefix pass (bf16 weights): T <= PREFILL_CHUNK prefix tokens at
 // positions p0 .. p0 + T - 1.  Arena buffers are DEVICE, sized for PREFILL_CHUNK rows.
 constexpr int PREFILL_CHUNK = 1024;
@@ -230,11 +236,8 @@ struct PrefillChunk {
     uint16_t *xhi, *xlo;               // [PREFILL_CHUNK, max(d_model, n_heads * d_head)] bf16 pair
     uint16_t *uhi, *ulo;               // [PREFILL_CHUNK, d_ffn] bf16 pair (lo behind hi)
     float2 *rope;                      // [PREFILL_CHUNK, d_head / 2]
+    PrefillForce force[4];             // QKV, attention output, gate and up, down
 };
-
-// How one product of a chunk is cut up: tile shape, token and column tiles, blocks that share a tile's k range and the steps
-// of each, and whether the epilogue runs in the product (else partial sums are left and added by another kernel).
-struct PrefillCut { int tile, t_tiles, n_tiles, splits, split_steps; bool fused; };
 
 constexpr int FUSED_MAX_EPI = 512;     // residual values one block of the fused kernel stages per phase
 constexpr int FUSED_PROF_BLOCKS = 512;  // blocks of the fused kernel whose phase clocks are kept
@@ -260,7 +263,7 @@ hipError_t nucleus(hipStream_t s, const NucleusArgs &a);
 hipError_t prefill_chunk(hipStream_t s, const PrefillChunk &c);
 hipError_t prefill_init();
 void prefill_cuts(const PrefillChunk &c, int T, PrefillCut (&cut)[4]);   // QKV, attention output, gate and up, down
-void prefill_tile(int tile, int &tokens, int &columns);
+int prefill_tile(int tile, int &tokens, int &columns);    // returns how many tile shapes there are
 hipError_t advance(hipStream_t s, DevState *st);
 hipError_t renorm(hipStream_t s, DevState *st, int k);
 hipError_t fill_i32(hipStream_t s, int32_t *p, int32_t v, int n);

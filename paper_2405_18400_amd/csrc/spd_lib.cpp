@@ -138,6 +138,7 @@ struct spd_ctx {
     size_t pinned_bytes;
     bool use_graph, timing, use_fused, use_dense;
     int fused_blocks;   // grid of the fused forward kernel; 0 = not available for this shape
+    PrefillForce force[4];   // tests only
     hipGraphExec_t step_exec, prefill_exec, nucleus_exec;
     spd_decode_cfg step_dc;
     spd_sample_cfg nucleus_sc;
@@ -437,6 +438,7 @@ int spd_create(const spd_model_cfg *cfg, const spd_weight_ptrs *w, void *workspa
     c->use_graph = true; c->timing = false; c->use_fused = true; c->fused_blocks = 0;
     c->use_dense = c->L.dense && spdk::prefill_init() == hipSuccess;
     c->step_exec = nullptr; c->prefill_exec = nullptr; c->nucleus_exec = nullptr;
+    std::memset(c->force, 0, sizeof(c->force));
     std::memset(&c->step_dc, 0, sizeof(c->step_dc));
     std::memset(c->kc_ms, 0, sizeof(c->kc_ms));
     std::memset(c->kc_n, 0, sizeof(c->kc_n));
@@ -560,6 +562,7 @@ static int run_prefix_pass(spd_ctx *c, int p0, int m) {
         pc.xhi = c->at<uint16_t>(c->L.pf_xhi); pc.xlo = c->at<uint16_t>(c->L.pf_xlo);
         pc.uhi = c->at<uint16_t>(c->L.pf_uhi); pc.ulo = c->at<uint16_t>(c->L.pf_ulo);
         pc.rope = c->at<float2>(c->L.pf_rope);
+        std::memcpy(pc.force, c->force, sizeof(pc.force));
         int last_T = 0;
         for (int at = p0; at < m; at += PREFILL_CHUNK) {
             pc.p0 = at; pc.T = last_T = (m - at < PREFILL_CHUNK) ? m - at : PREFILL_CHUNK;
@@ -943,16 +946,32 @@ int spd_test_ngram_table(const spd_ngram_host_tables *t, int32_t vocab, void *ou
     return SPD_OK;
 }
 
-int spd_test_prefill_cut(const spd_model_cfg *cfg, int32_t num_cu, int32_t n_tokens, int32_t product, int32_t *out) {
-    if (!out || check_cfg(cfg) || num_cu < 1 || n_tokens < 1 || n_tokens > PREFILL_CHUNK || product < 0 || product > 3) return SPD_EINVAL;
-    if (!make_layout(*cfg).dense) return SPD_EINVAL;
+static void prefill_cut_of(const spd_model_cfg &cfg, int num_cu, const PrefillForce *force, int n_tokens, int product, int32_t *out) {
     PrefillChunk pc{};
-    pc.d_model = cfg->d_model; pc.n_heads = cfg->n_heads; pc.n_kv_heads = cfg->n_kv_heads; pc.d_ffn = cfg->d_ffn; pc.num_cu = num_cu;
+    pc.d_model = cfg.d_model; pc.n_heads = cfg.n_heads; pc.n_kv_heads = cfg.n_kv_heads; pc.d_ffn = cfg.d_ffn; pc.num_cu = num_cu;
+    if (force) std::memcpy(pc.force, force, sizeof(pc.force));
     PrefillCut cut[4];
     spdk::prefill_cuts(pc, n_tokens, cut);
     int tokens, columns;
-    spdk::prefill_tile(cut[product].tile, tokens, columns);
+    (void)spdk::prefill_tile(cut[product].tile, tokens, columns);
     out[0] = tokens; out[1] = columns; out[2] = cut[product].splits; out[3] = cut[product].fused ? 1 : 0;
+}
+
+int spd_test_prefill_cut(const spd_model_cfg *cfg, int32_t num_cu, int32_t n_tokens, int32_t product, int32_t *out) {
+    if (!out || check_cfg(cfg) || num_cu < 1 || n_tokens < 1 || n_tokens > PREFILL_CHUNK || product < 0 || product > 3) return SPD_EINVAL;
+    if (!make_layout(*cfg).dense) return SPD_EINVAL;
+    prefill_cut_of(*cfg, num_cu, nullptr, n_tokens, product, out);
+    return SPD_OK;
+}
+
+int spd_test_force_prefill_cut(spd_ctx *c, int32_t product, int32_t tile, int32_t splits, int32_t n_tokens, int32_t *out) {
+    if (!c) return SPD_EINVAL;
+    int tokens, columns;
+    const int n_tiles = spdk::prefill_tile(0, tokens, columns);
+    if (!out || !c->L.dense || product < 0 || product > 3 || tile < -1 || tile >= n_tiles || n_tokens < 1 || n_tokens > PREFILL_CHUNK)
+        return fail(c, SPD_EINVAL, "no such product, tile shape or chunk");
+    c->force[product] = PrefillForce{tile + 1, splits};
+    prefill_cut_of(c->cfg, c->num_cu, c->force, n_tokens, product, out);
     return SPD_OK;
 }
 

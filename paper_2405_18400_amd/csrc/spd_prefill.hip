@@ -932,10 +932,11 @@ template <int EPI> static GemmFn gemm_kernel(int tile) {
 // Held against every shape and split, products of the 1B, 7B, 13B and 70B widths: the four products of a layer take 1.6 % longer
 // than with the best choice for each at the 33 lengths the constants were fitted to and 1.3 % at 26 others (at most 10 %);
 // with the chip's blocks counted and partial rounds priced as their share + 0.25, 7.7 and 8.4 % (at most 38 %).
-static PrefillCut cut_product(const PrefillChunk &c, int T, int N, int mats, int K, int epi, size_t part_floats) {
+static PrefillCut cut_product(const PrefillChunk &c, const PrefillForce &force, int T, int N, int mats, int K, int epi, size_t part_floats) {
     PrefillCut best{};
     double best_us = 1e30;
     for (int tile = 0; tile < N_TILES; ++tile) {
+        if (force.tile_1 != 0 && tile != force.tile_1 - 1) continue;
         const Tile &t = TILES[tile];
         const int t_tiles = (T + t.bm - 1) / t.bm, steps = K / KS;
         const bool can_fuse = epi == PE_QKV || (epi == PE_SWIGLU && gemm_kernel<PE_SWIGLU>(tile) != nullptr);
@@ -943,6 +944,7 @@ static PrefillCut cut_product(const PrefillChunk &c, int T, int N, int mats, int
             const int split_steps = (steps + want - 1) / want, splits = (steps + split_steps - 1) / split_steps;
             const bool fused = can_fuse && splits == 1;
             if (want > 1 && split_steps < 4) break;
+            if (force.tile_1 != 0 && splits != force.splits) continue;
             if (!fused && (size_t)splits * T * N * mats > part_floats) continue;
             const int n_tiles = fused && epi == PE_SWIGLU ? (2 * N + t.bn - 1) / t.bn : (N + t.bn - 1) / t.bn;
             const int cols = n_tiles * splits * (fused ? 1 : mats);
@@ -953,19 +955,19 @@ static PrefillCut cut_product(const PrefillChunk &c, int T, int N, int mats, int
             if (us < best_us) { best_us = us; best = PrefillCut{tile, t_tiles, n_tiles, splits, split_steps, fused}; }
         }
     }
-    return best;
+    return best.t_tiles > 0 ? best : cut_product(c, PrefillForce{0, 0}, T, N, mats, K, epi, part_floats);   // (what was asked for does not fit)
 }
 
 void prefill_cuts(const PrefillChunk &c, int T, PrefillCut (&cut)[4]) {
     const int d = c.d_model, dh = d / c.n_heads, nq = c.n_heads * dh, nkv = c.n_kv_heads * dh;
     const size_t room = (size_t)PREFILL_CHUNK * (d + nq);
-    cut[0] = cut_product(c, T, nq + 2 * nkv, 1, d, PE_QKV, (size_t)PREFILL_CHUNK * c.d_ffn);
-    cut[1] = cut_product(c, T, d, 1, nq, PE_PART, room);
-    cut[2] = cut_product(c, T, c.d_ffn, 2, d, PE_SWIGLU, room);
-    cut[3] = cut_product(c, T, d, 1, c.d_ffn, PE_PART, room);
+    cut[0] = cut_product(c, c.force[0], T, nq + 2 * nkv, 1, d, PE_QKV, (size_t)PREFILL_CHUNK * c.d_ffn);
+    cut[1] = cut_product(c, c.force[1], T, d, 1, nq, PE_PART, room);
+    cut[2] = cut_product(c, c.force[2], T, c.d_ffn, 2, d, PE_SWIGLU, room);
+    cut[3] = cut_product(c, c.force[3], T, d, 1, c.d_ffn, PE_PART, room);
 }
 
-void prefill_tile(int tile, int &tokens, int &columns) { tokens = TILES[tile].bm; columns = TILES[tile].bn; }
+int prefill_tile(int tile, int &tokens, int &columns) { tokens = TILES[tile].bm; columns = TILES[tile].bn; return N_TILES; }
 
 static void launch_gemm(hipStream_t s, GemmFn kernel, PrefillGemmArgs &a, const PrefillCut &cut, int mats) {
     a.t_tiles = cut.t_tiles; a.n_tiles = cut.n_tiles; a.splits = cut.splits; a.split_steps = cut.split_steps;

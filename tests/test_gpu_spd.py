@@ -258,10 +258,9 @@ def test_70b_shape_one_layer(forward_path):
 def test_dense_prefix_pass_matches_the_oracle_and_the_token_by_token_pass(m):
     """The prefix pass on the matrix cores (1024 tokens per weight pass) against the oracle's
     full-sequence forward and against the token-by-token pass: logits after the prefix, and
-    three timesteps on top of the cache it filled.  Sizes straddle the 32- and 64-token tiles
-    the 128-token activation tiles, the switch between the two GEMM kernels (96 tokens) and
-    the 1024-token chunk (1043 = one full chunk + a short one at a non-zero position); grouped
-    key/value heads."""
+    three timesteps on top of the cache it filled.  Sizes straddle the products' tiles of 32, 64
+    and 128 tokens and the 1024-token chunk (1043 = one full chunk + a short one at a non-zero
+    position); grouped key/value heads."""
     pkg = P()
     shape = synth.ModelShape("small-bf16-dense", 3, 512, 8, 2, 1408, 2048, "bf16")
     w = synth.make_weights(shape, seed=21)
@@ -284,12 +283,50 @@ def test_dense_prefix_pass_matches_the_oracle_and_the_token_by_token_pass(m):
     assert np.max(np.abs(logits[True] - logits[False])) <= 1e-4 * np.max(np.abs(logits[False]))
 
 
+PREFIX_TILES = [(32, 256), (64, 256), (64, 384), (128, 256), (128, 384), (64, 128), (32, 128)]
+QKV, ATTN_OUT, GATE_UP, DOWN = range(4)
+
+
+@pytest.mark.parametrize("kv_dtype,bound", [("fp32", 1e-4), ("fp16", 1e-3)])
+@pytest.mark.parametrize("m", [70, 230])
+def test_prefix_products_of_every_tile_shape(m, kv_dtype, bound):
+    """Every tile shape of the prefix products, with its epilogue in the product and as partial sums of one to five blocks per k
+    range, asked for one product at a time whatever the estimate would choose: the logits are those of the token-by-token
+    pass (whose activations are not cut to 16 bits; with an fp16 cache some entries go to the other neighbour).
+    m: token tiles of 32, 64 and 128 that end ragged, one to eight of them; columns: QKV 896, gate and up 1408 each, ragged in
+    tiles of 256 and 384; five query heads share a cached one."""
+    shape = synth.ModelShape("ragged-bf16", 3, 640, 10, 2, 1408, 1024, "bf16")
+    w = synth.make_weights(shape, seed=17)
+    prefix = synth.make_prefix_zipf(shape.vocab, m, seed=m)
+    sess = session(shape, w, max_ctx=m + 8, kv_dtype=kv_dtype)
+    seen = set()
+    try:
+        sess.spd_set_dense_prefill(False)
+        sess.spd_prefill(prefix)
+        want = sess.spd_read_logits()
+        sess.spd_set_dense_prefill(True)
+        for product in (QKV, ATTN_OUT, GATE_UP, DOWN):
+            for tile, size in enumerate(PREFIX_TILES):
+                for splits in (1, 2, 3, 4, 5):
+                    cut = sess.spd_test_force_prefill_cut(product, tile, splits, m)
+                    if cut[:3] != (*size, splits):      # too few steps for that many blocks (or, gate and up, no room for the sums)
+                        assert splits > (5 if product == DOWN else 2 if product == GATE_UP and m == 230 else 3), cut
+                        continue
+                    sess.spd_prefill(prefix)
+                    err = np.max(np.abs(sess.spd_read_logits() - want)) / np.max(np.abs(want))
+                    assert err <= bound, f"product {product}, tile {size}, {splits} blocks per k range: {err:.2e}"
+                    seen.add((product, size, cut[3]))
+            sess.spd_test_force_prefill_cut(product, -1, 0, m)
+    finally:
+        sess.close()
+    fused = {(QKV, t, True) for t in PREFIX_TILES} | {(GATE_UP, t, True) for t in PREFIX_TILES if t not in [(32, 256), (64, 384), (128, 384)]}
+    assert seen == fused | {(p, t, False) for p in (QKV, ATTN_OUT, GATE_UP, DOWN) for t in PREFIX_TILES}
+
+
 @pytest.mark.timeout(600)
 @pytest.mark.parametrize("m", [66, 531])
-def test_prefix_products_of_every_tile_shape(m):
-    """7B widths, one layer: together with the other prefix lengths tested, every tile shape of the prefix
-    products runs, fused and as partial sums (66: 64 tokens x 384 columns, split; 531: 128 x 256 with both
-    epilogues, 64 x 384 in five splits; 1030: 128 x 384; up to 64: 32 x 256 and 64 x 256)."""
+def test_prefix_products_at_7b_widths(m):
+    """As the estimate cuts them: 66 tokens (split k ranges throughout) and 531 (QKV, gate and up without)."""
     _layer_truncated(synth.LLAMA7B, 1, m, 2, 2, 31, "fused")
 
 
