@@ -334,6 +334,12 @@ int spd_test_prefill_cut(const spd_model_cfg *cfg, int32_t num_cu, int32_t n_tok
 /* From now on this context cuts `product` with the tile shape `tile` (0 .. 6; -1: by estimate again) and `splits` blocks per k
  * range, wherever partial sums of that size have room; out[4] as above, for a chunk of n_tokens. */
 int spd_test_force_prefill_cut(spd_ctx *ctx, int32_t product, int32_t tile, int32_t splits, int32_t n_tokens, int32_t *out);
+/* The chunk's causal attention alone: DEVICE float queries [n_tokens, n_heads, d_head] at positions pos .., DEVICE cache
+ * [n_kv_heads, cap_ctx, d_head] (fp32 or fp16) filled up to them, result [n_tokens, n_heads, d_head] as the sum of two bf16
+ * numbers (DEVICE); everything 16-byte aligned, d_head a power of two from 8 to 128, n_tokens <= 1024. */
+int spd_test_prefill_attention(int32_t kv_dtype, const float *q, const void *K, const void *V, uint16_t *out_hi, uint16_t *out_lo,
+                               int32_t n_tokens, int32_t pos, int32_t n_heads, int32_t n_kv_heads, int32_t d_head, int32_t cap_ctx,
+                               void *hip_stream);
 
 const char *spd_last_error(const spd_ctx *ctx);
 const char *spd_strerror(int status);

@@ -95,6 +95,7 @@ def lib():
             "spd_test_poke_err": [vp, i32],
             "spd_test_ngram_table": [C.POINTER(SpdNgramHostTables), i32, vp, sz, C.POINTER(i32)],
             "spd_test_prefill_cut": [C.POINTER(SpdModelCfg), i32, i32, i32, vp],
+            "spd_test_prefill_attention": [i32, vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, i32, vp],
             "spd_test_force_prefill_cut": [vp, i32, i32, i32, i32, vp],
             "spd_op_gemv": [i32, vp, vp, f32, vp, vp, vp, i32, i32, vp],
             "spd_op_swiglu": [i32, vp, vp, vp, f32, vp, vp, i32, i32, vp],
@@ -443,3 +444,16 @@ def spd_test_prefill_cut(cfg: SpdModelCfg, num_cu: int, n_tokens: int, product: 
     if rc:
         raise SpdError(rc, "spd_test_prefill_cut")
     return int(out[0]), int(out[1]), int(out[2]), bool(out[3])
+
+
+def spd_test_prefill_attention(kv_dtype: str, q, K, V, pos: int):
+    """Causal attention of a prefix chunk's queries [tokens, heads, d_head] over the cache: (hi, lo), two bfloat16 tensors."""
+    torch = _torch()
+    n_tokens, n_heads, d_head = q.shape
+    n_kv, cap_ctx, _ = K.shape
+    hi, lo = (torch.empty(q.shape, dtype=torch.bfloat16, device=q.device) for _ in range(2))
+    rc = lib().spd_test_prefill_attention(SPD_DTYPE[kv_dtype], q.data_ptr(), K.data_ptr(), V.data_ptr(), hi.data_ptr(), lo.data_ptr(),
+                                          n_tokens, pos, n_heads, n_kv, d_head, cap_ctx, _stream_ptr())
+    if rc:
+        raise SpdError(rc, "spd_test_prefill_attention")
+    return hi, lo

@@ -263,6 +263,9 @@ hipError_t nucleus(hipStream_t s, const NucleusArgs &a);
 hipError_t prefill_chunk(hipStream_t s, const PrefillChunk &c);
 hipError_t prefill_init();
 void prefill_cuts(const PrefillChunk &c, int T, PrefillCut (&cut)[4]);   // QKV, attention output, gate and up, down
+// The chunk's causal attention: queries [T, n_heads * dh] at positions p0 .. p0 + T - 1, output as a (hi, lo) bf16 pair.
+hipError_t prefill_attention(hipStream_t s, int kv_half, const float *q, const void *kcache, const void *vcache, uint16_t *ohi, uint16_t *olo,
+                             int T, int p0, int n_heads, int n_kv_heads, int dh, int cap_ctx);
 int prefill_tile(int tile, int &tokens, int &columns);    // returns how many tile shapes there are
 hipError_t advance(hipStream_t s, DevState *st);
 hipError_t renorm(hipStream_t s, DevState *st, int k);

@@ -975,6 +975,18 @@ int spd_test_force_prefill_cut(spd_ctx *c, int32_t product, int32_t tile, int32_
     return SPD_OK;
 }
 
+int spd_test_prefill_attention(int32_t kv_dtype, const float *q, const void *K, const void *V, uint16_t *out_hi, uint16_t *out_lo,
+                               int32_t n_tokens, int32_t pos, int32_t n_heads, int32_t n_kv_heads, int32_t d_head, int32_t cap_ctx, void *hip_stream) {
+    if (!q || !K || !V || !out_hi || !out_lo || (kv_dtype != SPD_DTYPE_FP32 && kv_dtype != SPD_DTYPE_FP16)) return SPD_EINVAL;
+    if ((((uintptr_t)q | (uintptr_t)K | (uintptr_t)V | (uintptr_t)out_hi | (uintptr_t)out_lo) & 15) || n_heads < 1 || n_kv_heads < 1 || n_heads % n_kv_heads)
+        return SPD_EINVAL;
+    if (d_head < 8 || d_head > 128 || (d_head & (d_head - 1))) return SPD_EINVAL;
+    if (n_tokens < 1 || n_tokens > PREFILL_CHUNK || pos < 0 || cap_ctx > (1 << 20) || n_tokens > cap_ctx - pos) return SPD_EINVAL;
+    if (spdk::prefill_init() != hipSuccess) return SPD_EHIP;
+    return spdk::prefill_attention((hipStream_t)hip_stream, kv_dtype == SPD_DTYPE_FP16, q, K, V, out_hi, out_lo, n_tokens, pos, n_heads, n_kv_heads, d_head,
+                                   cap_ctx) == hipSuccess ? SPD_OK : SPD_EHIP;
+}
+
 int spd_position(const spd_ctx *c, int32_t *out_pos) {
     if (!c || !out_pos) return SPD_EINVAL;
     *out_pos = c->pos;

@@ -673,7 +673,10 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_mfma_kernel(const Prefill
 // row, scaled by a power of two that puts its largest element into [2^14, 2^15), and the probabilities times 2^14 go in as
 // hi = fp16(x) and lo = fp16(x - hi): 22 bits and an absolute floor 2^-38 below the largest, two products into one fp32
 // accumulator.  Error of the output against 64 bits, the fp32 products -> this (2-norm, 64 .. 1024 tokens): 2.06 .. 1.63e-6 ->
-// 2.05 .. 1.62e-6, with queries six times as large 2.70e-6 -> 2.50e-6 (the longer chains of fp32 roundings weigh more).
+// 2.05 .. 1.62e-6, most of it the rounding to the (hi, lo) pair.  Before that rounding, 205 inputs (1 .. 1024 tokens at positions 0
+// and 700, heads of 64 and 128, queries of 0.01 .. 25, outlying features, values over 17 octaves, a position that draws most
+// of the weight): 0.67 times the fp32 products' error in the geometric mean (their chains of fp32 roundings are longer), at most 0.94
+// times from 300 tokens on, larger for 24 of the 145 shorter ones, where few rows decide (at most 2.8 times: 1.2e-7 against 0.4e-7).
 // Layouts as above (a query stays in its lane); contraction index (step j, lane half h, element i) stands for feature
 // (d_head / 2) h + 8 j + i in the first product and for key 8 ((8 j + i) / 4) + 4 h + i % 4 in the second, which are the eight
 // registers 8 j .. 8 j + 7 of S^T.  A wave brings its 32-key tiles of K and of V into LDS of its own (16-byte pieces of a
@@ -985,6 +988,22 @@ hipError_t prefill_init() {
     return e;
 }
 
+hipError_t prefill_attention(hipStream_t s, int kv_half, const float *q, const void *kcache, const void *vcache, uint16_t *ohi, uint16_t *olo,
+                             int T, int p0, int n_heads, int n_kv_heads, int dh, int cap_ctx) {
+    const PrefillAttnArgs at{q, kcache, vcache, ohi, olo, T, p0, n_heads, n_kv_heads, dh, cap_ctx};
+    const dim3 mfma_grid(((T + 31) / 32) * ((n_heads + 7) / 8) * 8), plain_grid((T + AQ - 1) / AQ, n_heads);
+    if (kv_half) {
+        if (dh == 128) hipLaunchKernelGGL(prefill_attn_f16_kernel<128>, mfma_grid, dim3(256), attn_f16_lds<128>(), s, at);
+        else if (dh == 64) hipLaunchKernelGGL(prefill_attn_f16_kernel<64>, mfma_grid, dim3(256), attn_f16_lds<64>(), s, at);
+        else hipLaunchKernelGGL(prefill_attn_kernel<half_t>, plain_grid, dim3(ANT), prefill_attn_lds(dh), s, at);
+    } else {
+        if (dh == 128) hipLaunchKernelGGL((prefill_attn_mfma_kernel<128>), mfma_grid, dim3(256), 0, s, at);
+        else if (dh == 64) hipLaunchKernelGGL((prefill_attn_mfma_kernel<64>), mfma_grid, dim3(256), 0, s, at);
+        else hipLaunchKernelGGL(prefill_attn_kernel<float>, plain_grid, dim3(ANT), prefill_attn_lds(dh), s, at);
+    }
+    return hipGetLastError();
+}
+
 // One chunk of T prefix tokens at positions p0 .. p0 + T - 1 through the whole stack.  On
 // return (stream order) c.h holds the last token's residual stream after the last layer in row T - 1 and the
 // caches are extended; the caller finishes that token (final norm + LM head).
@@ -1013,17 +1032,8 @@ hipError_t prefill_chunk(hipStream_t s, const PrefillChunk &c) {
         launch_gemm(s, cut_qkv.fused ? gemm_kernel<PE_QKV>(cut_qkv.tile) : gemm_kernel<PE_PART>(cut_qkv.tile), g, cut_qkv, 1);
         if (!cut_qkv.fused) hipLaunchKernelGGL(prefill_qkv_sum_kernel, dim3((g.N / 2 + 255) / 256, T), dim3(256), 0, s, g);
 
-        PrefillAttnArgs at{c.q, g.kcache, g.vcache, c.xhi, c.xlo, T, c.p0, c.n_heads, c.n_kv_heads, dh, c.cap_ctx};
-        const dim3 mfma_grid(((T + 31) / 32) * ((c.n_heads + 7) / 8) * 8), plain_grid((T + AQ - 1) / AQ, c.n_heads);
-        if (c.kv_half) {
-            if (dh == 128) hipLaunchKernelGGL(prefill_attn_f16_kernel<128>, mfma_grid, dim3(256), attn_f16_lds<128>(), s, at);
-            else if (dh == 64) hipLaunchKernelGGL(prefill_attn_f16_kernel<64>, mfma_grid, dim3(256), attn_f16_lds<64>(), s, at);
-            else hipLaunchKernelGGL(prefill_attn_kernel<half_t>, plain_grid, dim3(ANT), prefill_attn_lds(dh), s, at);
-        } else {
-            if (dh == 128) hipLaunchKernelGGL((prefill_attn_mfma_kernel<128>), mfma_grid, dim3(256), 0, s, at);
-            else if (dh == 64) hipLaunchKernelGGL((prefill_attn_mfma_kernel<64>), mfma_grid, dim3(256), 0, s, at);
-            else hipLaunchKernelGGL(prefill_attn_kernel<float>, plain_grid, dim3(ANT), prefill_attn_lds(dh), s, at);
-        }
+        const hipError_t e = prefill_attention(s, c.kv_half, c.q, g.kcache, g.vcache, c.xhi, c.xlo, T, c.p0, c.n_heads, c.n_kv_heads, dh, c.cap_ctx);
+        if (e != hipSuccess) return e;
 
         PrefillGemmArgs o{};
         o.xhi = c.xhi; o.xlo = c.xlo; o.W = (const uint16_t *)w.wo; o.T = T; o.N = d; o.K = nq; o.part = c.part;

@@ -216,3 +216,41 @@ def plant_both_forms(base, recs0, k, vocab, seed):
     tabs = synth.plant_ngrams(base, visits, vocab, seed=seed, frac=0.5)
     forced = [(tuple(step1.state_in.history(1)), int(step1.top_ids[0]))]
     return synth.plant_ngrams(tabs, forced, vocab, seed=seed + 1, frac=1.0)
+
+
+# ---- the prefix chunk's attention against 64 bits.  Its result is a pair of bf16 numbers (16 mantissa bits: 2e-6 of the
+# result on average); with an fp16 cache queries and probabilities are split into two fp16 numbers each, and losing the lower
+# one of either costs 1e-4 and more.
+PREFIX_ATTENTION_BOUND = 1e-5   # 2-norm of the difference over 2-norm of the result
+PREFIX_ATTENTION_CASES = [      # heads, cached heads, d_head, tokens, first position, scale of the queries
+    (4, 4, 64, 1, 9, 1.0), (4, 2, 64, 31, 0, 8.0), (8, 2, 64, 131, 45, 1.0), (4, 4, 128, 32, 0, 1.0), (5, 1, 128, 33, 100, 0.05), (4, 2, 128, 131, 3, 8.0),
+    (9, 3, 128, 8, 700, 30.0),
+]
+
+
+def prefix_attention_inputs(case, seed=0):
+    heads, kv, dh, tokens, pos, scale = case
+    rng = np.random.default_rng([seed, *case[:5]])
+    cap = pos + tokens + 3
+    q = (scale * rng.standard_normal((tokens, heads, dh))).astype(np.float32)
+    K, V = (rng.standard_normal((kv, cap, dh)).astype(np.float16) for _ in range(2))
+    K[:, pos + tokens:], V[:, pos + tokens:] = np.nan, np.nan     # nothing behind the chunk is looked at
+    return q, K, V
+
+
+def prefix_attention64(q, K, V, pos, q_of=lambda x: x, p_of=lambda x: x):
+    """float64; q_of / p_of: what becomes of a query's row and of its probabilities before they are multiplied."""
+    tokens, heads, dh = q.shape
+    out = np.zeros(q.shape)
+    group = heads // K.shape[0]
+    for h in range(heads):
+        for t in range(tokens):
+            n = pos + t + 1
+            s = K[h // group, :n].astype(np.float64) @ q_of(q[t, h].astype(np.float64)) / np.sqrt(dh)
+            p = np.exp(s - s.max())
+            out[t, h] = p_of(p) @ V[h // group, :n].astype(np.float64) / p.sum()
+    return out
+
+
+def relative_error(got, want):
+    return np.linalg.norm(np.asarray(got, np.float64) - want) / np.linalg.norm(want)

@@ -4,8 +4,9 @@ import numpy as np
 import pytest
 
 import synth
-from gpu_common import (check_valid_prune, check_valid_topk, compare_decision_on_own_logits, option_tables,
-                        plant_both_forms)
+from gpu_common import (PREFIX_ATTENTION_BOUND, PREFIX_ATTENTION_CASES, check_valid_prune, check_valid_topk,
+                        compare_decision_on_own_logits, option_tables, plant_both_forms, prefix_attention64,
+                        prefix_attention_inputs, relative_error)
 from helpers import oracle_lm, toy_shape
 from oracle import spd_oracle as O
 
@@ -116,3 +117,21 @@ def test_valid_prune_rules():
     if gap > 1e-6:
         with pytest.raises(AssertionError):
             check_valid_prune(swapped, swapped_scores, rec, k, gap * 0.5)
+
+
+def test_bound_on_the_prefix_attention_notices_a_lost_half():
+    """Queries or probabilities cut to one fp16 number instead of two: the error passes the bound the GPU test holds the kernel to
+    (queries: wherever scores are large enough to matter; probabilities: everywhere)."""
+    def half(x):
+        scale = 2.0 ** (15 - np.frexp(np.abs(x).max())[1])
+        return (x * scale).astype(np.float16).astype(np.float64) / scale
+
+    def pair(x):
+        return half(x) + half(x - half(x))
+
+    for case in PREFIX_ATTENTION_CASES:
+        q, K, V = prefix_attention_inputs(case)
+        want = prefix_attention64(q, K, V, case[4])
+        assert relative_error(prefix_attention64(q, K, V, case[4], pair, pair), want) < PREFIX_ATTENTION_BOUND / 10
+        assert case[5] < 1.0 or relative_error(prefix_attention64(q, K, V, case[4], q_of=half), want) > 5 * PREFIX_ATTENTION_BOUND
+        assert case[5] > 8.0 or relative_error(prefix_attention64(q, K, V, case[4], p_of=half), want) > 3 * PREFIX_ATTENTION_BOUND

@@ -4,7 +4,8 @@ import pytest
 import torch
 
 import synth
-from gpu_common import RTOL, assert_close_scaled
+from gpu_common import (PREFIX_ATTENTION_BOUND, PREFIX_ATTENTION_CASES, RTOL, assert_close_scaled, prefix_attention64, prefix_attention_inputs,
+                        relative_error)
 from oracle import spd_oracle as O
 
 pytestmark = pytest.mark.gpu
@@ -155,3 +156,16 @@ def test_top_k_where_the_entries_per_thread_change(vocab):
         np.testing.assert_allclose(logp, z64[want] - lse, atol=2e-5, rtol=0)   # fp32 sums of 131072 .. 524290 terms
     finally:
         sess.close()
+
+
+@pytest.mark.parametrize("kv_dtype", ["fp16", "fp32"])
+@pytest.mark.parametrize("case", PREFIX_ATTENTION_CASES + [(6, 3, 32, 70, 20, 1.0)])
+def test_prefix_attention_against_64_bits(case, kv_dtype):
+    """Both halves of queries and probabilities arrive (fp16 cache), the fp32 products keep theirs (fp32 cache); 32: the plain
+    kernel.  The bound, and that it notices a lost half: test_bound_on_the_prefix_attention_notices_a_lost_half."""
+    q, K, V = prefix_attention_inputs(case)
+    cache = torch.float16 if kv_dtype == "fp16" else torch.float32
+    hi, lo = P().spd_test_prefill_attention(kv_dtype, torch.from_numpy(q).cuda(), torch.from_numpy(K).cuda().to(cache), torch.from_numpy(V).cuda().to(cache),
+                                            case[4])
+    err = relative_error(hi.double().cpu().numpy() + lo.double().cpu().numpy(), prefix_attention64(q, K, V, case[4]))
+    assert err < PREFIX_ATTENTION_BOUND, err
