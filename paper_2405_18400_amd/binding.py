@@ -401,7 +401,7 @@ def spd_op_attention(dtype: str, q, K, V, out, n_ctx: int):
                                 n_heads, n_kv, d_head, n_ctx, cap_ctx, _stream_ptr())
     if rc:
         raise SpdError(rc, "spd_op_attention")
-    torch.cuda.current_stream().synchronize()   # scratch must outlive the kernel
+    torch.cuda.current_stream().synchronize()   # the call returns with its result in place
 
 
 def spd_op_attention_static(dtype: str, q, K, V, out, n_ctx: int):

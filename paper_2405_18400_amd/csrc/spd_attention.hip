@@ -17,7 +17,7 @@
 // kernel cleared first.  Measured, us per call in a row, before -> after: 32 heads x 128, fp16, 80
 // positions 9.8 -> 7.0 (host-bound; the kernel alone 2.0 + 5.8 -> 5.4), 1024 positions 27.7 -> 9.7;
 // fp32, 4096 positions 150 -> 29 (4.6 TB/s); 64 query heads on 8 key/value heads, fp32, 4097
-// positions 204 -> 16.0 (kernels 201 -> 11.8 + 3.8).
+// positions 204 -> 16.0 through the C entry (kernels 201 -> 11.8 + 3.8; the Python entry also waits for its result: 33).
 #include "spd_device.h"
 
 using namespace spdd;

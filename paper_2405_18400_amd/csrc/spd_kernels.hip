@@ -244,11 +244,7 @@ __global__ __launch_bounds__(BLOCK) void superpose_kernel(const SuperposeArgs a)
 }
 
 // ------------------------------------------------------------------ vocabulary top-k
-// Total order used everywhere: larger value first, then smaller index.
-__device__ __forceinline__ bool better(float va, int ia, float vb, int ib) {
-    return va > vb || (va == vb && ia < ib);
-}
-// The order as unsigned integers: a value's key rises with it and is 0 for an absent entry and for a NaN, which is never
+// Total order used everywhere: larger value first, then smaller index.  As unsigned integers: a value's key rises with it and is 0 for an absent entry and for a NaN, which is never
 // better than anything; -0 and 0 are equal.  With the inverted id below it an entry is one 64-bit word.
 __device__ __forceinline__ uint32_t value_key(float v) {
     const uint32_t u = __float_as_uint(v + 0.f);

@@ -372,8 +372,9 @@ int attention_args_status(int dtype, const float *q, const void *K, const void *
     return SPD_OK;
 }
 
-// `scratch`: DEVICE, 256-byte aligned, spd_op_attention_scratch_bytes() bytes: one line per head
-// (not used) followed by the chunks' partial results.
+// `scratch`: DEVICE, 256-byte aligned, spd_op_attention_scratch_bytes() bytes: one line per head, then
+// the chunks' partial results.  Nothing uses the lines any more; they stay in the size, by which the
+// static variant refuses shapes, and callers hold buffers of it.
 int attention_on_scratch(hipStream_t s, int dtype, const float *q, const void *K, const void *V, float *out,
                          void *scratch, int n_heads, int n_kv_heads, int d_head, int n_ctx, int cap_ctx) {
     float *part = (float *)((char *)scratch + up((size_t)n_heads * ATTN_COUNTER_STRIDE * 4));

@@ -143,7 +143,9 @@ enum { PE_PART = 0, PE_QKV = 1, PE_SWIGLU = 2 };
 
 struct PrefillGemmArgs {
     const uint16_t *xhi, *xlo;   // [T, K] bf16 pair
-    const uint16_t *W, *W2;      // [N, K] bf16; W2: the "up" matrix (PE_SWIGLU), or columns N .. 2 N - 1 (PE_PART; N a multiple of the tile), or null
+    // [N, K] bf16; W2: the "up" matrix (PE_SWIGLU), or columns N .. 2 N - 1 of the partial sums (PE_PART), or null.  Each matrix
+    // has n_tiles column tiles of its own; the last may be ragged: its rows are clamped and its stores masked (nc < N).
+    const uint16_t *W, *W2;
     int32_t T, N, K;
     int32_t t_tiles, n_tiles;    // token tiles; column tiles of W (and W2)
     int32_t splits, split_steps; // blocks that share a tile's k range, and steps per block
@@ -202,7 +204,8 @@ struct QkvRow {
 // waves split k, did it before; before -> after, us: 1024 tokens, 12288 x 4096: 290 -> 168 (187 with the rotary
 // epilogue); gate and up 2 x 11008 x 4096: 410 -> 335; 4096 x 11008: 248 -> 160; 256 tokens, 5120 x 13824: 214 -> 77;
 // 64 tokens, 12288 x 4096: 50 -> 24 (4.3 TB/s); gate and up: 73 -> 43; 4096 x 11008: 62 -> 25.  Weights go past
-// the L2's keep list (STREAM_W) where few token tiles read them: 5 % at 64 tokens; at 1024 it costs 2 %.
+// the L2's keep list (STREAM_W) in the tiles of 32 and 64 tokens: 2 .. 4 % faster where one token tile reads them, no
+// difference (1 %) at two to eight, up to 3 % slower at eleven and twelve; no difference in the tiles of 128 tokens.
 template <int KS> __device__ __forceinline__ int swz(int row) {
     static_assert(KS == 64, "rows of 128 bytes");
     return (row & 7) ^ ((row >> 3) & 1);
