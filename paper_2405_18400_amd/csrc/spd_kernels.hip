@@ -421,10 +421,14 @@ __device__ __forceinline__ void ngram_probes(const NgramDev &ng, const int32_t (
 // A chain of latencies.  Whatever does not depend on the kept tokens is asked for at the start: the first MERGE threads
 // select among the slices' candidates, wave by wave, while the others look up the drafts' context totals -- where that
 // selection takes as long as a lookup.  With few drafts it does not, and the totals are looked up together with the counts, a
-// group of lanes for each probe (`one_go`: the kernel at k = 1 .. 4, five orders, 9.1 .. 10.0 -> 5.9 .. 7.4 us).
+// group of lanes for each probe (ONE_GO: the kernel at k = 1 .. 4, five orders, 9.2 .. 10.2 -> 5.7 .. 7.1 us; a kernel of its own,
+// the other would take 0.15 us longer with both ways in it).
 // k = 8, five orders, 1.6 M slots: 28 -> 13 us (merge 2.9, ranks 0.6, hashes 0.8, probes 5.5, mixture and scores 1.1, prune and state 1.5).
 constexpr int ENT = 1024, MERGE = 256, MERGE_WAVES = MERGE / WAVE, GROUPS = ENT / PROBE_LANES;
 
+constexpr bool probes_in_one_go(int k) { return (k * k + k) * SPD_N_ORDERS <= GROUPS; }
+
+template <bool ONE_GO>
 __global__ __launch_bounds__(ENT) void expand_prune_kernel(const ExpandArgs a) {
     __shared__ unsigned long long entry[MERGE_WAVES * SPD_K_MAX], option[SPD_KK];
     __shared__ float sv[MERGE_WAVES * SPD_K_MAX];
@@ -464,7 +468,6 @@ __global__ __launch_bounds__(ENT) void expand_prune_kernel(const ExpandArgs a) {
     };
     const bool use_ng = !a.first && a.alpha != 0.0f;
     const int n_count = k * k * SPD_N_ORDERS, n_total = k * SPD_N_ORDERS;
-    const bool one_go = n_count + n_total <= GROUPS;
     if (tid < MERGE) {
         const int n_cand = a.n_part * k;
         constexpr int NR = TOPK_PART_MAX * SPD_K_MAX / MERGE;
@@ -512,7 +515,7 @@ __global__ __launch_bounds__(ENT) void expand_prune_kernel(const ExpandArgs a) {
         }
         const int e = u / PROBE_LANES;
         static_assert((ENT - MERGE) / PROBE_LANES >= SPD_K_MAX * SPD_N_ORDERS, "a group of lanes per context");
-        if (use_ng && !one_go && e < (n_total + PROBE_LANES - 1) / PROBE_LANES * PROBE_LANES) {   // (whole waves)
+        if (!ONE_GO && use_ng && e < (n_total + PROBE_LANES - 1) / PROBE_LANES * PROBE_LANES) {   // (whole waves)
             int tail[SPD_TAIL];
             int32_t key[1][6];
             unsigned long long total[1];
@@ -557,14 +560,14 @@ __global__ __launch_bounds__(ENT) void expand_prune_kernel(const ExpandArgs a) {
     } else {
         if (use_ng) {
             auto key_of = [&](int e, int32_t (&key)[6]) {          // probe e: draft, kept token, order; behind the counts: draft, order of a total
-                const bool total = e >= n_count;
+                const bool total = ONE_GO && e >= n_count;
                 const int i = total ? (e - n_count) / SPD_N_ORDERS : e / n_total;
                 int tail[SPD_TAIL];
 #pragma unroll
                 for (int q = 0; q < SPD_TAIL; ++q) tail[q] = s_tails[i][q];
                 return make_key(tail, SPD_MIN_ORDER + e % SPD_N_ORDERS, total ? NG_TOTAL : s_top[(e / SPD_N_ORDERS) % k], key);
             };
-            if (one_go) {
+            if constexpr (ONE_GO) {
                 const int n_probe = n_count + n_total, e = tid / PROBE_LANES;
                 if (tid / WAVE * (WAVE / PROBE_LANES) < n_probe) {     // (whole waves)
                     int32_t key[1][6];
@@ -773,7 +776,8 @@ hipError_t topk_partial(hipStream_t s, const TopkArgs &a) {
 }
 
 hipError_t expand_prune(hipStream_t s, const ExpandArgs &a) {
-    hipLaunchKernelGGL(expand_prune_kernel, dim3(1), dim3(ENT), 0, s, a);
+    if (!a.first && a.alpha != 0.0f && probes_in_one_go(a.k)) hipLaunchKernelGGL(expand_prune_kernel<true>, dim3(1), dim3(ENT), 0, s, a);
+    else hipLaunchKernelGGL(expand_prune_kernel<false>, dim3(1), dim3(ENT), 0, s, a);
     return hipGetLastError();
 }
 
