@@ -203,7 +203,7 @@ struct QkvRow {
 // rows round in LDS (160 bytes of LDS traffic per cycle wanted, 128 there) and, up to 96 tokens, one whose
 // waves split k, did it before; before -> after, us: 1024 tokens, 12288 x 4096: 290 -> 168 (187 with the rotary
 // epilogue); gate and up 2 x 11008 x 4096: 410 -> 335; 4096 x 11008: 248 -> 160; 256 tokens, 5120 x 13824: 214 -> 77;
-// 64 tokens, 12288 x 4096: 50 -> 24 (4.3 TB/s); gate and up: 73 -> 43; 4096 x 11008: 62 -> 25.  Weights go past
+// 64 tokens, 12288 x 4096: 50 -> 24 (4.3 TB/s); gate and up: 73 -> 50 (epilogue included); 4096 x 11008: 62 -> 25.  Weights go past
 // the L2's keep list (STREAM_W) in the tiles of 32 and 64 tokens: 2 .. 4 % faster where one token tile reads them, no
 // difference (1 %) at two to eight, up to 3 % slower at eleven and twelve; no difference in the tiles of 128 tokens.
 template <int KS> __device__ __forceinline__ int swz(int row) {
