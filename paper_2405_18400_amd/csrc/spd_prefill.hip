@@ -961,7 +961,8 @@ static PrefillCut cut_product(const PrefillChunk &c, const PrefillForce &force, 
             if (us < best_us) { best_us = us; best = PrefillCut{tile, t_tiles, n_tiles, splits, split_steps, fused}; }
         }
     }
-    return best.t_tiles > 0 ? best : cut_product(c, PrefillForce{0, 0}, T, N, mats, K, epi, part_floats);   // (what was asked for does not fit)
+    if (best.t_tiles == 0 && force.tile_1 != 0) return cut_product(c, PrefillForce{0, 0}, T, N, mats, K, epi, part_floats);   // (what was asked for does not fit)
+    return best;
 }
 
 void prefill_cuts(const PrefillChunk &c, int T, PrefillCut (&cut)[4]) {
