@@ -282,6 +282,8 @@ __device__ __forceinline__ float2 rope_cos_sin(const double *inv_freq, int i, in
     return make_float2((float)cos(ang), (float)sin(ang));
 }
 
+__device__ __forceinline__ int gemv_pos(const GemvArgs &a) { return a.st ? as_global(a.st)->pos : a.pos; }
+
 // ROPE_GIVEN: the caller supplies (cos, sin) of this unit's rotary angle in `given` instead
 // of having the angle evaluated on the spot.
 template <typename WT, int EPI, bool ROPE_GIVEN = false, bool COH = false>

@@ -90,7 +90,8 @@ struct GemvArgs {
     // EPI_QKV
     void *kcache, *vcache;      // [n_kv_heads, cap_ctx, d_head], fp32 or (kv_half) fp16
     int32_t kv_half;
-    const DevState *st;         // position
+    const DevState *st;         // position, or null: pos
+    int32_t pos;
     const double *inv_freq;     // [d_head / 2]
     int32_t n_q_rows, n_kv_rows, d_head, cap_ctx;
     int32_t first_block;        // fused kernel: blocks below this index take no rows of this phase
@@ -236,6 +237,9 @@ struct PrefillChunk {
     uint16_t *xhi, *xlo;               // [PREFILL_CHUNK, max(d_model, n_heads * d_head)] bf16 pair
     uint16_t *uhi, *ulo;               // [PREFILL_CHUNK, d_ffn] bf16 pair (lo behind hi)
     float2 *rope;                      // [PREFILL_CHUNK, d_head / 2]
+    bool final;                        // the prefix ends with this chunk
+    float *attn_part;                  // the stand-alone attention's partial results, as in AttnArgs
+    int32_t max_splits;
     PrefillForce force[4];             // QKV, attention output, gate and up, down
 };
 

@@ -131,7 +131,7 @@ __global__ __launch_bounds__(BLOCK) void gemv_kernel(const GemvArgs a) {
         }
         acc0 = wave_sum(acc0);
         acc1 = wave_sum(acc1);
-        if (lane == 0) gemv_epilogue<WT, EPI>(a, unit, acc0, acc1, EPI == EPI_QKV ? a.st->pos : 0);
+        if (lane == 0) gemv_epilogue<WT, EPI>(a, unit, acc0, acc1, EPI == EPI_QKV ? gemv_pos(a) : 0);
         unit = next_unit;
     }
 }
@@ -231,7 +231,7 @@ __global__ __launch_bounds__(NW * WAVE, gemv_waves(NI)) void gemv_stream_kernel(
                 for (int q = 0; q < wpr; ++q) { acc0 += part[r & 1][w + q].x; acc1 += part[r & 1][w + q].y; }
             }
         }
-        if (seg == 0 && lane == WAVE - 1 && unit < n_units) gemv_epilogue<WT, EPI>(a, unit, acc0, acc1, EPI == EPI_QKV ? a.st->pos : 0);
+        if (seg == 0 && lane == WAVE - 1 && unit < n_units) gemv_epilogue<WT, EPI>(a, unit, acc0, acc1, EPI == EPI_QKV ? gemv_pos(a) : 0);
     }
 }
 

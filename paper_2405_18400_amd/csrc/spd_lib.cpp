@@ -563,10 +563,12 @@ static int run_prefix_pass(spd_ctx *c, int p0, int m) {
         pc.xhi = c->at<uint16_t>(c->L.pf_xhi); pc.xlo = c->at<uint16_t>(c->L.pf_xlo);
         pc.uhi = c->at<uint16_t>(c->L.pf_uhi); pc.ulo = c->at<uint16_t>(c->L.pf_ulo);
         pc.rope = c->at<float2>(c->L.pf_rope);
+        pc.attn_part = c->at<float>(c->L.part); pc.max_splits = c->L.max_splits;
         std::memcpy(pc.force, c->force, sizeof(pc.force));
         int last_T = 0;
         for (int at = p0; at < m; at += PREFILL_CHUNK) {
             pc.p0 = at; pc.T = last_T = (m - at < PREFILL_CHUNK) ? m - at : PREFILL_CHUNK;
+            pc.final = at + pc.T == m;
             HIPCHK(c, spdk::prefill_chunk(c->stream, pc));
         }
         GemvArgs g{};

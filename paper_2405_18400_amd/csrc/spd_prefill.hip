@@ -61,16 +61,16 @@ struct PrefillNormArgs {
     const int32_t *tokens;       // EMBED: token ids of the chunk
     const float *part;           // [splits, T, d]
     float *h;                    // [T, d]: the residual, updated in place
-    const uint16_t *gain;        // null: only h is wanted
+    const uint16_t *gain;
     uint16_t *hi, *lo;           // [T, d]
-    int32_t T, d, splits, first_row;
+    int32_t T, d, splits;
     float eps;
 };
 
 template <bool EMBED>
 __global__ __launch_bounds__(256) void prefill_norm_kernel(const PrefillNormArgs a) {
     __shared__ float red[256 / WAVE];
-    const int t = a.first_row + blockIdx.x, d = a.d;
+    const int t = blockIdx.x, d = a.d;
     const size_t row = (size_t)t * d;
     const size_t from = EMBED ? (size_t)as_global(a.tokens)[t] * d : row;
     float v[NORM_RUNS][8];
@@ -109,7 +109,6 @@ __global__ __launch_bounds__(256) void prefill_norm_kernel(const PrefillNormArgs
             for (int e = 0; e < 8; ++e) ss += v[i][e] * v[i][e];
         }
     }
-    if (a.gain == nullptr) return;
     const float tot = block_sum<256>(ss, red);
     const float rs = 1.0f / sqrtf(tot / (float)d + a.eps);
 #pragma unroll
@@ -1008,17 +1007,25 @@ hipError_t prefill_attention(hipStream_t s, int kv_half, const float *q, const v
     return hipGetLastError();
 }
 
-// One chunk of T prefix tokens at positions p0 .. p0 + T - 1 through the whole stack.  On
-// return (stream order) c.h holds the last token's residual stream after the last layer in row T - 1 and the
-// caches are extended; the caller finishes that token (final norm + LM head).
+// One chunk of T prefix tokens at positions p0 .. p0 + T - 1 through the whole stack.  Only the prefix's last token goes
+// on into the final norm and the LM head, and nothing reads what the last layer makes of the others but their keys and values.
+// So that layer's big product has the key and value rows only, and its query, attention, output projection and feed-forward
+// run for that one token, through the timestep's own operators (fp32 activations); a chunk that is not the prefix's last ends
+// with the keys and values.  Bound of that tail: the layer's weights at HBM's rate, whatever T is.  us for a whole
+// pass, all tokens -> this: four layers of the 7B widths, 1024 tokens 3292 -> 2705, 64 tokens 658 -> 626; three of the 13B, 256
+// tokens 1277 -> 1063.
+// On return (stream order) the caches are extended and, after the final chunk, c.h holds the last token's residual stream after
+// the last layer in row T - 1; the caller finishes that token (final norm + LM head).
 hipError_t prefill_chunk(hipStream_t s, const PrefillChunk &c) {
     const int T = c.T, d = c.d_model, dh = d / c.n_heads, nq = c.n_heads * dh, nkv = c.n_kv_heads * dh;
     hipLaunchKernelGGL(rope_table_kernel, dim3((T * (dh / 2) + 255) / 256), dim3(256), 0, s, c.inv_freq, c.p0, T, dh / 2, c.rope);
     PrefillCut cut[4];
     prefill_cuts(c, T, cut);
-    const PrefillCut &cut_qkv = cut[0], &cut_o = cut[1], &cut_gu = cut[2], &cut_down = cut[3];
+    const PrefillCut &cut_o = cut[1], &cut_gu = cut[2], &cut_down = cut[3];
+    const PrefillCut cut_kv = cut_product(c, c.force[0], T, 2 * nkv, 1, d, PE_QKV, (size_t)PREFILL_CHUNK * c.d_ffn);
     for (int l = 0; l < c.n_layers; ++l) {
         const spd_layer_weights &w = c.layers[l];
+        const bool last = l == c.n_layers - 1;
         PrefillNormArgs n{};
         n.h = c.h; n.gain = (const uint16_t *)w.attn_norm; n.hi = c.xhi; n.lo = c.xlo; n.T = T; n.d = d; n.eps = c.eps; n.part = c.part;
         if (l == 0) {
@@ -1029,12 +1036,15 @@ hipError_t prefill_chunk(hipStream_t s, const PrefillChunk &c) {
             hipLaunchKernelGGL((prefill_norm_kernel<false>), dim3(T), dim3(256), 0, s, n);
         }
         PrefillGemmArgs g{};
-        g.xhi = c.xhi; g.xlo = c.xlo; g.W = (const uint16_t *)w.wqkv; g.T = T; g.N = nq + 2 * nkv; g.K = d; g.part = (float *)c.uhi;
+        g.n_q_rows = last ? 0 : nq; g.n_kv_rows = nkv; g.N = g.n_q_rows + 2 * nkv;
+        g.xhi = c.xhi; g.xlo = c.xlo; g.W = (const uint16_t *)w.wqkv + (size_t)(nq - g.n_q_rows) * d; g.T = T; g.K = d; g.part = (float *)c.uhi;
         g.q = c.q; g.kcache = c.kv + (size_t)(2 * l) * c.kv_layer_bytes;
         g.vcache = c.kv + (size_t)(2 * l + 1) * c.kv_layer_bytes; g.kv_half = c.kv_half;
-        g.rope = c.rope; g.n_q_rows = nq; g.n_kv_rows = nkv; g.d_head = dh; g.cap_ctx = c.cap_ctx; g.p0 = c.p0;
+        g.rope = c.rope; g.d_head = dh; g.cap_ctx = c.cap_ctx; g.p0 = c.p0;
+        const PrefillCut &cut_qkv = last ? cut_kv : cut[0];
         launch_gemm(s, cut_qkv.fused ? gemm_kernel<PE_QKV>(cut_qkv.tile) : gemm_kernel<PE_PART>(cut_qkv.tile), g, cut_qkv, 1);
         if (!cut_qkv.fused) hipLaunchKernelGGL(prefill_qkv_sum_kernel, dim3((g.N / 2 + 255) / 256, T), dim3(256), 0, s, g);
+        if (last) break;
 
         const hipError_t e = prefill_attention(s, c.kv_half, c.q, g.kcache, g.vcache, c.xhi, c.xlo, T, c.p0, c.n_heads, c.n_kv_heads, dh, c.cap_ctx);
         if (e != hipSuccess) return e;
@@ -1055,11 +1065,27 @@ hipError_t prefill_chunk(hipStream_t s, const PrefillChunk &c) {
         dn.xhi = c.uhi; dn.xlo = c.ulo; dn.W = (const uint16_t *)w.w_down; dn.T = T; dn.N = d; dn.K = c.d_ffn; dn.part = c.part;
         launch_gemm(s, gemm_kernel<PE_PART>(cut_down.tile), dn, cut_down, 1);
     }
-    // after the last layer only the last token's row is wanted
-    PrefillNormArgs n{};
-    n.h = c.h; n.part = c.part; n.T = T; n.d = d; n.splits = cut_down.splits; n.first_row = T - 1;
-    hipLaunchKernelGGL((prefill_norm_kernel<false>), dim3(1), dim3(256), 0, s, n);
-    return hipGetLastError();
+    if (!c.final) return hipGetLastError();
+
+    const spd_layer_weights &w = c.layers[c.n_layers - 1];
+    float *h = c.h + (size_t)(T - 1) * d, *att = (float *)c.xhi, *u = (float *)c.uhi;    // (buffers the products are done with)
+    GemvArgs q{};
+    q.W = w.wqkv; q.gain = w.attn_norm; q.eps = c.eps; q.x = h; q.y = c.q; q.rows = q.n_q_rows = nq; q.cols = d; q.n_kv_rows = nkv; q.d_head = dh;
+    q.cap_ctx = c.cap_ctx; q.inv_freq = c.inv_freq; q.pos = c.p0 + T - 1;
+    hipError_t e = gemv(s, SPD_DTYPE_BF16, EPI_QKV, q, c.num_cu);
+    const char *kv = c.kv + (size_t)(2 * (c.n_layers - 1)) * c.kv_layer_bytes;
+    const AttnArgs at{c.q, kv, kv + c.kv_layer_bytes, att, c.attn_part, nullptr, nullptr, c.p0 + T, c.n_heads, c.n_kv_heads, dh, c.cap_ctx, 0, c.max_splits};
+    if (e == hipSuccess) e = attention(s, c.kv_half ? SPD_DTYPE_FP16 : SPD_DTYPE_FP32, at);
+    GemvArgs o{};
+    o.W = w.wo; o.x = att; o.resid = o.y = h; o.rows = d; o.cols = nq;
+    if (e == hipSuccess) e = gemv(s, SPD_DTYPE_BF16, EPI_RESID, o, c.num_cu);
+    GemvArgs f{};
+    f.W = w.w_gate; f.W2 = w.w_up; f.gain = w.ffn_norm; f.eps = c.eps; f.x = h; f.y = u; f.rows = c.d_ffn; f.cols = d;
+    if (e == hipSuccess) e = gemv(s, SPD_DTYPE_BF16, EPI_SWIGLU, f, c.num_cu);
+    GemvArgs dn{};
+    dn.W = w.w_down; dn.x = u; dn.resid = dn.y = h; dn.rows = d; dn.cols = c.d_ffn;
+    if (e == hipSuccess) e = gemv(s, SPD_DTYPE_BF16, EPI_RESID, dn, c.num_cu);
+    return e;
 }
 
 }  // namespace spdk

@@ -283,6 +283,33 @@ def test_dense_prefix_pass_matches_the_oracle_and_the_token_by_token_pass(m):
     assert np.max(np.abs(logits[True] - logits[False])) <= 1e-4 * np.max(np.abs(logits[False]))
 
 
+@pytest.mark.parametrize("layers,heads,kv_heads", [(1, 4, 1), (2, 16, 1), (1, 6, 6), (2, 64, 4)])
+@pytest.mark.parametrize("m", [8, 65, 1024, 1025, 1029])
+@pytest.mark.parametrize("kv_dtype,bound", [("fp32", 1e-4), ("fp16", 1e-3)])
+def test_last_layer_of_the_prefix_pass_runs_for_the_last_token(layers, heads, kv_heads, m, kv_dtype, bound):
+    """Key and value rows of the last layer for every token (16 .. 768 of them: less than a tile, ragged), the rest of it for the
+    prefix's last token, in a chunk's last row or alone in a chunk of its own (1025): the logits are those of the token-by-token
+    pass (bounds as above: 16-bit activations, an fp16 cache's roundings), and so are a timestep's on top of the cache."""
+    shape = synth.ModelShape("tail-bf16", layers, 384 if heads == 6 else 512, heads, kv_heads, 640, 512, "bf16")
+    w = synth.make_weights(shape, seed=m)
+    prefix = synth.make_prefix_zipf(shape.vocab, m, seed=m)
+    sess = session(shape, w, max_ctx=m + 4, kv_dtype=kv_dtype)
+    got = {}
+    try:
+        for dense in (True, False):
+            sess.spd_set_dense_prefill(dense)
+            sess.spd_prefill(prefix)
+            got[dense] = [sess.spd_read_logits()]
+            sess.spd_step(P().SpdDecodeCfg(2, 0.0, 1.0, 0.1))
+            sess.spd_set_state(np.tile(prefix[:5], (2, 1)).astype(np.int32), np.array([-1.0, -2.0], np.float32))
+            sess.spd_step(P().SpdDecodeCfg(2, 0.0, 1.0, 0.1))
+            got[dense].append(sess.spd_read_logits())
+    finally:
+        sess.close()
+    for x, y in zip(got[True], got[False]):
+        assert np.max(np.abs(x - y)) <= bound * np.max(np.abs(y))
+
+
 PREFIX_TILES = [(32, 256), (64, 256), (64, 384), (128, 256), (128, 384), (64, 128), (32, 128)]
 QKV, ATTN_OUT, GATE_UP, DOWN = range(4)
 
