@@ -29,6 +29,7 @@ __device__ __forceinline__ uint16_t bf16_rn(float v) {
     return (uint16_t)(u >> 16);
 }
 __device__ __forceinline__ float bf16_f(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 // x = hi + lo up to 2^-17 |x|
 __device__ __forceinline__ void split_store(uint16_t *hi, uint16_t *lo, size_t at, float x) {
     const uint16_t h = bf16_rn(x);
@@ -36,6 +37,14 @@ __device__ __forceinline__ void split_store(uint16_t *hi, uint16_t *lo, size_t a
     as_global(lo)[at] = bf16_rn(x - bf16_f(h));
 }
 
+// Four consecutive elements, one 8-byte store per half.
+__device__ __forceinline__ void split_store4(uint16_t *hi, uint16_t *lo, size_t at, f32x4 y) {
+    uint32_t h[4], l[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { h[e] = bf16_rn(y[e]); l[e] = bf16_rn(y[e] - bf16_f((uint16_t)h[e])); }
+    *(u32x2 __attribute__((address_space(1))) *)(hi + at) = u32x2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
+    *(u32x2 __attribute__((address_space(1))) *)(lo + at) = u32x2{l[0] | (l[1] << 16), l[2] | (l[3] << 16)};
+}
 // Eight consecutive elements, one 16-byte store per half.
 __device__ __forceinline__ void split_store8(uint16_t *hi, uint16_t *lo, size_t at, const float (&y)[8]) {
     uint32_t h[4], l[4];
@@ -148,6 +157,7 @@ struct PrefillGemmArgs {
     int32_t T, N, K;
     int32_t t_tiles, n_tiles;    // token tiles; column tiles of W (and W2)
     int32_t splits, split_steps; // blocks that share a tile's k range, and steps per block
+    int32_t rotate;              // blocks start at different places of their k range
     float *part;                 // PE_PART: [splits, T, N (2 N with W2)]
     // PE_QKV
     float *q;                    // [T, n_q_rows]
@@ -158,15 +168,15 @@ struct PrefillGemmArgs {
     uint16_t *uhi, *ulo;         // PE_SWIGLU: [T, N]
 };
 
-// Row nc of the fused QKV product: what its values become, and where they go.  `other` is the value of the rotary
-// partner (row nc ^ 1).
-struct QkvRow {
-    bool rotates, odd, is_q;
-    int pair;                    // of the head's rotary pairs
-    char *to;                    // token 0's element
+// Rows nc .. nc + 3 of the fused QKV product (nc a multiple of 4, d_head of 8: one head's, two rotary pairs): what their values become,
+// and where they go.
+struct QkvRows {
+    bool rotates, is_q;
+    int pair;                    // the first of the head's two rotary pairs
+    char *to;                    // token 0's element nc
     size_t stride;               // elements from token to token
-    __device__ __forceinline__ QkvRow(const PrefillGemmArgs &a, int nc) {
-        rotates = nc < a.n_q_rows + a.n_kv_rows; odd = nc & 1; is_q = nc < a.n_q_rows;
+    __device__ __forceinline__ QkvRows(const PrefillGemmArgs &a, int nc) {
+        rotates = nc < a.n_q_rows + a.n_kv_rows; is_q = nc < a.n_q_rows;
         const int rr = is_q ? nc : rotates ? nc - a.n_q_rows : nc - a.n_q_rows - a.n_kv_rows;
         const int head = rr / a.d_head, f = rr % a.d_head;
         pair = f / 2;
@@ -178,37 +188,55 @@ struct QkvRow {
             stride = (size_t)a.d_head;
         }
     }
-    __device__ __forceinline__ float2 angle(const PrefillGemmArgs &a, int t) const {     // (cos, sin); only asked for where it rotates
-        typedef float f32x2 __attribute__((ext_vector_type(2)));
-        const f32x2 cs = *(const f32x2 __attribute__((address_space(1))) *)(a.rope + (size_t)t * (a.d_head / 2) + pair);
-        return make_float2(cs.x, cs.y);
+    // (cos, sin) of both pairs; only asked for where it rotates
+    __device__ __forceinline__ float4 angles(const PrefillGemmArgs &a, int t) const {
+        return global_load_float4((const float *)(a.rope + (size_t)t * (a.d_head / 2) + pair));
     }
-    __device__ __forceinline__ void put(const PrefillGemmArgs &a, int t, float v, float other, float2 cs) const {
-        if (rotates) v = odd ? __fadd_rn(__fmul_rn(other, cs.y), __fmul_rn(v, cs.x)) : __fsub_rn(__fmul_rn(v, cs.x), __fmul_rn(other, cs.y));
-        if (is_q || !a.kv_half) as_global((float *)to)[(size_t)t * stride] = v;
-        else Store<half_t>::store1(to, (size_t)t * stride, v);
+    __device__ __forceinline__ void put(const PrefillGemmArgs &a, int t, f32x4 v, float4 cs) const {
+        if (rotates) {
+            const f32x4 x = v;
+            v.x = __fsub_rn(__fmul_rn(x.x, cs.x), __fmul_rn(x.y, cs.y));
+            v.y = __fadd_rn(__fmul_rn(x.x, cs.y), __fmul_rn(x.y, cs.x));
+            v.z = __fsub_rn(__fmul_rn(x.z, cs.z), __fmul_rn(x.w, cs.w));
+            v.w = __fadd_rn(__fmul_rn(x.z, cs.w), __fmul_rn(x.w, cs.z));
+        }
+        if (is_q || !a.kv_half) {
+            *(f32x4 __attribute__((address_space(1))) *)((float *)to + (size_t)t * stride) = v;
+        } else {
+            const uint32_t lo = (uint32_t)Store<half_t>::bits(v.x) | ((uint32_t)Store<half_t>::bits(v.y) << 16);
+            const uint32_t hi = (uint32_t)Store<half_t>::bits(v.z) | ((uint32_t)Store<half_t>::bits(v.w) << 16);
+            *(u32x2 __attribute__((address_space(1))) *)((uint16_t *)to + (size_t)t * stride) = u32x2{lo, hi};
+        }
     }
 };
 
 // A block of WM x WN waves makes a tile of BM = 32 TT WM tokens x BN = 32 NT WN columns; a wave's share is
-// TT x NT accumulators of 32 x 32.  Per step of KS k the tile's operands (x hi, x lo, W: rows of KS elements)
-// go from memory straight into LDS (no registers in between), ST steps deep: while step s is multiplied, steps
-// s + 1 .. s + ST - 1 are on their way, and one barrier per step says both "step s has arrived" and "the buffer
-// of step s - 1 may be overwritten".  A load instruction fills 1 KB of LDS in lane order, so the rows lie
-// unpadded; the 16-byte pieces of a row are permuted by the row number (`swz`: the lane picks which piece of
-// the row it fetches), which spreads any 8 and any 16 consecutive rows' reads of one piece over all banks.
-// What bounds it: with 128-token tiles the matrix cores at the clock they hold under such products; with few tokens
-// the weight stream (HBM) and each launch's ramp.  A kernel of 64-token tiles whose waves each turned their own 32 weight
-// rows round in LDS (160 bytes of LDS traffic per cycle wanted, 128 there) and, up to 96 tokens, one whose
-// waves split k, did it before; before -> after, us: 1024 tokens, 12288 x 4096: 290 -> 168 (187 with the rotary
-// epilogue); gate and up 2 x 11008 x 4096: 410 -> 335; 4096 x 11008: 248 -> 160; 256 tokens, 5120 x 13824: 214 -> 77;
-// 64 tokens, 12288 x 4096: 50 -> 24 (4.3 TB/s); gate and up: 73 -> 50 (epilogue included); 4096 x 11008: 62 -> 25.  Weights go past
-// the L2's keep list (STREAM_W) in the tiles of 32 and 64 tokens: 2 .. 4 % faster where one token tile reads them, no
+// 2 TT x 2 NT accumulators of 16 x 16 (v_mfma_f32_16x16x32_bf16: with random operands it holds 1.87 .. 2.03 PFLOP/s where the
+// 32 x 32 x 16 form holds 1.70 .. 1.76: power is the limit, both reach 2.48 on zeros).  Per step of 64 k the tile's operands
+// (x hi, x lo, W: rows of 64 elements) go from memory straight into LDS (no registers in between), ST steps deep, and from there
+// half a step ahead into registers: while one half is multiplied the other is read, the first half of the next step behind
+// the step's one barrier, so the matrix cores have work while it is passed.  A load instruction fills 1 KB of LDS in lane
+// order, so the rows lie unpadded; the 16-byte pieces of a row are permuted by the row number (`swz`: the lane picks which
+// piece of the row it fetches) so that the lanes LDS serves together in such a read -- 0 .. 3, 12 .. 15 and 20 .. 27, and so on --
+// find rows of both parities, eight different pieces each: no bank conflicts (row & 7 ^ row >> 3 & 1, right for operands of 32
+// rows, left half of the reads' cycles to conflicts).
+// What bounds it: with 128-token tiles the matrix cores at the clock they hold under such products (on zeros the same launch takes
+// 20 % less) and the loads' way into LDS (without them 18 % less); with few tokens the weight stream and each launch's ramp.
+// Before (products of 32 x 32 x 16, operands read behind the barrier, a lane's results in a column) -> after, us: 1024 tokens,
+// 12288 x 4096 with the rotary epilogue 187 -> 176; gate and up 2 x 11008 x 4096 335 -> 313; 4096 x 11008 175 -> 163; 512 tokens,
+// 2 x 28672 x 8192 838 -> 760; the best shape of each product over the widths of 1B .. 70B: 0.99 times the time up to 64 tokens,
+// 0.96 at 160 .. 384, 0.92 at 1024.
+// Tried: four waves of 64 x 128 (20 % slower: one wave per SIMD), steps of 32 k (64 bytes of a row: half of every cache line
+// fetched twice, 2.5 instead of 4.8 TB/s), a second barrier that frees a buffer earlier, wave priorities, touching the lines of
+// coming steps so that they are in the L2 (0 .. 5 % slower), waves that load x only or W only (-9 .. +13 %).
+// Where a block starts within its k range (`turn`): rows whose length is a power of two lie 8 KB or 16 KB apart, and blocks that all
+// walk them from the same end keep hitting the same memory channels: 4.9 and 4.5 TB/s for a stream of 128-byte pieces, 7.0
+// from rows of 10 or 22 KB.  Blocks of different XCDs, and neighbours on one, therefore start an eighth of the range apart and wrap
+// round: 7B gate and up for 8 tokens 39.5 -> 33, for 64 45.3 -> 38 (two splits); the 70B widths' products 0.84 .. 0.98 times.
+// Other row lengths gain nothing, and with more than one token tile the L2 loses the x that neighbours read together (2 .. 5 % slower).
+// Weights go past the L2's keep list (STREAM_W) in the tiles of 32 and 64 tokens: 2 .. 4 % faster where one token tile reads them, no
 // difference (1 %) at two to eight, up to 3 % slower at eleven and twelve; no difference in the tiles of 128 tokens.
-template <int KS> __device__ __forceinline__ int swz(int row) {
-    static_assert(KS == 64, "rows of 128 bytes");
-    return (row & 7) ^ ((row >> 3) & 1);
-}
+__device__ __forceinline__ int swz(int row) { return (row >> 1) & 7; }
 
 template <int EPI, int WM, int WN, int TT, int NT, int KS, int ST, bool STREAM_W>
 __global__ __launch_bounds__(64 * WM * WN, WM * WN >= 4 ? WM * WN / 4 : 1) void prefill_gemm_kernel(const PrefillGemmArgs a) {
@@ -218,6 +246,7 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN >= 4 ? WM * WN / 4 : 1) void 
     constexpr int PER = ROWS / (RPL * NWV);                // load instructions per wave and stage
     constexpr int STAGE = ROWS * ROWB;
     constexpr int NG = EPI == PE_SWIGLU ? NT / 2 : NT;     // column tiles of a wave per matrix (PE_SWIGLU: gate, then the same units of up)
+    static_assert(KS == 64 && ST >= 2, "two halves of 32 k; rows of 128 bytes");
     static_assert(ROWS % (RPL * NWV) == 0 && BM % RPL == 0 && BN % (2 * RPL) == 0, "whole load instructions");
     extern __shared__ __align__(16) char stages[];         // [ST][STAGE]
     const int lane = threadIdx.x & (WAVE - 1), w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
@@ -254,10 +283,12 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN >= 4 ? WM * WN / 4 : 1) void 
             rows = a.N;
         }
         rsrc[i] = row_resource(base, (uint32_t)rows * (uint32_t)a.K * 2u);
-        off[i] = ((uint32_t)min(row, rows - 1) * (uint32_t)a.K + (uint32_t)s0 * KS) * 2u + 16u * (uint32_t)((lane % (WAVE / RPL)) ^ swz<KS>(q + r));
+        off[i] = ((uint32_t)min(row, rows - 1) * (uint32_t)a.K + (uint32_t)s0 * KS) * 2u + 16u * (uint32_t)((lane % (WAVE / RPL)) ^ swz(q + r));
     }
-    auto fetch = [&](int s) {
-        char *to = stages + (s % ST) * STAGE;
+    const int turn = a.rotate ? (xcd + 3 * (slot / a.t_tiles)) % 8 * n_steps / 8 : 0;
+    auto fetch = [&](int step) {
+        char *to = stages + (step % ST) * STAGE;
+        const int s = step + turn < n_steps ? step + turn : step + turn - n_steps;
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
             if (STREAM_W && RPL * NWV * i >= 2 * BM) load16_to_lds<2>(rsrc[i], to + (w + NWV * i) * 1024, off[i], s * ROWB);
@@ -265,106 +296,111 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN >= 4 ? WM * WN / 4 : 1) void 
         }
     };
 
+    // Operands of half a step in registers, 16 rows of 32 k per piece of work: lane -> row l % 16, k 8 (l / 16) ..  The weights
+    // are the first operand, so a lane ends up with one token's values of four consecutive columns.
     const int wm = w / WN, wn = w % WN;
-    const int x_row = 32 * TT * wm + lane % 32;
-    auto w_row = [&](int nt) {
-        return 2 * BM + lane % 32 + (nt / NG) * (BN / 2) + 32 * (NG * wn + nt % NG);
-    };
-    f32x16 acc[NT][TT];
+    constexpr int NT16 = 2 * NT, TT16 = 2 * TT, NG16 = 2 * NG;
+    const int x_row = 32 * TT * wm + lane % 16;
+    auto w_row = [&](int nt) { return 2 * BM + lane % 16 + (nt / NG16) * (BN / 2) + 16 * (NG16 * wn + nt % NG16); };
+    struct Half { bf16x8 w[NT16], hi[TT16], lo[TT16]; };
+    f32x4 acc[NT16][TT16];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
+    for (int nt = 0; nt < NT16; ++nt)
 #pragma unroll
-        for (int tt = 0; tt < TT; ++tt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[nt][tt][r] = 0.f;
-    auto multiply = [&](int s) {
+        for (int tt = 0; tt < TT16; ++tt) acc[nt][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto read = [&](Half &f, int s, int half) {
         const char *from = stages + (s % ST) * STAGE;
-        auto piece = [&](int row, int j) { return __builtin_bit_cast(bf16x8, *(const u32x4 *)(from + row * ROWB + 16 * ((2 * j + lane / 32) ^ swz<KS>(row)))); };
+        auto piece = [&](int row) { return __builtin_bit_cast(bf16x8, *(const u32x4 *)(from + row * ROWB + 16 * ((4 * half + lane / 16) ^ swz(row)))); };
 #pragma unroll
-        for (int j = 0; j < KS / 16; ++j) {
-            bf16x8 wv[NT], xh[TT], xl[TT];
+        for (int nt = 0; nt < NT16; ++nt) f.w[nt] = piece(w_row(nt));
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) wv[nt] = piece(w_row(nt), j);
-#pragma unroll
-            for (int tt = 0; tt < TT; ++tt) { xh[tt] = piece(x_row + 32 * tt, j); xl[tt] = piece(BM + x_row + 32 * tt, j); }
-#pragma unroll
-            for (int tt = 0; tt < TT; ++tt)
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) acc[nt][tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xh[tt], wv[nt], acc[nt][tt], 0, 0, 0);
-#pragma unroll
-            for (int tt = 0; tt < TT; ++tt)
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) acc[nt][tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xl[tt], wv[nt], acc[nt][tt], 0, 0, 0);
-        }
+        for (int tt = 0; tt < TT16; ++tt) { f.hi[tt] = piece(x_row + 16 * tt); f.lo[tt] = piece(BM + x_row + 16 * tt); }
     };
-    // The compiler does not count loads into LDS: the waits are written out.  Before the barrier every wave has
-    // its own loads of step s in LDS (all but the (ST - 2) PER youngest have arrived: loads arrive in order) and
-    // its reads of step s - 1 behind it.
-    for (int s = 0; s < ST - 1 && s < n_steps; ++s) fetch(s);
+    auto multiply = [&](const Half &f) {
+#pragma unroll
+        for (int tt = 0; tt < TT16; ++tt)
+#pragma unroll
+            for (int nt = 0; nt < NT16; ++nt) acc[nt][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.w[nt], f.hi[tt], acc[nt][tt], 0, 0, 0);
+#pragma unroll
+        for (int tt = 0; tt < TT16; ++tt)
+#pragma unroll
+            for (int nt = 0; nt < NT16; ++nt) acc[nt][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.w[nt], f.lo[tt], acc[nt][tt], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // The compiler does not count loads into LDS: the waits are written out.  One barrier per step, in its middle: before it every
+    // wave has its own loads of step s + 1 in LDS (all but the (ST - 2) PER youngest have arrived: loads arrive in order) and
+    // its last reads of step s behind it, so behind it step s + 1 may be read and the buffer of step s filled again.
+    Half f0, f1;
+    for (int s = 0; s < ST && s < n_steps; ++s) fetch(s);
+    if (n_steps >= ST) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((ST - 1) * PER) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    read(f0, 0, 0);
     int s = 0;
-    for (; s + ST - 1 < n_steps; ++s) {
+    for (; s + ST < n_steps; ++s) {
+        read(f1, s, 1);
+        multiply(f0);
         asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((ST - 2) * PER) : "memory");
-        fetch(s + ST - 1);
-        multiply(s);
+        fetch(s + ST);
+        read(f0, s + 1, 0);
+        multiply(f1);
     }
     for (; s < n_steps; ++s) {
-        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        multiply(s);
+        read(f1, s, 1);
+        multiply(f0);
+        if (s + 1 < n_steps) {
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            read(f0, s + 1, 0);
+        }
+        multiply(f1);
     }
 
-    // C layout: lane -> column, register r -> token 8 (r / 4) + 4 (lane / 32) + r % 4
+    // lane -> token l % 16 of a piece, register r -> column 4 (l / 16) + r
 #pragma unroll
-    for (int nt = 0; nt < NG; ++nt) {
-        const int nc = n0 + 32 * (NG * wn + nt) + lane % 32;
-        const QkvRow row(a, EPI == PE_QKV ? nc : 0);
+    for (int nt = 0; nt < NG16; ++nt) {
+        const int nc = n0 + 16 * (NG16 * wn + nt) + 4 * (lane / 16);
+        const QkvRows rows(a, EPI == PE_QKV ? nc : 0);
+        float4 cs[TT16];
+        if (EPI == PE_QKV && rows.rotates) {    // (one trip for all)
 #pragma unroll
-        for (int tt = 0; tt < TT; ++tt) {
-            const int tb = t0 + 32 * (TT * wm + tt) + 4 * (lane / 32);
-            float2 cs[16];
-            if (EPI == PE_QKV && row.rotates) {    // (one trip for all sixteen)
+            for (int tt = 0; tt < TT16; ++tt) cs[tt] = rows.angles(a, min(t0 + 16 * (TT16 * wm + tt) + lane % 16, a.T - 1));
+        }
 #pragma unroll
-                for (int r = 0; r < 16; ++r) cs[r] = row.angle(a, min(tb + 8 * (r / 4) + r % 4, a.T - 1));
-            }
+        for (int tt = 0; tt < TT16; ++tt) {
+            const int t = t0 + 16 * (TT16 * wm + tt) + lane % 16;
+            if (t >= a.T || nc >= a.N) continue;
+            const f32x4 v = acc[nt][tt];
+            if (EPI == PE_QKV) {
+                rows.put(a, t, v, cs[tt]);
+            } else if (EPI == PE_PART) {
+                const size_t ld = (size_t)a.N * n_mats;
+                *(f32x4 __attribute__((address_space(1))) *)(a.part + ((size_t)split * a.T + t) * ld + (second ? a.N : 0) + nc) = v;
+            } else {
+                const f32x4 up = acc[(nt + NG16) % NT16][tt];
+                f32x4 y;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int t = tb + 8 * (r / 4) + (r % 4);
-                const float v = acc[nt][tt][r];
-                const bool exists = t < a.T && nc < a.N;
-                if (EPI == PE_QKV) {
-                    const float other = dpp_move<0xB1, 0xF>(v, 0.f);   // the rotary partner's column sits in the neighbouring lane
-                    if (exists) row.put(a, t, v, other, cs[r]);
-                } else if (EPI == PE_PART) {
-                    const size_t ld = (size_t)a.N * n_mats;
-                    if (exists) as_global(a.part)[((size_t)split * a.T + t) * ld + (second ? a.N : 0) + nc] = v;
-                } else if (exists) {
-                    const float up = acc[(nt + NG) % NT][tt][r];
-                    split_store(a.uhi, a.ulo, (size_t)t * a.N + nc, v / (1.0f + expf(-v)) * up);
-                }
+                for (int r = 0; r < 4; ++r) y[r] = v[r] / (1.0f + expf(-v[r])) * up[r];
+                split_store4(a.uhi, a.ulo, (size_t)t * a.N + nc, y);
             }
         }
     }
 }
 
-// The partial sums of a split QKV product, added in split order, through its epilogue.  A thread has a rotary pair.
+// The partial sums of a split QKV product, added in split order, through its epilogue.  A thread has four rows.
 __global__ __launch_bounds__(256) void prefill_qkv_sum_kernel(const PrefillGemmArgs a) {
-    const int t = blockIdx.y, nc = 2 * (blockIdx.x * 256 + threadIdx.x);
+    const int t = blockIdx.y, nc = 4 * (blockIdx.x * 256 + threadIdx.x);
     if (nc >= a.N) return;
-    float v0 = 0.f, v1 = 0.f;
+    const QkvRows rows(a, nc);
+    const float4 cs = rows.rotates ? rows.angles(a, t) : make_float4(1.f, 0.f, 1.f, 0.f);
+    f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
     for (int s = 0; s < a.splits; s += 4) {
-        float p0[4], p1[4];
+        float4 p[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const size_t at = ((size_t)min(s + q, a.splits - 1) * a.T + t) * a.N + nc;
-            p0[q] = as_global(a.part)[at]; p1[q] = as_global(a.part)[at + 1];
-        }
+        for (int q = 0; q < 4; ++q) p[q] = global_load_float4(a.part + ((size_t)min(s + q, a.splits - 1) * a.T + t) * a.N + nc);
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            if (s + q < a.splits) { v0 += p0[q]; v1 += p1[q]; }
+            if (s + q < a.splits) { v.x += p[q].x; v.y += p[q].y; v.z += p[q].z; v.w += p[q].w; }
     }
-    const QkvRow even(a, nc), odd(a, nc + 1);
-    const float2 cs = even.rotates ? even.angle(a, t) : make_float2(1.f, 0.f);
-    even.put(a, t, v0, v1, cs);
-    odd.put(a, t, v1, v0, cs);
+    rows.put(a, t, v, cs);
 }
 
 // The same for gate and up: SiLU(gate) * up as the (hi, lo) pair.  A thread has 8 units.
@@ -904,13 +940,11 @@ namespace spdk {
 size_t prefill_attn_lds(int d_head) { return (size_t)(AQ * (d_head + 4) + AK * (d_head + 4) + AK * d_head + AQ * (AK + 1)) * sizeof(float); }
 
 // The tile shapes: one block per compute unit, k steps of 64.  What a step takes a block: `step_us` when all compute units
-// have one, `alone_us` when few do (sweeps over tiles of 64 .. 512 columns, k steps of 32 / 64 / 128, 2 .. 10 stages, 4, 8 and
-// 16 waves; at 128 tokens the products bound it -- 1130 .. 1230 TFLOP/s over the chip, a large library product reaches
-// 1220 -- and at 32 what one compute unit pulls of the weights).
+// have one, `alone_us` when few do (fitted to the sweep below; at 128 tokens the products bound it, at 32 the loads).
 constexpr int KS = 64;
 struct Tile { int bm, bn, stages, waves; double step_us, alone_us; };
-constexpr Tile TILES[] = {{32, 256, 4, 8, 0.68, 0.68}, {64, 256, 3, 8, 1.02, 0.81}, {64, 384, 2, 8, 1.50, 1.40}, {128, 256, 2, 8, 1.70, 1.18},
-                          {128, 384, 2, 8, 2.40, 1.70}, {64, 128, 4, 4, 0.63, 0.48}, {32, 128, 5, 2, 0.53, 0.46}};
+constexpr Tile TILES[] = {{32, 256, 4, 8, 0.73, 0.69}, {64, 256, 3, 8, 1.02, 0.78}, {64, 384, 2, 8, 1.64, 1.48}, {128, 256, 2, 8, 1.64, 1.25},
+                          {128, 384, 2, 8, 2.10, 2.00}, {64, 128, 4, 4, 0.63, 0.46}, {32, 128, 5, 2, 0.51, 0.45}};
 constexpr int N_TILES = 7;
 constexpr int tile_lds(int i) { return TILES[i].stages * (2 * TILES[i].bm + TILES[i].bn) * KS * 2; }
 
@@ -933,10 +967,9 @@ template <int EPI> static GemmFn gemm_kernel(int tile) {
 // compute units: counted over the whole chip 22 columns x 11 token tiles seem to fit 256 compute units once, and take two
 // rounds (7B output projection, 700 tokens, 64 x 384 in two splits: 114 us; 128 x 256: 63).  A last, partly empty round takes
 // between alone_us and step_us a step (128 x 256 at 1.25 and 1.75 rounds: 3.2 and 3.5 us).  The weights come at
-// 6.4 TB/s at best; partial sums are written and read at 4.3 TB/s and, where the product has an epilogue, cost one more launch.
-// Held against every shape and split, products of the 1B, 7B, 13B and 70B widths: the four products of a layer take 1.6 % longer
-// than with the best choice for each at the 33 lengths the constants were fitted to and 1.3 % at 26 others (at most 10 %);
-// with the chip's blocks counted and partial rounds priced as their share + 0.25, 7.7 and 8.4 % (at most 38 %).
+// 7.8 TB/s at best (part of them from the memory-side cache); partial sums are written and read at 4.7 TB/s and, where the product has an epilogue, cost one more launch.
+// Held against every shape and split at 11 lengths from 8 to 1024, products of the 1B, 7B, 13B and 70B widths: the four products of a
+// layer take 0.7 % longer than with the best choice for each, at most 5.3 % (the constants of the kernel before: 2.0 and 7.1 %).
 static PrefillCut cut_product(const PrefillChunk &c, const PrefillForce &force, int T, int N, int mats, int K, int epi, size_t part_floats) {
     PrefillCut best{};
     double best_us = 1e30;
@@ -955,8 +988,8 @@ static PrefillCut cut_product(const PrefillChunk &c, const PrefillForce &force, 
             const int cols = n_tiles * splits * (fused ? 1 : mats);
             const double rounds = (double)((cols + 7) / 8) * t_tiles / (c.num_cu / 8.0), whole = std::floor(rounds), rest = rounds - whole;
             const double step = whole * t.step_us + (rest > 0.0 ? t.alone_us + (t.step_us - t.alone_us) * rest : 0.0);
-            double us = std::max(step * split_steps, (double)N * K * mats * 2 / 6.4e6);
-            if (!fused) us += (double)splits * T * N * mats * 8 / 4.3e6 + (epi == PE_PART ? 0.0 : 3.7);
+            double us = std::max(step * split_steps, (double)N * K * mats * 2 / 7.8e6);
+            if (!fused) us += (double)splits * T * N * mats * 8 / 4.7e6 + (epi == PE_PART ? 0.0 : 3.7);
             if (us < best_us) { best_us = us; best = PrefillCut{tile, t_tiles, n_tiles, splits, split_steps, fused}; }
         }
     }
@@ -977,6 +1010,7 @@ int prefill_tile(int tile, int &tokens, int &columns) { tokens = TILES[tile].bm;
 
 static void launch_gemm(hipStream_t s, GemmFn kernel, PrefillGemmArgs &a, const PrefillCut &cut, int mats) {
     a.t_tiles = cut.t_tiles; a.n_tiles = cut.n_tiles; a.splits = cut.splits; a.split_steps = cut.split_steps;
+    a.rotate = cut.t_tiles == 1 && a.K >= 4096 && (a.K & (a.K - 1)) == 0;
     const int cols = cut.n_tiles * mats * cut.splits;
     hipLaunchKernelGGL(kernel, dim3((cols + 7) / 8 * 8 * cut.t_tiles), dim3(TILES[cut.tile].waves * WAVE), tile_lds(cut.tile), s, a);
 }
@@ -1043,7 +1077,7 @@ hipError_t prefill_chunk(hipStream_t s, const PrefillChunk &c) {
         g.rope = c.rope; g.d_head = dh; g.cap_ctx = c.cap_ctx; g.p0 = c.p0;
         const PrefillCut &cut_qkv = last ? cut_kv : cut[0];
         launch_gemm(s, cut_qkv.fused ? gemm_kernel<PE_QKV>(cut_qkv.tile) : gemm_kernel<PE_PART>(cut_qkv.tile), g, cut_qkv, 1);
-        if (!cut_qkv.fused) hipLaunchKernelGGL(prefill_qkv_sum_kernel, dim3((g.N / 2 + 255) / 256, T), dim3(256), 0, s, g);
+        if (!cut_qkv.fused) hipLaunchKernelGGL(prefill_qkv_sum_kernel, dim3((g.N / 4 + 255) / 256, T), dim3(256), 0, s, g);
         if (last) break;
 
         const hipError_t e = prefill_attention(s, c.kv_half, c.q, g.kcache, g.vcache, c.xhi, c.xlo, T, c.p0, c.n_heads, c.n_kv_heads, dh, c.cap_ctx);

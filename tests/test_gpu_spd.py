@@ -350,6 +350,32 @@ def test_prefix_products_of_every_tile_shape(m, kv_dtype, bound):
     assert seen == fused | {(p, t, False) for p in (QKV, ATTN_OUT, GATE_UP, DOWN) for t in PREFIX_TILES}
 
 
+@pytest.mark.parametrize("m", [9, 32, 61])
+def test_prefix_products_that_start_inside_their_k_range(m):
+    """Rows of 8 KB and one token tile: blocks start an eighth of their k range apart and wrap round, with 4 to 64 steps per
+    block (less than an eighth's worth, ragged eighths, a last split shorter than the others); bound as above."""
+    shape = synth.ModelShape("rotated-bf16", 2, 4096, 32, 4, 4096, 512, "bf16")
+    w = synth.make_weights(shape, seed=3)
+    sess = session(shape, w, max_ctx=m + 8)
+    prefix = synth.make_prefix_zipf(shape.vocab, m, seed=m)
+    try:
+        sess.spd_set_dense_prefill(False)
+        sess.spd_prefill(prefix)
+        want = sess.spd_read_logits()
+        sess.spd_set_dense_prefill(True)
+        for product in (QKV, ATTN_OUT, GATE_UP, DOWN):
+            for tile, size in enumerate(PREFIX_TILES):
+                for splits in (1, 3, 6, 7, 11, 16):
+                    if size[0] > 64 or sess.spd_test_force_prefill_cut(product, tile, splits, m)[:3] != (*size, splits):
+                        continue
+                    sess.spd_prefill(prefix)
+                    err = np.max(np.abs(sess.spd_read_logits() - want)) / np.max(np.abs(want))
+                    assert err <= 1e-4, f"product {product}, tile {size}, {splits} blocks per k range: {err:.2e}"
+            sess.spd_test_force_prefill_cut(product, -1, 0, m)
+    finally:
+        sess.close()
+
+
 @pytest.mark.timeout(600)
 @pytest.mark.parametrize("m", [66, 531])
 def test_prefix_products_at_7b_widths(m):
