@@ -216,8 +216,9 @@ struct PrefillCut { int tile, t_tiles, n_tiles, splits, split_steps; bool fused;
 // What a test asks for instead of the estimate (tile_1: its tile shape + 1, 0: nothing).
 struct PrefillForce { int32_t tile_1, splits; };
 
-// One chunk of the dense prefix pass (bf16 weights): T <= PREFILL_CHUNK prefix tokens at
-// positions p0 .. p0 + T - 1.  Arena buffers are DEVICE, sized for PREFILL_CHUNK rows.
+// One chunk of the dense prefix pass: T <= PREFILL_CHUNK prefix tokens at positions p0 .. p0 + T - 1.  Arena buffers are DEVICE, sized
+// for PREFILL_CHUNK rows (fp32 models: no more than max_ctx).  For an fp32 model xhi is the attention output and uhi the feed-forward's inner vector, both
+// in fp32; it has no part, xlo and ulo.
 constexpr int PREFILL_CHUNK = 1024;
 struct PrefillChunk {
     const void *embed;
@@ -265,11 +266,13 @@ hipError_t topk_partial(hipStream_t s, const TopkArgs &a);
 hipError_t expand_prune(hipStream_t s, const ExpandArgs &a);
 hipError_t nucleus(hipStream_t s, const NucleusArgs &a);
 hipError_t prefill_chunk(hipStream_t s, const PrefillChunk &c);
+hipError_t prefill32_chunk(hipStream_t s, const PrefillChunk &c);      // fp32 models
 hipError_t prefill_init();
 void prefill_cuts(const PrefillChunk &c, int T, PrefillCut (&cut)[4]);   // QKV, attention output, gate and up, down
-// The chunk's causal attention: queries [T, n_heads * dh] at positions p0 .. p0 + T - 1, output as a (hi, lo) bf16 pair.
+// The chunk's causal attention: queries [T, n_heads * dh] at positions p0 .. p0 + T - 1, output as a (hi, lo) bf16 pair, or (fp32 cache,
+// out32 given) in fp32.
 hipError_t prefill_attention(hipStream_t s, int kv_half, const float *q, const void *kcache, const void *vcache, uint16_t *ohi, uint16_t *olo,
-                             int T, int p0, int n_heads, int n_kv_heads, int dh, int cap_ctx);
+                             int T, int p0, int n_heads, int n_kv_heads, int dh, int cap_ctx, float *out32 = nullptr);
 int prefill_tile(int tile, int &tokens, int &columns);    // returns how many tile shapes there are
 hipError_t advance(hipStream_t s, DevState *st);
 hipError_t renorm(hipStream_t s, DevState *st, int k);

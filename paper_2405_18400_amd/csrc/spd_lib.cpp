@@ -22,7 +22,7 @@ const char *const KC_NAMES[KC_N] = {"superpose", "gemv_qkv", "attention", "gemv_
 
 struct Layout {
     size_t pf_h, pf_part, pf_q, pf_xhi, pf_xlo, pf_uhi, pf_ulo, pf_rope;   // dense prefix pass arena (0 = none)
-    bool dense;
+    bool dense, chunk32;   // the prefix pass on the matrix cores exists: bf16 models; fp32 models
     size_t state, sync, layers_dev, prof, act, logits, part, counters, inv_freq, prefix, hist_tok, hist_par, pv, pi, pm, ps, pn, nuc_pb, nuc_count, nuc_hist, nuc_bk, kv, total;
     size_t kv_layer_bytes;   // K (or V) of one layer
     size_t arena_bytes;      // one activation arena
@@ -112,6 +112,17 @@ Layout make_layout(const spd_model_cfg &c) {
         L.pf_ulo = take((size_t)PREFILL_CHUNK * c.d_ffn * 2);
         L.pf_rope = take((size_t)PREFILL_CHUNK * (dh / 2) * 8);
     }
+    // the same for fp32 models: heads its attention has a kernel for, whole pieces of 16 k, 32-bit offsets into a matrix
+    L.chunk32 = c.dtype == SPD_DTYPE_FP32 && (dh == 64 || dh == 128) && c.d_model % 16 == 0 && c.d_ffn % 16 == 0 && c.n_layers > 0 &&
+                (long long)(c.d_ffn > 3 * c.d_model ? c.d_ffn : 3 * c.d_model) * c.d_model < (1ll << 29);
+    if (L.chunk32) {
+        const size_t rows = c.max_ctx < PREFILL_CHUNK ? c.max_ctx : PREFILL_CHUNK;
+        L.pf_h = take(rows * c.d_model * 4);
+        L.pf_q = take(rows * c.d_model * 4);
+        L.pf_xhi = take(rows * c.d_model * 4);
+        L.pf_uhi = take(rows * c.d_ffn * 4);
+        L.pf_rope = take(rows * (dh / 2) * 8);
+    }
     L.kv_layer_bytes = up((size_t)c.n_kv_heads * c.max_ctx * dh * (c.kv_dtype == SPD_DTYPE_FP16 ? 2 : 4));
     L.kv = take(L.kv_layer_bytes * 2 * (size_t)c.n_layers);
     L.total = o;
@@ -136,7 +147,7 @@ struct spd_ctx {
     std::vector<int32_t> text;   // committed tokens: the prefix, extended by spd_commit
     char *pinned;
     size_t pinned_bytes;
-    bool use_graph, timing, use_fused, use_dense;
+    bool use_graph, timing, use_fused, use_dense, use_chunk32;
     int fused_blocks;   // grid of the fused forward kernel; 0 = not available for this shape
     PrefillForce force[4];   // tests only
     hipGraphExec_t step_exec, prefill_exec, nucleus_exec;
@@ -353,6 +364,7 @@ const char *check_dc(const spd_ctx *c, const spd_decode_cfg *dc) {
 }
 
 constexpr int DENSE_PREFILL_MIN = 8;   // shorter prefixes go token by token
+constexpr int CHUNK32_MIN = 2;         // the same for fp32 models (two tokens of two layers of 256 wide: 68 us, 113 one by one)
 
 bool graphs_usable(const spd_ctx *c) { return c->use_graph && !c->timing && c->stream != nullptr; }
 
@@ -437,7 +449,9 @@ int spd_create(const spd_model_cfg *cfg, const spd_weight_ptrs *w, void *workspa
     std::memset(&c->ng, 0, sizeof(c->ng));
     c->state = ST_CREATED; c->pos = 0; c->n_gen = 0; c->k = 0;
     c->use_graph = true; c->timing = false; c->use_fused = true; c->fused_blocks = 0;
-    c->use_dense = c->L.dense && spdk::prefill_init() == hipSuccess;
+    const bool prefill_ready = (c->L.dense || c->L.chunk32) && spdk::prefill_init() == hipSuccess;
+    c->use_dense = c->L.dense && prefill_ready;
+    c->use_chunk32 = c->L.chunk32 && prefill_ready;
     c->step_exec = nullptr; c->prefill_exec = nullptr; c->nucleus_exec = nullptr;
     std::memset(c->force, 0, sizeof(c->force));
     std::memset(&c->step_dc, 0, sizeof(c->step_dc));
@@ -534,7 +548,7 @@ static int run_prefix_pass(spd_ctx *c, int p0, int m) {
     DevState *hs = (DevState *)c->pinned;
     std::memset(hs, 0, sizeof(DevState));
     const int n = m - p0;
-    const bool dense = c->use_dense && n >= DENSE_PREFILL_MIN;
+    const bool dense = (c->use_dense && n >= DENSE_PREFILL_MIN) || (c->use_chunk32 && n >= CHUNK32_MIN);
     hs->pos = dense ? m : p0;      // (the dense pass takes its positions from the host)
     for (int q = 0; q < SPD_TAIL; ++q) {
         const int src = m - SPD_TAIL + q;
@@ -569,7 +583,7 @@ static int run_prefix_pass(spd_ctx *c, int p0, int m) {
         for (int at = p0; at < m; at += PREFILL_CHUNK) {
             pc.p0 = at; pc.T = last_T = (m - at < PREFILL_CHUNK) ? m - at : PREFILL_CHUNK;
             pc.final = at + pc.T == m;
-            HIPCHK(c, spdk::prefill_chunk(c->stream, pc));
+            HIPCHK(c, c->use_chunk32 ? spdk::prefill32_chunk(c->stream, pc) : spdk::prefill_chunk(c->stream, pc));
         }
         GemvArgs g{};
         g.W = c->lm_head; g.gain = c->final_norm; g.eps = mc.rms_eps; g.x = pc.h + (size_t)(last_T - 1) * mc.d_model;
@@ -1018,6 +1032,7 @@ int spd_set_dense_prefill(spd_ctx *c, int32_t enable) {
     if (!c) return SPD_EINVAL;
     if (enable && !c->L.dense) return fail(c, SPD_EINVAL, "no dense prefix pass for this model (bf16 weights, d_head <= 128, widths divisible by 128, d_model <= 8192)");
     c->use_dense = enable != 0;
+    if (!enable) c->use_chunk32 = false;
     return SPD_OK;
 }
 

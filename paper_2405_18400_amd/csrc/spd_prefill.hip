@@ -15,6 +15,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 using namespace spdd;
 
@@ -444,6 +445,7 @@ struct PrefillAttnArgs {
     const float *q;               // [T, n_heads * d_head]
     const void *kcache, *vcache;  // [n_kv_heads, cap_ctx, d_head] in the kernel's KT
     uint16_t *ohi, *olo;          // [T_pad, n_heads * d_head]
+    float *o32;                   // heads of 64 and 128 over an fp32 cache: the output in fp32 instead, or null
     int32_t T, p0, n_heads, n_kv_heads, d_head, cap_ctx;
 };
 
@@ -570,8 +572,10 @@ __global__ __launch_bounds__(ANT) void prefill_attn_kernel(const PrefillAttnArgs
 // Q sits in LDS in operand order; K and V come straight from the cache into the same registers,
 // one after the other, which keeps a wave under half the register file: two waves share a
 // SIMD and one computes while the other waits for its loads.
-template <int DH>
-__global__ __launch_bounds__(256, 2) void prefill_attn_mfma_kernel(const PrefillAttnArgs a) {
+// F32: for an fp32 model, output in fp32 and no sum longer than on the step path: scores in eight chains, a tile's
+// part of the output in four, and what an addition to the running output and sum rounds away is kept beside them.
+template <int DH, bool F32>
+__global__ __launch_bounds__(256, F32 ? 1 : 2) void prefill_attn_mfma_kernel(const PrefillAttnArgs a) {
     constexpr int HALF = DH / 2, NT = DH / 32, NWV = 4;
     constexpr int SLOT = (2 + 16 * NT) * WAVE;               // one wave's partial result: m, sum, O^T
     __shared__ float q_lds[HALF * WAVE];
@@ -600,19 +604,24 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_mfma_kernel(const Prefill
     const int qpos = a.p0 + q0 + c;                          // cached positions 0 .. qpos are visible to this lane's query
     const int last_key = a.p0 + min(q0 + 31, a.T - 1);       // last position any query of the tile sees
     float m = -INFINITY, lsum = 0.f;
-    f32x16 o[NT];
+    constexpr int CHAINS = F32 ? 8 : 1, PV_CHAINS = F32 ? 4 : 1;
+    f32x16 o[NT], rest[NT];
+    float lrest = 0.f;
 #pragma unroll
     for (int dt = 0; dt < NT; ++dt)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
+        for (int r = 0; r < 16; ++r) o[dt][r] = rest[dt][r] = 0.f;
     __syncthreads();                                         // Q is in place
 
     for (int k0 = 32 * w; k0 <= last_key; k0 += 32 * NWV) {
         f32x16 st;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) st[r] = 0.f;
         {
             float kreg[HALF];
+            f32x16 part[CHAINS];
+#pragma unroll
+            for (int q = 0; q < CHAINS; ++q)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) part[q][r] = 0.f;
             const size_t krow = head_at + (size_t)min(k0 + c, last_key) * DH + HALF * h;
 #pragma unroll
             for (int i = 0; i < HALF; i += 4) {
@@ -620,7 +629,12 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_mfma_kernel(const Prefill
                 kreg[i] = v.x; kreg[i + 1] = v.y; kreg[i + 2] = v.z; kreg[i + 3] = v.w;
             }
 #pragma unroll
-            for (int i = 0; i < HALF; ++i) st = __builtin_amdgcn_mfma_f32_32x32x2f32(kreg[i], q_lds[i * WAVE + lane], st, 0, 0, 0);
+            for (int i = 0; i < HALF; ++i) part[i % CHAINS] = __builtin_amdgcn_mfma_f32_32x32x2f32(kreg[i], q_lds[i * WAVE + lane], part[i % CHAINS], 0, 0, 0);
+#pragma unroll
+            for (int n = CHAINS / 2; n > 0; n /= 2)
+#pragma unroll
+                for (int q = 0; q < n; ++q) part[q] += part[q + n];
+            st = part[0];
         }
         __builtin_amdgcn_sched_barrier(0);
         // V of this tile: requested once K's registers are free (a second wave on the same
@@ -649,20 +663,54 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_mfma_kernel(const Prefill
         const float ref = mx == -INFINITY ? 0.f : mx;
         const float alpha = expf(m - ref);
         float psum = 0.f;
+        if (F32) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) { st[r] = expf(st[r] - ref); psum += st[r]; }
-        lsum = lsum * alpha + psum;
+            for (int r = 0; r < 16; ++r) st[r] = expf(st[r] - ref);
+            float two[8];
+#pragma unroll
+            for (int r = 0; r < 8; ++r) two[r] = st[r] + st[r + 8];
+            psum = ((two[0] + two[4]) + (two[1] + two[5])) + ((two[2] + two[6]) + (two[3] + two[7]));
+            const float before = lsum * alpha, after = before + psum, moved = after - before;
+            lrest = lrest * alpha + ((before - (after - moved)) + (psum - moved));
+            lsum = after;
+        } else {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) { st[r] = expf(st[r] - ref); psum += st[r]; }
+            lsum = lsum * alpha + psum;
+        }
         m = mx;
 #pragma unroll
         for (int dt = 0; dt < NT; ++dt) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) o[dt][r] *= alpha;
+            if (F32) {
+                f32x16 part[PV_CHAINS];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) o[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(vreg[dt][i], st[i], o[dt], 0, 0, 0);
+                for (int q = 0; q < PV_CHAINS; ++q)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) part[q][r] = 0.f;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) part[i % PV_CHAINS] = __builtin_amdgcn_mfma_f32_32x32x2f32(vreg[dt][i], st[i], part[i % PV_CHAINS], 0, 0, 0);
+                const f32x16 v = (part[0] + part[1 % PV_CHAINS]) + (part[2 % PV_CHAINS] + part[3 % PV_CHAINS]);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const float after = o[dt][r] + v[r], moved = after - o[dt][r];
+                    rest[dt][r] = rest[dt][r] * alpha + ((o[dt][r] - (after - moved)) + (v[r] - moved));
+                    o[dt][r] = after;
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) o[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(vreg[dt][i], st[i], o[dt], 0, 0, 0);
+            }
         }
         __builtin_amdgcn_sched_barrier(0);
     }
 
+    if (F32) {
+        lsum += lrest;
+#pragma unroll
+        for (int dt = 0; dt < NT; ++dt) o[dt] += rest[dt];
+    }
     // merge: waves 2, 3 -> waves 0, 1; wave 1 -> wave 0.  Wave 0 holds key 0, visible to every
     // query, so the merged maximum is finite.
     auto put = [&](int slot) {
@@ -701,7 +749,10 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_mfma_kernel(const Prefill
         for (int r = 0; r < 16; ++r) {                       // row rho of product tile dt is feature NT rho + dt
             const size_t at = (size_t)t * nqd + head * DH + NT * (8 * (r / 4) + 4 * h + r % 4);
 #pragma unroll
-            for (int dt = 0; dt < NT; ++dt) split_store(a.ohi, a.olo, at + dt, o[dt][r] * inv);
+            for (int dt = 0; dt < NT; ++dt) {
+                if (F32) as_global(a.o32)[at + dt] = o[dt][r] / lsum;
+                else split_store(a.ohi, a.olo, at + dt, o[dt][r] * inv);
+            }
         }
     }
 }
@@ -931,6 +982,177 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_f16_kernel(const PrefillA
     }
 }
 
+// ------------------------------------------------------------------ fp32 models
+// The same pass in fp32 (v_mfma_f32_16x16x4_f32): these models' token-by-token pass takes a chain of dependent phases per token
+// whatever they weigh.  A block of four waves makes a tile of 16 TT tokens x 16 NT columns (PE_SWIGLU: 16 units, gate and up); the
+// waves take every fourth piece of 16 k, straight from memory into registers, U pieces ahead.  A lane holds four consecutive k
+// of its row, so product c of a piece contracts k = 4 (lane / 16) + c, in accumulators of its own; after U pieces they are added up, and
+// what that addition to the running sum rounds away is kept beside it.  So no sum is longer than in the matrix-vector kernel:
+// logits behind 3 .. 1030 tokens of four models (256 .. 2048 wide, six seeds each) differ from 64 bits by 0.98 times what the
+// token-by-token pass leaves (0.90 .. 1.08; with one chain per product and plain sums 1.3, up to 1.5).
+// RMSNorm has no pass of its own: x * gain is what is multiplied, the sum of squares comes along (a block reads its tokens' rows
+// from end to end), and the results are scaled.
+// Bound by latency: 16 tokens of two layers of 256 wide, 13 launches, 812 us token by token -> 74 with the logits; 1030 tokens 55 700 -> 271,
+// of two layers of 2048 wide 97 000 -> 2700.
+enum { PE_RESID = 3 };
+struct Prefill32Args : PrefillGemmArgs {
+    const float *x;              // [T, K]
+    const float *gain;           // [K] or null: no normalisation
+    const float *W32, *W232;     // [N, K]; "up" (PE_SWIGLU)
+    float *y;                    // PE_RESID: [T, N], added to in place; PE_SWIGLU: [T, N]
+    float eps;
+};
+
+template <int EPI, int TT, int NT>
+__global__ __launch_bounds__(256) void prefill32_gemm_kernel(const Prefill32Args a) {
+    constexpr int U = TT * NT == 1 ? 4 : 2;
+    static_assert(EPI != PE_SWIGLU || NT == 2, "gate, up");
+    __shared__ float4 sums[4][NT * TT][WAVE];
+    __shared__ float squares[4][TT][WAVE];
+    const int lane = threadIdx.x & (WAVE - 1), w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;       // all token tiles of a column tile on one XCD
+    const int tile_y = (slot / a.t_tiles) * 8 + xcd, t0 = (slot % a.t_tiles) * 16 * TT;
+    if (tile_y >= a.n_tiles) return;
+    const int n0 = tile_y * 16 * (EPI == PE_SWIGLU ? 1 : NT);
+    const uint32_t row_bytes = (uint32_t)a.K * 4u, none = 0xFFFFFFF0u;      // (past every extent: zeros, no traffic)
+    const __amdgpu_buffer_rsrc_t xr = row_resource(a.x, (uint32_t)a.T * row_bytes), gr = row_resource(a.gain, a.gain != nullptr ? row_bytes : 0u);
+    const __amdgpu_buffer_rsrc_t wr = row_resource(a.W32, (uint32_t)a.N * row_bytes);
+    const __amdgpu_buffer_rsrc_t ur = row_resource(EPI == PE_SWIGLU ? a.W232 : a.W32, (uint32_t)a.N * row_bytes);
+    uint32_t x_at[TT], w_at[NT];
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) { const int t = t0 + 16 * tt + lane % 16; x_at[tt] = t < a.T ? (uint32_t)t * row_bytes : none; }
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) { const int n = n0 + lane % 16 + (EPI == PE_SWIGLU ? 0 : 16 * nt); w_at[nt] = n < a.N ? (uint32_t)n * row_bytes : none; }
+    const int pieces = a.K / 16, mine = (pieces - w + 3) / 4;    // piece i of this wave: 4 i + w
+    const bool normed = a.gain != nullptr;
+    struct Batch { float4 x[U][TT], w[U][NT], g[U]; };
+    auto as_float4 = [](u32x4 v) { return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w)); };
+    auto request = [&](Batch &b, int i0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool there = i0 + u < mine;
+            const uint32_t k = 64u * (uint32_t)(4 * (i0 + u) + w) + 16u * (uint32_t)(lane / 16);
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt) b.x[u][tt] = as_float4(buffer_load16(xr, there && x_at[tt] != none ? x_at[tt] + k : none));
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) b.w[u][nt] = as_float4(buffer_load16(EPI == PE_SWIGLU && nt == 1 ? ur : wr, there && w_at[nt] != none ? w_at[nt] + k : none));
+            if (normed) b.g[u] = as_float4(buffer_load16(gr, there ? k : none));
+        }
+    };
+    f32x4 total[NT][TT], rest[NT][TT];
+    float ss[TT];
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) {
+        ss[tt] = 0.f;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            total[nt][tt] = rest[nt][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+    auto multiply = [&](const Batch &b) {
+        f32x4 acc[2][4][NT][TT];                                 // (two pieces of U take turns: chains of U / 2 products)
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            float xv[TT][4];
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt) {
+                const float4 v = b.x[u][tt];
+                xv[tt][0] = v.x; xv[tt][1] = v.y; xv[tt][2] = v.z; xv[tt][3] = v.w;
+                if (normed) {
+                    ss[tt] += (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
+                    xv[tt][0] *= b.g[u].x; xv[tt][1] *= b.g[u].y; xv[tt][2] *= b.g[u].z; xv[tt][3] *= b.g[u].w;
+                }
+            }
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                const float wv[4] = {b.w[u][nt].x, b.w[u][nt].y, b.w[u][nt].z, b.w[u][nt].w};
+#pragma unroll
+                for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) acc[u % 2][c][nt][tt] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[c], xv[tt][c], u < 2 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[u % 2][c][nt][tt], 0, 0, 0);
+            }
+        }
+        // what an addition to the running sum rounds away is kept beside it
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt) {
+                auto four = [&](int q) { return (acc[q][0][nt][tt] + acc[q][1][nt][tt]) + (acc[q][2][nt][tt] + acc[q][3][nt][tt]); };
+                const f32x4 v = four(0) + four(1);
+                const f32x4 t = total[nt][tt] + v, moved = t - total[nt][tt];
+                rest[nt][tt] += (total[nt][tt] - (t - moved)) + (v - moved);
+                total[nt][tt] = t;
+            }
+    };
+    Batch b0, b1;
+    request(b0, 0);
+    for (int i = 0; i < mine; i += 2 * U) {
+        request(b1, i + U);
+        multiply(b0);
+        request(b0, i + 2 * U);
+        multiply(b1);
+    }
+
+    // lane -> token l % 16 of a piece, register r -> column 4 (l / 16) + r; the waves' shares in wave order
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt) {
+            const f32x4 v = total[nt][tt] + rest[nt][tt];
+            sums[w][nt * TT + tt][lane] = make_float4(v.x, v.y, v.z, v.w);
+        }
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) squares[w][tt][lane] = ss[tt];
+    __syncthreads();
+    constexpr int FIRST = EPI == PE_SWIGLU ? TT : NT * TT;       // (gate and up go together)
+    for (int e = w; e < FIRST; e += 4) {
+        const int nt = e / TT, tt = e % TT, t = t0 + 16 * tt + lane % 16, nc = n0 + 16 * nt + 4 * (lane / 16);
+        float rs = 1.f;
+        if (normed) {
+            float sq = 0.f;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                float part = 0.f;
+#pragma unroll
+                for (int g = 0; g < 4; ++g) part += squares[q][tt][16 * g + lane % 16];
+                sq += part;
+            }
+            rs = 1.0f / sqrtf(sq / (float)a.K + a.eps);
+        }
+        auto sum = [&](int at) {
+            const float4 p = sums[0][at][lane], q = sums[1][at][lane], r = sums[2][at][lane], s = sums[3][at][lane];
+            return f32x4{(p.x + q.x) + (r.x + s.x), (p.y + q.y) + (r.y + s.y), (p.z + q.z) + (r.z + s.z), (p.w + q.w) + (r.w + s.w)} * rs;
+        };
+        const f32x4 v = sum(e);
+        if (t >= a.T || nc >= a.N) continue;
+        if (EPI == PE_QKV) {
+            const QkvRows rows(a, nc);
+            rows.put(a, t, v, rows.rotates ? rows.angles(a, t) : make_float4(1.f, 0.f, 1.f, 0.f));
+        } else {
+            f32x4 __attribute__((address_space(1))) *to = (f32x4 __attribute__((address_space(1))) *)(a.y + (size_t)t * a.N + nc);
+            if (EPI == PE_RESID) {
+                *to = *to + v;
+            } else {
+                const f32x4 up = sum(TT + tt);
+                f32x4 y;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) y[r] = v[r] / (1.0f + expf(-v[r])) * up[r];
+                *to = y;
+            }
+        }
+    }
+}
+
+// The chunk's embeddings and its rotary table.
+__global__ __launch_bounds__(256) void prefill32_start_kernel(const float *embed, const int32_t *tokens, float *h, int d, const double *inv_freq, int p0, int T, int half, float2 *table) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < T * (d / 4)) {
+        const float4 v = global_load_float4(embed + (size_t)as_global(tokens)[i / (d / 4)] * d + 4 * (i % (d / 4)));
+        *(f32x4 __attribute__((address_space(1))) *)(h + 4 * (size_t)i) = f32x4{v.x, v.y, v.z, v.w};
+    }
+    if (i < T * half) table[i] = rope_cos_sin(inv_freq, i % half, p0 + i / half);
+}
+
 template <int DH> constexpr int attn_f16_lds() { return 4 * 2 * 32 * DH * 2 + 32 * DH * 4; }
 
 }  // namespace
@@ -1026,19 +1248,43 @@ hipError_t prefill_init() {
 }
 
 hipError_t prefill_attention(hipStream_t s, int kv_half, const float *q, const void *kcache, const void *vcache, uint16_t *ohi, uint16_t *olo,
-                             int T, int p0, int n_heads, int n_kv_heads, int dh, int cap_ctx) {
-    const PrefillAttnArgs at{q, kcache, vcache, ohi, olo, T, p0, n_heads, n_kv_heads, dh, cap_ctx};
+                             int T, int p0, int n_heads, int n_kv_heads, int dh, int cap_ctx, float *out32) {
+    const PrefillAttnArgs at{q, kcache, vcache, ohi, olo, out32, T, p0, n_heads, n_kv_heads, dh, cap_ctx};
     const dim3 mfma_grid(((T + 31) / 32) * ((n_heads + 7) / 8) * 8), plain_grid((T + AQ - 1) / AQ, n_heads);
     if (kv_half) {
         if (dh == 128) hipLaunchKernelGGL(prefill_attn_f16_kernel<128>, mfma_grid, dim3(256), attn_f16_lds<128>(), s, at);
         else if (dh == 64) hipLaunchKernelGGL(prefill_attn_f16_kernel<64>, mfma_grid, dim3(256), attn_f16_lds<64>(), s, at);
         else hipLaunchKernelGGL(prefill_attn_kernel<half_t>, plain_grid, dim3(ANT), prefill_attn_lds(dh), s, at);
     } else {
-        if (dh == 128) hipLaunchKernelGGL((prefill_attn_mfma_kernel<128>), mfma_grid, dim3(256), 0, s, at);
-        else if (dh == 64) hipLaunchKernelGGL((prefill_attn_mfma_kernel<64>), mfma_grid, dim3(256), 0, s, at);
+        if (dh == 128 && out32) hipLaunchKernelGGL((prefill_attn_mfma_kernel<128, true>), mfma_grid, dim3(256), 0, s, at);
+        else if (dh == 64 && out32) hipLaunchKernelGGL((prefill_attn_mfma_kernel<64, true>), mfma_grid, dim3(256), 0, s, at);
+        else if (out32) return hipErrorInvalidValue;
+        else if (dh == 128) hipLaunchKernelGGL((prefill_attn_mfma_kernel<128, false>), mfma_grid, dim3(256), 0, s, at);
+        else if (dh == 64) hipLaunchKernelGGL((prefill_attn_mfma_kernel<64, false>), mfma_grid, dim3(256), 0, s, at);
         else hipLaunchKernelGGL(prefill_attn_kernel<float>, plain_grid, dim3(ANT), prefill_attn_lds(dh), s, at);
     }
     return hipGetLastError();
+}
+
+// What is left of the last layer for the prefix's last token, whose query is in `q`: attention, output projection and feed-forward through the
+// timestep's own operators, on row T - 1 of c.h in place.
+static hipError_t last_token(hipStream_t s, const PrefillChunk &c, int dtype, const float *q, float *att, float *u) {
+    const spd_layer_weights &w = c.layers[c.n_layers - 1];
+    const int T = c.T, d = c.d_model, dh = d / c.n_heads, nq = c.n_heads * dh;
+    float *h = c.h + (size_t)(T - 1) * d;
+    const char *kv = c.kv + (size_t)(2 * (c.n_layers - 1)) * c.kv_layer_bytes;
+    const AttnArgs at{q, kv, kv + c.kv_layer_bytes, att, c.attn_part, nullptr, nullptr, c.p0 + T, c.n_heads, c.n_kv_heads, dh, c.cap_ctx, 0, c.max_splits};
+    hipError_t e = attention(s, c.kv_half ? SPD_DTYPE_FP16 : SPD_DTYPE_FP32, at);
+    GemvArgs o{};
+    o.W = w.wo; o.x = att; o.resid = o.y = h; o.rows = d; o.cols = nq;
+    if (e == hipSuccess) e = gemv(s, dtype, EPI_RESID, o, c.num_cu);
+    GemvArgs f{};
+    f.W = w.w_gate; f.W2 = w.w_up; f.gain = w.ffn_norm; f.eps = c.eps; f.x = h; f.y = u; f.rows = c.d_ffn; f.cols = d;
+    if (e == hipSuccess) e = gemv(s, dtype, EPI_SWIGLU, f, c.num_cu);
+    GemvArgs dn{};
+    dn.W = w.w_down; dn.x = u; dn.resid = dn.y = h; dn.rows = d; dn.cols = c.d_ffn;
+    if (e == hipSuccess) e = gemv(s, dtype, EPI_RESID, dn, c.num_cu);
+    return e;
 }
 
 // One chunk of T prefix tokens at positions p0 .. p0 + T - 1 through the whole stack.  Only the prefix's last token goes
@@ -1101,25 +1347,47 @@ hipError_t prefill_chunk(hipStream_t s, const PrefillChunk &c) {
     }
     if (!c.final) return hipGetLastError();
 
-    const spd_layer_weights &w = c.layers[c.n_layers - 1];
-    float *h = c.h + (size_t)(T - 1) * d, *att = (float *)c.xhi, *u = (float *)c.uhi;    // (buffers the products are done with)
     GemvArgs q{};
-    q.W = w.wqkv; q.gain = w.attn_norm; q.eps = c.eps; q.x = h; q.y = c.q; q.rows = q.n_q_rows = nq; q.cols = d; q.n_kv_rows = nkv; q.d_head = dh;
-    q.cap_ctx = c.cap_ctx; q.inv_freq = c.inv_freq; q.pos = c.p0 + T - 1;
-    hipError_t e = gemv(s, SPD_DTYPE_BF16, EPI_QKV, q, c.num_cu);
-    const char *kv = c.kv + (size_t)(2 * (c.n_layers - 1)) * c.kv_layer_bytes;
-    const AttnArgs at{c.q, kv, kv + c.kv_layer_bytes, att, c.attn_part, nullptr, nullptr, c.p0 + T, c.n_heads, c.n_kv_heads, dh, c.cap_ctx, 0, c.max_splits};
-    if (e == hipSuccess) e = attention(s, c.kv_half ? SPD_DTYPE_FP16 : SPD_DTYPE_FP32, at);
-    GemvArgs o{};
-    o.W = w.wo; o.x = att; o.resid = o.y = h; o.rows = d; o.cols = nq;
-    if (e == hipSuccess) e = gemv(s, SPD_DTYPE_BF16, EPI_RESID, o, c.num_cu);
-    GemvArgs f{};
-    f.W = w.w_gate; f.W2 = w.w_up; f.gain = w.ffn_norm; f.eps = c.eps; f.x = h; f.y = u; f.rows = c.d_ffn; f.cols = d;
-    if (e == hipSuccess) e = gemv(s, SPD_DTYPE_BF16, EPI_SWIGLU, f, c.num_cu);
-    GemvArgs dn{};
-    dn.W = w.w_down; dn.x = u; dn.resid = dn.y = h; dn.rows = d; dn.cols = c.d_ffn;
-    if (e == hipSuccess) e = gemv(s, SPD_DTYPE_BF16, EPI_RESID, dn, c.num_cu);
-    return e;
+    q.W = c.layers[c.n_layers - 1].wqkv; q.gain = c.layers[c.n_layers - 1].attn_norm; q.eps = c.eps; q.x = c.h + (size_t)(T - 1) * d; q.y = c.q;
+    q.rows = q.n_q_rows = nq; q.cols = d; q.n_kv_rows = nkv; q.d_head = dh; q.cap_ctx = c.cap_ctx; q.inv_freq = c.inv_freq; q.pos = c.p0 + T - 1;
+    const hipError_t e = gemv(s, SPD_DTYPE_BF16, EPI_QKV, q, c.num_cu);
+    if (e != hipSuccess) return e;
+    return last_token(s, c, SPD_DTYPE_BF16, c.q, (float *)c.xhi, (float *)c.uhi);    // (buffers the products are done with)
+}
+
+// The same pass for an fp32 model, without partial sums.
+hipError_t prefill32_chunk(hipStream_t s, const PrefillChunk &c) {
+    const int T = c.T, d = c.d_model, dh = d / c.n_heads, nq = c.n_heads * dh, nkv = c.n_kv_heads * dh;
+    float *att = (float *)c.xhi, *u = (float *)c.uhi;
+    hipLaunchKernelGGL(prefill32_start_kernel, dim3((T * (d / 4) + 255) / 256), dim3(256), 0, s, (const float *)c.embed, c.prefix + c.p0, c.h, d, c.inv_freq, c.p0, T,
+                       dh / 2, c.rope);
+    auto product = [&](auto epi, Prefill32Args &a, const float *x, const void *gain, const void *W, const void *W2, int N, int K, float *y) {
+        constexpr int EPI = decltype(epi)::value;
+        a.x = x; a.gain = (const float *)gain; a.W32 = (const float *)W; a.W232 = (const float *)W2; a.N = N; a.K = K; a.y = y; a.T = T; a.eps = c.eps;
+        // one piece of 16 tokens where there are no more; two of 16 columns where that still gives every compute unit a block
+        const int tt = T <= 16 ? 1 : 2, nt = EPI == PE_SWIGLU || (long long)N * T >= 1024ll * c.num_cu ? 2 : 1;
+        a.t_tiles = (T + 16 * tt - 1) / (16 * tt); a.n_tiles = EPI == PE_SWIGLU ? (N + 15) / 16 : (N + 16 * nt - 1) / (16 * nt);
+        constexpr int N1 = EPI == PE_SWIGLU ? 2 : 1;
+        void (*kernel)(Prefill32Args) = tt == 1 ? (nt == 1 ? prefill32_gemm_kernel<EPI, 1, N1> : prefill32_gemm_kernel<EPI, 1, 2>)
+                                                : (nt == 1 ? prefill32_gemm_kernel<EPI, 2, N1> : prefill32_gemm_kernel<EPI, 2, 2>);
+        hipLaunchKernelGGL(kernel, dim3((a.n_tiles + 7) / 8 * 8 * a.t_tiles), dim3(256), 0, s, a);
+    };
+    for (int l = 0; l < c.n_layers; ++l) {
+        const spd_layer_weights &w = c.layers[l];
+        Prefill32Args g{};
+        g.q = c.q; g.kcache = c.kv + (size_t)(2 * l) * c.kv_layer_bytes; g.vcache = c.kv + (size_t)(2 * l + 1) * c.kv_layer_bytes;
+        g.rope = c.rope; g.n_q_rows = nq; g.n_kv_rows = nkv; g.d_head = dh; g.cap_ctx = c.cap_ctx; g.p0 = c.p0;
+        product(std::integral_constant<int, PE_QKV>{}, g, c.h, w.attn_norm, w.wqkv, nullptr, nq + 2 * nkv, d, nullptr);
+        if (l == c.n_layers - 1) break;
+        const hipError_t e = prefill_attention(s, 0, c.q, g.kcache, g.vcache, nullptr, nullptr, T, c.p0, c.n_heads, c.n_kv_heads, dh, c.cap_ctx, att);
+        if (e != hipSuccess) return e;
+        Prefill32Args o{}, f{}, dn{};
+        product(std::integral_constant<int, PE_RESID>{}, o, att, nullptr, w.wo, nullptr, d, nq, c.h);
+        product(std::integral_constant<int, PE_SWIGLU>{}, f, c.h, w.ffn_norm, w.w_gate, w.w_up, c.d_ffn, d, u);
+        product(std::integral_constant<int, PE_RESID>{}, dn, u, nullptr, w.w_down, nullptr, d, c.d_ffn, c.h);
+    }
+    if (!c.final) return hipGetLastError();
+    return last_token(s, c, SPD_DTYPE_FP32, c.q + (size_t)(T - 1) * nq, att, u);
 }
 
 }  // namespace spdk

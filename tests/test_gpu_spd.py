@@ -310,6 +310,36 @@ def test_last_layer_of_the_prefix_pass_runs_for_the_last_token(layers, heads, kv
         assert np.max(np.abs(x - y)) <= bound * np.max(np.abs(y))
 
 
+FP32_CHUNKS = [synth.ModelShape("fp32-256", 2, 256, 4, 4, 1024, 512, "fp32"), synth.ModelShape("fp32-gqa", 3, 512, 8, 2, 1008, 512, "fp32"),
+               synth.ModelShape("fp32-128", 1, 384, 3, 1, 464, 512, "fp32"), synth.ModelShape("fp32-heads-of-16", 2, 336, 21, 7, 1008, 512, "fp32")]
+
+
+@pytest.mark.parametrize("shape", FP32_CHUNKS, ids=lambda s: s.name)
+@pytest.mark.parametrize("m", [2, 3, 15, 16, 17, 32, 33, 64, 100, 1025])
+def test_fp32_prefix_pass_matches_the_token_by_token_pass(shape, m):
+    """An fp32 model's prefix as chunks (one and two pieces of 16 tokens, ragged; 1025: a token in a chunk of its own; gate and up ragged
+    against a batch of pieces; the last shape has no such pass): logits as token by token, and those of a timestep on top of the
+    cache.  Either pass is 2 .. 7e-7 from 64 bits: 5e-6 of the largest logit leaves room for both."""
+    w = synth.make_weights(shape, seed=m)
+    prefix = synth.make_prefix_uniform(shape.vocab, m, seed=m)
+    sess = session(shape, w, max_ctx=m + 4)
+    got = []
+    try:
+        for token_by_token in (False, True):
+            if token_by_token:
+                sess.spd_set_dense_prefill(False)
+            sess.spd_prefill(prefix)
+            got.append([sess.spd_read_logits()])
+            sess.spd_step(P().SpdDecodeCfg(2, 0.0, 1.0, 0.1))
+            sess.spd_set_state(np.resize(prefix, (2, 5)).astype(np.int32), np.array([-1.0, -2.0], np.float32))
+            sess.spd_step(P().SpdDecodeCfg(2, 0.0, 1.0, 0.1))
+            got[-1].append(sess.spd_read_logits())
+    finally:
+        sess.close()
+    for x, y in zip(*got):
+        assert np.max(np.abs(x - y)) <= 5e-6 * np.max(np.abs(y))
+
+
 PREFIX_TILES = [(32, 256), (64, 256), (64, 384), (128, 256), (128, 384), (64, 128), (32, 128)]
 QKV, ATTN_OUT, GATE_UP, DOWN = range(4)
 
