@@ -371,7 +371,10 @@ class Session:
 
 # ---- stand-alone operators (device tensors in, device tensors out; caller's current stream)
 def _stream_ptr():
-    return _torch().cuda.current_stream().cuda_stream
+    """The calling thread's current stream on its current device, without the Stream object around it: building that
+    took 2.9 of the 7.2 us such a call took the host (now 0.4 of 4.7)."""
+    torch = _torch()
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def spd_op_gemv(dtype: str, W, x, y, gain=None, eps=0.0, residual=None):
@@ -397,11 +400,12 @@ def spd_op_attention(dtype: str, q, K, V, out, n_ctx: int):
     n_kv, cap_ctx, _ = K.shape
     scratch = torch.empty(lib().spd_op_attention_scratch_bytes(n_heads, d_head, cap_ctx) + 256, dtype=torch.uint8, device=q.device)
     ptr = (scratch.data_ptr() + 255) // 256 * 256
+    stream = torch.cuda.current_stream()
     rc = lib().spd_op_attention(SPD_DTYPE[dtype], q.data_ptr(), K.data_ptr(), V.data_ptr(), out.data_ptr(), ptr,
-                                n_heads, n_kv, d_head, n_ctx, cap_ctx, _stream_ptr())
+                                n_heads, n_kv, d_head, n_ctx, cap_ctx, stream.cuda_stream)
     if rc:
         raise SpdError(rc, "spd_op_attention")
-    torch.cuda.current_stream().synchronize()   # the call returns with its result in place
+    stream.synchronize()   # the call returns with its result in place
 
 
 def spd_op_attention_static(dtype: str, q, K, V, out, n_ctx: int):

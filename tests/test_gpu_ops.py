@@ -169,3 +169,18 @@ def test_prefix_attention_against_64_bits(case, kv_dtype):
                                             case[4])
     err = relative_error(hi.double().cpu().numpy() + lo.double().cpu().numpy(), prefix_attention64(q, K, V, case[4]))
     assert err < PREFIX_ATTENTION_BOUND, err
+
+
+def test_operators_run_on_the_callers_current_stream():
+    """The handle the operators launch on is torch's current stream, inside and outside a stream context and per thread."""
+    import threading
+    from paper_2405_18400_amd import binding
+    same = lambda: binding._stream_ptr() == torch.cuda.current_stream().cuda_stream  # noqa: E731
+    side, seen = torch.cuda.Stream(), []
+    with torch.cuda.stream(side):
+        seen += [same(), binding._stream_ptr() == side.cuda_stream]
+        other = threading.Thread(target=lambda: seen.extend([same(), binding._stream_ptr() != side.cuda_stream]))
+        other.start()
+        other.join()
+    seen += [same(), binding._stream_ptr() != side.cuda_stream]
+    assert all(seen) and len(seen) == 6
