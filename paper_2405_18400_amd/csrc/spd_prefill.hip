@@ -62,10 +62,10 @@ __device__ __forceinline__ void split_store8(uint16_t *hi, uint16_t *lo, size_t 
 // ------------------------------------------------------------------ residual stream, norms, rotary table
 // The residual stream between two products, one block per token: h = embedding of the token (EMBED), or
 // h = residual + the partial sums of the product before it, added in split order; then
-// xn = h * rsqrt(mean h^2 + eps) * gain as the (hi, lo) pair.  A thread keeps its runs of 8 consecutive
-// features in registers (one read of the row) and writes each run as one 16-byte store per half.
-constexpr int NORM_RUNS = 4;      // runs per thread: d_model <= 256 * 8 * NORM_RUNS
-
+// xn = h * rsqrt(mean h^2 + eps) * gain as the (hi, lo) pair.  A thread has 8 consecutive features (d_model / 8 threads, whole
+// waves, at most 1024: d_model <= 8192) and asks for all it needs at once, up to eight splits and the gain: one trip to memory.
+// Bound by that trip with few tokens, by the bytes with many: 64 tokens of 4096 in 8 splits 6.5 -> 5.2 us, 1024 tokens in 2
+// splits 15.6 -> 15.2 (256 threads with two to four runs of 8 features, splits four at a time, the gain behind the sum of squares).
 struct PrefillNormArgs {
     const uint16_t *embed;       // EMBED: [vocab, d]
     const int32_t *tokens;       // EMBED: token ids of the chunk
@@ -78,65 +78,62 @@ struct PrefillNormArgs {
 };
 
 template <bool EMBED>
-__global__ __launch_bounds__(256) void prefill_norm_kernel(const PrefillNormArgs a) {
-    __shared__ float red[256 / WAVE];
-    const int t = blockIdx.x, d = a.d;
-    const size_t row = (size_t)t * d;
-    const size_t from = EMBED ? (size_t)as_global(a.tokens)[t] * d : row;
-    float v[NORM_RUNS][8];
+__global__ __launch_bounds__(1024) void prefill_norm_kernel(const PrefillNormArgs a) {
+    __shared__ float red[1024 / WAVE];
+    const int t = blockIdx.x, d = a.d, c = 8 * threadIdx.x;
+    const bool mine = c < d;
+    const size_t at = (size_t)t * d + (mine ? c : 0);
+    auto take = [&](const float *x, float (&y)[8]) {
+        const float4 p = global_load_float4(x), q = global_load_float4(x + 4);
+        y[0] = p.x; y[1] = p.y; y[2] = p.z; y[3] = p.w; y[4] = q.x; y[5] = q.y; y[6] = q.z; y[7] = q.w;
+    };
+    auto widen = [](u32x4 g, float (&y)[8]) {
+        const uint32_t w[4] = {g.x, g.y, g.z, g.w};
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) { y[e] = __uint_as_float(w[e / 2] << 16); y[e + 1] = __uint_as_float(w[e / 2] & 0xFFFF0000u); }
+    };
+    float v[8];
+    const u32x4 gw = global_load16(a.gain + (mine ? c : 0));
+    if (EMBED) {
+        widen(global_load16(a.embed + (size_t)as_global(a.tokens)[t] * d + (mine ? c : 0)), v);
+    } else {
+        constexpr int AT_ONCE = 8;
+        float more[AT_ONCE][8], sum[8];
+        take(a.h + at, v);
+        for (int s = 0; s < a.splits; s += AT_ONCE) {
+#pragma unroll
+            for (int q = 0; q < AT_ONCE; ++q)
+                if (s + q < a.splits) take(a.part + (size_t)(s + q) * a.T * d + at, more[q]);
+#pragma unroll
+            for (int q = 0; q < AT_ONCE; ++q)
+                if (s + q < a.splits) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) sum[e] = s + q == 0 ? more[q][e] : sum[e] + more[q][e];
+                }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] += sum[e];
+    }
     float ss = 0.f;
 #pragma unroll
-    for (int i = 0; i < NORM_RUNS; ++i) {
-        const int c = 8 * (threadIdx.x + 256 * i);
-        if (c < d) {
-            if (EMBED) {
-                const u32x4 g = global_load16(a.embed + from + c);
-                const uint32_t gw[4] = {g.x, g.y, g.z, g.w};
-#pragma unroll
-                for (int e = 0; e < 8; e += 2) { v[i][e] = __uint_as_float(gw[e / 2] << 16); v[i][e + 1] = __uint_as_float(gw[e / 2] & 0xFFFF0000u); }
-            } else {
-                auto take = [&](const float *x, float (&y)[8]) {
-                    const float4 p = global_load_float4(x), q = global_load_float4(x + 4);
-                    y[0] = p.x; y[1] = p.y; y[2] = p.z; y[3] = p.w; y[4] = q.x; y[5] = q.y; y[6] = q.z; y[7] = q.w;
-                };
-                take(a.h + row + c, v[i]);
-                float sum[8], more[4][8];
-                take(a.part + row + c, sum);
-                for (int s = 1; s < a.splits; s += 4) {   // four at a time: each is a trip to memory (a split past the last re-reads it with weight 0)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) take(a.part + (size_t)min(s + q, a.splits - 1) * a.T * d + row + c, more[q]);
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) sum[e] += s + q < a.splits ? more[q][e] : 0.f;
-                }
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[i][e] += sum[e];
-            }
-            *(f32x4 __attribute__((address_space(1))) *)(a.h + row + c) = f32x4{v[i][0], v[i][1], v[i][2], v[i][3]};
-            *(f32x4 __attribute__((address_space(1))) *)(a.h + row + c + 4) = f32x4{v[i][4], v[i][5], v[i][6], v[i][7]};
-#pragma unroll
-            for (int e = 0; e < 8; ++e) ss += v[i][e] * v[i][e];
-        }
+    for (int e = 0; e < 8; ++e) ss += v[e] * v[e];
+    ss = wave_sum_last(mine ? ss : 0.f);
+    if (threadIdx.x % WAVE == WAVE - 1) red[threadIdx.x / WAVE] = ss;
+    if (mine) {
+        *(f32x4 __attribute__((address_space(1))) *)(a.h + at) = f32x4{v[0], v[1], v[2], v[3]};
+        *(f32x4 __attribute__((address_space(1))) *)(a.h + at + 4) = f32x4{v[4], v[5], v[6], v[7]};
     }
-    const float tot = block_sum<256>(ss, red);
+    __syncthreads();
+    if (!mine) return;
+    float tot = 0.f, g[8];
+    for (int w = 0; w < (int)blockDim.x / WAVE; ++w) tot += red[w];
     const float rs = 1.0f / sqrtf(tot / (float)d + a.eps);
+    widen(gw, g);
 #pragma unroll
-    for (int i = 0; i < NORM_RUNS; ++i) {
-        const int c = 8 * (threadIdx.x + 256 * i);
-        if (c < d) {
-            const u32x4 g = global_load16(a.gain + c);
-            float y[8];
-#pragma unroll
-            for (int e = 0; e < 8; e += 2) {
-                const uint32_t gw = e < 2 ? g.x : e < 4 ? g.y : e < 6 ? g.z : g.w;
-                y[e] = v[i][e] * rs * __uint_as_float(gw << 16);
-                y[e + 1] = v[i][e + 1] * rs * __uint_as_float(gw & 0xFFFF0000u);
-            }
-            split_store8(a.hi, a.lo, row + c, y);
-        }
-    }
+    for (int e = 0; e < 8; ++e) v[e] = v[e] * rs * g[e];
+    split_store8(a.hi, a.lo, at, v);
 }
+static int norm_threads(int d) { return (d / 8 + WAVE - 1) / WAVE * WAVE; }
 
 // (cos, sin) of (p0 + t) * theta^(-2i/d_head), in double as everywhere else
 __global__ void rope_table_kernel(const double *inv_freq, int p0, int T, int half, float2 *table) {
@@ -1287,11 +1284,16 @@ static hipError_t last_token(hipStream_t s, const PrefillChunk &c, int dtype, co
     return e;
 }
 
+// The last layer's query rows stay in the product of all tokens while that costs less than a launch of their own (a matrix-vector product over
+// them, in fp32): up to this many tokens x rows x k.  A whole pass over two layers, rows in the product against by themselves: 1B widths
+// 0.92 (8 tokens) .. 0.99 (512); 7B 0.94 (8) .. 0.98 (160), 1.01 (192), 1.04 (512); 13B 0.96 .. 0.98 (128), 1.01 (192); 70B 0.98 (8) .. 0.99 (64), 1.01 (96).
+constexpr long long LAST_QUERY_WITH = 3000000000ll;
+
 // One chunk of T prefix tokens at positions p0 .. p0 + T - 1 through the whole stack.  Only the prefix's last token goes
 // on into the final norm and the LM head, and nothing reads what the last layer makes of the others but their keys and values.
 // So that layer's big product has the key and value rows only, and its query, attention, output projection and feed-forward
 // run for that one token, through the timestep's own operators (fp32 activations); a chunk that is not the prefix's last ends
-// with the keys and values.  Bound of that tail: the layer's weights at HBM's rate, whatever T is.  us for a whole
+// with the keys and values.  (With few tokens the query rows stay in the big product: LAST_QUERY_WITH.)  Bound of that tail: the layer's weights at HBM's rate, whatever T is.  us for a whole
 // pass, all tokens -> this: four layers of the 7B widths, 1024 tokens 3292 -> 2705, 64 tokens 658 -> 626; three of the 13B, 256
 // tokens 1277 -> 1063.
 // On return (stream order) the caches are extended and, after the final chunk, c.h holds the last token's residual stream after
@@ -1302,7 +1304,8 @@ hipError_t prefill_chunk(hipStream_t s, const PrefillChunk &c) {
     PrefillCut cut[4];
     prefill_cuts(c, T, cut);
     const PrefillCut &cut_o = cut[1], &cut_gu = cut[2], &cut_down = cut[3];
-    const PrefillCut cut_kv = cut_product(c, c.force[0], T, 2 * nkv, 1, d, PE_QKV, (size_t)PREFILL_CHUNK * c.d_ffn);
+    const bool own_query = (long long)T * nq * d > LAST_QUERY_WITH;
+    const PrefillCut cut_last = own_query ? cut_product(c, c.force[0], T, 2 * nkv, 1, d, PE_QKV, (size_t)PREFILL_CHUNK * c.d_ffn) : cut[0];
     for (int l = 0; l < c.n_layers; ++l) {
         const spd_layer_weights &w = c.layers[l];
         const bool last = l == c.n_layers - 1;
@@ -1310,18 +1313,18 @@ hipError_t prefill_chunk(hipStream_t s, const PrefillChunk &c) {
         n.h = c.h; n.gain = (const uint16_t *)w.attn_norm; n.hi = c.xhi; n.lo = c.xlo; n.T = T; n.d = d; n.eps = c.eps; n.part = c.part;
         if (l == 0) {
             n.embed = (const uint16_t *)c.embed; n.tokens = c.prefix + c.p0;
-            hipLaunchKernelGGL((prefill_norm_kernel<true>), dim3(T), dim3(256), 0, s, n);
+            hipLaunchKernelGGL((prefill_norm_kernel<true>), dim3(T), dim3(norm_threads(d)), 0, s, n);
         } else {
             n.splits = cut_down.splits;
-            hipLaunchKernelGGL((prefill_norm_kernel<false>), dim3(T), dim3(256), 0, s, n);
+            hipLaunchKernelGGL((prefill_norm_kernel<false>), dim3(T), dim3(norm_threads(d)), 0, s, n);
         }
         PrefillGemmArgs g{};
-        g.n_q_rows = last ? 0 : nq; g.n_kv_rows = nkv; g.N = g.n_q_rows + 2 * nkv;
+        g.n_q_rows = last && own_query ? 0 : nq; g.n_kv_rows = nkv; g.N = g.n_q_rows + 2 * nkv;
         g.xhi = c.xhi; g.xlo = c.xlo; g.W = (const uint16_t *)w.wqkv + (size_t)(nq - g.n_q_rows) * d; g.T = T; g.K = d; g.part = (float *)c.uhi;
         g.q = c.q; g.kcache = c.kv + (size_t)(2 * l) * c.kv_layer_bytes;
         g.vcache = c.kv + (size_t)(2 * l + 1) * c.kv_layer_bytes; g.kv_half = c.kv_half;
         g.rope = c.rope; g.d_head = dh; g.cap_ctx = c.cap_ctx; g.p0 = c.p0;
-        const PrefillCut &cut_qkv = last ? cut_kv : cut[0];
+        const PrefillCut &cut_qkv = last ? cut_last : cut[0];
         launch_gemm(s, cut_qkv.fused ? gemm_kernel<PE_QKV>(cut_qkv.tile) : gemm_kernel<PE_PART>(cut_qkv.tile), g, cut_qkv, 1);
         if (!cut_qkv.fused) hipLaunchKernelGGL(prefill_qkv_sum_kernel, dim3((g.N / 4 + 255) / 256, T), dim3(256), 0, s, g);
         if (last) break;
@@ -1333,7 +1336,7 @@ hipError_t prefill_chunk(hipStream_t s, const PrefillChunk &c) {
         o.xhi = c.xhi; o.xlo = c.xlo; o.W = (const uint16_t *)w.wo; o.T = T; o.N = d; o.K = nq; o.part = c.part;
         launch_gemm(s, gemm_kernel<PE_PART>(cut_o.tile), o, cut_o, 1);
         n.splits = cut_o.splits; n.gain = (const uint16_t *)w.ffn_norm;
-        hipLaunchKernelGGL((prefill_norm_kernel<false>), dim3(T), dim3(256), 0, s, n);
+        hipLaunchKernelGGL((prefill_norm_kernel<false>), dim3(T), dim3(norm_threads(d)), 0, s, n);
 
         PrefillGemmArgs f{};
         f.xhi = c.xhi; f.xlo = c.xlo; f.W = (const uint16_t *)w.w_gate; f.W2 = (const uint16_t *)w.w_up; f.T = T; f.N = c.d_ffn; f.K = d; f.part = c.part;
@@ -1346,13 +1349,14 @@ hipError_t prefill_chunk(hipStream_t s, const PrefillChunk &c) {
         launch_gemm(s, gemm_kernel<PE_PART>(cut_down.tile), dn, cut_down, 1);
     }
     if (!c.final) return hipGetLastError();
+    if (!own_query) return last_token(s, c, SPD_DTYPE_BF16, c.q + (size_t)(T - 1) * nq, (float *)c.xhi, (float *)c.uhi);    // (buffers the products are done with)
 
     GemvArgs q{};
     q.W = c.layers[c.n_layers - 1].wqkv; q.gain = c.layers[c.n_layers - 1].attn_norm; q.eps = c.eps; q.x = c.h + (size_t)(T - 1) * d; q.y = c.q;
     q.rows = q.n_q_rows = nq; q.cols = d; q.n_kv_rows = nkv; q.d_head = dh; q.cap_ctx = c.cap_ctx; q.inv_freq = c.inv_freq; q.pos = c.p0 + T - 1;
     const hipError_t e = gemv(s, SPD_DTYPE_BF16, EPI_QKV, q, c.num_cu);
     if (e != hipSuccess) return e;
-    return last_token(s, c, SPD_DTYPE_BF16, c.q, (float *)c.xhi, (float *)c.uhi);    // (buffers the products are done with)
+    return last_token(s, c, SPD_DTYPE_BF16, c.q, (float *)c.xhi, (float *)c.uhi);
 }
 
 // The same pass for an fp32 model, without partial sums.
