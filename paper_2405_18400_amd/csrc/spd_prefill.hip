@@ -208,8 +208,8 @@ struct QkvRows {
     }
 };
 
-// A block of WM x WN waves makes a tile of BM = 32 TT WM tokens x BN = 32 NT WN columns; a wave's share is
-// 2 TT x 2 NT accumulators of 16 x 16 (v_mfma_f32_16x16x32_bf16: with random operands it holds 1.87 .. 2.03 PFLOP/s where the
+// A block of WM x WN waves makes a tile of BM = 16 TT WM tokens x BN = 16 NT WN columns; a wave's share is
+// TT x NT accumulators of 16 x 16 (v_mfma_f32_16x16x32_bf16: with random operands it holds 1.87 .. 2.03 PFLOP/s where the
 // 32 x 32 x 16 form holds 1.70 .. 1.76: power is the limit, both reach 2.48 on zeros).  Per step of 64 k the tile's operands
 // (x hi, x lo, W: rows of 64 elements) go from memory straight into LDS (no registers in between), ST steps deep, and from there
 // half a step ahead into registers: while one half is multiplied the other is read, the first half of the next step behind
@@ -238,7 +238,7 @@ __device__ __forceinline__ int swz(int row) { return (row >> 1) & 7; }
 
 template <int EPI, int WM, int WN, int TT, int NT, int KS, int ST, bool STREAM_W>
 __global__ __launch_bounds__(64 * WM * WN, WM * WN >= 4 ? WM * WN / 4 : 1) void prefill_gemm_kernel(const PrefillGemmArgs a) {
-    constexpr int NWV = WM * WN, BM = 32 * TT * WM, BN = 32 * NT * WN;
+    constexpr int NWV = WM * WN, BM = 16 * TT * WM, BN = 16 * NT * WN;
     constexpr int ROWB = KS * 2, RPL = 1024 / ROWB;        // bytes per row; rows one load instruction of a wave brings
     constexpr int ROWS = 2 * BM + BN;                      // rows of a stage: x hi, x lo, W
     constexpr int PER = ROWS / (RPL * NWV);                // load instructions per wave and stage
@@ -297,32 +297,31 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN >= 4 ? WM * WN / 4 : 1) void 
     // Operands of half a step in registers, 16 rows of 32 k per piece of work: lane -> row l % 16, k 8 (l / 16) ..  The weights
     // are the first operand, so a lane ends up with one token's values of four consecutive columns.
     const int wm = w / WN, wn = w % WN;
-    constexpr int NT16 = 2 * NT, TT16 = 2 * TT, NG16 = 2 * NG;
-    const int x_row = 32 * TT * wm + lane % 16;
-    auto w_row = [&](int nt) { return 2 * BM + lane % 16 + (nt / NG16) * (BN / 2) + 16 * (NG16 * wn + nt % NG16); };
-    struct Half { bf16x8 w[NT16], hi[TT16], lo[TT16]; };
-    f32x4 acc[NT16][TT16];
+    const int x_row = 16 * TT * wm + lane % 16;
+    auto w_row = [&](int nt) { return 2 * BM + lane % 16 + (nt / NG) * (BN / 2) + 16 * (NG * wn + nt % NG); };
+    struct Half { bf16x8 w[NT], hi[TT], lo[TT]; };
+    f32x4 acc[NT][TT];
 #pragma unroll
-    for (int nt = 0; nt < NT16; ++nt)
+    for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-        for (int tt = 0; tt < TT16; ++tt) acc[nt][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int tt = 0; tt < TT; ++tt) acc[nt][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
     auto read = [&](Half &f, int s, int half) {
         const char *from = stages + (s % ST) * STAGE;
         auto piece = [&](int row) { return __builtin_bit_cast(bf16x8, *(const u32x4 *)(from + row * ROWB + 16 * ((4 * half + lane / 16) ^ swz(row)))); };
 #pragma unroll
-        for (int nt = 0; nt < NT16; ++nt) f.w[nt] = piece(w_row(nt));
+        for (int nt = 0; nt < NT; ++nt) f.w[nt] = piece(w_row(nt));
 #pragma unroll
-        for (int tt = 0; tt < TT16; ++tt) { f.hi[tt] = piece(x_row + 16 * tt); f.lo[tt] = piece(BM + x_row + 16 * tt); }
+        for (int tt = 0; tt < TT; ++tt) { f.hi[tt] = piece(x_row + 16 * tt); f.lo[tt] = piece(BM + x_row + 16 * tt); }
     };
     auto multiply = [&](const Half &f) {
 #pragma unroll
-        for (int tt = 0; tt < TT16; ++tt)
+        for (int tt = 0; tt < TT; ++tt)
 #pragma unroll
-            for (int nt = 0; nt < NT16; ++nt) acc[nt][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.w[nt], f.hi[tt], acc[nt][tt], 0, 0, 0);
+            for (int nt = 0; nt < NT; ++nt) acc[nt][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.w[nt], f.hi[tt], acc[nt][tt], 0, 0, 0);
 #pragma unroll
-        for (int tt = 0; tt < TT16; ++tt)
+        for (int tt = 0; tt < TT; ++tt)
 #pragma unroll
-            for (int nt = 0; nt < NT16; ++nt) acc[nt][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.w[nt], f.lo[tt], acc[nt][tt], 0, 0, 0);
+            for (int nt = 0; nt < NT; ++nt) acc[nt][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.w[nt], f.lo[tt], acc[nt][tt], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
     };
     // The compiler does not count loads into LDS: the waits are written out.  One barrier per step, in its middle: before it every
@@ -354,17 +353,17 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN >= 4 ? WM * WN / 4 : 1) void 
 
     // lane -> token l % 16 of a piece, register r -> column 4 (l / 16) + r
 #pragma unroll
-    for (int nt = 0; nt < NG16; ++nt) {
-        const int nc = n0 + 16 * (NG16 * wn + nt) + 4 * (lane / 16);
+    for (int nt = 0; nt < NG; ++nt) {
+        const int nc = n0 + 16 * (NG * wn + nt) + 4 * (lane / 16);
         const QkvRows rows(a, EPI == PE_QKV ? nc : 0);
-        float4 cs[TT16];
+        float4 cs[TT];
         if (EPI == PE_QKV && rows.rotates) {    // (one trip for all)
 #pragma unroll
-            for (int tt = 0; tt < TT16; ++tt) cs[tt] = rows.angles(a, min(t0 + 16 * (TT16 * wm + tt) + lane % 16, a.T - 1));
+            for (int tt = 0; tt < TT; ++tt) cs[tt] = rows.angles(a, min(t0 + 16 * (TT * wm + tt) + lane % 16, a.T - 1));
         }
 #pragma unroll
-        for (int tt = 0; tt < TT16; ++tt) {
-            const int t = t0 + 16 * (TT16 * wm + tt) + lane % 16;
+        for (int tt = 0; tt < TT; ++tt) {
+            const int t = t0 + 16 * (TT * wm + tt) + lane % 16;
             if (t >= a.T || nc >= a.N) continue;
             const f32x4 v = acc[nt][tt];
             if (EPI == PE_QKV) {
@@ -373,7 +372,7 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN >= 4 ? WM * WN / 4 : 1) void 
                 const size_t ld = (size_t)a.N * n_mats;
                 *(f32x4 __attribute__((address_space(1))) *)(a.part + ((size_t)split * a.T + t) * ld + (second ? a.N : 0) + nc) = v;
             } else {
-                const f32x4 up = acc[(nt + NG16) % NT16][tt];
+                const f32x4 up = acc[(nt + NG) % NT][tt];
                 f32x4 y;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) y[r] = v[r] / (1.0f + expf(-v[r])) * up[r];
@@ -1158,26 +1157,40 @@ namespace spdk {
 
 size_t prefill_attn_lds(int d_head) { return (size_t)(AQ * (d_head + 4) + AK * (d_head + 4) + AK * d_head + AQ * (AK + 1)) * sizeof(float); }
 
-// The tile shapes: one block per compute unit, k steps of 64.  What a step takes a block: `step_us` when all compute units
+// The tile shapes: one block per compute unit, k steps of 64.  Gate and up, the widest product, leaves the chip idlest where its tiles do
+// not come out even (7B widths: 86 tiles of 256 columns; three rounds at 1024 tokens where 2.7 would do), and has shapes of its own:
+// its time over 41 lengths from 8 to 1024 and four widths 0.91 in the geometric mean, 0.61 at best (7B, 384 tokens: 175 -> 107 us), the four
+// products' of a layer 0.96.  What a step takes a block: `step_us` when all compute units
 // have one, `alone_us` when few do (fitted to the sweep below; at 128 tokens the products bound it, at 32 the loads).
 constexpr int KS = 64;
 struct Tile { int bm, bn, stages, waves; double step_us, alone_us; };
-constexpr Tile TILES[] = {{32, 256, 4, 8, 0.73, 0.69}, {64, 256, 3, 8, 1.02, 0.78}, {64, 384, 2, 8, 1.64, 1.48}, {128, 256, 2, 8, 1.64, 1.25},
-                          {128, 384, 2, 8, 2.10, 2.00}, {64, 128, 4, 4, 0.63, 0.46}, {32, 128, 5, 2, 0.51, 0.45}};
-constexpr int N_TILES = 7;
+constexpr Tile TILES[] = {{32, 256, 4, 8, 0.75, 0.75}, {64, 256, 3, 8, 1.00, 0.89}, {64, 384, 2, 8, 1.62, 1.52}, {128, 256, 2, 8, 1.60, 1.46},
+                          {128, 384, 2, 8, 2.30, 2.10}, {64, 128, 4, 4, 0.62, 0.45}, {32, 128, 5, 2, 0.51, 0.51},
+                          // gate and up only
+                          {64, 96, 5, 4, 0.58, 0.45}, {64, 192, 4, 8, 0.86, 0.73}, {128, 192, 2, 8, 1.49, 1.10}, {128, 320, 2, 8, 1.92, 1.72},
+                          {128, 384, 2, 8, 2.16, 1.95}, {192, 192, 2, 8, 1.78, 1.53}, {192, 256, 2, 8, 2.16, 1.87}};
+constexpr int N_ANY = 7, N_TILES = 14;
 constexpr int tile_lds(int i) { return TILES[i].stages * (2 * TILES[i].bm + TILES[i].bn) * KS * 2; }
 
 typedef void (*GemmFn)(PrefillGemmArgs);
 template <int EPI> static GemmFn gemm_kernel(int tile) {
-    constexpr bool GU = EPI == PE_SWIGLU;    // gate and up side by side take an even number of column tiles per wave
+    constexpr bool GU = EPI == PE_SWIGLU, QKV = EPI == PE_QKV;    // gate and up side by side take an even number of column pieces per wave
+    constexpr int ANY = QKV ? (int)PE_PART : EPI;
     switch (tile) {
-        case 0: return GU ? nullptr : prefill_gemm_kernel<GU ? (int)PE_PART : EPI, 1, 8, 1, 1, KS, 4, true>;
-        case 1: return prefill_gemm_kernel<EPI, 2, 4, 1, 2, KS, 3, true>;
-        case 2: return GU ? nullptr : prefill_gemm_kernel<GU ? (int)PE_PART : EPI, 2, 4, 1, 3, KS, 2, true>;
-        case 3: return prefill_gemm_kernel<EPI, 2, 4, 2, 2, KS, 2, false>;
-        case 4: return GU ? nullptr : prefill_gemm_kernel<GU ? (int)PE_PART : EPI, 2, 4, 2, 3, KS, 2, false>;
-        case 5: return prefill_gemm_kernel<EPI, 2, 2, 1, 2, KS, 4, true>;
-        default: return prefill_gemm_kernel<EPI, 1, 2, 1, 2, KS, 5, true>;
+        case 0: return GU ? nullptr : prefill_gemm_kernel<GU ? (int)PE_PART : EPI, 1, 8, 2, 2, KS, 4, true>;
+        case 1: return prefill_gemm_kernel<EPI, 2, 4, 2, 4, KS, 3, true>;
+        case 2: return GU ? nullptr : prefill_gemm_kernel<GU ? (int)PE_PART : EPI, 2, 4, 2, 6, KS, 2, true>;
+        case 3: return prefill_gemm_kernel<EPI, 2, 4, 4, 4, KS, 2, false>;
+        case 4: return GU ? nullptr : prefill_gemm_kernel<GU ? (int)PE_PART : EPI, 2, 4, 4, 6, KS, 2, false>;
+        case 5: return prefill_gemm_kernel<EPI, 2, 2, 2, 4, KS, 4, true>;
+        case 6: return prefill_gemm_kernel<EPI, 1, 2, 2, 4, KS, 5, true>;
+        case 7: return QKV ? nullptr : prefill_gemm_kernel<ANY, 4, 1, 1, 6, KS, 5, true>;
+        case 8: return QKV ? nullptr : prefill_gemm_kernel<ANY, 4, 2, 1, 6, KS, 4, true>;
+        case 9: return QKV ? nullptr : prefill_gemm_kernel<ANY, 4, 2, 2, 6, KS, 2, false>;
+        case 10: return QKV ? nullptr : prefill_gemm_kernel<ANY, 4, 2, 2, 10, KS, 2, false>;
+        case 11: return QKV ? nullptr : prefill_gemm_kernel<ANY, 4, 2, 2, 12, KS, 2, false>;
+        case 12: return QKV ? nullptr : prefill_gemm_kernel<ANY, 4, 2, 3, 6, KS, 2, false>;
+        default: return QKV ? nullptr : prefill_gemm_kernel<ANY, 4, 2, 3, 8, KS, 2, false>;
     }
 }
 
@@ -1186,13 +1199,14 @@ template <int EPI> static GemmFn gemm_kernel(int tile) {
 // compute units: counted over the whole chip 22 columns x 11 token tiles seem to fit 256 compute units once, and take two
 // rounds (7B output projection, 700 tokens, 64 x 384 in two splits: 114 us; 128 x 256: 63).  A last, partly empty round takes
 // between alone_us and step_us a step (128 x 256 at 1.25 and 1.75 rounds: 3.2 and 3.5 us).  The weights come at
-// 7.8 TB/s at best (part of them from the memory-side cache); partial sums are written and read at 4.7 TB/s and, where the product has an epilogue, cost one more launch.
-// Held against every shape and split at 11 lengths from 8 to 1024, products of the 1B, 7B, 13B and 70B widths: the four products of a
-// layer take 0.7 % longer than with the best choice for each, at most 5.3 % (the constants of the kernel before: 2.0 and 7.1 %).
+// 7.8 TB/s at best (part of them from the memory-side cache); partial sums are written and read at 4.6 TB/s
+// and, where the product has an epilogue, cost one more launch.
+// Held against every shape and split, products of the 1B, 7B, 13B and 70B widths: the four products of a layer take 1.0 % longer than with
+// the best choice for each at the 28 lengths the constants were fitted to and 0.9 % at 14 others (at most 8 %).
 static PrefillCut cut_product(const PrefillChunk &c, const PrefillForce &force, int T, int N, int mats, int K, int epi, size_t part_floats) {
     PrefillCut best{};
     double best_us = 1e30;
-    for (int tile = 0; tile < N_TILES; ++tile) {
+    for (int tile = 0; tile < (epi == PE_SWIGLU ? N_TILES : N_ANY); ++tile) {
         if (force.tile_1 != 0 && tile != force.tile_1 - 1) continue;
         const Tile &t = TILES[tile];
         const int t_tiles = (T + t.bm - 1) / t.bm, steps = K / KS;
@@ -1208,7 +1222,7 @@ static PrefillCut cut_product(const PrefillChunk &c, const PrefillForce &force, 
             const double rounds = (double)((cols + 7) / 8) * t_tiles / (c.num_cu / 8.0), whole = std::floor(rounds), rest = rounds - whole;
             const double step = whole * t.step_us + (rest > 0.0 ? t.alone_us + (t.step_us - t.alone_us) * rest : 0.0);
             double us = std::max(step * split_steps, (double)N * K * mats * 2 / 7.8e6);
-            if (!fused) us += (double)splits * T * N * mats * 8 / 4.7e6 + (epi == PE_PART ? 0.0 : 3.7);
+            if (!fused) us += (double)splits * T * N * mats * 8 / 4.6e6 + (epi == PE_PART ? 0.0 : 2.2);
             if (us < best_us) { best_us = us; best = PrefillCut{tile, t_tiles, n_tiles, splits, split_steps, fused}; }
         }
     }

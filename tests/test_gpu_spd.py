@@ -380,6 +380,42 @@ def test_prefix_products_of_every_tile_shape(m, kv_dtype, bound):
     assert seen == fused | {(p, t, False) for p in (QKV, ATTN_OUT, GATE_UP, DOWN) for t in PREFIX_TILES}
 
 
+GATE_UP_TILES = [(64, 96), (64, 192), (128, 192), (128, 320), (128, 384), (192, 192), (192, 256)]
+
+
+@pytest.mark.parametrize("m", [30, 70, 193, 230, 385])
+def test_gate_and_up_of_every_tile_shape(m):
+    """The shapes only gate and up has, asked for one after the other, as one block per k range with its epilogue and as partial sums: token tiles
+    of 64, 128 and 192 that end ragged; 1408 units in halves of 48 .. 192, ragged in most.  Bound as above.  For other products they do not exist."""
+    shape = synth.ModelShape("ragged-bf16", 3, 640, 10, 2, 1408, 1024, "bf16")
+    w = synth.make_weights(shape, seed=19)
+    prefix = synth.make_prefix_zipf(shape.vocab, m, seed=m)
+    sess = session(shape, w, max_ctx=m + 8)
+    seen = set()
+    try:
+        sess.spd_set_dense_prefill(False)
+        sess.spd_prefill(prefix)
+        want = sess.spd_read_logits()
+        sess.spd_set_dense_prefill(True)
+        for tile, size in enumerate(GATE_UP_TILES, len(PREFIX_TILES)):
+            for splits in (1, 2, 3):
+                cut = sess.spd_test_force_prefill_cut(GATE_UP, tile, splits, m)
+                if cut[:3] != (*size, splits):
+                    continue
+                assert cut[3] == (splits == 1)
+                sess.spd_prefill(prefix)
+                err = np.max(np.abs(sess.spd_read_logits() - want)) / np.max(np.abs(want))
+                assert err <= 1e-4, f"tile {size}, {splits} blocks per k range: {err:.2e}"
+                seen.add((size, cut[3]))
+            sess.spd_test_force_prefill_cut(GATE_UP, -1, 0, m)
+            for product in (QKV, ATTN_OUT, DOWN):
+                assert sess.spd_test_force_prefill_cut(product, tile, 1, m)[:2] in PREFIX_TILES
+                sess.spd_test_force_prefill_cut(product, -1, 0, m)
+    finally:
+        sess.close()
+    assert {s for s, fused in seen if fused} == set(GATE_UP_TILES) and (m > 230 or {s for s, fused in seen if not fused} == set(GATE_UP_TILES))
+
+
 @pytest.mark.parametrize("m", [9, 32, 61])
 def test_prefix_products_that_start_inside_their_k_range(m):
     """Rows of 8 KB and one token tile: blocks start an eighth of their k range apart and wrap round, with 4 to 64 steps per
