@@ -565,40 +565,57 @@ __global__ __launch_bounds__(ANT) void prefill_attn_kernel(const PrefillAttnArgs
 // its k index (step i, lane half h) stands for key 8 (i / 4) + 4 h + i % 4: the probabilities
 // never leave their registers.  For the first product k index (i, h) stands for feature
 // (d_head / 2) h + i, so a lane reads half a row of K as contiguous 16-byte pieces.
-// Q sits in LDS in operand order; K and V come straight from the cache into the same registers,
-// one after the other, which keeps a wave under half the register file: two waves share a
-// SIMD and one computes while the other waits for its loads.
+// Q and a wave's 32-key tile of K go through LDS, pieces permuted by the row: fetched by the lane that multiplies them, every load
+// touches 64 cache lines for 16 bytes each, and what the 8 waves of a compute unit fetch that way does not stay in its 32 KB cache.
+// V's rows are contiguous over the lanes and come straight into registers, asked for in front of the first product; K's next tile
+// is asked for behind it.  Two waves share a SIMD (80 KB of LDS per block) and one computes while the other waits.
+// What bounds it: the fp32 products with long contexts (1024 tokens of 32 heads of 128 cannot take less than 56 us), start, merge
+// and end with short ones.  Before (K from each lane's own rows, results stored two bytes at a time) -> this, heads of 128, with the
+// placement below: 256 tokens of 40 heads 33.5 -> 21.5 us, 512 of 64 (8 cached) 87 -> 63, 1024 of 32 130 -> 105; the same results.
 // F32: for an fp32 model, output in fp32 and no sum longer than on the step path: scores in eight chains, a tile's
 // part of the output in four, and what an addition to the running output and sum rounds away is kept beside them.
+template <int DH> constexpr int attn_mfma_lds() { return (4 * 32 + 32) * DH * 4; }
 template <int DH, bool F32>
 __global__ __launch_bounds__(256, F32 ? 1 : 2) void prefill_attn_mfma_kernel(const PrefillAttnArgs a) {
     constexpr int HALF = DH / 2, NT = DH / 32, NWV = 4;
-    constexpr int SLOT = (2 + 16 * NT) * WAVE;               // one wave's partial result: m, sum, O^T
-    __shared__ float q_lds[HALF * WAVE];
-    __shared__ float merge[2 * SLOT];
-    const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE, h = lane / 32, c = lane % 32;
+    constexpr int ROWB = DH * 4, PIECES = ROWB / 16, TILE = 32 * ROWB, LOADS = TILE / 1024;
+    constexpr int SLOT = (2 + 16 * NT) * WAVE;               // one wave's partial result: m, sum, O^T (floats)
+    static_assert(2 * SLOT * 4 <= attn_mfma_lds<DH>(), "the partial results take the place of the tiles");
+    extern __shared__ __align__(16) char tiles[];            // [NWV] tiles of K, then Q: 32 rows each
+    const int lane = threadIdx.x & (WAVE - 1), w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE), h = lane / 32, c = lane % 32;
     // Workgroups go to the 8 XCDs round-robin: all query tiles of a head are placed on one XCD (its
-    // L2 then holds that head's keys and values once), the tiles that see the most keys first.
+    // L2 then holds that head's keys and values once), over all its heads the tiles that see the most keys first: head after
+    // head the last heads' longest tiles start last (heads of 128, us: fp32 cache, 256 tokens of 40 heads 26 -> 21.5, 1024 of 32
+    // 124 -> 105; fp16 cache, 512 of 64 35 -> 30, 1024 of 32 47 -> 44).
     const int q_tiles = (a.T + 31) / 32;
-    const int xcd = blockIdx.x % 8, slot_in_xcd = blockIdx.x / 8;
-    const int head = (slot_in_xcd / q_tiles) * 8 + xcd;
+    const int xcd = blockIdx.x % 8, slot_in_xcd = blockIdx.x / 8, head_groups = (a.n_heads + 7) / 8;
+    const int head = (slot_in_xcd % head_groups) * 8 + xcd;
     if (head >= a.n_heads) return;
     const int kvh = head / (a.n_heads / a.n_kv_heads);
-    const int q0 = (q_tiles - 1 - slot_in_xcd % q_tiles) * 32;
+    const int q0 = (q_tiles - 1 - slot_in_xcd / head_groups) * 32;
     const int nqd = a.n_heads * DH;
     const float scale = 1.0f / sqrtf((float)DH);
-    if (w == 0) {   // this lane's operand values of Q: query q0 + c (clamped), features HALF h + i
-        const float *qrow = a.q + (size_t)min(q0 + c, a.T - 1) * nqd + (size_t)head * DH + HALF * h;
-#pragma unroll
-        for (int i = 0; i < HALF; i += 4) {
-            const float4 v = global_load_float4(qrow + i);
-            q_lds[(i + 0) * WAVE + lane] = v.x; q_lds[(i + 1) * WAVE + lane] = v.y;
-            q_lds[(i + 2) * WAVE + lane] = v.z; q_lds[(i + 3) * WAVE + lane] = v.w;
-        }
-    }
     const size_t head_at = (size_t)kvh * a.cap_ctx * DH;
     const int qpos = a.p0 + q0 + c;                          // cached positions 0 .. qpos are visible to this lane's query
     const int last_key = a.p0 + min(q0 + 31, a.T - 1);       // last position any query of the tile sees
+    char *k_tile = tiles + w * TILE, *q_tile = tiles + NWV * TILE;
+    auto fetch = [&](int k0) {                               // (a row past the last re-reads it: its scores are masked)
+        const int rows = min(32, last_key - k0 + 1);
+        const __amdgpu_buffer_rsrc_t rsrc = row_resource((const float *)a.kcache + head_at + (size_t)k0 * DH, (uint32_t)rows * ROWB);
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) {
+            const int row = (lane + WAVE * i) / PIECES;
+            load16_to_lds(rsrc, k_tile + 1024 * i, (uint32_t)min(row, rows - 1) * ROWB + 16u * (uint32_t)((lane % PIECES) ^ (row & 15)), 0);
+        }
+    };
+    int k0 = 32 * w;
+    if (k0 <= last_key) fetch(k0);
+#pragma unroll
+    for (int i = 0; i < 32 * PIECES / 256; ++i) {
+        const int row = (threadIdx.x + 256 * i) / PIECES, piece = threadIdx.x % PIECES;
+        const float4 v = global_load_float4(a.q + (size_t)min(q0 + row, a.T - 1) * nqd + (size_t)head * DH + 4 * piece);
+        *(float4 *)(q_tile + row * ROWB + 16 * (piece ^ (row & 15))) = v;
+    }
     float m = -INFINITY, lsum = 0.f;
     constexpr int CHAINS = F32 ? 8 : 1, PV_CHAINS = F32 ? 4 : 1;
     f32x16 o[NT], rest[NT];
@@ -607,45 +624,50 @@ __global__ __launch_bounds__(256, F32 ? 1 : 2) void prefill_attn_mfma_kernel(con
     for (int dt = 0; dt < NT; ++dt)
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[dt][r] = rest[dt][r] = 0.f;
-    __syncthreads();                                         // Q is in place
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");           // Q is in place (K stays under way)
 
-    for (int k0 = 32 * w; k0 <= last_key; k0 += 32 * NWV) {
+    for (; k0 <= last_key; k0 += 32 * NWV) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                      // K of this tile is in LDS
+        float vreg[NT][16];
+        auto request_v = [&]() {         // one 16-byte piece per key: features NT c .. NT c + NT - 1, one for each product tile
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const size_t vrow = head_at + (size_t)min(k0 + 8 * (i / 4) + 4 * h + i % 4, last_key) * DH + NT * c;
+                if (NT == 4) {
+                    const float4 v = global_load_float4((const float *)a.vcache + vrow);
+                    vreg[0][i] = v.x; vreg[1][i] = v.y; vreg[2][i] = v.z; vreg[3 % NT][i] = v.w;
+                } else {
+                    vreg[0][i] = as_global((const float *)a.vcache)[vrow]; vreg[1 % NT][i] = as_global((const float *)a.vcache)[vrow + 1];
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        if (!F32) request_v();
         f32x16 st;
         {
-            float kreg[HALF];
             f32x16 part[CHAINS];
 #pragma unroll
             for (int q = 0; q < CHAINS; ++q)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) part[q][r] = 0.f;
-            const size_t krow = head_at + (size_t)min(k0 + c, last_key) * DH + HALF * h;
 #pragma unroll
-            for (int i = 0; i < HALF; i += 4) {
-                const float4 v = global_load_float4((const float *)a.kcache + krow + i);
-                kreg[i] = v.x; kreg[i + 1] = v.y; kreg[i + 2] = v.z; kreg[i + 3] = v.w;
+            for (int j = 0; j < HALF / 4; ++j) {
+                const int at = c * ROWB + 16 * (((PIECES / 2) * h + j) ^ (c & 15));
+                const float4 kv = *(const float4 *)(k_tile + at), qv = *(const float4 *)(q_tile + at);
+                const float ke[4] = {kv.x, kv.y, kv.z, kv.w}, qe[4] = {qv.x, qv.y, qv.z, qv.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) part[(4 * j + e) % CHAINS] = __builtin_amdgcn_mfma_f32_32x32x2f32(ke[e], qe[e], part[(4 * j + e) % CHAINS], 0, 0, 0);
+                if (F32 && j % 2 == 1) __builtin_amdgcn_sched_barrier(0);     // (all pieces at once: spills)
             }
-#pragma unroll
-            for (int i = 0; i < HALF; ++i) part[i % CHAINS] = __builtin_amdgcn_mfma_f32_32x32x2f32(kreg[i], q_lds[i * WAVE + lane], part[i % CHAINS], 0, 0, 0);
 #pragma unroll
             for (int n = CHAINS / 2; n > 0; n /= 2)
 #pragma unroll
                 for (int q = 0; q < n; ++q) part[q] += part[q + n];
             st = part[0];
         }
-        __builtin_amdgcn_sched_barrier(0);
-        // V of this tile: requested once K's registers are free (a second wave on the same
-        // SIMD covers the wait), in flight during the softmax
-        float vreg[NT][16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {   // one 16-byte piece per key: features NT c .. NT c + NT - 1, one for each product tile
-            const size_t vrow = head_at + (size_t)min(k0 + 8 * (i / 4) + 4 * h + i % 4, last_key) * DH + NT * c;
-            if (NT == 4) {
-                const float4 v = global_load_float4((const float *)a.vcache + vrow);
-                vreg[0][i] = v.x; vreg[1][i] = v.y; vreg[2][i] = v.z; vreg[3 % NT][i] = v.w;
-            } else {
-                vreg[0][i] = as_global((const float *)a.vcache)[vrow]; vreg[1 % NT][i] = as_global((const float *)a.vcache)[vrow + 1];
-            }
-        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                    // K has been read
+        if (F32) request_v();                                                 // (the chains leave no registers for it before)
+        if (k0 + 32 * NWV <= last_key) fetch(k0 + 32 * NWV);
         __builtin_amdgcn_sched_barrier(0);
         float mx = m;
 #pragma unroll
@@ -707,10 +729,10 @@ __global__ __launch_bounds__(256, F32 ? 1 : 2) void prefill_attn_mfma_kernel(con
 #pragma unroll
         for (int dt = 0; dt < NT; ++dt) o[dt] += rest[dt];
     }
-    // merge: waves 2, 3 -> waves 0, 1; wave 1 -> wave 0.  Wave 0 holds key 0, visible to every
-    // query, so the merged maximum is finite.
+    // merge: waves 2, 3 -> waves 0, 1; then all threads put those two together (over the tiles, which nobody needs any
+    // more).  Wave 0 holds key 0, visible to every query, so the merged maximum is finite.
     auto put = [&](int slot) {
-        float *b = merge + slot * SLOT;
+        float *b = (float *)tiles + slot * SLOT;
         b[lane] = m; b[WAVE + lane] = lsum;
 #pragma unroll
         for (int dt = 0; dt < NT; ++dt)
@@ -718,7 +740,7 @@ __global__ __launch_bounds__(256, F32 ? 1 : 2) void prefill_attn_mfma_kernel(con
             for (int r = 0; r < 16; ++r) b[(2 + 16 * dt + r) * WAVE + lane] = o[dt][r];
     };
     auto take = [&](int slot) {
-        const float *b = merge + slot * SLOT;
+        const float *b = (const float *)tiles + slot * SLOT;
         const float m2 = b[lane], mt = fmaxf(m, m2);
         const float ref = mt == -INFINITY ? 0.f : mt;
         const float f1 = expf(m - ref), f2 = expf(m2 - ref);
@@ -729,26 +751,36 @@ __global__ __launch_bounds__(256, F32 ? 1 : 2) void prefill_attn_mfma_kernel(con
             for (int r = 0; r < 16; ++r) o[dt][r] = o[dt][r] * f1 + b[(2 + 16 * dt + r) * WAVE + lane] * f2;
         m = mt;
     };
+    __syncthreads();
     if (w >= 2) put(w - 2);
     __syncthreads();
     if (w < 2) take(w);
     __syncthreads();
-    if (w == 1) put(0);
+    if (w < 2) put(w);
     __syncthreads();
-    if (w != 0) return;
-    take(0);
-    lsum += __shfl_xor(lsum, 32);
-    const int t = q0 + c;
-    if (t < a.T) {
-        const float inv = 1.0f / lsum;
+    // thread -> query c, features F (tid / 32) .. + F - 1; row rho of product tile dt is feature NT rho + dt
+    constexpr int F = DH / 8;
+    const float *b0 = (const float *)tiles, *b1 = b0 + SLOT;
+    const int qc = threadIdx.x % 32, f0 = F * (threadIdx.x / 32), t = q0 + qc;
+    const float mt = fmaxf(b0[qc], b1[qc]);
+    const float f1 = expf(b0[qc] - mt), f2 = expf(b1[qc] - mt);
+    const float sum = (b0[WAVE + qc] * f1 + b1[WAVE + qc] * f2) + (b0[WAVE + 32 + qc] * f1 + b1[WAVE + 32 + qc] * f2), inv = 1.0f / sum;
+    if (t >= a.T) return;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {                       // row rho of product tile dt is feature NT rho + dt
-            const size_t at = (size_t)t * nqd + head * DH + NT * (8 * (r / 4) + 4 * h + r % 4);
+    for (int e0 = 0; e0 < F; e0 += 8) {
+        float y[8];
 #pragma unroll
-            for (int dt = 0; dt < NT; ++dt) {
-                if (F32) as_global(a.o32)[at + dt] = o[dt][r] / lsum;
-                else split_store(a.ohi, a.olo, at + dt, o[dt][r] * inv);
-            }
+        for (int e = 0; e < 8; ++e) {
+            const int f = f0 + e0 + e, dt = f % NT, rho = f / NT, r = 4 * (rho / 8) + rho % 4, at = (2 + 16 * dt + r) * WAVE + 32 * ((rho / 4) % 2) + qc;
+            const float v = b0[at] * f1 + b1[at] * f2;
+            y[e] = F32 ? v / sum : v * inv;
+        }
+        const size_t at = (size_t)t * nqd + head * DH + f0 + e0;
+        if (F32) {
+            *(f32x4 __attribute__((address_space(1))) *)(a.o32 + at) = f32x4{y[0], y[1], y[2], y[3]};
+            *(f32x4 __attribute__((address_space(1))) *)(a.o32 + at + 4) = f32x4{y[4], y[5], y[6], y[7]};
+        } else {
+            split_store8(a.ohi, a.olo, at, y);
         }
     }
 }
@@ -786,11 +818,11 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_f16_kernel(const PrefillA
     extern __shared__ __align__(16) char tiles[];            // [NWV][K, V][TILE], then Q: 32 rows of fp32, pieces permuted by the row
     const int lane = threadIdx.x & (WAVE - 1), w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE), h = lane / 32, c = lane % 32;
     const int q_tiles = (a.T + 31) / 32;
-    const int xcd = blockIdx.x % 8, slot_in_xcd = blockIdx.x / 8;   // (placement as above)
-    const int head = (slot_in_xcd / q_tiles) * 8 + xcd;
+    const int xcd = blockIdx.x % 8, slot_in_xcd = blockIdx.x / 8, head_groups = (a.n_heads + 7) / 8;   // (placement as above)
+    const int head = (slot_in_xcd % head_groups) * 8 + xcd;
     if (head >= a.n_heads) return;
     const int kvh = head / (a.n_heads / a.n_kv_heads);
-    const int q0 = (q_tiles - 1 - slot_in_xcd % q_tiles) * 32;
+    const int q0 = (q_tiles - 1 - slot_in_xcd / head_groups) * 32;
     const int nqd = a.n_heads * DH;
     const int qpos = a.p0 + q0 + c;                          // cached positions 0 .. qpos are visible to this lane's query
     const int last_key = a.p0 + min(q0 + 31, a.T - 1);       // last position any query of the tile sees
@@ -1252,6 +1284,8 @@ hipError_t prefill_init() {
     hipError_t e = hipFuncSetAttribute((const void *)prefill_attn_kernel<float>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)prefill_attn_lds(128));
     if (e == hipSuccess) e = hipFuncSetAttribute((const void *)prefill_attn_kernel<half_t>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)prefill_attn_lds(128));
     if (e == hipSuccess) e = hipFuncSetAttribute((const void *)prefill_attn_f16_kernel<128>, hipFuncAttributeMaxDynamicSharedMemorySize, attn_f16_lds<128>());
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void *)prefill_attn_mfma_kernel<128, false>, hipFuncAttributeMaxDynamicSharedMemorySize, attn_mfma_lds<128>());
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void *)prefill_attn_mfma_kernel<128, true>, hipFuncAttributeMaxDynamicSharedMemorySize, attn_mfma_lds<128>());
     for (int tile = 0; tile < N_TILES; ++tile)
         for (GemmFn k : {gemm_kernel<PE_PART>(tile), gemm_kernel<PE_QKV>(tile), gemm_kernel<PE_SWIGLU>(tile)})
             if (e == hipSuccess && k != nullptr) e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, tile_lds(tile));
@@ -1267,11 +1301,11 @@ hipError_t prefill_attention(hipStream_t s, int kv_half, const float *q, const v
         else if (dh == 64) hipLaunchKernelGGL(prefill_attn_f16_kernel<64>, mfma_grid, dim3(256), attn_f16_lds<64>(), s, at);
         else hipLaunchKernelGGL(prefill_attn_kernel<half_t>, plain_grid, dim3(ANT), prefill_attn_lds(dh), s, at);
     } else {
-        if (dh == 128 && out32) hipLaunchKernelGGL((prefill_attn_mfma_kernel<128, true>), mfma_grid, dim3(256), 0, s, at);
-        else if (dh == 64 && out32) hipLaunchKernelGGL((prefill_attn_mfma_kernel<64, true>), mfma_grid, dim3(256), 0, s, at);
+        if (dh == 128 && out32) hipLaunchKernelGGL((prefill_attn_mfma_kernel<128, true>), mfma_grid, dim3(256), attn_mfma_lds<128>(), s, at);
+        else if (dh == 64 && out32) hipLaunchKernelGGL((prefill_attn_mfma_kernel<64, true>), mfma_grid, dim3(256), attn_mfma_lds<64>(), s, at);
         else if (out32) return hipErrorInvalidValue;
-        else if (dh == 128) hipLaunchKernelGGL((prefill_attn_mfma_kernel<128, false>), mfma_grid, dim3(256), 0, s, at);
-        else if (dh == 64) hipLaunchKernelGGL((prefill_attn_mfma_kernel<64, false>), mfma_grid, dim3(256), 0, s, at);
+        else if (dh == 128) hipLaunchKernelGGL((prefill_attn_mfma_kernel<128, false>), mfma_grid, dim3(256), attn_mfma_lds<128>(), s, at);
+        else if (dh == 64) hipLaunchKernelGGL((prefill_attn_mfma_kernel<64, false>), mfma_grid, dim3(256), attn_mfma_lds<64>(), s, at);
         else hipLaunchKernelGGL(prefill_attn_kernel<float>, plain_grid, dim3(ANT), prefill_attn_lds(dh), s, at);
     }
     return hipGetLastError();

@@ -171,6 +171,20 @@ def test_prefix_attention_against_64_bits(case, kv_dtype):
     assert err < PREFIX_ATTENTION_BOUND, err
 
 
+@pytest.mark.parametrize("kv_dtype", ["fp16", "fp32"])
+@pytest.mark.parametrize("case", [(18, 6, 64, 97, 0, 1.0), (12, 3, 128, 161, 250, 2.0), (1, 1, 128, 64, 0, 1.0)])
+def test_prefix_attention_where_heads_and_tiles_share_an_xcd(case, kv_dtype):
+    """Query tiles are placed longest first over all heads of an XCD, whose last round of heads is ragged here; up to four tiles
+    of keys per wave.  Every (query, head) is written: the bound is that of the test above."""
+    q, K, V = prefix_attention_inputs(case)
+    cache = torch.float16 if kv_dtype == "fp16" else torch.float32
+    hi, lo = P().spd_test_prefill_attention(kv_dtype, torch.from_numpy(q).cuda(), torch.from_numpy(K).cuda().to(cache), torch.from_numpy(V).cuda().to(cache),
+                                            case[4])
+    got, want = hi.double().cpu().numpy() + lo.double().cpu().numpy(), prefix_attention64(q, K, V, case[4])
+    for h in range(case[0]):
+        assert relative_error(got[:, h], want[:, h]) < PREFIX_ATTENTION_BOUND, h
+
+
 def test_operators_run_on_the_callers_current_stream():
     """The handle the operators launch on is torch's current stream, inside and outside a stream context and per thread."""
     import threading
