@@ -167,6 +167,7 @@ struct ExpandArgs {
     int32_t first, advance;
     int32_t *hist_tok, *hist_par;  // [max_gen, SPD_K_MAX]
     int32_t max_gen;
+    uint32_t *arrived;             // blocks whose slice is done; zero between launches
 };
 
 // Activation vectors of one forward pass.  Every vector a phase produces has an address of
@@ -263,7 +264,8 @@ size_t gemv_lds_bytes(int dtype, int cols);
 hipError_t attention(hipStream_t s, int dtype, const AttnArgs &a);
 hipError_t superpose(hipStream_t s, int dtype, const SuperposeArgs &a);
 hipError_t topk_partial(hipStream_t s, const TopkArgs &a);
-hipError_t expand_prune(hipStream_t s, const ExpandArgs &a);
+bool expand_needs_topk(const ExpandArgs &a);   // whether topk_partial has to run before it; else it does that too
+hipError_t expand_prune(hipStream_t s, const TopkArgs &t, const ExpandArgs &a);
 hipError_t nucleus(hipStream_t s, const NucleusArgs &a);
 hipError_t prefill_chunk(hipStream_t s, const PrefillChunk &c);
 hipError_t prefill32_chunk(hipStream_t s, const PrefillChunk &c);      // fp32 models

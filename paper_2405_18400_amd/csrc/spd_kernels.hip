@@ -314,11 +314,13 @@ template <int PARTS> __device__ __forceinline__ int rank_among(const unsigned lo
 // rounds went over the block.
 // NR: entries of the slice per thread, the least of 4, 8, 16 and 32 that hold it (4 up to vocabularies of 131072): each is looked at
 // in every round (131074 entries, the kernel: 4.1 us at k = 1 with the rounds over the block, 5.6 with 32 entries, 4.1 with 8; 262144: 5.4, 6.0, 4.4).
-template <int NR>
-__global__ __launch_bounds__(BLOCK) void topk_partial_kernel(const TopkArgs a) {
-    __shared__ unsigned long long entry[NWAVE * SPD_K_MAX];
-    __shared__ float sv[NWAVE * SPD_K_MAX], wave_max[NWAVE], wave_exp[NWAVE], wave_min[NWAVE];
-    __shared__ int si[NWAVE * SPD_K_MAX];
+struct TopkScratch {
+    unsigned long long entry[NWAVE * SPD_K_MAX];
+    float sv[NWAVE * SPD_K_MAX], wave_max[NWAVE], wave_exp[NWAVE], wave_min[NWAVE];
+    int si[NWAVE * SPD_K_MAX];
+};
+// Before the barrier: every wave's share; behind it: the block's result (COH: written through, for a block of the same launch).
+template <int NR> __device__ __forceinline__ void topk_share(const TopkArgs &a, TopkScratch &s) {
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE, b = blockIdx.x, k = a.k;
     const int lo = b * a.per_part, hi = min(a.vocab, lo + a.per_part);
     float rv[NR];
@@ -333,7 +335,7 @@ __global__ __launch_bounds__(BLOCK) void topk_partial_kernel(const TopkArgs a) {
     float kv;
     int ki;
     wave_top_k(k, key, [&](int q) { return lo + tid + q * BLOCK; }, kv, ki);
-    if (lane < k) { sv[w * k + lane] = kv; si[w * k + lane] = ki; entry[w * k + lane] = ki == INT_MAX ? 0ull : entry_key(kv, ki); }
+    if (lane < k) { s.sv[w * k + lane] = kv; s.si[w * k + lane] = ki; s.entry[w * k + lane] = ki == INT_MAX ? 0ull : entry_key(kv, ki); }
     // x -> x / tau is monotonic for tau > 0: the largest logit gives the largest z
     const float mx = __fdiv_rn(read_lane(kv, 0), a.tau), ref = mx == -INFINITY ? 0.f : mx;   // (a share without entries, or of -inf alone: every term is 0)
     float sm = 0.f, lowest = INFINITY;
@@ -342,19 +344,34 @@ __global__ __launch_bounds__(BLOCK) void topk_partial_kernel(const TopkArgs a) {
         if (lo + tid + q * BLOCK < hi) { sm += expf(__fdiv_rn(rv[q], a.tau) - ref); lowest = fminf(lowest, rv[q]); }
     sm = wave_sum_last(sm);
     lowest = -wave_max_last(-lowest);
-    if (lane == WAVE - 1) { wave_max[w] = mx; wave_exp[w] = sm; wave_min[w] = lowest; }
-    __syncthreads();
+    if (lane == WAVE - 1) { s.wave_max[w] = mx; s.wave_exp[w] = sm; s.wave_min[w] = lowest; }
+}
+template <bool COH> __device__ __forceinline__ void topk_result(const TopkArgs &a, const TopkScratch &s) {
+    const int tid = threadIdx.x, b = blockIdx.x, k = a.k;
+    const int lo = b * a.per_part, hi = min(a.vocab, lo + a.per_part);
     constexpr int PARTS = BLOCK / (NWAVE * SPD_K_MAX);
-    const int rank = rank_among<PARTS>(entry, NWAVE * k), t = tid / PARTS;
-    if (t < NWAVE * k && rank < k && tid % PARTS == 0) { a.pv[b * SPD_K_MAX + rank] = sv[t]; a.pi[b * SPD_K_MAX + rank] = si[t]; }
-    if (tid == BLOCK - 1) {
-        float m = -INFINITY, s = 0.f, l = INFINITY;
-#pragma unroll
-        for (int q = 0; q < NWAVE; ++q) { m = fmaxf(m, wave_max[q]); l = fminf(l, wave_min[q]); }
-#pragma unroll
-        for (int q = 0; q < NWAVE; ++q) s += wave_max[q] == -INFINITY ? wave_exp[q] : wave_exp[q] * expf(wave_max[q] - m);
-        a.pm[b] = m; a.ps[b] = s; a.pn[b] = lo < hi ? __fdiv_rn(l, a.tau) : INFINITY;
+    const int rank = rank_among<PARTS>(s.entry, NWAVE * k), t = tid / PARTS;
+    if (t < NWAVE * k && rank < k && tid % PARTS == 0) {
+        act_store<COH>(a.pv + b * SPD_K_MAX + rank, s.sv[t]);
+        act_store<COH>((float *)a.pi + b * SPD_K_MAX + rank, __int_as_float(s.si[t]));
     }
+    if (tid == BLOCK - 1) {
+        float m = -INFINITY, sum = 0.f, l = INFINITY;
+#pragma unroll
+        for (int q = 0; q < NWAVE; ++q) { m = fmaxf(m, s.wave_max[q]); l = fminf(l, s.wave_min[q]); }
+#pragma unroll
+        for (int q = 0; q < NWAVE; ++q) sum += s.wave_max[q] == -INFINITY ? s.wave_exp[q] : s.wave_exp[q] * expf(s.wave_max[q] - m);
+        act_store<COH>(a.pm + b, m);
+        act_store<COH>(a.ps + b, sum);
+        if (!COH) a.pn[b] = lo < hi ? __fdiv_rn(l, a.tau) : INFINITY;      // (for the nucleus sampler alone)
+    }
+}
+template <int NR>
+__global__ __launch_bounds__(BLOCK) void topk_partial_kernel(const TopkArgs a) {
+    __shared__ TopkScratch s;
+    topk_share<NR>(a, s);
+    __syncthreads();
+    topk_result<false>(a, s);
 }
 
 // ------------------------------------------------------------------ expand, interpolate, prune
@@ -414,22 +431,28 @@ __device__ __forceinline__ void ngram_probes(const NgramDev &ng, const int32_t (
     }
 }
 
-// One block.  Merges the per-slice top-k into the global KeepTopK and log-softmax, builds the
+// Merges the per-slice top-k into the global KeepTopK and log-softmax, builds the
 // k x k options, probes the n-gram store for every (draft, kept token, order), applies the
 // mixture (Eq. 3), the interpolation (Eq. 4) or the penalty form (Eq. 5), keeps the k best
-// options and rewrites the draft state.
+// options and rewrites the draft state.  One block's work; NR > 0: the block that is last to finish its slice goes on with it.
 // A chain of latencies.  Whatever does not depend on the kept tokens is asked for at the start: the first MERGE threads
-// select among the slices' candidates, wave by wave, while the others look up the drafts' context totals -- where that
-// selection takes as long as a lookup.  With few drafts it does not, and the totals are looked up together with the counts, a
-// group of lanes for each probe (ONE_GO: the kernel at k = 1 .. 4, five orders, 9.2 .. 10.2 -> 5.7 .. 7.1 us; a kernel of its own,
-// the other would take 0.15 us longer with both ways in it).
-// k = 8, five orders, 1.6 M slots: 28 -> 13 us (merge 2.9, ranks 0.6, hashes 0.8, probes 5.5, mixture and scores 1.1, prune and state 1.5).
+// select in the block's slice while the others look up the drafts' context totals, in every block, since any may be the last.  With
+// few drafts the totals are looked up together with the counts, a group of lanes for each probe (ONE_GO: the kernel at
+// k = 1 .. 4, five orders, 9.2 .. 10.2 -> 5.7 .. 7.1 us).
+// One launch or two (NR = 0: the slices are a launch of their own), a timestep's decisions from 32000 logits, launched one by one, two
+// -> one: no n-grams 8.9 -> 7.6 us at k = 1, 11.2 -> 10.9 at 8; five orders 15.6 -> 15.5 at k = 5, 22.8 -> 21.8 at 10.  With few drafts and
+// n-grams there is nothing to hide in the slices' time (10.35 -> 10.53 at k = 3) and two stay.
+// k = 8, five orders, 1.6 M slots: 28 -> 13 us behind the slices (merge 2.9, ranks 0.6, hashes 0.8, probes 5.5, mixture and scores 1.1, prune
+// and state 1.5).
 constexpr int ENT = 1024, MERGE = 256, MERGE_WAVES = MERGE / WAVE, GROUPS = ENT / PROBE_LANES;
 
 constexpr bool probes_in_one_go(int k) { return (k * k + k) * SPD_N_ORDERS <= GROUPS; }
 
-template <bool ONE_GO>
-__global__ __launch_bounds__(ENT) void expand_prune_kernel(const ExpandArgs a) {
+template <int NR, bool ONE_GO>
+__global__ __launch_bounds__(ENT) void expand_prune_kernel(const TopkArgs slice, const ExpandArgs a) {
+    static_assert(MERGE == BLOCK, "the waves that merge are those that select");
+    __shared__ TopkScratch scratch;
+    __shared__ int is_last;
     __shared__ unsigned long long entry[MERGE_WAVES * SPD_K_MAX], option[SPD_KK];
     __shared__ float sv[MERGE_WAVES * SPD_K_MAX];
     __shared__ int si[MERGE_WAVES * SPD_K_MAX];
@@ -469,43 +492,7 @@ __global__ __launch_bounds__(ENT) void expand_prune_kernel(const ExpandArgs a) {
     const bool use_ng = !a.first && a.alpha != 0.0f;
     const int n_count = k * k * SPD_N_ORDERS, n_total = k * SPD_N_ORDERS;
     if (tid < MERGE) {
-        const int n_cand = a.n_part * k;
-        constexpr int NR = TOPK_PART_MAX * SPD_K_MAX / MERGE;
-        auto candidate = [&](int q, float &v, int &i) {
-            const int c = tid + q * MERGE, at = (c / k) * SPD_K_MAX + (c % k);
-            v = c < n_cand ? as_global(a.pv)[at] : -INFINITY;
-            i = c < n_cand ? as_global(a.pi)[at] : INT_MAX;
-        };
-        float cv[NR];
-        int ci[NR];
-        candidate(0, cv[0], ci[0]);
-        if (n_cand > MERGE) {
-#pragma unroll
-            for (int q = 1; q < NR; ++q) candidate(q, cv[q], ci[q]);
-        }
-        if (tid < WAVE) {   // log-sum-exp over the slices: M = max of the maxima, S = sum of sum-exp * exp(max - M)
-            float m = -INFINITY, sum = 0.f;
-            for (int b = lane; b < a.n_part; b += WAVE) m = fmaxf(m, a.pm[b]);
-            const float M = read_lane(wave_max_last(m), WAVE - 1);
-            for (int b = lane; b < a.n_part; b += WAVE) sum += a.ps[b] * expf(a.pm[b] - M);
-            const float S = read_lane(wave_sum_last(sum), WAVE - 1);
-            if (lane == 0) s_lse = M + logf(S);
-        }
-        float kv;
-        int ki;
-        auto select = [&](auto count) {
-            constexpr int N = decltype(count)::value;
-            uint32_t key[N];
-#pragma unroll
-            for (int q = 0; q < N; ++q) key[q] = ci[q] == INT_MAX ? 0u : value_key(cv[q]);
-            wave_top_k(k, key, [&](int q) { return ci[q]; }, kv, ki);
-        };
-        if (n_cand > MERGE) select(std::integral_constant<int, NR>());
-        else select(std::integral_constant<int, 1>());
-        if (lane < k) {
-            const int at = (tid / WAVE) * k + lane;
-            sv[at] = kv; si[at] = ki; entry[at] = ki == INT_MAX ? 0ull : entry_key(kv, ki);
-        }
+        if constexpr (NR > 0) topk_share<NR>(slice, scratch);
     } else {
         const int u = tid - MERGE;
         if (u < SPD_K_MAX) {
@@ -525,6 +512,65 @@ __global__ __launch_bounds__(ENT) void expand_prune_kernel(const ExpandArgs a) {
             const uint64_t home[1] = {known && e < n_total ? ngram_home(ngram_hash(key[0]), a.ng.capacity) : NO_HOME};
             ngram_probes<1>(a.ng, key, home, total);
             if (e < n_total && u % PROBE_LANES == 0) s_tot[e] = total[0];
+        }
+    }
+    if constexpr (NR > 0) {
+        __syncthreads();
+        if (tid < MERGE) {
+            topk_result<true>(slice, scratch);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's write-through stores have been acknowledged
+        }
+        __syncthreads();
+        if (tid == 0) is_last = __hip_atomic_fetch_add(as_global(a.arrived), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+        __syncthreads();
+        if (!is_last) return;
+        if (tid == 0) __hip_atomic_store(as_global(a.arrived), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
+    }
+    if (tid < MERGE) {
+        const int n_cand = a.n_part * k;
+        constexpr int NC = TOPK_PART_MAX * SPD_K_MAX / MERGE;
+        auto candidate = [&](int q, float &v, int &i) {
+            const int c = tid + q * MERGE, at = (c / k) * SPD_K_MAX + (c % k);
+            v = c < n_cand ? act_load<(NR > 0)>(a.pv + at) : -INFINITY;
+            i = c < n_cand ? __float_as_int(act_load<(NR > 0)>((const float *)a.pi + at)) : INT_MAX;
+        };
+        float cv[NC];
+        int ci[NC];
+        candidate(0, cv[0], ci[0]);
+        if (n_cand > MERGE) {
+#pragma unroll
+            for (int q = 1; q < NC; ++q) candidate(q, cv[q], ci[q]);
+        }
+        if (tid < WAVE) {   // log-sum-exp over the slices: M = max of the maxima, S = sum of sum-exp * exp(max - M)
+            static_assert(TOPK_PART_MAX == 2 * WAVE, "two slices per lane");
+            float pm[2], ps[2], sum = 0.f;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int b = lane + q * WAVE;
+                pm[q] = b < a.n_part ? act_load<(NR > 0)>(a.pm + b) : -INFINITY;
+                ps[q] = b < a.n_part ? act_load<(NR > 0)>(a.ps + b) : 0.f;
+            }
+            const float M = read_lane(wave_max_last(fmaxf(pm[0], pm[1])), WAVE - 1);
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                if (lane + q * WAVE < a.n_part) sum += ps[q] * expf(pm[q] - M);
+            const float S = read_lane(wave_sum_last(sum), WAVE - 1);
+            if (lane == 0) s_lse = M + logf(S);
+        }
+        float kv;
+        int ki;
+        auto select = [&](auto count) {
+            constexpr int N = decltype(count)::value;
+            uint32_t key[N];
+#pragma unroll
+            for (int q = 0; q < N; ++q) key[q] = ci[q] == INT_MAX ? 0u : value_key(cv[q]);
+            wave_top_k(k, key, [&](int q) { return ci[q]; }, kv, ki);
+        };
+        if (n_cand > MERGE) select(std::integral_constant<int, NC>());
+        else select(std::integral_constant<int, 1>());
+        if (lane < k) {
+            const int at = (tid / WAVE) * k + lane;
+            sv[at] = kv; si[at] = ki; entry[at] = ki == INT_MAX ? 0ull : entry_key(kv, ki);
         }
     }
     __syncthreads();
@@ -775,10 +821,19 @@ hipError_t topk_partial(hipStream_t s, const TopkArgs &a) {
     return hipGetLastError();
 }
 
-hipError_t expand_prune(hipStream_t s, const ExpandArgs &a) {
-    if (!a.first && a.alpha != 0.0f && probes_in_one_go(a.k)) hipLaunchKernelGGL(expand_prune_kernel<true>, dim3(1), dim3(ENT), 0, s, a);
-    else hipLaunchKernelGGL(expand_prune_kernel<false>, dim3(1), dim3(ENT), 0, s, a);
-    return hipGetLastError();
+bool expand_needs_topk(const ExpandArgs &a) { return !a.first && a.alpha != 0.0f && probes_in_one_go(a.k); }
+
+hipError_t expand_prune(hipStream_t s, const TopkArgs &t, const ExpandArgs &a) {
+    auto go = [&](auto kernel, int blocks) {
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(ENT), 0, s, t, a);
+        return hipGetLastError();
+    };
+    if (expand_needs_topk(a)) return go(expand_prune_kernel<0, true>, 1);
+    if (t.per_part <= 4 * BLOCK) return go(expand_prune_kernel<4, false>, t.n_part);
+    if (t.per_part <= 8 * BLOCK) return go(expand_prune_kernel<8, false>, t.n_part);
+    if (t.per_part <= 16 * BLOCK) return go(expand_prune_kernel<16, false>, t.n_part);
+    if (t.per_part <= 32 * BLOCK) return go(expand_prune_kernel<32, false>, t.n_part);
+    return hipErrorInvalidValue;   // (vocabularies stay below 2^20)
 }
 
 hipError_t advance(hipStream_t s, DevState *st) {

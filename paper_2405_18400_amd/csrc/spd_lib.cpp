@@ -292,8 +292,6 @@ hipError_t enqueue_forward(spd_ctx *c, int mode, int k, bool head) {
 hipError_t enqueue_decide(spd_ctx *c, const spd_decode_cfg &dc, const float *logits, int first, int advance) {
     TopkArgs t{logits, c->cfg.vocab, dc.k, c->L.n_part, c->L.per_part, dc.tau,
                c->at<float>(c->L.pv), c->at<int32_t>(c->L.pi), c->at<float>(c->L.pm), c->at<float>(c->L.ps), c->at<float>(c->L.pn)};
-    hipError_t e = launch(c, KC_TOPK, [&] { return spdk::topk_partial(c->stream, t); });
-    if (e != hipSuccess) return e;
     ExpandArgs x{};
     x.st = c->st(); x.pv = t.pv; x.pi = t.pi; x.pm = t.pm; x.ps = t.ps; x.n_part = c->L.n_part;
     x.ng = c->ng;
@@ -302,7 +300,12 @@ hipError_t enqueue_decide(spd_ctx *c, const spd_decode_cfg &dc, const float *log
     x.first = first; x.advance = advance;
     x.hist_tok = c->at<int32_t>(c->L.hist_tok); x.hist_par = c->at<int32_t>(c->L.hist_par);
     x.max_gen = c->cfg.max_ctx;
-    return launch(c, KC_EXPAND, [&] { return spdk::expand_prune(c->stream, x); });
+    x.arrived = c->at<uint32_t>(c->L.nuc_count);    // (one or the other on the context's stream)
+    if (spdk::expand_needs_topk(x)) {
+        const hipError_t e = launch(c, KC_TOPK, [&] { return spdk::topk_partial(c->stream, t); });
+        if (e != hipSuccess) return e;
+    }
+    return launch(c, KC_EXPAND, [&] { return spdk::expand_prune(c->stream, t, x); });
 }
 
 // Post-forward part of one nucleus-sampling step: slice statistics, then the sampler

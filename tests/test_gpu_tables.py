@@ -109,3 +109,37 @@ def test_tables_replaced_between_timesteps(tiny):
         assert all(np.any(p > 0) for p in seen), "a timestep without any n-gram hit does not test the tables"
     finally:
         sess.close()
+
+
+@pytest.mark.parametrize("k", [1, 5, 10])
+@pytest.mark.parametrize("vocab", [700, 5122, 131074])
+def test_decisions_whose_last_slice_goes_on(vocab, k):
+    """One slice, a ragged number of them and the first with more entries per thread; with n-grams (five drafts and more) and without the
+    same launch selects and decides, timestep after timestep: scripted logits, no gap allowance."""
+    import torch
+    pkg = P()
+    shape = synth.ModelShape("one-head", 1, 64, 1, 1, 128, vocab, "fp32")
+    rng = np.random.default_rng([vocab, k])
+    corpus = rng.integers(0, 40, size=3000)
+    tabs = {n: np.unique(np.lib.stride_tricks.sliding_window_view(corpus, n), axis=0, return_counts=True) for n in range(2, 7)}
+    tabs = {n: (np.ascontiguousarray(keys, np.int32), counts.astype(np.uint32)) for n, (keys, counts) in tabs.items()}
+    lam, pre = synth.PAPER_LAMBDAS, corpus[:7].astype(np.int32)
+    sess = pkg.Session(shape, synth.make_weights(shape, seed=1), max_ctx=32, k_max=16)
+    try:
+        sess.spd_load_ngrams(tabs, lam)
+        otabs = O.NgramTables(tabs)
+        sess.spd_prefill(pre)
+        for alpha in (0.54, 0.0):
+            dc, cfg, state = pkg.SpdDecodeCfg(k, alpha, 1.0, 0.1), O.DecodeCfg(k, alpha, 1.0, 0.1, lam), None
+            for step in range(4):
+                z = rng.standard_normal(vocab).astype(np.float32) - 12.0
+                top = np.concatenate([rng.choice(40, size=12, replace=False), [vocab - 1]])
+                z[top] = rng.permutation(len(top)).astype(np.float32) / 2
+                state, rec = O.first_step(z, pre, cfg) if state is None else O.expand_and_prune(state, z, otabs, cfg)
+                sess.spd_expand_prune(dc, torch.from_numpy(z).cuda(), first=(step == 0))
+                tails, scores, _ = sess.spd_get_state()
+                assert list(sess.spd_get_step_info(k)[0]) == list(rec.top_ids)
+                np.testing.assert_allclose(scores, state.logscores, rtol=1e-5, atol=1e-5)     # sums of fp32 logarithms
+                assert np.array_equal(tails, tails_of(state))
+    finally:
+        sess.close()
