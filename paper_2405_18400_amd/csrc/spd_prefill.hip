@@ -75,6 +75,10 @@ struct PrefillNormArgs {
     uint16_t *hi, *lo;           // [T, d]
     int32_t T, d, splits;
     float eps;
+    // EMBED: the chunk's rotary table comes along, a launch less: (cos, sin) of (p0 + t) * theta^(-2i/d_head), in double as everywhere else
+    const double *inv_freq;
+    float2 *rope;                // [T, half]
+    int32_t p0, half;
 };
 
 template <bool EMBED>
@@ -114,6 +118,7 @@ __global__ __launch_bounds__(1024) void prefill_norm_kernel(const PrefillNormArg
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] += sum[e];
     }
+    if (EMBED && (int)threadIdx.x < a.half) a.rope[(size_t)t * a.half + threadIdx.x] = rope_cos_sin(a.inv_freq, threadIdx.x, a.p0 + t);
     float ss = 0.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) ss += v[e] * v[e];
@@ -134,14 +139,6 @@ __global__ __launch_bounds__(1024) void prefill_norm_kernel(const PrefillNormArg
     split_store8(a.hi, a.lo, at, v);
 }
 static int norm_threads(int d) { return (d / 8 + WAVE - 1) / WAVE * WAVE; }
-
-// (cos, sin) of (p0 + t) * theta^(-2i/d_head), in double as everywhere else
-__global__ void rope_table_kernel(const double *inv_freq, int p0, int T, int half, float2 *table) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= T * half) return;
-    const float2 cs = rope_cos_sin(inv_freq, i % half, p0 + i / half);
-    table[i] = cs;
-}
 
 // ------------------------------------------------------------------ GEMM on the matrix cores
 // PE_PART: partial sums over this block's share of k, to `part`; the consumer adds the splits.
@@ -752,10 +749,12 @@ __global__ __launch_bounds__(256, F32 ? 1 : 2) void prefill_attn_mfma_kernel(con
         m = mt;
     };
     __syncthreads();
-    if (w >= 2) put(w - 2);
-    __syncthreads();
-    if (w < 2) take(w);
-    __syncthreads();
+    if (last_key >= 2 * 32) {            // (else those waves had no keys)
+        if (w >= 2) put(w - 2);
+        __syncthreads();
+        if (w < 2) take(w);
+        __syncthreads();
+    }
     if (w < 2) put(w);
     __syncthreads();
     // thread -> query c, features F (tid / 32) .. + F - 1; row rho of product tile dt is feature NT rho + dt
@@ -985,10 +984,12 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_f16_kernel(const PrefillA
         m = mt;
     };
     __syncthreads();
-    if (w >= 2) put(w - 2);
-    __syncthreads();
-    if (w < 2) take(w);
-    __syncthreads();
+    if (last_key >= 2 * 32) {            // (else those waves had no keys)
+        if (w >= 2) put(w - 2);
+        __syncthreads();
+        if (w < 2) take(w);
+        __syncthreads();
+    }
     if (w < 2) put(w);
     __syncthreads();
     // thread -> query c, features F (tid / 32) .. + F - 1; row rho of product tile dt is feature NT rho + dt
@@ -1348,7 +1349,6 @@ constexpr long long LAST_QUERY_WITH = 3000000000ll;
 // the last layer in row T - 1; the caller finishes that token (final norm + LM head).
 hipError_t prefill_chunk(hipStream_t s, const PrefillChunk &c) {
     const int T = c.T, d = c.d_model, dh = d / c.n_heads, nq = c.n_heads * dh, nkv = c.n_kv_heads * dh;
-    hipLaunchKernelGGL(rope_table_kernel, dim3((T * (dh / 2) + 255) / 256), dim3(256), 0, s, c.inv_freq, c.p0, T, dh / 2, c.rope);
     PrefillCut cut[4];
     prefill_cuts(c, T, cut);
     const PrefillCut &cut_o = cut[1], &cut_gu = cut[2], &cut_down = cut[3];
@@ -1361,6 +1361,7 @@ hipError_t prefill_chunk(hipStream_t s, const PrefillChunk &c) {
         n.h = c.h; n.gain = (const uint16_t *)w.attn_norm; n.hi = c.xhi; n.lo = c.xlo; n.T = T; n.d = d; n.eps = c.eps; n.part = c.part;
         if (l == 0) {
             n.embed = (const uint16_t *)c.embed; n.tokens = c.prefix + c.p0;
+            n.inv_freq = c.inv_freq; n.rope = c.rope; n.p0 = c.p0; n.half = dh / 2;
             hipLaunchKernelGGL((prefill_norm_kernel<true>), dim3(T), dim3(norm_threads(d)), 0, s, n);
         } else {
             n.splits = cut_down.splits;
