@@ -1,7 +1,7 @@
 // Dense prefix pass: the first-timestep forward over the prefix M (Section 3, "First
 // Timestep") for a whole chunk of prefix tokens at once, so that the weights are read once per
 // chunk instead of once per token.  Here the work IS a dense contraction, [tokens, d] x
-// [rows, d]^T, and runs on the matrix cores (v_mfma_f32_32x32x16_bf16).
+// [rows, d]^T, and runs on the matrix cores (v_mfma_f32_16x16x32_bf16).
 //
 // Precision: the step path multiplies bf16 weights with fp32 activations.  To stay within
 // rounding of it, an activation x is fed as two bf16 terms, hi = bf16(x) and lo = bf16(x - hi)
