@@ -1412,8 +1412,9 @@ hipError_t prefill_chunk(hipStream_t s, const PrefillChunk &c) {
 hipError_t prefill32_chunk(hipStream_t s, const PrefillChunk &c) {
     const int T = c.T, d = c.d_model, dh = d / c.n_heads, nq = c.n_heads * dh, nkv = c.n_kv_heads * dh;
     float *att = (float *)c.xhi, *u = (float *)c.uhi;
-    hipLaunchKernelGGL(prefill32_start_kernel, dim3((T * (d / 4) + 255) / 256), dim3(256), 0, s, (const float *)c.embed, c.prefix + c.p0, c.h, d, c.inv_freq, c.p0, T,
-                       dh / 2, c.rope);
+    // (one head: its angles outnumber a token's pieces of four)
+    hipLaunchKernelGGL(prefill32_start_kernel, dim3((T * std::max(d / 4, dh / 2) + 255) / 256), dim3(256), 0, s, (const float *)c.embed, c.prefix + c.p0, c.h, d, c.inv_freq,
+                       c.p0, T, dh / 2, c.rope);
     auto product = [&](auto epi, Prefill32Args &a, const float *x, const void *gain, const void *W, const void *W2, int N, int K, float *y) {
         constexpr int EPI = decltype(epi)::value;
         a.x = x; a.gain = (const float *)gain; a.W32 = (const float *)W; a.W232 = (const float *)W2; a.N = N; a.K = K; a.y = y; a.T = T; a.eps = c.eps;

@@ -311,14 +311,15 @@ def test_last_layer_of_the_prefix_pass_runs_for_the_last_token(layers, heads, kv
 
 
 FP32_CHUNKS = [synth.ModelShape("fp32-256", 2, 256, 4, 4, 1024, 512, "fp32"), synth.ModelShape("fp32-gqa", 3, 512, 8, 2, 1008, 512, "fp32"),
-               synth.ModelShape("fp32-128", 1, 384, 3, 1, 464, 512, "fp32"), synth.ModelShape("fp32-heads-of-16", 2, 336, 21, 7, 1008, 512, "fp32")]
+               synth.ModelShape("fp32-128", 1, 384, 3, 1, 464, 512, "fp32"), synth.ModelShape("fp32-heads-of-16", 2, 336, 21, 7, 1008, 512, "fp32"),
+               synth.ModelShape("fp32-one-head-64", 2, 64, 1, 1, 208, 512, "fp32"), synth.ModelShape("fp32-one-head-128", 2, 128, 1, 1, 464, 512, "fp32")]
 
 
 @pytest.mark.parametrize("shape", FP32_CHUNKS, ids=lambda s: s.name)
-@pytest.mark.parametrize("m", [2, 3, 15, 16, 17, 32, 33, 64, 100, 1025])
+@pytest.mark.parametrize("m", [2, 3, 5, 9, 15, 16, 17, 32, 33, 64, 100, 1025])
 def test_fp32_prefix_pass_matches_the_token_by_token_pass(shape, m):
     """An fp32 model's prefix as chunks (one and two pieces of 16 tokens, ragged; 1025: a token in a chunk of its own; gate and up ragged
-    against a batch of pieces; the last shape has no such pass): logits as token by token, and those of a timestep on top of the
+    against a batch of pieces; one head: its rotary table is the larger part of what the pass sets up; heads of 16 have no such pass): logits as token by token, and those of a timestep on top of the
     cache.  Either pass is 2 .. 7e-7 from 64 bits: 5e-6 of the largest logit leaves room for both."""
     w = synth.make_weights(shape, seed=m)
     prefix = synth.make_prefix_uniform(shape.vocab, m, seed=m)
