@@ -251,11 +251,11 @@ int spd_get_fused(const spd_ctx *ctx, int32_t *out_enabled);
  * products on the matrix cores, reading the weights once per chunk.  Both fill the same cache
  * and leave the same logits up to fp32 rounding.  A dense pass exists for bf16 weights,
  * d_head <= 128, d_model <= 8192 and d_model, d_ffn, n_heads * d_head divisible by 128; it adds
- * 1024 rows of activations to spd_workspace_bytes.  spd_set_dense_prefill switches (SPD_EINVAL
- * when asked for a dense pass the model has none for).
+ * 1024 rows of activations to spd_workspace_bytes.
  * fp32 models with heads of 64 or 128 and d_model, d_ffn divisible by 16 take prefixes of two tokens or more the same
- * way, with every product and sum in fp32 (1024 rows, or max_ctx if that is less, in spd_workspace_bytes).  For them
- * spd_set_dense_prefill(0) selects the token-by-token pass for good, and spd_get_dense_prefill says 0. */
+ * way, with every product and sum in fp32 (1024 rows, or max_ctx if that is less, in spd_workspace_bytes).
+ * spd_set_dense_prefill switches between the passes, back and forth (SPD_EINVAL when asked for a dense pass the model has
+ * none for); spd_get_dense_prefill says whether the dense one is in use. */
 int spd_set_dense_prefill(spd_ctx *ctx, int32_t enable);
 int spd_get_dense_prefill(const spd_ctx *ctx, int32_t *out_enabled);
 

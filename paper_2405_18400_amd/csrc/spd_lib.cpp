@@ -147,7 +147,7 @@ struct spd_ctx {
     std::vector<int32_t> text;   // committed tokens: the prefix, extended by spd_commit
     char *pinned;
     size_t pinned_bytes;
-    bool use_graph, timing, use_fused, use_dense, use_chunk32;
+    bool use_graph, timing, use_fused, use_dense;
     int fused_blocks;   // grid of the fused forward kernel; 0 = not available for this shape
     PrefillForce force[4];   // tests only
     hipGraphExec_t step_exec, prefill_exec, nucleus_exec;
@@ -452,9 +452,7 @@ int spd_create(const spd_model_cfg *cfg, const spd_weight_ptrs *w, void *workspa
     std::memset(&c->ng, 0, sizeof(c->ng));
     c->state = ST_CREATED; c->pos = 0; c->n_gen = 0; c->k = 0;
     c->use_graph = true; c->timing = false; c->use_fused = true; c->fused_blocks = 0;
-    const bool prefill_ready = (c->L.dense || c->L.chunk32) && spdk::prefill_init() == hipSuccess;
-    c->use_dense = c->L.dense && prefill_ready;
-    c->use_chunk32 = c->L.chunk32 && prefill_ready;
+    c->use_dense = (c->L.dense || c->L.chunk32) && spdk::prefill_init() == hipSuccess;
     c->step_exec = nullptr; c->prefill_exec = nullptr; c->nucleus_exec = nullptr;
     std::memset(c->force, 0, sizeof(c->force));
     std::memset(&c->step_dc, 0, sizeof(c->step_dc));
@@ -551,7 +549,7 @@ static int run_prefix_pass(spd_ctx *c, int p0, int m) {
     DevState *hs = (DevState *)c->pinned;
     std::memset(hs, 0, sizeof(DevState));
     const int n = m - p0;
-    const bool dense = (c->use_dense && n >= DENSE_PREFILL_MIN) || (c->use_chunk32 && n >= CHUNK32_MIN);
+    const bool dense = c->use_dense && n >= (c->L.chunk32 ? CHUNK32_MIN : DENSE_PREFILL_MIN);
     hs->pos = dense ? m : p0;      // (the dense pass takes its positions from the host)
     for (int q = 0; q < SPD_TAIL; ++q) {
         const int src = m - SPD_TAIL + q;
@@ -586,7 +584,7 @@ static int run_prefix_pass(spd_ctx *c, int p0, int m) {
         for (int at = p0; at < m; at += PREFILL_CHUNK) {
             pc.p0 = at; pc.T = last_T = (m - at < PREFILL_CHUNK) ? m - at : PREFILL_CHUNK;
             pc.final = at + pc.T == m;
-            HIPCHK(c, c->use_chunk32 ? spdk::prefill32_chunk(c->stream, pc) : spdk::prefill_chunk(c->stream, pc));
+            HIPCHK(c, c->L.chunk32 ? spdk::prefill32_chunk(c->stream, pc) : spdk::prefill_chunk(c->stream, pc));
         }
         GemvArgs g{};
         g.W = c->lm_head; g.gain = c->final_norm; g.eps = mc.rms_eps; g.x = pc.h + (size_t)(last_T - 1) * mc.d_model;
@@ -1033,9 +1031,10 @@ int spd_set_fused(spd_ctx *c, int32_t enable) {
 
 int spd_set_dense_prefill(spd_ctx *c, int32_t enable) {
     if (!c) return SPD_EINVAL;
-    if (enable && !c->L.dense) return fail(c, SPD_EINVAL, "no dense prefix pass for this model (bf16 weights, d_head <= 128, widths divisible by 128, d_model <= 8192)");
+    if (enable && !c->L.dense && !c->L.chunk32)
+        return fail(c, SPD_EINVAL, "no dense prefix pass for this model (bf16 weights: d_head <= 128, widths divisible by 128, d_model <= 8192; "
+                                   "fp32 weights: d_head 64 or 128, widths divisible by 16)");
     c->use_dense = enable != 0;
-    if (!enable) c->use_chunk32 = false;
     return SPD_OK;
 }
 

@@ -584,14 +584,42 @@ def test_fp16_cache_graph_replay_is_bit_exact_across_the_switch_of_reading_width
         sess.close()
 
 
-def test_dense_prefix_pass_is_refused_where_it_does_not_exist(tiny):
-    shape, w, tabs, prefix = tiny           # fp32 weights
-    sess = session(shape, w)
+@pytest.mark.parametrize("shape", [FP32_CHUNKS[3], synth.ModelShape("bf16-320", 1, 320, 5, 5, 640, 512, "bf16")], ids=lambda s: s.name)
+def test_dense_prefix_pass_is_refused_where_it_does_not_exist(shape):
+    sess = session(shape, synth.make_weights(shape, seed=1))
     try:
         assert not sess.spd_get_dense_prefill()
         with pytest.raises(P().SpdError):
             sess.spd_set_dense_prefill(True)
         sess.spd_set_dense_prefill(False)
+        assert not sess.spd_get_dense_prefill()
+    finally:
+        sess.close()
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_dense_prefix_pass_is_switched_off_and_on_again(dtype):
+    """What the getter says is what runs (a token-by-token pass of m tokens is m launches of the forward, the dense one none), and setting
+    what it said restores it: the logits are those of the pass before, bit for bit."""
+    shape = synth.ModelShape("switch", 2, 256, 4, 4, 512, 512, dtype)
+    prefix = synth.make_prefix_uniform(shape.vocab, 20, seed=3)
+    sess = session(shape, synth.make_weights(shape, seed=3))
+    try:
+        seen = []
+        for _ in range(2):
+            was = sess.spd_get_dense_prefill()
+            for on in (was, False, was):
+                sess.spd_set_dense_prefill(on)
+                assert sess.spd_get_dense_prefill() == on
+                sess.spd_set_kernel_timing(True)
+                sess.spd_prefill(prefix)
+                launches = sess.spd_get_kernel_timing()["fused_forward"][1]
+                sess.spd_set_kernel_timing(False)
+                assert launches == (0 if on else len(prefix))
+                seen.append((on, sess.spd_read_logits()))
+        for on, z in seen:
+            assert np.array_equal(z, next(y for o, y in seen if o == on))
+        assert {on for on, _ in seen} == {True, False}
     finally:
         sess.close()
 
