@@ -264,7 +264,7 @@ size_t gemv_lds_bytes(int dtype, int cols);
 hipError_t attention(hipStream_t s, int dtype, const AttnArgs &a);
 hipError_t superpose(hipStream_t s, int dtype, const SuperposeArgs &a);
 hipError_t topk_partial(hipStream_t s, const TopkArgs &a);
-bool expand_needs_topk(const ExpandArgs &a);   // whether topk_partial has to run before it; else it does that too
+bool expand_needs_topk(const TopkArgs &t, const ExpandArgs &a);   // whether topk_partial has to run before it; else it does that too
 hipError_t expand_prune(hipStream_t s, const TopkArgs &t, const ExpandArgs &a);
 hipError_t nucleus(hipStream_t s, const NucleusArgs &a);
 hipError_t prefill_chunk(hipStream_t s, const PrefillChunk &c);

@@ -434,21 +434,24 @@ __device__ __forceinline__ void ngram_probes(const NgramDev &ng, const int32_t (
 // Merges the per-slice top-k into the global KeepTopK and log-softmax, builds the
 // k x k options, probes the n-gram store for every (draft, kept token, order), applies the
 // mixture (Eq. 3), the interpolation (Eq. 4) or the penalty form (Eq. 5), keeps the k best
-// options and rewrites the draft state.  One block's work; NR > 0: the block that is last to finish its slice goes on with it.
+// options and rewrites the draft state.  One block's work; SLICES: the block that is last to finish its slice goes on with it.
 // A chain of latencies.  Whatever does not depend on the kept tokens is asked for at the start: the first MERGE threads
 // select in the block's slice while the others look up the drafts' context totals, in every block, since any may be the last.  With
 // few drafts the totals are looked up together with the counts, a group of lanes for each probe (ONE_GO: the kernel at
 // k = 1 .. 4, five orders, 9.2 .. 10.2 -> 5.7 .. 7.1 us).
-// One launch or two (NR = 0: the slices are a launch of their own), a timestep's decisions from 32000 logits, launched one by one, two
+// One launch or two (not SLICES: they are a launch of their own), a timestep's decisions from 32000 logits, launched one by one, two
 // -> one: no n-grams 8.9 -> 7.6 us at k = 1, 11.2 -> 10.9 at 8; five orders 15.6 -> 15.5 at k = 5, 22.8 -> 21.8 at 10.  With few drafts and
-// n-grams there is nothing to hide in the slices' time (10.35 -> 10.53 at k = 3) and two stay.
+// n-grams there is nothing to hide in the slices' time (10.35 -> 10.53 at k = 3) and two stay.  Two also where a slice has more than 1024
+// entries (vocabularies from 131074 on): of a block of 1024 threads 256 select, 5 .. 32 entries each, in every one of 128 blocks.  One -> two there,
+// 131074 .. 700000 entries, k = 1 .. 8: 0.83 .. 1.00 times for the first timestep and without n-grams (262146, k = 4: 12.8 -> 11.7 us), 0.93 .. 0.98 with
+// them from k = 5 on.
 // k = 8, five orders, 1.6 M slots: 28 -> 13 us behind the slices (merge 2.9, ranks 0.6, hashes 0.8, probes 5.5, mixture and scores 1.1, prune
 // and state 1.5).
 constexpr int ENT = 1024, MERGE = 256, MERGE_WAVES = MERGE / WAVE, GROUPS = ENT / PROBE_LANES;
 
 constexpr bool probes_in_one_go(int k) { return (k * k + k) * SPD_N_ORDERS <= GROUPS; }
 
-template <int NR, bool ONE_GO>
+template <bool SLICES, bool ONE_GO>
 __global__ __launch_bounds__(ENT) void expand_prune_kernel(const TopkArgs slice, const ExpandArgs a) {
     static_assert(MERGE == BLOCK, "the waves that merge are those that select");
     __shared__ TopkScratch scratch;
@@ -492,7 +495,7 @@ __global__ __launch_bounds__(ENT) void expand_prune_kernel(const TopkArgs slice,
     const bool use_ng = !a.first && a.alpha != 0.0f;
     const int n_count = k * k * SPD_N_ORDERS, n_total = k * SPD_N_ORDERS;
     if (tid < MERGE) {
-        if constexpr (NR > 0) topk_share<NR>(slice, scratch);
+        if constexpr (SLICES) topk_share<4>(slice, scratch);
     } else {
         const int u = tid - MERGE;
         if (u < SPD_K_MAX) {
@@ -514,7 +517,7 @@ __global__ __launch_bounds__(ENT) void expand_prune_kernel(const TopkArgs slice,
             if (e < n_total && u % PROBE_LANES == 0) s_tot[e] = total[0];
         }
     }
-    if constexpr (NR > 0) {
+    if constexpr (SLICES) {
         __syncthreads();
         if (tid < MERGE) {
             topk_result<true>(slice, scratch);
@@ -531,8 +534,8 @@ __global__ __launch_bounds__(ENT) void expand_prune_kernel(const TopkArgs slice,
         constexpr int NC = TOPK_PART_MAX * SPD_K_MAX / MERGE;
         auto candidate = [&](int q, float &v, int &i) {
             const int c = tid + q * MERGE, at = (c / k) * SPD_K_MAX + (c % k);
-            v = c < n_cand ? act_load<(NR > 0)>(a.pv + at) : -INFINITY;
-            i = c < n_cand ? __float_as_int(act_load<(NR > 0)>((const float *)a.pi + at)) : INT_MAX;
+            v = c < n_cand ? act_load<SLICES>(a.pv + at) : -INFINITY;
+            i = c < n_cand ? __float_as_int(act_load<SLICES>((const float *)a.pi + at)) : INT_MAX;
         };
         float cv[NC];
         int ci[NC];
@@ -547,8 +550,8 @@ __global__ __launch_bounds__(ENT) void expand_prune_kernel(const TopkArgs slice,
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
                 const int b = lane + q * WAVE;
-                pm[q] = b < a.n_part ? act_load<(NR > 0)>(a.pm + b) : -INFINITY;
-                ps[q] = b < a.n_part ? act_load<(NR > 0)>(a.ps + b) : 0.f;
+                pm[q] = b < a.n_part ? act_load<SLICES>(a.pm + b) : -INFINITY;
+                ps[q] = b < a.n_part ? act_load<SLICES>(a.ps + b) : 0.f;
             }
             const float M = read_lane(wave_max_last(fmaxf(pm[0], pm[1])), WAVE - 1);
 #pragma unroll
@@ -821,19 +824,17 @@ hipError_t topk_partial(hipStream_t s, const TopkArgs &a) {
     return hipGetLastError();
 }
 
-bool expand_needs_topk(const ExpandArgs &a) { return !a.first && a.alpha != 0.0f && probes_in_one_go(a.k); }
+static bool in_one_go(const ExpandArgs &a) { return !a.first && a.alpha != 0.0f && probes_in_one_go(a.k); }
+bool expand_needs_topk(const TopkArgs &t, const ExpandArgs &a) { return in_one_go(a) || t.per_part > 4 * BLOCK; }
 
 hipError_t expand_prune(hipStream_t s, const TopkArgs &t, const ExpandArgs &a) {
     auto go = [&](auto kernel, int blocks) {
         hipLaunchKernelGGL(kernel, dim3(blocks), dim3(ENT), 0, s, t, a);
         return hipGetLastError();
     };
-    if (expand_needs_topk(a)) return go(expand_prune_kernel<0, true>, 1);
-    if (t.per_part <= 4 * BLOCK) return go(expand_prune_kernel<4, false>, t.n_part);
-    if (t.per_part <= 8 * BLOCK) return go(expand_prune_kernel<8, false>, t.n_part);
-    if (t.per_part <= 16 * BLOCK) return go(expand_prune_kernel<16, false>, t.n_part);
-    if (t.per_part <= 32 * BLOCK) return go(expand_prune_kernel<32, false>, t.n_part);
-    return hipErrorInvalidValue;   // (vocabularies stay below 2^20)
+    if (in_one_go(a)) return go(expand_prune_kernel<false, true>, 1);
+    if (expand_needs_topk(t, a)) return go(expand_prune_kernel<false, false>, 1);
+    return go(expand_prune_kernel<true, false>, t.n_part);
 }
 
 hipError_t advance(hipStream_t s, DevState *st) {

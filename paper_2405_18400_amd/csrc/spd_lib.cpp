@@ -301,7 +301,7 @@ hipError_t enqueue_decide(spd_ctx *c, const spd_decode_cfg &dc, const float *log
     x.hist_tok = c->at<int32_t>(c->L.hist_tok); x.hist_par = c->at<int32_t>(c->L.hist_par);
     x.max_gen = c->cfg.max_ctx;
     x.arrived = c->at<uint32_t>(c->L.nuc_count);    // (one or the other on the context's stream)
-    if (spdk::expand_needs_topk(x)) {
+    if (spdk::expand_needs_topk(t, x)) {
         const hipError_t e = launch(c, KC_TOPK, [&] { return spdk::topk_partial(c->stream, t); });
         if (e != hipSuccess) return e;
     }

@@ -112,10 +112,11 @@ def test_tables_replaced_between_timesteps(tiny):
 
 
 @pytest.mark.parametrize("k", [1, 5, 10])
-@pytest.mark.parametrize("vocab", [700, 5122, 131074])
+@pytest.mark.parametrize("vocab", [700, 5122, 131072, 131074])
 def test_decisions_whose_last_slice_goes_on(vocab, k):
-    """One slice, a ragged number of them and the first with more entries per thread; with n-grams (five drafts and more) and without the
-    same launch selects and decides, timestep after timestep: scripted logits, no gap allowance."""
+    """One slice, a ragged number of them, the last and the first vocabulary of slices of up to 1024 entries: up to there, with n-grams (five
+    drafts and more) and without the same launch selects and decides, timestep after timestep, else the slices have a launch of
+    their own: scripted logits, no gap allowance."""
     import torch
     pkg = P()
     shape = synth.ModelShape("one-head", 1, 64, 1, 1, 128, vocab, "fp32")
@@ -129,6 +130,7 @@ def test_decisions_whose_last_slice_goes_on(vocab, k):
         sess.spd_load_ngrams(tabs, lam)
         otabs = O.NgramTables(tabs)
         sess.spd_prefill(pre)
+        sess.spd_set_kernel_timing(True)
         for alpha in (0.54, 0.0):
             dc, cfg, state = pkg.SpdDecodeCfg(k, alpha, 1.0, 0.1), O.DecodeCfg(k, alpha, 1.0, 0.1, lam), None
             for step in range(4):
@@ -141,5 +143,7 @@ def test_decisions_whose_last_slice_goes_on(vocab, k):
                 assert list(sess.spd_get_step_info(k)[0]) == list(rec.top_ids)
                 np.testing.assert_allclose(scores, state.logscores, rtol=1e-5, atol=1e-5)     # sums of fp32 logarithms
                 assert np.array_equal(tails, tails_of(state))
+        launches = sess.spd_get_kernel_timing()
+        assert launches["expand_prune"][1] == 8 and launches["topk_partial"][1] == (8 if vocab > 131072 else 3 if k < 5 else 0)
     finally:
         sess.close()
