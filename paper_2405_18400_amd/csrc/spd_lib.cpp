@@ -367,7 +367,17 @@ const char *check_dc(const spd_ctx *c, const spd_decode_cfg *dc) {
 }
 
 constexpr int DENSE_PREFILL_MIN = 8;   // shorter prefixes go token by token
-constexpr int CHUNK32_MIN = 2;         // the same for fp32 models (two tokens of two layers of 256 wide: 68 us, 113 one by one)
+// The same for fp32 models: three, whose chunk takes 0.37 .. 0.75 times what they take one by one (up to six layers).  Two tokens, 80 models, as a chunk against one by
+// one: 0.54 .. 0.98 times up to three layers (1.01 at worst), and beyond where no wave's share of a product's k is long against the tiles
+// there are.  The persistent forward is the faster way from 1280 wide with a feed-forward past 4096 (four layers 0.95 .. 1.05, 12 and more
+// 1.07 .. 1.18: 24 layers of 2048 wide, 2170 us as a chunk, 1836 one by one); a kernel per product, the way of wider rows, only
+// with a feed-forward beyond eight times the width (1.02 .. 1.27).
+int chunk32_min(const spd_ctx *c) {
+    const spd_model_cfg &m = c->cfg;
+    const bool persistent = c->use_fused && c->fused_blocks > 0;
+    const bool slow = persistent ? m.d_model > 1024 && m.d_ffn > 4096 : m.d_model <= 2048 && m.d_ffn > 8 * m.d_model;
+    return m.n_layers > 3 && slow ? 3 : 2;
+}
 
 bool graphs_usable(const spd_ctx *c) { return c->use_graph && !c->timing && c->stream != nullptr; }
 
@@ -549,7 +559,7 @@ static int run_prefix_pass(spd_ctx *c, int p0, int m) {
     DevState *hs = (DevState *)c->pinned;
     std::memset(hs, 0, sizeof(DevState));
     const int n = m - p0;
-    const bool dense = c->use_dense && n >= (c->L.chunk32 ? CHUNK32_MIN : DENSE_PREFILL_MIN);
+    const bool dense = c->use_dense && n >= (c->L.chunk32 ? chunk32_min(c) : DENSE_PREFILL_MIN);
     hs->pos = dense ? m : p0;      // (the dense pass takes its positions from the host)
     for (int q = 0; q < SPD_TAIL; ++q) {
         const int src = m - SPD_TAIL + q;

@@ -341,6 +341,27 @@ def test_fp32_prefix_pass_matches_the_token_by_token_pass(shape, m):
         assert np.max(np.abs(x - y)) <= 5e-6 * np.max(np.abs(y))
 
 
+@pytest.mark.parametrize("layers,d,heads,ffn,fused,chunk", [
+    (4, 1152, 9, 4112, True, False), (3, 1152, 9, 4112, True, True), (4, 1024, 8, 4112, True, True), (4, 1152, 9, 4096, True, True), (4, 1152, 9, 4112, False, True),
+    (4, 128, 2, 6160, False, False), (3, 128, 2, 6160, False, True), (4, 256, 4, 2048, False, True)])
+def test_fp32_prefix_of_two_tokens_goes_the_faster_way(layers, d, heads, ffn, fused, chunk):
+    """Either side of every line of the rule, with the persistent forward and with a kernel per product (feed-forwards past 6144 have no
+    other): two tokens are one chunk, which makes no launch of the forward, or two forwards; three are always a chunk."""
+    shape = synth.ModelShape("two", layers, d, heads, heads, ffn, 512, "fp32")
+    sess = session(shape, synth.make_weights(shape, seed=2))
+    try:
+        if not fused:
+            sess.spd_set_fused(False)
+        for m, forwards in ((2, 0 if chunk else 2), (3, 0)):
+            sess.spd_set_kernel_timing(True)
+            sess.spd_prefill(np.arange(m, dtype=np.int32))
+            t = sess.spd_get_kernel_timing()
+            assert t["fused_forward"][1] == (forwards if fused else 0) and t["gemv_qkv"][1] == (0 if fused else forwards * layers)
+            assert np.isfinite(sess.spd_read_logits()).all()
+    finally:
+        sess.close()
+
+
 PREFIX_TILES = [(32, 256), (64, 256), (64, 384), (128, 256), (128, 384), (64, 128), (32, 128)]
 QKV, ATTN_OUT, GATE_UP, DOWN = range(4)
 
