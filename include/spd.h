@@ -253,7 +253,8 @@ int spd_get_fused(const spd_ctx *ctx, int32_t *out_enabled);
  * d_head <= 128, d_model <= 8192 and d_model, d_ffn, n_heads * d_head divisible by 128; it adds
  * 1024 rows of activations to spd_workspace_bytes.
  * fp32 models with heads of 64 or 128 and d_model, d_ffn divisible by 16 take prefixes of three tokens or more the same
- * way (two where that is the faster pass), with every product and sum in fp32 (1024 rows, or max_ctx if that is less, in spd_workspace_bytes).
+ * way (two where that is the faster pass), with every product and sum in fp32 (1024 rows, or max_ctx if that is less, in
+ * spd_workspace_bytes; a workspace without them is taken too, and such a context has no dense pass).
  * spd_set_dense_prefill switches between the passes, back and forth (SPD_EINVAL when asked for a dense pass the model has
  * none for); spd_get_dense_prefill says whether the dense one is in use. */
 int spd_set_dense_prefill(spd_ctx *ctx, int32_t enable);

@@ -23,7 +23,7 @@ const char *const KC_NAMES[KC_N] = {"superpose", "gemv_qkv", "attention", "gemv_
 struct Layout {
     size_t pf_h, pf_part, pf_q, pf_xhi, pf_xlo, pf_uhi, pf_ulo, pf_rope;   // dense prefix pass arena (0 = none)
     bool dense, chunk32;   // the prefix pass on the matrix cores exists: bf16 models; fp32 models
-    size_t state, sync, layers_dev, prof, act, logits, part, counters, inv_freq, prefix, hist_tok, hist_par, pv, pi, pm, ps, pn, nuc_pb, nuc_count, nuc_hist, nuc_bk, kv, total;
+    size_t state, sync, layers_dev, prof, act, logits, part, counters, inv_freq, prefix, hist_tok, hist_par, pv, pi, pm, ps, pn, nuc_pb, nuc_count, nuc_hist, nuc_bk, kv, least, total;
     size_t kv_layer_bytes;   // K (or V) of one layer
     size_t arena_bytes;      // one activation arena
     int max_splits, n_part, per_part;
@@ -112,7 +112,11 @@ Layout make_layout(const spd_model_cfg &c) {
         L.pf_ulo = take((size_t)PREFILL_CHUNK * c.d_ffn * 2);
         L.pf_rope = take((size_t)PREFILL_CHUNK * (dh / 2) * 8);
     }
-    // the same for fp32 models: heads its attention has a kernel for, whole pieces of 16 k, 32-bit offsets into a matrix
+    L.kv_layer_bytes = up((size_t)c.n_kv_heads * c.max_ctx * dh * (c.kv_dtype == SPD_DTYPE_FP16 ? 2 : 4));
+    L.kv = take(L.kv_layer_bytes * 2 * (size_t)c.n_layers);
+    // the same for fp32 models: heads its attention has a kernel for, whole pieces of 16 k, 32-bit offsets into a matrix.  It
+    // lies last: a context whose workspace ends before it goes without
+    L.least = o;
     L.chunk32 = c.dtype == SPD_DTYPE_FP32 && (dh == 64 || dh == 128) && c.d_model % 16 == 0 && c.d_ffn % 16 == 0 && c.n_layers > 0 &&
                 (long long)(c.d_ffn > 3 * c.d_model ? c.d_ffn : 3 * c.d_model) * c.d_model < (1ll << 29);
     if (L.chunk32) {
@@ -123,8 +127,6 @@ Layout make_layout(const spd_model_cfg &c) {
         L.pf_uhi = take(rows * c.d_ffn * 4);
         L.pf_rope = take(rows * (dh / 2) * 8);
     }
-    L.kv_layer_bytes = up((size_t)c.n_kv_heads * c.max_ctx * dh * (c.kv_dtype == SPD_DTYPE_FP16 ? 2 : 4));
-    L.kv = take(L.kv_layer_bytes * 2 * (size_t)c.n_layers);
     L.total = o;
     return L;
 }
@@ -447,8 +449,9 @@ int spd_create(const spd_model_cfg *cfg, const spd_weight_ptrs *w, void *workspa
         for (const void *p : ps)
             if (!p || misaligned(p)) return SPD_EINVAL;
     }
-    const Layout L = make_layout(*cfg);
-    if (((uintptr_t)workspace & (ALIGN - 1)) || workspace_bytes < L.total) return SPD_EWORKSPACE;
+    Layout L = make_layout(*cfg);
+    if (((uintptr_t)workspace & (ALIGN - 1)) || workspace_bytes < L.least) return SPD_EWORKSPACE;
+    if (workspace_bytes < L.total) L.chunk32 = false;
 
     spd_ctx *c = new (std::nothrow) spd_ctx();
     if (!c) return SPD_EINVAL;

@@ -618,6 +618,37 @@ def test_dense_prefix_pass_is_refused_where_it_does_not_exist(shape):
         sess.close()
 
 
+@pytest.mark.parametrize("max_ctx", [40, 1500])
+def test_fp32_workspace_without_the_chunk_pass(max_ctx, monkeypatch):
+    """A workspace that has no room for the chunk's rows (all but its last byte, none) makes a context without that pass, with the logits of
+    the token-by-token one; a byte less than the rest is refused."""
+    from paper_2405_18400_amd import binding
+    shape = synth.ModelShape("small-workspace", 2, 256, 4, 2, 512, 512, "fp32")
+    w, prefix = synth.make_weights(shape, seed=4), synth.make_prefix_uniform(shape.vocab, 30, seed=4)
+    whole, rows = binding.spd_workspace_bytes(binding.model_cfg(shape, max_ctx, 8)), min(max_ctx, 1024)
+    up = lambda n: (n + 255) // 256 * 256  # noqa: E731
+    chunk = 3 * up(rows * 256 * 4) + up(rows * 512 * 4) + up(rows * 32 * 8)
+    logits = []
+    for size in (whole, whole - 1, whole - chunk):
+        monkeypatch.setattr(binding, "spd_workspace_bytes", lambda cfg: size)
+        sess = session(shape, w, max_ctx=max_ctx)
+        try:
+            assert sess.spd_get_dense_prefill() == (size == whole)
+            if size == whole:
+                sess.spd_set_dense_prefill(False)
+            else:
+                with pytest.raises(P().SpdError):
+                    sess.spd_set_dense_prefill(True)
+            sess.spd_prefill(prefix)
+            logits.append(sess.spd_read_logits())
+        finally:
+            sess.close()
+    assert all(np.array_equal(z, logits[0]) for z in logits)
+    monkeypatch.setattr(binding, "spd_workspace_bytes", lambda cfg: whole - chunk - 1)
+    with pytest.raises(P().SpdError):
+        session(shape, w, max_ctx=max_ctx)
+
+
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 def test_dense_prefix_pass_is_switched_off_and_on_again(dtype):
     """What the getter says is what runs (a token-by-token pass of m tokens is m launches of the forward, the dense one none), and setting
