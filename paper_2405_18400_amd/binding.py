@@ -374,7 +374,8 @@ def _stream_ptr():
     """The calling thread's current stream on its current device, without the Stream object around it: building that
     took 2.9 of the 7.2 us such a call took the host (now 0.4 of 4.7)."""
     torch = _torch()
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)      # (private to torch: a build may lack it)
+    return raw(torch.cuda.current_device()) if raw is not None else torch.cuda.current_stream().cuda_stream
 
 
 def spd_op_gemv(dtype: str, W, x, y, gain=None, eps=0.0, residual=None):

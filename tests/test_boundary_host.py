@@ -35,6 +35,15 @@ def test_every_declared_symbol_is_exported(pkg):
         assert hasattr(L, n), f"{n} declared in spd.h but not exported by libspd.so"
 
 
+@pytest.mark.parametrize("private", [True, False])
+def test_stream_handle_with_and_without_the_private_torch_function(pkg, monkeypatch, private):
+    from types import SimpleNamespace
+    cuda = SimpleNamespace(current_device=lambda: 3, current_stream=lambda: SimpleNamespace(cuda_stream=70))
+    torch = SimpleNamespace(cuda=cuda, _C=SimpleNamespace(**({"_cuda_getCurrentRawStream": lambda device: 40 + device} if private else {})))
+    monkeypatch.setattr(pkg.binding, "_torch", lambda: torch)
+    assert pkg.binding._stream_ptr() == (43 if private else 70)
+
+
 def test_workspace_bytes_and_config_validation(pkg):
     cfg = pkg.binding.model_cfg(synth.LLAMA7B, 128, 8)
     need = pkg.spd_workspace_bytes(cfg)
