@@ -335,9 +335,12 @@ int spd_test_ngram_table(const spd_ngram_host_tables *t, int32_t vocab, void *ou
  * compute units (host only, no GPU): out[4] = tokens and columns of a tile, blocks that share a tile's k range, 1 where the
  * product runs its epilogue itself.  SPD_EINVAL for models without a dense pass. */
 int spd_test_prefill_cut(const spd_model_cfg *cfg, int32_t num_cu, int32_t n_tokens, int32_t product, int32_t *out);
-/* From now on this context cuts `product` with the tile shape `tile` (0 .. 6; -1: by estimate again) and `splits` blocks per k
+/* From now on this context cuts `product` with the tile shape `tile` (0 .. 6, for gate and up 0 .. 13; -1: by estimate again) and `splits` blocks per k
  * range, wherever partial sums of that size have room; out[4] as above, for a chunk of n_tokens. */
 int spd_test_force_prefill_cut(spd_ctx *ctx, int32_t product, int32_t tile, int32_t splits, int32_t n_tokens, int32_t *out);
+/* From now on this context's dense pass takes the last layer's query rows with the key and value rows (mode 1), in a product of their own for
+ * the last token (2), or as measured (0); *out_own: whether a chunk of n_tokens has that product. */
+int spd_test_force_last_query(spd_ctx *ctx, int32_t mode, int32_t n_tokens, int32_t *out_own);
 /* The chunk's causal attention alone: DEVICE float queries [n_tokens, n_heads, d_head] at positions pos .., DEVICE cache
  * [n_kv_heads, cap_ctx, d_head] (fp32 or fp16) filled up to them, result [n_tokens, n_heads, d_head] as the sum of two bf16
  * numbers (DEVICE); everything 16-byte aligned, d_head a power of two from 8 to 128, n_tokens <= 1024. */

@@ -97,6 +97,7 @@ def lib():
             "spd_test_prefill_cut": [C.POINTER(SpdModelCfg), i32, i32, i32, vp],
             "spd_test_prefill_attention": [i32, vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, i32, vp],
             "spd_test_force_prefill_cut": [vp, i32, i32, i32, i32, vp],
+            "spd_test_force_last_query": [vp, i32, i32, C.POINTER(i32)],
             "spd_op_gemv": [i32, vp, vp, f32, vp, vp, vp, i32, i32, vp],
             "spd_op_swiglu": [i32, vp, vp, vp, f32, vp, vp, i32, i32, vp],
             "spd_op_attention": [i32, vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, vp],
@@ -331,6 +332,12 @@ class Session:
         out = np.zeros(4, np.int32)
         self._chk(self.L.spd_test_force_prefill_cut(self.ctx, product, tile, splits, n_tokens, _np_ptr(out)), "spd_test_force_prefill_cut")
         return int(out[0]), int(out[1]), int(out[2]), bool(out[3])
+
+    def spd_test_force_last_query(self, mode: int, n_tokens: int) -> bool:
+        """-> whether the last layer's query has a product of its own in a chunk of n_tokens."""
+        out = C.c_int32(0)
+        self._chk(self.L.spd_test_force_last_query(self.ctx, mode, n_tokens, C.byref(out)), "spd_test_force_last_query")
+        return bool(out.value)
 
     def spd_position(self) -> int:
         out = C.c_int32(0)

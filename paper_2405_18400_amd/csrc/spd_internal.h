@@ -243,6 +243,7 @@ struct PrefillChunk {
     float *attn_part;                  // the stand-alone attention's partial results, as in AttnArgs
     int32_t max_splits;
     PrefillForce force[4];             // QKV, attention output, gate and up, down
+    int32_t force_query;               // tests only: the last layer's query rows in the big product (1), in a product of their own (2), or as measured (0)
 };
 
 constexpr int FUSED_MAX_EPI = 512;     // residual values one block of the fused kernel stages per phase
@@ -270,6 +271,7 @@ hipError_t nucleus(hipStream_t s, const NucleusArgs &a);
 hipError_t prefill_chunk(hipStream_t s, const PrefillChunk &c);
 hipError_t prefill32_chunk(hipStream_t s, const PrefillChunk &c);      // fp32 models
 hipError_t prefill_init();
+bool prefill_own_query(const PrefillChunk &c, int T);   // whether the last layer's query has a product of its own
 void prefill_cuts(const PrefillChunk &c, int T, PrefillCut (&cut)[4]);   // QKV, attention output, gate and up, down
 // The chunk's causal attention: queries [T, n_heads * dh] at positions p0 .. p0 + T - 1, output as a (hi, lo) bf16 pair, or (fp32 cache,
 // out32 given) in fp32.

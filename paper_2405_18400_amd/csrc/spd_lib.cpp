@@ -152,6 +152,7 @@ struct spd_ctx {
     bool use_graph, timing, use_fused, use_dense;
     int fused_blocks;   // grid of the fused forward kernel; 0 = not available for this shape
     PrefillForce force[4];   // tests only
+    int force_query;         // tests only
     hipGraphExec_t step_exec, prefill_exec, nucleus_exec;
     spd_decode_cfg step_dc;
     spd_sample_cfg nucleus_sc;
@@ -468,6 +469,7 @@ int spd_create(const spd_model_cfg *cfg, const spd_weight_ptrs *w, void *workspa
     c->use_dense = (c->L.dense || c->L.chunk32) && spdk::prefill_init() == hipSuccess;
     c->step_exec = nullptr; c->prefill_exec = nullptr; c->nucleus_exec = nullptr;
     std::memset(c->force, 0, sizeof(c->force));
+    c->force_query = 0;
     std::memset(&c->step_dc, 0, sizeof(c->step_dc));
     std::memset(c->kc_ms, 0, sizeof(c->kc_ms));
     std::memset(c->kc_n, 0, sizeof(c->kc_n));
@@ -593,6 +595,7 @@ static int run_prefix_pass(spd_ctx *c, int p0, int m) {
         pc.rope = c->at<float2>(c->L.pf_rope);
         pc.attn_part = c->at<float>(c->L.part); pc.max_splits = c->L.max_splits;
         std::memcpy(pc.force, c->force, sizeof(pc.force));
+        pc.force_query = c->force_query;
         int last_T = 0;
         for (int at = p0; at < m; at += PREFILL_CHUNK) {
             pc.p0 = at; pc.T = last_T = (m - at < PREFILL_CHUNK) ? m - at : PREFILL_CHUNK;
@@ -1003,6 +1006,16 @@ int spd_test_force_prefill_cut(spd_ctx *c, int32_t product, int32_t tile, int32_
         return fail(c, SPD_EINVAL, "no such product, tile shape or chunk");
     c->force[product] = PrefillForce{tile + 1, splits};
     prefill_cut_of(c->cfg, c->num_cu, c->force, n_tokens, product, out);
+    return SPD_OK;
+}
+
+int spd_test_force_last_query(spd_ctx *c, int32_t mode, int32_t n_tokens, int32_t *out_own) {
+    if (!c) return SPD_EINVAL;
+    if (!out_own || !c->L.dense || mode < 0 || mode > 2 || n_tokens < 1 || n_tokens > PREFILL_CHUNK) return fail(c, SPD_EINVAL, "no such mode or chunk");
+    c->force_query = mode;
+    PrefillChunk pc{};
+    pc.d_model = c->cfg.d_model; pc.force_query = mode;
+    *out_own = spdk::prefill_own_query(pc, n_tokens) ? 1 : 0;
     return SPD_OK;
 }
 

@@ -1337,6 +1337,9 @@ static hipError_t last_token(hipStream_t s, const PrefillChunk &c, int dtype, co
 // them, in fp32): up to this many tokens x rows x k.  A whole pass over two layers, rows in the product against by themselves: 1B widths
 // 0.92 (8 tokens) .. 0.99 (512); 7B 0.94 (8) .. 0.98 (160), 1.01 (192), 1.04 (512); 13B 0.96 .. 0.98 (128), 1.01 (192); 70B 0.98 (8) .. 0.99 (64), 1.01 (96).
 constexpr long long LAST_QUERY_WITH = 3000000000ll;
+bool prefill_own_query(const PrefillChunk &c, int T) {
+    return c.force_query != 0 ? c.force_query == 2 : (long long)T * c.d_model * c.d_model > LAST_QUERY_WITH;
+}
 
 // One chunk of T prefix tokens at positions p0 .. p0 + T - 1 through the whole stack.  Only the prefix's last token goes
 // on into the final norm and the LM head, and nothing reads what the last layer makes of the others but their keys and values.
@@ -1352,7 +1355,7 @@ hipError_t prefill_chunk(hipStream_t s, const PrefillChunk &c) {
     PrefillCut cut[4];
     prefill_cuts(c, T, cut);
     const PrefillCut &cut_o = cut[1], &cut_gu = cut[2], &cut_down = cut[3];
-    const bool own_query = (long long)T * nq * d > LAST_QUERY_WITH;
+    const bool own_query = prefill_own_query(c, T);
     const PrefillCut cut_last = own_query ? cut_product(c, c.force[0], T, 2 * nkv, 1, d, PE_QKV, (size_t)PREFILL_CHUNK * c.d_ffn) : cut[0];
     for (int l = 0; l < c.n_layers; ++l) {
         const spd_layer_weights &w = c.layers[l];

@@ -284,30 +284,66 @@ def test_dense_prefix_pass_matches_the_oracle_and_the_token_by_token_pass(m):
 
 
 @pytest.mark.parametrize("layers,heads,kv_heads", [(1, 4, 1), (2, 16, 1), (1, 6, 6), (2, 64, 4)])
-@pytest.mark.parametrize("m", [8, 65, 1024, 1025, 1029])
+@pytest.mark.parametrize("m", [8, 65, 1024, 1025, 1029, 1040])
 @pytest.mark.parametrize("kv_dtype,bound", [("fp32", 1e-4), ("fp16", 1e-3)])
 def test_last_layer_of_the_prefix_pass_runs_for_the_last_token(layers, heads, kv_heads, m, kv_dtype, bound):
-    """Key and value rows of the last layer for every token (16 .. 768 of them: less than a tile, ragged), the rest of it for the
-    prefix's last token, in a chunk's last row or alone in a chunk of its own (1025): the logits are those of the token-by-token
-    pass (bounds as above: 16-bit activations, an fp16 cache's roundings), and so are a timestep's on top of the cache."""
+    """Key and value rows of the last layer for every token, with the query rows or without them (then 64 .. 768 rows: less than a tile,
+    ragged), the rest of it for the prefix's last token, in a chunk's last row, alone or among a few in a chunk of its own (from 1025): the
+    logits are those of the token-by-token pass (bounds as above: 16-bit activations, an fp16 cache's roundings), and so are a
+    timestep's on top of the cache and those behind a committed draft of ten tokens, a chunk at a position that is no multiple of anything."""
     shape = synth.ModelShape("tail-bf16", layers, 384 if heads == 6 else 512, heads, kv_heads, 640, 512, "bf16")
     w = synth.make_weights(shape, seed=m)
     prefix = synth.make_prefix_zipf(shape.vocab, m, seed=m)
-    sess = session(shape, w, max_ctx=m + 4, kv_dtype=kv_dtype)
-    got = {}
+    sess = session(shape, w, max_ctx=m + 24, kv_dtype=kv_dtype)
+    dc, got = P().SpdDecodeCfg(2, 0.0, 1.0, 0.1), {}
     try:
-        for dense in (True, False):
-            sess.spd_set_dense_prefill(dense)
+        for mode in (2, 1, None):
+            sess.spd_set_dense_prefill(mode is not None)
+            if mode is not None:
+                assert all(sess.spd_test_force_last_query(mode, T) == (mode == 2) for T in (1, 8, 1024))
             sess.spd_prefill(prefix)
-            got[dense] = [sess.spd_read_logits()]
-            sess.spd_step(P().SpdDecodeCfg(2, 0.0, 1.0, 0.1))
+            got[mode] = [sess.spd_read_logits()]
+            sess.spd_step(dc)
             sess.spd_set_state(np.tile(prefix[:5], (2, 1)).astype(np.int32), np.array([-1.0, -2.0], np.float32))
-            sess.spd_step(P().SpdDecodeCfg(2, 0.0, 1.0, 0.1))
-            got[dense].append(sess.spd_read_logits())
+            sess.spd_step(dc)
+            got[mode].append(sess.spd_read_logits())
+        # a draft committed behind the prefix: its tokens are passed again from position m on; the whole text, one by one
+        for mode in (2, 1):
+            sess.spd_set_dense_prefill(True)
+            sess.spd_test_force_last_query(mode, 10)
+            sess.spd_prefill(prefix)
+            for _ in range(10):
+                sess.spd_step(dc)
+            _, toks = sess.spd_commit(0.0)
+            assert len(toks) == 10
+            got[mode].append(sess.spd_read_logits())
+            sess.spd_set_dense_prefill(False)
+            sess.spd_prefill(np.concatenate([prefix, toks]))
+            got[mode, "text"] = sess.spd_read_logits()
     finally:
         sess.close()
-    for x, y in zip(got[True], got[False]):
-        assert np.max(np.abs(x - y)) <= bound * np.max(np.abs(y))
+    for mode in (1, 2):
+        for x, y in zip(got[mode], [*got[None], got[mode, "text"]], strict=True):
+            assert np.max(np.abs(x - y)) <= bound * np.max(np.abs(y))
+
+
+def test_last_query_goes_with_the_others_up_to_a_size():
+    """The rule itself, on both sides of its line: 178 and 179 tokens of 4096 x 4096."""
+    shape = synth.ModelShape("wide-query-bf16", 1, 4096, 32, 1, 128, 512, "bf16")
+    w = synth.make_weights(shape, seed=6)
+    sess = session(shape, w, max_ctx=1216, kv_dtype="fp16")
+    try:
+        assert [sess.spd_test_force_last_query(0, T) for T in (178, 179, 1024)] == [False, True, True]
+        logits = []
+        for dense in (True, False):
+            sess.spd_set_dense_prefill(dense)
+            for m in (178, 179, 1024 + 180):
+                sess.spd_prefill(synth.make_prefix_zipf(shape.vocab, m, seed=m))
+                logits.append(sess.spd_read_logits())
+    finally:
+        sess.close()
+    for x, y in zip(logits[:3], logits[3:], strict=True):
+        assert np.max(np.abs(x - y)) <= 1e-3 * np.max(np.abs(y))
 
 
 FP32_CHUNKS = [synth.ModelShape("fp32-256", 2, 256, 4, 4, 1024, 512, "fp32"), synth.ModelShape("fp32-gqa", 3, 512, 8, 2, 1008, 512, "fp32"),
