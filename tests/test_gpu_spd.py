@@ -56,11 +56,13 @@ def select_path(sess, path):
 
 
 def run_teacher_forced(shape, w, tabs, lambdas, prefix, k, alpha, n_tokens, tau=1.0, delta=0.1, max_ctx=64,
-                       path="fused", kv_dtype="fp32"):
+                       path="fused", kv_dtype="fp32", dense=None):
     pkg = P()
     sess = session(shape, w, max_ctx=max_ctx, kv_dtype=kv_dtype)
     try:
         select_path(sess, path)
+        if dense is not None:
+            sess.spd_set_dense_prefill(dense)
         if tabs is not None:
             sess.spd_load_ngrams(tabs, lambdas)
         dc = pkg.SpdDecodeCfg(k, alpha, tau, delta)
@@ -73,11 +75,13 @@ def run_teacher_forced(shape, w, tabs, lambdas, prefix, k, alpha, n_tokens, tau=
         sess.close()
 
 
-def test_tiny_config_as_specified(tiny, forward_path):
-    """BASELINE config 1: 2-layer fp32 model, bigram+trigram tables, k = 3, 10 tokens, alpha 0.5."""
+@pytest.mark.parametrize("dense", [True, False])
+def test_tiny_config_as_specified(tiny, forward_path, dense):
+    """2-layer fp32 model of the smallest workload, bigram+trigram tables, k = 3, 10 tokens, alpha 0.5; its prefix as a chunk and token by
+    token through the forward."""
     shape, w, tabs, prefix = tiny
     lam = (0.01, 0.04, 0.0, 0.0, 0.0)
-    _, recs, stats = run_teacher_forced(shape, w, tabs, lam, prefix, 3, 0.5, 10, path=forward_path)
+    _, recs, stats = run_teacher_forced(shape, w, tabs, lam, prefix, 3, 0.5, 10, path=forward_path, dense=dense)
     assert sum(s.get("vocab_decisive", False) for s in stats) >= 8
 
 
@@ -115,11 +119,12 @@ def test_bf16_small_model_gqa(forward_path):
     assert_hit_paths_compared(stats, need_penalty=False)   # vocabulary of 2048: every draft finds some overlap
 
 
-def test_long_prefix_crosses_attention_chunks(forward_path):
+@pytest.mark.parametrize("dense", [True, False])
+def test_long_prefix_crosses_attention_chunks(forward_path, dense):
     shape = synth.ModelShape("small-fp32", 2, 256, 4, 2, 512, 1024, "fp32")
     w = synth.make_weights(shape, seed=6)
     prefix = synth.make_prefix_uniform(shape.vocab, 300, seed=6)
-    run_teacher_forced(shape, w, None, synth.PAPER_LAMBDAS, prefix, 3, 0.0, 4, max_ctx=600, path=forward_path)
+    run_teacher_forced(shape, w, None, synth.PAPER_LAMBDAS, prefix, 3, 0.0, 4, max_ctx=600, path=forward_path, dense=dense)
 
 
 def test_many_attention_items(forward_path):
@@ -347,25 +352,28 @@ def test_last_query_goes_with_the_others_up_to_a_size():
 
 
 FP32_CHUNKS = [synth.ModelShape("fp32-256", 2, 256, 4, 4, 1024, 512, "fp32"), synth.ModelShape("fp32-gqa", 3, 512, 8, 2, 1008, 512, "fp32"),
-               synth.ModelShape("fp32-128", 1, 384, 3, 1, 464, 512, "fp32"), synth.ModelShape("fp32-heads-of-16", 2, 336, 21, 7, 1008, 512, "fp32"),
-               synth.ModelShape("fp32-one-head-64", 2, 64, 1, 1, 208, 512, "fp32"), synth.ModelShape("fp32-one-head-128", 2, 128, 1, 1, 464, 512, "fp32")]
+               synth.ModelShape("fp32-128", 1, 384, 3, 1, 464, 512, "fp32"), synth.ModelShape("fp32-one-head-64", 2, 64, 1, 1, 208, 512, "fp32"),
+               synth.ModelShape("fp32-one-head-128", 2, 128, 1, 1, 464, 512, "fp32")]
 
 
 @pytest.mark.parametrize("shape", FP32_CHUNKS, ids=lambda s: s.name)
 @pytest.mark.parametrize("m", [2, 3, 5, 9, 15, 16, 17, 32, 33, 64, 100, 1025])
 def test_fp32_prefix_pass_matches_the_token_by_token_pass(shape, m):
     """An fp32 model's prefix as chunks (one and two pieces of 16 tokens, ragged; 1025: a token in a chunk of its own; gate and up ragged
-    against a batch of pieces; one head: its rotary table is the larger part of what the pass sets up; heads of 16 have no such pass): logits as token by token, and those of a timestep on top of the
-    cache.  Either pass is 2 .. 7e-7 from 64 bits: 5e-6 of the largest logit leaves room for both."""
+    against a batch of pieces; one head: its rotary table is the larger part of what the pass sets up): logits as token by token, and those
+    of a timestep on top of the cache.  Either pass is 2 .. 7e-7 from 64 bits, which the oracle's sums are for up to 33 tokens here: 2e-6
+    of the largest logit leaves room for one, 5e-6 for both."""
     w = synth.make_weights(shape, seed=m)
     prefix = synth.make_prefix_uniform(shape.vocab, m, seed=m)
     sess = session(shape, w, max_ctx=m + 4)
     got = []
     try:
-        for token_by_token in (False, True):
-            if token_by_token:
-                sess.spd_set_dense_prefill(False)
+        for chunks in (True, False):
+            sess.spd_set_dense_prefill(chunks)
+            sess.spd_set_kernel_timing(True)
             sess.spd_prefill(prefix)
+            assert sess.spd_get_dense_prefill() == chunks and sess.spd_get_kernel_timing()["fused_forward"][1] == (0 if chunks else m)
+            sess.spd_set_kernel_timing(False)
             got.append([sess.spd_read_logits()])
             sess.spd_step(P().SpdDecodeCfg(2, 0.0, 1.0, 0.1))
             sess.spd_set_state(np.resize(prefix, (2, 5)).astype(np.int32), np.array([-1.0, -2.0], np.float32))
@@ -375,6 +383,11 @@ def test_fp32_prefix_pass_matches_the_token_by_token_pass(shape, m):
         sess.close()
     for x, y in zip(*got):
         assert np.max(np.abs(x - y)) <= 5e-6 * np.max(np.abs(y))
+    if m <= 33:
+        lm = make_oracle(shape, w, np.float64)
+        want = lm.forward(lm.embedding_rows(prefix))
+        for x, _ in got:
+            assert np.max(np.abs(x - want)) <= 2e-6 * np.max(np.abs(want))
 
 
 @pytest.mark.parametrize("layers,d,heads,ffn,fused,chunk", [
@@ -641,7 +654,7 @@ def test_fp16_cache_graph_replay_is_bit_exact_across_the_switch_of_reading_width
         sess.close()
 
 
-@pytest.mark.parametrize("shape", [FP32_CHUNKS[3], synth.ModelShape("bf16-320", 1, 320, 5, 5, 640, 512, "bf16")], ids=lambda s: s.name)
+@pytest.mark.parametrize("shape", [synth.ModelShape("fp32-heads-of-16", 2, 336, 21, 7, 1008, 512, "fp32"), synth.ModelShape("bf16-320", 1, 320, 5, 5, 640, 512, "bf16")], ids=lambda s: s.name)
 def test_dense_prefix_pass_is_refused_where_it_does_not_exist(shape):
     sess = session(shape, synth.make_weights(shape, seed=1))
     try:
@@ -713,7 +726,7 @@ def test_dense_prefix_pass_is_switched_off_and_on_again(dtype):
 
 
 def test_fused_and_per_operator_forward_agree(tiny):
-    """Same inputs through both forward paths: logits agree to fp32 rounding, drafts are equal."""
+    """Same inputs through both forward paths, from the prefix on: logits agree to fp32 rounding."""
     shape, w, tabs, prefix = tiny
     pkg = P()
     out = {}
@@ -721,6 +734,7 @@ def test_fused_and_per_operator_forward_agree(tiny):
         sess = session(shape, w)
         try:
             select_path(sess, path)
+            sess.spd_set_dense_prefill(False)
             sess.spd_prefill(prefix)
             logits = sess.spd_read_logits()
             drafts, scores = sess.spd_generate(prefix, pkg.SpdDecodeCfg(3, 0.0, 1.0, 0.1), 6)
@@ -753,13 +767,15 @@ def test_per_operator_attention_where_the_merge_begins(max_ctx):
         sess.close()
 
 
-def test_generate_free_running_matches_until_first_undecided_step(tiny):
+@pytest.mark.parametrize("dense", [True, False])
+def test_generate_free_running_matches_until_first_undecided_step(tiny, dense):
     shape, w, tabs, prefix = tiny
     pkg = P()
     lam = (0.01, 0.04, 0.0, 0.0, 0.0)
     planted = planted_tables(shape, w, tabs, prefix, 3, 10)
     sess = session(shape, w)
     try:
+        sess.spd_set_dense_prefill(dense)
         sess.spd_load_ngrams(planted, lam)
         dc = pkg.SpdDecodeCfg(3, 0.5, 1.0, 0.1)
         drafts, scores = sess.spd_generate(prefix, dc, 10)
