@@ -493,7 +493,7 @@ def test_prefix_products_that_start_inside_their_k_range(m):
     block (less than an eighth's worth, ragged eighths, a last split shorter than the others); bound as above."""
     shape = synth.ModelShape("rotated-bf16", 2, 4096, 32, 4, 4096, 512, "bf16")
     w = synth.make_weights(shape, seed=3)
-    sess = session(shape, w, max_ctx=m + 8)
+    sess, seen = session(shape, w, max_ctx=m + 8), set()
     prefix = synth.make_prefix_zipf(shape.vocab, m, seed=m)
     try:
         sess.spd_set_dense_prefill(False)
@@ -503,14 +503,18 @@ def test_prefix_products_that_start_inside_their_k_range(m):
         for product in (QKV, ATTN_OUT, GATE_UP, DOWN):
             for tile, size in enumerate(PREFIX_TILES):
                 for splits in (1, 3, 6, 7, 11, 16):
-                    if size[0] > 64 or sess.spd_test_force_prefill_cut(product, tile, splits, m)[:3] != (*size, splits):
+                    if size[0] > 64 or size[0] < m or sess.spd_test_force_prefill_cut(product, tile, splits, m)[:3] != (*size, splits):
                         continue
+                    seen.add((product, size, splits))
                     sess.spd_prefill(prefix)
                     err = np.max(np.abs(sess.spd_read_logits() - want)) / np.max(np.abs(want))
                     assert err <= 1e-4, f"product {product}, tile {size}, {splits} blocks per k range: {err:.2e}"
             sess.spd_test_force_prefill_cut(product, -1, 0, m)
     finally:
         sess.close()
+    # (61 tokens' partial sums of QKV in 16 splits have no room)
+    assert seen == {(p, t, n) for p in (QKV, ATTN_OUT, GATE_UP, DOWN) for t in PREFIX_TILES for n in (1, 3, 6, 7, 11, 16)
+                    if m <= t[0] <= 64 and not (m == 61 and p == QKV and n == 16)}
 
 
 @pytest.mark.timeout(600)
