@@ -128,8 +128,10 @@ def cpu_baseline(shape, weights, tables, lambdas, prefix, k, alpha, tau, delta):
 
 def probe_sweep(pkg, shape, weights, tables, lambdas, prefix, tau, delta, args):
     """Cost of the n-gram stage against the number of orders interpolated (the storage-saving
-    variant keeps n = 2..4 only) and against k: average duration of the expand_prune kernel
-    (k^2 options x orders probes of the hash tables, interpolation, prune) and of the whole step."""
+    variant keeps n = 2..4 only) and against k: average duration of a timestep's decisions (selection
+    from the logits' slices, k^2 options x orders probes of the hash tables, interpolation, prune: one launch
+    or two, by k and tables, so only their sum compares across rows), of the expand_prune launch, which
+    selects too where it is the only one, and of the whole step."""
     import torch
     n_steps = min(args.steps, 24)
     sess = pkg.Session(shape, weights, max_ctx=len(prefix) + args.warmup + n_steps + 4, k_max=16, kv_dtype=args.kv_dtype)
@@ -159,9 +161,10 @@ def probe_sweep(pkg, shape, weights, tables, lambdas, prefix, tau, delta, args):
                 sess.spd_step(dc, fetch=False)
             timing = sess.spd_get_kernel_timing()
             sess.spd_set_kernel_timing(False)
-            ms, n = timing["expand_prune"]
+            us = {name: timing[name][0] * 1e3 / n_steps for name in ("topk_partial", "expand_prune")}
             rows.append({"orders": list(orders) if orders else [], "entries": sum(len(tables[n][1]) for n in (orders or ())),
-                         "alpha": alpha, "k": k, "expand_prune_us": ms * 1e3 / n, "ms_per_step": step_ms})
+                         "alpha": alpha, "k": k, "launches": 2 if timing["topk_partial"][1] else 1, "decisions_us": sum(us.values()),
+                         "expand_prune_us": us["expand_prune"], "ms_per_step": step_ms})
     sess.close()
     print(json.dumps({"probe_sweep": rows, "workload": shape.name, "prefix": len(prefix), "steps": n_steps}))
 
@@ -236,7 +239,7 @@ def main():
     ap.add_argument("--copy-calibration", action="store_true",
                     help="also run one plain 1 GiB device-to-device copy (a known traffic for scaling HBM counters)")
     ap.add_argument("--probe-sweep", action="store_true",
-                    help="instead of the benchmark: time the n-gram stage (expand_prune kernel) against the "
+                    help="instead of the benchmark: time the n-gram stage (a timestep's decisions) against the "
                          "orders loaded (none, 2..3, 2..4, 2..6) and k = 1, 3, 5, 10; prints one JSON line")
     ap.add_argument("--phase-clocks", action="store_true",
                     help="instead of the benchmark: per-phase clock stamps of the fused forward kernel (a table)")

@@ -263,7 +263,9 @@ int spd_get_dense_prefill(const spd_ctx *ctx, int32_t *out_enabled);
 /* Per-kernel timing for profiling runs: when enabled, spd_step launches kernels one by one
  * with a HIP event pair around each and accumulates the elapsed time per kernel class.
  * spd_get_kernel_timing fills HOST arrays of up to `cap` entries (class name pointers valid
- * for the ctx lifetime, total milliseconds, launch counts), sets *out_n, and synchronises. */
+ * for the ctx lifetime, total milliseconds, launch counts), sets *out_n, and synchronises.  "expand_prune" includes the
+ * selection from the logits' slices where one launch does both ("topk_partial" then has none); a dense prefix pass is not
+ * timed. */
 int spd_set_kernel_timing(spd_ctx *ctx, int32_t enable);
 int spd_get_kernel_timing(spd_ctx *ctx, int32_t cap, const char **out_names, float *out_ms,
                           int64_t *out_launches, int32_t *out_n);
