@@ -798,8 +798,8 @@ __global__ __launch_bounds__(256, F32 ? 1 : 2) void prefill_attn_mfma_kernel(con
 // registers 8 j .. 8 j + 7 of S^T.  A wave brings its 32-key tiles of K and of V into LDS of its own (16-byte pieces of a
 // key's row permuted by the row, as in the GEMM), each tile as soon as the one before has been read: no barrier, and the
 // waits are counted by hand.  What bounds it now is the vector unit (16 exponentials and 32 splits per lane and tile).
-// us per chunk and layer, heads of 128, the fp32 products -> this: 1024 tokens of 32 heads 143 -> 51, 512 of 64 (8 cached) 98 -> 45,
-// 64 of 32 16 -> 8.6.
+// us per chunk and layer, heads of 128, the fp32 products -> this, in one placement: 1024 tokens of 32 heads 143 -> 51, 512 of 64 (8 cached) 98 -> 45,
+// 64 of 32 16 -> 8.6; with the present one 44, 30 and 8.0 (the fp32 products 105, 63).
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 constexpr float P_SCALE = 16384.f;
 
@@ -1022,7 +1022,8 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_f16_kernel(const PrefillA
 // RMSNorm has no pass of its own: x * gain is what is multiplied, the sum of squares comes along (a block reads its tokens' rows
 // from end to end), and the results are scaled.
 // Bound by latency: 16 tokens of two layers of 256 wide, 13 launches, 812 us token by token -> 74 with the logits; 1030 tokens 55 700 -> 271,
-// of two layers of 2048 wide 97 000 -> 2700.
+// of two layers of 2048 wide 97 000 -> 2700.  Few tokens, 768 .. 2048 wide: the 48 .. 128 blocks of a product fetch its rows in
+// pieces of 64 bytes, 2 TB/s where the matrix-vector kernels reach 4.5, so two tokens may go one by one.
 enum { PE_RESID = 3 };
 struct Prefill32Args : PrefillGemmArgs {
     const float *x;              // [T, K]
@@ -1193,7 +1194,8 @@ size_t prefill_attn_lds(int d_head) { return (size_t)(AQ * (d_head + 4) + AK * (
 // The tile shapes: one block per compute unit, k steps of 64.  Gate and up, the widest product, leaves the chip idlest where its tiles do
 // not come out even (7B widths: 86 tiles of 256 columns; three rounds at 1024 tokens where 2.7 would do), and has shapes of its own:
 // its time over 41 lengths from 8 to 1024 and four widths 0.91 in the geometric mean, 0.61 at best (7B, 384 tokens: 175 -> 107 us), the four
-// products' of a layer 0.96.  What a step takes a block: `step_us` when all compute units
+// products' of a layer 0.96.  The other products were not measured with them; entry 11 is entry 4 with its waves the other way round, which
+// gate and up needs for its halves, and of the two the faster per step.  What a step takes a block: `step_us` when all compute units
 // have one, `alone_us` when few do (fitted to the sweep below; at 128 tokens the products bound it, at 32 the loads).
 constexpr int KS = 64;
 struct Tile { int bm, bn, stages, waves; double step_us, alone_us; };
@@ -1343,11 +1345,10 @@ bool prefill_own_query(const PrefillChunk &c, int T) {
 
 // One chunk of T prefix tokens at positions p0 .. p0 + T - 1 through the whole stack.  Only the prefix's last token goes
 // on into the final norm and the LM head, and nothing reads what the last layer makes of the others but their keys and values.
-// So that layer's big product has the key and value rows only, and its query, attention, output projection and feed-forward
-// run for that one token, through the timestep's own operators (fp32 activations); a chunk that is not the prefix's last ends
-// with the keys and values.  (With few tokens the query rows stay in the big product: LAST_QUERY_WITH.)  Bound of that tail: the layer's weights at HBM's rate, whatever T is.  us for a whole
-// pass, all tokens -> this: four layers of the 7B widths, 1024 tokens 3292 -> 2705, 64 tokens 658 -> 626; three of the 13B, 256
-// tokens 1277 -> 1063.
+// So that layer's big product has the key and value rows only (with few tokens the query rows too: LAST_QUERY_WITH), and the rest
+// of it runs for that one token, through the timestep's own operators (fp32 activations); a chunk that is not the prefix's last ends
+// with the keys and values.  Bound of that tail: the layer's weights at HBM's rate, whatever T is.  us for a whole pass, all tokens
+// -> this: four layers of the 7B widths, 1024 tokens 3292 -> 2705, 64 tokens 658 -> 626; three of the 13B, 256 tokens 1277 -> 1063.
 // On return (stream order) the caches are extended and, after the final chunk, c.h holds the last token's residual stream after
 // the last layer in row T - 1; the caller finishes that token (final norm + LM head).
 hipError_t prefill_chunk(hipStream_t s, const PrefillChunk &c) {
