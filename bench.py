@@ -364,7 +364,7 @@ def main():
     greedy_ms = (time.perf_counter() - t1) * 1e3 / K
 
     # the paper's own comparison (Section 4.3): k independent passes of nucleus sampling, here
-    # top-p 0.9 (BASELINE config 3), each step = the same forward + the sampler; seeded draws
+    # top-p 0.9, each step = the same forward + the sampler; seeded draws
     sc = pkg.SpdSampleCfg(0.9, tau)
     us = np.random.default_rng(0).random(max(W + K + 1, 8)).astype(np.float32)
     sess.spd_prefill(prefix)

@@ -56,7 +56,7 @@ def tiny():
 
 @pytest.mark.parametrize("top_p,tau", [(0.9, 1.0), (0.5, 0.7), (1.0, 1.3)])
 def test_pass_teacher_forced(tiny, top_p, tau):
-    """BASELINE config 3's comparison decoder on the tiny model: 12 tokens, seeded draws; after
+    """The benchmark's comparison decoder on the tiny model: 12 tokens, seeded draws; after
     every token the oracle's token is written back so each step is compared on its own."""
     shape, w, prefix = tiny
     pkg = P()

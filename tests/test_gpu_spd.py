@@ -138,9 +138,8 @@ def test_many_attention_items(forward_path):
 
 
 def test_vocabulary_of_140k_tokens(forward_path):
-    """A vocabulary larger than 128 slices of 1024 entries: the per-slice top-k kernel then has
-    more entries per slice than its threads keep in registers and walks the rest from memory;
-    k = 5 of 140000."""
+    """A vocabulary larger than 128 slices of 1024 entries: more than four entries per thread of a slice, and the slices in a launch of
+    their own; k = 5 of 140000."""
     shape = synth.ModelShape("vocab140k-fp32", 1, 128, 2, 2, 256, 140000, "fp32")
     w = synth.make_weights(shape, seed=14)
     prefix = synth.make_prefix_uniform(shape.vocab, 7, seed=14)
@@ -239,7 +238,7 @@ def test_7b_shape_two_layers_context_of_two_load_batches(forward_path):
 
 @pytest.mark.timeout(600)
 def test_7b_shape_two_layers_config3_context(forward_path):
-    """BASELINE config 3's context and largest k at the 7B widths, two layers: a 1030-token
+    """The benchmark's longest context and largest k at the 7B widths, two layers: a 1030-token
     prefix (dense prefix pass over a chunk boundary of its token arena), attention cut into
     chunks that are merged across blocks, k = 8."""
     _layer_truncated(synth.LLAMA7B, 2, 1030, 8, 3, 7, forward_path)
@@ -247,14 +246,14 @@ def test_7b_shape_two_layers_config3_context(forward_path):
 
 @pytest.mark.timeout(600)
 def test_13b_shape_two_layers(forward_path):
-    """BASELINE config 4's widths (d_model 5120, 40 heads, FFN 13824: rows of 1.25 and 3.375
+    """The 13B widths (d_model 5120, 40 heads, FFN 13824: rows of 1.25 and 3.375
     block passes), k = 5, two of its 40 layers."""
     _layer_truncated(synth.LLAMA13B, 2, 140, 5, 4, 13, forward_path)
 
 
 @pytest.mark.timeout(600)
 def test_70b_shape_one_layer(forward_path):
-    """BASELINE config 5's widths (d_model 8192, 64 query heads on 8 key/value heads, FFN
+    """The 70B widths (d_model 8192, 64 query heads on 8 key/value heads, FFN
     28672), k = 3, one of its 80 layers; the prefix crosses an attention chunk."""
     _layer_truncated(synth.LLAMA70B, 1, 131, 3, 3, 70, forward_path)
 
@@ -545,7 +544,7 @@ def test_fp16_cache_small_model_gqa(forward_path):
 @pytest.mark.parametrize("prefix_len,k", [(40, 3), (200, 3), (300, 5), (1030, 8)])
 def test_fp16_cache_7b_shape_two_layers(forward_path, prefix_len, k):
     """Llama-2-7B widths, two layers, fp16 cache: a short context, one attention item per head in
-    two batches of loads (200), chunks merged across blocks (300, and BASELINE config 3's 1030
+    two batches of loads (200), chunks merged across blocks (300, and the benchmark's 1030
     with k = 8, whose prefix also crosses a chunk of the dense prefix pass)."""
     stats = _layer_truncated(synth.LLAMA7B, 2, prefix_len, k, 3, 8, forward_path, kv_dtype="fp16")
     assert max(s["logit_err"] for s in stats if "logit_err" in s) < FP16_CACHE_LOGIT_ERR
@@ -998,7 +997,7 @@ def test_error_paths(tiny):
 @pytest.mark.timeout(900)
 @pytest.mark.parametrize("kv_dtype", ["fp16", "fp32"])
 def test_full_size_7b_shape_teacher_forced(kv_dtype):
-    """BASELINE config 2 at its real size and in the launch configuration the benchmark times
+    """The headline workload at its real size and in the launch configuration the benchmark times
     (fused forward, graph replay, fp16 cache; and with the fp32 cache): Llama-2-7B shape, bf16,
     64-token Zipf prefix, k = 3, alpha = 0.54, synthetic n = 2..6 tables.  The oracle runs the
     full model on the host (a few seconds per step), so three timesteps are compared,
