@@ -223,7 +223,9 @@ struct QkvRows {
 // 0.96 at 160 .. 384, 0.92 at 1024.
 // Tried: four waves of 64 x 128 (20 % slower: one wave per SIMD), steps of 32 k (64 bytes of a row: half of every cache line
 // fetched twice, 2.5 instead of 4.8 TB/s), a second barrier that frees a buffer earlier, wave priorities, touching the lines of
-// coming steps so that they are in the L2 (0 .. 5 % slower), waves that load x only or W only (-9 .. +13 %).
+// coming steps so that they are in the L2 (0 .. 5 % slower), waves that load x only or W only (-9 .. +13 %), four waves of 64 x 192 with the
+// order below (8 .. 22 % slower), W from memory straight into the registers of the one wave that multiplies it, x alone through LDS (two to six
+// steps ahead; 1.00 .. 1.08 times the time from 256 tokens on, 1.1 .. 1.2 at 64).
 // Where a block starts within its k range (`turn`): rows whose length is a power of two lie 8 KB or 16 KB apart, and blocks that all
 // walk them from the same end keep hitting the same memory channels: 4.9 and 4.5 TB/s for a stream of 128-byte pieces, 7.0
 // from rows of 10 or 22 KB.  Blocks of different XCDs, and neighbours on one, therefore start an eighth of the range apart and wrap
@@ -281,14 +283,11 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN >= 4 ? WM * WN / 4 : 1) void 
         off[i] = ((uint32_t)min(row, rows - 1) * (uint32_t)a.K + (uint32_t)s0 * KS) * 2u + 16u * (uint32_t)((lane % (WAVE / RPL)) ^ swz(q + r));
     }
     const int turn = a.rotate ? (xcd + 3 * (slot / a.t_tiles)) % 8 * n_steps / 8 : 0;
-    auto fetch = [&](int step) {
+    auto load = [&](int step, int i) {
         char *to = stages + (step % ST) * STAGE;
         const int s = step + turn < n_steps ? step + turn : step + turn - n_steps;
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            if (STREAM_W && RPL * NWV * i >= 2 * BM) load16_to_lds<2>(rsrc[i], to + (w + NWV * i) * 1024, off[i], s * ROWB);
-            else load16_to_lds<0>(rsrc[i], to + (w + NWV * i) * 1024, off[i], s * ROWB);
-        }
+        if (STREAM_W && RPL * NWV * i >= 2 * BM) load16_to_lds<2>(rsrc[i], to + (w + NWV * i) * 1024, off[i], s * ROWB);
+        else load16_to_lds<0>(rsrc[i], to + (w + NWV * i) * 1024, off[i], s * ROWB);
     };
 
     // Operands of half a step in registers, 16 rows of 32 k per piece of work: lane -> row l % 16, k 8 (l / 16) ..  The weights
@@ -302,51 +301,67 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN >= 4 ? WM * WN / 4 : 1) void 
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt) acc[nt][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    auto read = [&](Half &f, int s, int half) {
-        const char *from = stages + (s % ST) * STAGE;
-        auto piece = [&](int row) { return __builtin_bit_cast(bf16x8, *(const u32x4 *)(from + row * ROWB + 16 * ((4 * half + lane / 16) ^ swz(row)))); };
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) f.w[nt] = piece(w_row(nt));
-#pragma unroll
-        for (int tt = 0; tt < TT; ++tt) { f.hi[tt] = piece(x_row + 16 * tt); f.lo[tt] = piece(BM + x_row + 16 * tt); }
+    // The order is written out, an instruction of the memory pipes between every few products (`sched_barrier`): left to itself the
+    // compiler sinks a half's reads to the end of the products they should run beside, and every half begins with a wait for all of
+    // them.  us, so -> written out: 1024 tokens, 12288 x 4096 169 -> 163, gate and up 306 -> 295, 4096 x 4096 70 -> 66; 256 tokens,
+    // 15360 x 5120 131 -> 125 (128 x 256); whole passes 1.01 (64 and 256 tokens) .. 1.03 times as fast (1024).  What is left is power: the same
+    // launch on zeros takes 115 us instead of 163, without its loads 139, without its reads 135, its products alone 107.
+    auto half_of = [&](int s, int half) { return (uint32_t)((s % ST) * STAGE + 16 * ((4 * half + lane / 16) ^ swz(lane % 16))); };   // (16 rows on: the same permutation)
+    constexpr int READS = NT + 2 * TT, PRODUCTS = 2 * NT * TT;
+    auto read = [&](Half &f, uint32_t at, int i) {         // in the order of use
+        auto piece = [&](int row) { return __builtin_bit_cast(bf16x8, *(const u32x4 *)(stages + at + row * ROWB)); };
+        if (i == 0) f.hi[0] = piece(x_row);
+        else if (i <= NT) f.w[i - 1] = piece(w_row(i - 1));
+        else if (i < NT + TT) f.hi[i - NT] = piece(x_row + 16 * (i - NT));
+        else f.lo[i - NT - TT] = piece(BM + x_row + 16 * (i - NT - TT));
     };
-    auto multiply = [&](const Half &f) {
+    auto product = [&](const Half &f, int i) {
+        const int tt = i / NT % TT, nt = i % NT;
+        acc[nt][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.w[nt], i < NT * TT ? f.hi[tt] : f.lo[tt], acc[nt][tt], 0, 0, 0);
+    };
+    // the products of one half, the reads of the next and (behind the barrier) the loads of a coming step beside them
+    auto work = [&](const Half &f, Half &g, uint32_t at, bool reads, bool loads, int step) {
+        int r = 0, l = 0;
 #pragma unroll
-        for (int tt = 0; tt < TT; ++tt)
+        for (int i = 0; i < PRODUCTS; ++i) {
+            constexpr int UNTIL = PRODUCTS * 3 / 4;
+            if (reads && i < UNTIL) {
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) acc[nt][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.w[nt], f.hi[tt], acc[nt][tt], 0, 0, 0);
+                for (; r < ((i + 1) * READS + UNTIL - 1) / UNTIL; ++r) read(g, at, r);
+            }
+            if (loads && i < UNTIL) {
 #pragma unroll
-        for (int tt = 0; tt < TT; ++tt)
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) acc[nt][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.w[nt], f.lo[tt], acc[nt][tt], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
+                for (; l < ((i + 1) * PER + UNTIL - 1) / UNTIL; ++l) load(step, l);
+            }
+            product(f, i);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     };
     // The compiler does not count loads into LDS: the waits are written out.  One barrier per step, in its middle: before it every
     // wave has its own loads of step s + 1 in LDS (all but the (ST - 2) PER youngest have arrived: loads arrive in order) and
     // its last reads of step s behind it, so behind it step s + 1 may be read and the buffer of step s filled again.
     Half f0, f1;
-    for (int s = 0; s < ST && s < n_steps; ++s) fetch(s);
+    for (int s = 0; s < ST && s < n_steps; ++s) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) load(s, i);
+    }
     if (n_steps >= ST) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((ST - 1) * PER) : "memory");
     else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    read(f0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < READS; ++i) read(f0, half_of(0, 0), i);
     int s = 0;
     for (; s + ST < n_steps; ++s) {
-        read(f1, s, 1);
-        multiply(f0);
+        work(f0, f1, half_of(s, 1), true, false, 0);
         asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((ST - 2) * PER) : "memory");
-        fetch(s + ST);
-        read(f0, s + 1, 0);
-        multiply(f1);
+        work(f1, f0, half_of(s + 1, 0), true, true, s + ST);
     }
-    for (; s < n_steps; ++s) {
-        read(f1, s, 1);
-        multiply(f0);
-        if (s + 1 < n_steps) {
-            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-            read(f0, s + 1, 0);
-        }
-        multiply(f1);
+    for (; s + 1 < n_steps; ++s) {
+        work(f0, f1, half_of(s, 1), true, false, 0);
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        work(f1, f0, half_of(s + 1, 0), true, false, 0);
     }
+    work(f0, f1, half_of(s, 1), true, false, 0);
+    work(f1, f0, 0, false, false, 0);
 
     // lane -> token l % 16 of a piece, register r -> column 4 (l / 16) + r
 #pragma unroll
