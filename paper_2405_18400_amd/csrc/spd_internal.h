@@ -258,6 +258,7 @@ constexpr int ATTN_CHUNK_MAX = 512;
 
 // p[0 .. n) = v
 struct FillRange { int32_t *p; int32_t v, n; };
+struct DraftArgs { int32_t k, tails[SPD_K_MAX][SPD_TAIL]; float logscore[SPD_K_MAX]; };
 
 namespace spdk {
 hipError_t gemv(hipStream_t s, int dtype, int epi, const GemvArgs &a, int num_cu);
@@ -279,7 +280,7 @@ hipError_t prefill_attention(hipStream_t s, int kv_half, const float *q, const v
                              int T, int p0, int n_heads, int n_kv_heads, int dh, int cap_ctx, float *out32 = nullptr);
 int prefill_tile(int tile, int &tokens, int &columns);    // returns how many tile shapes there are
 hipError_t advance(hipStream_t s, DevState *st);
-hipError_t renorm(hipStream_t s, DevState *st, int k);
+hipError_t set_drafts(hipStream_t s, DevState *st, const DraftArgs &a);
 hipError_t fill_i32(hipStream_t s, int32_t *p, int32_t v, int n);
 hipError_t fill3_i32(hipStream_t s, const FillRange &a, const FillRange &b, const FillRange &c);   // one launch
 // Fused forward: 0 if no instantiation serves this shape, else resident blocks per CU.

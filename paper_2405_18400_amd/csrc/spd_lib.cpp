@@ -883,17 +883,13 @@ int spd_set_state(spd_ctx *c, int32_t k, const int32_t *tails, const float *sc) 
         for (int q = 0; q < SPD_TAIL; ++q)
             if (tails[i * SPD_TAIL + q] >= c->cfg.vocab) return fail(c, SPD_EINVAL, "tail token id >= vocab");
     }
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-    DevState *hs = (DevState *)c->pinned;
-    std::memset(hs, 0, sizeof(DevState));
+    DraftArgs d{};
+    d.k = k;
     for (int i = 0; i < k; ++i) {
-        std::memcpy(hs->tails[i], tails + i * SPD_TAIL, SPD_TAIL * 4);
-        hs->logscore[i] = sc[i];
+        std::memcpy(d.tails[i], tails + i * SPD_TAIL, SPD_TAIL * 4);
+        d.logscore[i] = sc[i];
     }
-    DevState *d = c->st();
-    HIPCHK(c, hipMemcpyAsync(d->tails, hs->tails, sizeof(hs->tails), hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, hipMemcpyAsync(d->logscore, hs->logscore, sizeof(hs->logscore), hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, spdk::renorm(c->stream, d, k));
+    HIPCHK(c, spdk::set_drafts(c->stream, c->st(), d));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     return SPD_OK;
 }
