@@ -292,7 +292,7 @@ def main():
         for _ in range(n_steps):
             sess.spd_step(dc, fetch=False)
 
-    # prefill + first timestep + warm-up (captures the step graph), untimed
+    # prefill + first timestep + warm-up (captures the step graph where there is one), untimed
     sess.spd_prefill(prefix)
     sess.spd_step(dc, fetch=False)
     run(W)
@@ -442,7 +442,7 @@ def main():
                                f"alpha={alpha}, tau={tau}, delta={delta}, n-gram tables n=2..6 with "
                                f"{sum(len(v[1]) for v in tables.values())} entries; {K} consecutive timesteps "
                                f"(context {m + 1 + W}..{m + W + K})",
-                   "k": k, "prefix": m, "graph": not args.no_graph, "fused_forward": sess.spd_get_fused(),
+                   "k": k, "prefix": m, "graph": not args.no_graph and not sess.spd_get_fused(), "fused_forward": sess.spd_get_fused(),
                    "kv_cache": args.kv_dtype},
         "pct_peak_hbm": 100.0 * step_gbs / HBM_PEAK_GBS,
         "gpu_ms_per_step_events": gpu_ms / K,

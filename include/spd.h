@@ -234,7 +234,8 @@ int spd_get_nucleus_info(spd_ctx *ctx, int32_t *out_size, float *out_mass, float
 /* Current position (= number of cached positions) as tracked by the host. */
 int spd_position(const spd_ctx *ctx, int32_t *out_pos);
 
-/* Turn the captured-graph replay of spd_step on (default) or off (plain launches). */
+/* Turn the captured-graph replay of spd_step on (default) or off (plain launches).  It applies to the forward of one kernel per
+ * matrix-vector product; a timestep of the persistent forward is two or three launches, which are made plainly either way. */
 int spd_set_graph(spd_ctx *ctx, int32_t enable);
 
 /* The transformer forward of a timestep runs either as one persistent kernel ("fused": the

@@ -1,5 +1,5 @@
 // libspd host side: context, workspace carving, launch sequencing, HIP-graph replay of the
-// timestep, and the C ABI declared in spd.h.  No device memory is allocated here.
+// per-operator timestep, and the C ABI declared in spd.h.  No device memory is allocated here.
 #include "spd_internal.h"
 
 #include <cmath>
@@ -382,7 +382,13 @@ int chunk32_min(const spd_ctx *c) {
     return m.n_layers > 3 && slow ? 3 : 2;
 }
 
-bool graphs_usable(const spd_ctx *c) { return c->use_graph && !c->timing && c->stream != nullptr; }
+// A graph is for the forward of one kernel per product (a dozen launches and more).  With the persistent forward a timestep is two or
+// three launches, a prefix token two, and the graph's own start costs more than they do.  us per timestep, graph -> plain launches, enqueued
+// one behind the other | with results fetched: tiny fp32 model 64.1 -> 59.0 | 78.1 -> 72.2, four layers of the 1B widths 183.9 -> 179.2 |
+// 198.4 -> 191.7, 7B 2234 -> 2224 | 2246 -> 2238; the host's share 15 -> 8, and the first timestep captures nothing.  One kernel per
+// product: 54.4 -> 50.4, 168.5 -> 165.2, 2730 -> 2725, but the host's share 15 -> 36, 28 -> 59, 72 -> 478 (16 layers of the 1B widths,
+// 551 -> 556 in all): the graph stays.
+bool graphs_usable(const spd_ctx *c) { return c->use_graph && !c->timing && c->stream != nullptr && !(c->use_fused && c->fused_blocks > 0); }
 
 }  // namespace
 

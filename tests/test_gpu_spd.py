@@ -811,6 +811,31 @@ def test_generate_free_running_matches_until_first_undecided_step(tiny, dense):
         sess.close()
 
 
+def test_graph_replay_of_the_per_operator_forward_equals_plain_launches(tiny):
+    """The graphs (timestep, nucleus timestep, prefix token) are the per-operator forward's: replayed several times, with a new prefix and
+    the program's own calls between, and each time the bits of plain launches; with the persistent forward the switch changes nothing."""
+    shape, w, tabs, prefix = tiny
+    pkg = P()
+    dc, sc = pkg.SpdDecodeCfg(3, 0.5, 1.0, 0.1), pkg.SpdSampleCfg(0.9, 1.0)
+    sess = session(shape, w)
+    try:
+        sess.spd_load_ngrams(tabs, (0.01, 0.04, 0.0, 0.0, 0.0))
+        sess.spd_set_dense_prefill(False)
+        for fused in (False, True):
+            sess.spd_set_fused(fused)
+            runs = []
+            for graph in (False, True, True, False, True):
+                sess.spd_set_graph(graph)
+                drafts, scores = sess.spd_generate(prefix, dc, 7)
+                logits = sess.spd_read_logits()
+                sess.spd_prefill(prefix[:9])
+                sampled = [sess.spd_nucleus_step(sc, u) for u in (0.2, 0.9, 0.4, 0.6)]
+                runs.append((drafts.tolist(), scores.tolist(), logits.tolist(), sampled))
+            assert all(r == runs[0] for r in runs)
+    finally:
+        sess.close()
+
+
 def test_k1_is_greedy_on_the_gpu(tiny):
     shape, w, _, prefix = tiny
     pkg = P()
