@@ -380,18 +380,22 @@ __global__ __launch_bounds__(BLOCK) void topk_partial_kernel(const TopkArgs a) {
 // counts is the number of trips (at a load factor of 0.7 some of a step's 60 .. 360 probes walk past four slots, few past
 // eight) and of cache lines a load instruction touches (with a probe per lane every one of its 16 loads touched 64
 // lines); 360 probes 6 .. 15 -> 5.5 us, with the table in order of home slots.
-// The slots are examined in probing order, so the result is that of a slot-by-slot walk; all lanes of a group get it.
+// The slots are examined in probing order, so the result is that of a slot-by-slot walk.  found(u, count) is called by the lane whose slot
+// holds probe u's key, if any does.  All waves of a block probe on one compute unit, so instructions count as much as trips do: the hitting
+// lane goes on by itself (no shuffles), an 8-lane mask is cut from half a ballot, the keys come from where they were hashed, and a group
+// takes only as many probes as its wave has.  Cycles for the counts of k = 5, 8, 10 and five orders: 13600, 14500, 16400 -> 3900, 7100, 11300.
 constexpr int PROBE_LANES = 8;
 // `home`: the key's home slot, NO_HOME: not wanted (its 64-bit multiplications are dear: one lane's work, not eight's).
 constexpr uint64_t NO_HOME = ~0ull;
-template <int N>
-__device__ __forceinline__ void ngram_probes(const NgramDev &ng, const int32_t (&key)[N][6], const uint64_t (&home)[N], unsigned long long (&count)[N]) {
-    const int lane = threadIdx.x & (WAVE - 1), j = lane % PROBE_LANES, first = lane - j;
+template <int N, typename F>
+__device__ __forceinline__ void ngram_probes(const NgramDev &ng, const int32_t (&key)[N][6], const uint64_t (&home)[N], F &&found) {
+    const int lane = threadIdx.x & (WAVE - 1), j = lane % PROBE_LANES, first = (lane - j) % 32;
+    auto group_of = [&](unsigned long long mask) { return ((lane < 32 ? (uint32_t)mask : (uint32_t)(mask >> 32)) >> first) & 0xFFu; };
+    const uint32_t before = (1u << j) - 1u;
     uint64_t at[N];
     bool open[N];
 #pragma unroll
     for (int u = 0; u < N; ++u) {
-        count[u] = 0ull;
         open[u] = home[u] != NO_HOME;
         at[u] = home[u] + (uint64_t)j;
         while (open[u] && at[u] >= ng.capacity) at[u] -= ng.capacity;
@@ -406,23 +410,19 @@ __device__ __forceinline__ void ngram_probes(const NgramDev &ng, const int32_t (
                 lo[u] = global_load16(sl);
                 hi[u] = global_load16((const char *)sl + 16);
             }
+        const bool past = p + j > ng.max_probe;
 #pragma unroll
         for (int u = 0; u < N; ++u) {
             bool hit = false, end = false;
-            uint32_t c0 = 0, c1 = 0;
             if (open[u]) {
-                const bool past = p + j > ng.max_probe;
+                const uint32_t differs = (lo[u].x ^ (uint32_t)key[u][0]) | (lo[u].y ^ (uint32_t)key[u][1]) | (lo[u].z ^ (uint32_t)key[u][2]) |
+                                         (lo[u].w ^ (uint32_t)key[u][3]) | (hi[u].x ^ (uint32_t)key[u][4]) | (hi[u].y ^ (uint32_t)key[u][5]);
                 end = past || (int32_t)lo[u].x == NG_EMPTY;
-                hit = !past && (int32_t)lo[u].x == key[u][0] && (int32_t)lo[u].y == key[u][1] && (int32_t)lo[u].z == key[u][2] &&
-                      (int32_t)lo[u].w == key[u][3] && (int32_t)hi[u].x == key[u][4] && (int32_t)hi[u].y == key[u][5];
-                c0 = hi[u].z; c1 = hi[u].w;
+                hit = !past && differs == 0u;
             }
-            const uint32_t hits = (uint32_t)(__ballot(hit) >> first) & 0xFFu, ends = (uint32_t)(__ballot(end) >> first) & 0xFFu;
-            const int at_hit = hits ? __ffs((int)hits) - 1 : PROBE_LANES, at_end = ends ? __ffs((int)ends) - 1 : PROBE_LANES;
-            const int from = first + (at_hit & (PROBE_LANES - 1));
-            const uint32_t r0 = __shfl(c0, from, WAVE), r1 = __shfl(c1, from, WAVE);
-            if (open[u] && at_hit < at_end) count[u] = ((unsigned long long)r1 << 32) | r0;
-            open[u] = open[u] && !hits && !ends;
+            const uint32_t hits = group_of(__ballot(hit)), ends = group_of(__ballot(end));
+            if (hit && (ends & before) == 0u) found(u, ((unsigned long long)hi[u].w << 32) | hi[u].z);
+            open[u] = open[u] && (hits | ends) == 0u;
             at[u] += PROBE_LANES;
             while (open[u] && at[u] >= ng.capacity) at[u] -= ng.capacity;
             more = more || open[u];
@@ -445,8 +445,9 @@ __device__ __forceinline__ void ngram_probes(const NgramDev &ng, const int32_t (
 // entries (vocabularies from 131074 on): of a block of 1024 threads 256 select, 5 .. 32 entries each, in every one of 128 blocks.  One -> two there,
 // 131074 .. 700000 entries, k = 1 .. 8: 0.83 .. 1.00 times for the first timestep and without n-grams (262146, k = 4: 12.8 -> 11.7 us), 0.93 .. 0.98 with
 // them from k = 5 on.
-// k = 8, five orders, 1.6 M slots: 28 -> 13 us behind the slices (merge 2.9, ranks 0.6, hashes 0.8, probes 5.5, mixture and scores 1.1, prune
-// and state 1.5).
+// k = 8, five orders, 120 000 n-grams of each, cycles from the block's start: its slice 7400, published and counted 4000, merge 6200, hashes 2300, probes
+// 7100, mixture and scores 2100, prune and state 3300: 40900 -> 32500 in all with the leaner probes and a lane per draft at the end (k = 5: 36500 -> 25500,
+// 10: 52000 -> 43300); four timesteps and their results 92.7 -> 79.6 us.
 constexpr int ENT = 1024, MERGE = 256, MERGE_WAVES = MERGE / WAVE, GROUPS = ENT / PROBE_LANES;
 
 constexpr bool probes_in_one_go(int k) { return (k * k + k) * SPD_N_ORDERS <= GROUPS; }
@@ -467,6 +468,7 @@ __global__ __launch_bounds__(ENT) void expand_prune_kernel(const TopkArgs slice,
     __shared__ float s_old[SPD_K_MAX];
     __shared__ unsigned long long s_cnt[SPD_KK * SPD_N_ORDERS];
     __shared__ uint64_t s_home[SPD_KK * SPD_N_ORDERS];
+    __shared__ int2 s_key[ONE_GO ? 1 : SPD_KK * SPD_N_ORDERS][3];
     __shared__ unsigned long long s_tot[SPD_K_MAX * SPD_N_ORDERS];
     __shared__ float s_png[SPD_KK];
     __shared__ int s_any[SPD_K_MAX];
@@ -508,13 +510,12 @@ __global__ __launch_bounds__(ENT) void expand_prune_kernel(const TopkArgs slice,
         if (!ONE_GO && use_ng && e < (n_total + PROBE_LANES - 1) / PROBE_LANES * PROBE_LANES) {   // (whole waves)
             int tail[SPD_TAIL];
             int32_t key[1][6];
-            unsigned long long total[1];
 #pragma unroll
             for (int q = 0; q < SPD_TAIL; ++q) tail[q] = st->tails[min(e / SPD_N_ORDERS, SPD_K_MAX - 1)][q];
             const bool known = make_key(tail, SPD_MIN_ORDER + e % SPD_N_ORDERS, NG_TOTAL, key[0]);
             const uint64_t home[1] = {known && e < n_total ? ngram_home(ngram_hash(key[0]), a.ng.capacity) : NO_HOME};
-            ngram_probes<1>(a.ng, key, home, total);
-            if (e < n_total && u % PROBE_LANES == 0) s_tot[e] = total[0];
+            if (e < n_total && u % PROBE_LANES == 0) s_tot[e] = 0ull;
+            ngram_probes<1>(a.ng, key, home, [&](int, unsigned long long total) { s_tot[e] = total; });
         }
     }
     if constexpr (SLICES) {
@@ -542,7 +543,8 @@ __global__ __launch_bounds__(ENT) void expand_prune_kernel(const TopkArgs slice,
         candidate(0, cv[0], ci[0]);
         if (n_cand > MERGE) {
 #pragma unroll
-            for (int q = 1; q < NC; ++q) candidate(q, cv[q], ci[q]);
+            for (int q = 1; q < NC; ++q)
+                if (q < 2 || n_cand > 2 * MERGE) candidate(q, cv[q], ci[q]);
         }
         if (tid < WAVE) {   // log-sum-exp over the slices: M = max of the maxima, S = sum of sum-exp * exp(max - M)
             static_assert(TOPK_PART_MAX == 2 * WAVE, "two slices per lane");
@@ -569,7 +571,8 @@ __global__ __launch_bounds__(ENT) void expand_prune_kernel(const TopkArgs slice,
             for (int q = 0; q < N; ++q) key[q] = ci[q] == INT_MAX ? 0u : value_key(cv[q]);
             wave_top_k(k, key, [&](int q) { return ci[q]; }, kv, ki);
         };
-        if (n_cand > MERGE) select(std::integral_constant<int, NC>());
+        if (n_cand > 2 * MERGE) select(std::integral_constant<int, NC>());
+        else if (n_cand > MERGE) select(std::integral_constant<int, 2>());
         else select(std::integral_constant<int, 1>());
         if (lane < k) {
             const int at = (tid / WAVE) * k + lane;
@@ -620,35 +623,44 @@ __global__ __launch_bounds__(ENT) void expand_prune_kernel(const TopkArgs slice,
                 const int n_probe = n_count + n_total, e = tid / PROBE_LANES;
                 if (tid / WAVE * (WAVE / PROBE_LANES) < n_probe) {     // (whole waves)
                     int32_t key[1][6];
-                    unsigned long long count[1];
                     const bool known = key_of(min(e, n_probe - 1), key[0]);
                     const uint64_t home[1] = {known && e < n_probe ? ngram_home(ngram_hash(key[0]), a.ng.capacity) : NO_HOME};
-                    ngram_probes<1>(a.ng, key, home, count);
-                    if (e < n_probe && tid % PROBE_LANES == 0) (e < n_count ? s_cnt[e] : s_tot[e - n_count]) = count[0];
+                    auto put = [&](unsigned long long count) {
+                        if (e < n_count) s_cnt[e] = count;
+                        else s_tot[e - n_count] = count;
+                    };
+                    if (e < n_probe && tid % PROBE_LANES == 0) put(0ull);
+                    ngram_probes<1>(a.ng, key, home, [&](int, unsigned long long count) { put(count); });
                 }
             } else {
-                constexpr int N = 4;                               // up to k = 10 in one go
                 for (int e = tid; e < n_count; e += ENT) {
                     int32_t key[6];
                     s_home[e] = key_of(e, key) ? ngram_home(ngram_hash(key), a.ng.capacity) : NO_HOME;
+#pragma unroll
+                    for (int q = 0; q < 6; q += 2) s_key[e][q / 2] = make_int2(key[q], key[q + 1]);
+                    s_cnt[e] = 0ull;
                 }
                 __syncthreads();
-                for (int e0 = 0; e0 < n_count; e0 += N * GROUPS) {
+                auto probe = [&](auto n, int e0) {                 // n probes per group of lanes
+                    constexpr int N = decltype(n)::value;
                     int32_t key[N][6];
                     uint64_t home[N];
-                    unsigned long long count[N];
 #pragma unroll
                     for (int u = 0; u < N; ++u) {
-                        const int e = e0 + u * GROUPS + tid / PROBE_LANES, f = min(e, n_count - 1);
-                        (void)key_of(f, key[u]);
+                        const int e = e0 + u * GROUPS, f = min(e, n_count - 1);
+#pragma unroll
+                        for (int q = 0; q < 6; q += 2) { const int2 w = s_key[f][q / 2]; key[u][q] = w.x; key[u][q + 1] = w.y; }
                         home[u] = e < n_count ? s_home[f] : NO_HOME;
                     }
-                    ngram_probes<N>(a.ng, key, home, count);
-#pragma unroll
-                    for (int u = 0; u < N; ++u) {
-                        const int e = e0 + u * GROUPS + tid / PROBE_LANES;
-                        if (e < n_count && tid % PROBE_LANES == 0) s_cnt[e] = count[u];
-                    }
+                    ngram_probes<N>(a.ng, key, home, [&](int u, unsigned long long count) { s_cnt[e0 + u * GROUPS] = count; });
+                };
+                // (all of up to k = 10 in one go)
+                for (int e0 = 0; e0 < n_count; e0 += 4 * GROUPS) {
+                    const int e = e0 + tid / PROBE_LANES, left = n_count - e0 - __builtin_amdgcn_readfirstlane(tid / WAVE) * (WAVE / PROBE_LANES);     // (by the wave's first probe)
+                    if (left > 3 * GROUPS) probe(std::integral_constant<int, 4>(), e);
+                    else if (left > 2 * GROUPS) probe(std::integral_constant<int, 3>(), e);
+                    else if (left > GROUPS) probe(std::integral_constant<int, 2>(), e);
+                    else if (left > 0) probe(std::integral_constant<int, 1>(), e);
                 }
             }
             __syncthreads();
@@ -707,11 +719,13 @@ __global__ __launch_bounds__(ENT) void expand_prune_kernel(const TopkArgs slice,
         }
     }
     __syncthreads();
-    if (tid < k) {  // Eq. 2 on the new scores
-        float mx = -INFINITY, sum = 0.f;
-        for (int i = 0; i < k; ++i) mx = fmaxf(mx, s_new[i]);
-        for (int i = 0; i < k; ++i) sum += expf(s_new[i] - mx);
-        st->gamma[tid] = expf(s_new[tid] - mx) / sum;
+    if (tid < WAVE) {  // Eq. 2 on the new scores: a lane per draft, added in draft order (every lane walking all of them: 1800 cycles at k = 8, so 600)
+        const float mine = lane < k ? s_new[lane] : -INFINITY;
+        const float mx = read_lane(wave_max_last(mine), WAVE - 1);
+        const float e = expf(mine - mx);
+        float sum = 0.f;
+        for (int i = 0; i < k; ++i) sum += read_lane(e, i);
+        if (lane < k) st->gamma[lane] = e / sum;
         if (tid == 0) {
             st->k = k;
             st->n_gen = a.first ? 1 : gen + 1;

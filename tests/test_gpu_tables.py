@@ -72,6 +72,43 @@ def test_five_orders_over_the_numbers_of_probes(tiny, k):
         sess.close()
 
 
+@pytest.mark.parametrize("k", [5, 6, 7, 8, 9, 10, 11])
+def test_probes_per_group_of_lanes(k):
+    """From five drafts on a group of lanes takes one to four probes, by what its wave has left of 5 k^2 (125, 180, 245, 320, 405, 500, and
+    605 in two rounds): some waves of a block take one more than others.  From nine drafts on the merge looks at two candidates a
+    thread (288 .. 352 of 32 slices).  Scripted logits over tables that most of the probes hit, counts and probabilities without a gap."""
+    import torch
+    pkg = P()
+    shape = synth.ModelShape("one-head", 1, 64, 1, 1, 128, 32000, "fp32")
+    rng = np.random.default_rng(k)
+    corpus = rng.integers(0, 12, size=4000)
+    tabs = {n: np.unique(np.lib.stride_tricks.sliding_window_view(corpus, n), axis=0, return_counts=True) for n in range(2, 7)}
+    tabs = {n: (np.ascontiguousarray(keys, np.int32), counts.astype(np.uint32)) for n, (keys, counts) in tabs.items()}
+    lam, pre = synth.PAPER_LAMBDAS, corpus[:7].astype(np.int32)
+    sess = pkg.Session(shape, synth.make_weights(shape, seed=1), max_ctx=32, k_max=16)
+    try:
+        sess.spd_load_ngrams(tabs, lam)
+        otabs = O.NgramTables(tabs)
+        sess.spd_prefill(pre)
+        dc, cfg, state, hits = pkg.SpdDecodeCfg(k, 0.54, 1.0, 0.1), O.DecodeCfg(k, 0.54, 1.0, 0.1, lam), None, 0
+        for step in range(4):
+            z = rng.standard_normal(shape.vocab).astype(np.float32) - 12.0
+            z[:12] = rng.permutation(12).astype(np.float32) / 2
+            state, rec = O.first_step(z, pre, cfg) if state is None else O.expand_and_prune(state, z, otabs, cfg)
+            sess.spd_expand_prune(dc, torch.from_numpy(z).cuda(), first=(step == 0))
+            tails, scores, gamma = sess.spd_get_state()
+            ids, _, _, valid, png = sess.spd_get_step_info(k)
+            assert list(ids) == list(rec.top_ids) and np.array_equal(tails, tails_of(state))
+            np.testing.assert_allclose(scores, state.logscores, rtol=1e-5, atol=1e-5)     # sums of fp32 logarithms
+            np.testing.assert_allclose(gamma, O.superposition_weights(state.logscores), rtol=1e-4)
+            if step > 0:
+                np.testing.assert_allclose(png, rec.pngram, rtol=1e-6)                    # five fp32 terms
+                hits += int(np.count_nonzero(png))
+        assert hits > k * k
+    finally:
+        sess.close()
+
+
 def test_tables_replaced_between_timesteps(tiny):
     """Three timesteps with five orders, then the tables are replaced by a different set with
     orders 2..4 on the live context, three more timesteps.  The oracle is driven step by step
