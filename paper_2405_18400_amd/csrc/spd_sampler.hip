@@ -39,6 +39,8 @@ constexpr int ID_BITS = 23;        // token ids in a key (vocab <= 2^23)
 constexpr int ITEMS = 32;          // entries per thread that stage B keeps in registers (vocab <= 32768; else they are re-read)
 constexpr float FX_ONE = 1099511627776.0f;   // 2^40: probability 1 in fixed point
 
+// exp(x) in fixed point, <= 2^40 (1 + a few ulp); the same bits wherever it is formed from an entry's logit.
+__device__ __forceinline__ unsigned long long fixed_point(float x) { return (unsigned long long)(expf(x) * FX_ONE); }
 // Ascending in (probability descending, id ascending); pf < 2^41.
 __device__ __forceinline__ unsigned long long sort_key(unsigned long long pf, int id) {
     return (((1ull << 41) - 1ull - pf) << ID_BITS) | (unsigned long long)(unsigned)id;
@@ -47,6 +49,24 @@ __device__ __forceinline__ unsigned long long sort_key(unsigned long long pf, in
 // A sum over the wave that every lane gets (no LDS, no barrier).
 __device__ __forceinline__ float wave_all_sum(float v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wave_sum_last(v)), WAVE - 1)); }
 __device__ __forceinline__ float wave_all_max(float v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wave_max_last(v)), WAVE - 1)); }
+
+// 64-bit sums by lane-crossing moves (a shuffle is a trip through LDS per half and step).
+template <int CTRL, int ROW_MASK = 0xF> __device__ __forceinline__ unsigned long long dpp_add64(unsigned long long v) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, ROW_MASK, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, ROW_MASK, 0xF, false);
+    return v + (((unsigned long long)hi << 32) | lo);
+}
+__device__ __forceinline__ unsigned long long wave_scan64(unsigned long long v) {   // inclusive
+    v = dpp_add64<0x111>(v); v = dpp_add64<0x112>(v); v = dpp_add64<0x114>(v); v = dpp_add64<0x118>(v);   // row_shr 1, 2, 4, 8
+    v = dpp_add64<0x142, 0xA>(v);                                                                       // row 0 -> 1, row 2 -> 3
+    return dpp_add64<0x143, 0xC>(v);                                                                    // rows 0, 1 -> 2, 3
+}
+template <int LANES> __device__ __forceinline__ unsigned long long group_sum64(unsigned long long v) {   // over 4 or 16 lanes, in all of them
+    static_assert(LANES == 4 || LANES == 16, "a quad or a row");
+    v = dpp_add64<0xB1>(v); v = dpp_add64<0x4E>(v);
+    if (LANES == 16) { v = dpp_add64<0x141>(v); v = dpp_add64<0x140>(v); }
+    return v;
+}
 
 struct Stage {                                  // LDS of stage B
     unsigned long long hm[2][NB + 1];          // [level 1 / deeper levels]: per bucket, entry count above mass (one atomic add per
@@ -77,17 +97,13 @@ __device__ __forceinline__ unsigned count_of(unsigned long long w) { return (uns
 // hm (NB values, this thread's two given) -> exclusive prefix sums, totals at index NB; this thread's three come back in
 // registers, everybody's are in LDS after the next barrier.
 __device__ __forceinline__ void prefix_sums(Stage &s, int lv, unsigned long long a0, unsigned long long a1, unsigned long long (&out)[3]) {
-    const int t = threadIdx.x, lane = t & (WAVE - 1), w = t / WAVE;
-    unsigned long long m = a0 + a1;
-#pragma unroll
-    for (int o = 1; o < WAVE; o <<= 1) {        // inclusive scan over the wave
-        const unsigned long long um = __shfl_up(m, o, WAVE);
-        if (lane >= o) m += um;
-    }
+    const int t = threadIdx.x, lane = t & (WAVE - 1), w = __builtin_amdgcn_readfirstlane(t / WAVE);
+    const unsigned long long m = wave_scan64(a0 + a1);
     if (lane == WAVE - 1) s.wm[w] = m;
     __syncthreads();
     unsigned long long pm = 0;
-    for (int q = 0; q < w; ++q) pm += s.wm[q];
+#pragma unroll
+    for (int q = 0; q < SNW - 1; ++q) pm += q < w ? s.wm[q] : 0ull;
     const unsigned long long em = pm + m - (a0 + a1);
     s.hm[lv][2 * t] = em; s.hm[lv][2 * t + 1] = em + a0;
     if (t == SNT - 1) s.hm[lv][NB] = em + a0 + a1;
@@ -120,8 +136,8 @@ __device__ __forceinline__ int crossing(Stage &s, int lv, unsigned long long x) 
     return b;
 }
 
-// Per entry, written by stage A: one word with the first-level bucket above the probability
-// (x 2^40).  Written through to memory and read back coherently (the writers sit behind other
+// Per entry, written by stage A where its bucket number does not stay in registers (not CACHED): one word with the first-level
+// bucket above the probability (x 2^40).  Written through to memory and read back coherently (the writers sit behind other
 // L2 caches; a device-wide fence would write back and invalidate whole caches -- tens of
 // microseconds -- where this is 8 bytes per entry).
 constexpr int PB_SHIFT = 48;
@@ -132,14 +148,16 @@ __device__ __forceinline__ unsigned long long load_pb(const unsigned long long *
 }
 // The entries i = tid, tid + SNT, ... that stage B walks several times.  The first walk reads
 // their words, CH at a time (one dependent trip to memory per CH entries: these walks are
-// chains of latencies, not bandwidth).  CACHED: it leaves the bucket numbers in registers, two
-// per register, and the later walks -- which look for the entries of ONE bucket -- read only
-// the words of those; otherwise every walk reads all words again.
+// chains of latencies, not bandwidth).  CACHED: the bucket numbers alone are stored, two to a
+// register here, and the walks -- which look for the entries of ONE bucket -- read only the
+// logits of those; otherwise every walk reads all words again.
 constexpr int CH = 16;
 template <bool CACHED>
 struct Entries {
     const unsigned long long *pb;
     int vocab;
+    const float *logits;
+    float tau, lse;
     unsigned bk[CACHED ? ITEMS / 2 : 1];
     // CACHED: entry c of this thread is token 8 (tid + SNT (c / 8)) + c % 8 -- its bucket numbers are
     // four 16-byte pieces of the per-entry bucket array (0xFFFF past the vocabulary)
@@ -153,50 +171,46 @@ struct Entries {
             bk[4 * r] = v.x; bk[4 * r + 1] = v.y; bk[4 * r + 2] = v.z; bk[4 * r + 3] = v.w;
         }
     }
-    // f(i, bucket of entry i, its probability) for every entry of this thread
+    // f(an entry's bucket, its probability) for every entry of this thread
     template <typename F>
     __device__ __forceinline__ void first_walk(F &&f) {
-        const int rounds = CACHED ? ITEMS / CH : (vocab + SNT * CH - 1) / (SNT * CH);
+        static_assert(!CACHED, "");
+        for (int i0 = threadIdx.x; i0 < vocab; i0 += SNT * CH) {
+            unsigned long long w[CH];
 #pragma unroll
-        for (int r = 0; r < (CACHED ? ITEMS / CH : 1); ++r) {
-            for (int rr = CACHED ? r : 0; rr < (CACHED ? r + 1 : rounds); ++rr) {
-                unsigned long long w[CH];
-#pragma unroll
-                for (int c = 0; c < CH; ++c) {
-                    const int i = threadIdx.x + (rr * CH + c) * SNT;
-                    w[c] = i < vocab ? load_pb(pb, i) : NO_ENTRY;
-                }
-#pragma unroll
-                for (int c = 0; c < CH; ++c) {
-                    const int i = threadIdx.x + (rr * CH + c) * SNT;
-                    const unsigned b = (unsigned)(w[c] >> PB_SHIFT);      // NO_ENTRY: 0xFFFF, no bucket
-                    if (CACHED) {
-                        if (c & 1) bk[(r * CH + c) / 2] |= b << 16;
-                        else bk[(r * CH + c) / 2] = b;
-                    }
-                    if (w[c] != NO_ENTRY) f(i, (int)b, w[c] & P_MASK);
-                }
+            for (int c = 0; c < CH; ++c) {
+                const int i = i0 + c * SNT;
+                w[c] = i < vocab ? load_pb(pb, i) : NO_ENTRY;
             }
+#pragma unroll
+            for (int c = 0; c < CH; ++c)
+                if (w[c] != NO_ENTRY) f((int)(w[c] >> PB_SHIFT), w[c] & P_MASK);
         }
     }
-    // f(i, its probability) for every entry of this thread in bucket b1
+    // f(i, its probability, its logit) for every entry of this thread in bucket b1
     template <typename F>
     __device__ __forceinline__ void walk_bucket(int b1, F &&f) {
         if (CACHED) {
-            static_assert(ITEMS <= 32, "one bit per entry");
-            unsigned hits = 0u;
+            static_assert(ITEMS == 32, "one bit per entry");
+            unsigned others = 0u;                   // bit 15 - r: the lower number of register r is another; bit 31 - r: the upper one
             const unsigned both = (unsigned)b1 | ((unsigned)b1 << 16);
 #pragma unroll
-            for (int r = 0; r < ITEMS / 2; ++r) {   // two bucket numbers per register
-                const unsigned x = bk[r] ^ both;
-                hits |= (unsigned)((x & 0xFFFFu) == 0u) << (2 * r);
-                hits |= (unsigned)((x >> 16) == 0u) << (2 * r + 1);
+            for (int r = 0; r < ITEMS / 2; ++r) {   // (three instructions for two bucket numbers: the block's waves share four SIMDs)
+                unsigned other;
+                asm("v_pk_min_u16 %0, %1, %2" : "=v"(other) : "v"(bk[r] ^ both), "v"(0x00010001u));
+                others = (others << 1) | other;
             }
-            while (hits) {   // (few: a bucket holds some dozens of the block's entries)
-                const int c = __ffs(hits) - 1;
+            unsigned hits = ~others;
+            while (hits) {   // (few: a bucket holds some dozens of the block's entries; two at a time)
+                const int c0 = __ffs(hits) - 1;
                 hits &= hits - 1u;
-                const int i = entry(c);
-                f(i, load_pb(pb, i) & P_MASK);
+                const bool two = hits != 0u;
+                const int c1 = two ? __ffs(hits) - 1 : c0;
+                hits &= hits - 1u;
+                const int i0 = entry(2 * (15 - c0 % 16) + c0 / 16), i1 = entry(2 * (15 - c1 % 16) + c1 / 16);
+                const float l0 = as_global(logits)[i0], l1 = as_global(logits)[i1];
+                f(i0, fixed_point(__fdiv_rn(l0, tau) - lse), l0);
+                if (two) f(i1, fixed_point(__fdiv_rn(l1, tau) - lse), l1);
             }
         } else {
             for (int i0 = threadIdx.x; i0 < vocab; i0 += SNT * CH) {
@@ -208,7 +222,7 @@ struct Entries {
                 }
 #pragma unroll
                 for (int c = 0; c < CH; ++c)
-                    if ((int)(w[c] >> PB_SHIFT) == b1) f(i0 + c * SNT, w[c] & P_MASK);
+                    if ((int)(w[c] >> PB_SHIFT) == b1) f(i0 + c * SNT, w[c] & P_MASK, as_global(logits)[i0 + c * SNT]);
             }
         }
     }
@@ -230,7 +244,7 @@ __device__ __forceinline__ void search(Stage &s, Entries<CACHED> &en, unsigned l
         if (!cut) {   // the key range of the bucket's entries
             if (t == 0) { s.kmin = ~0ull; s.kmax = 0ull; }
             __syncthreads();
-            en.walk_bucket(b1, [&](int i, unsigned long long pf) {
+            en.walk_bucket(b1, [&](int i, unsigned long long pf, float) {
                 const unsigned long long k = sort_key(pf, i);
                 atomicMin(&s.kmin, k);
                 atomicMax(&s.kmax, k);
@@ -244,7 +258,7 @@ __device__ __forceinline__ void search(Stage &s, Entries<CACHED> &en, unsigned l
         const int sh = bits > 11 ? bits - 11 : 0;                  // (k - klo) >> sh < 2048
         s.hm[1][2 * t] = 0ull; s.hm[1][2 * t + 1] = 0ull;
         __syncthreads();
-        en.walk_bucket(b1, [&](int i, unsigned long long pf) {
+        en.walk_bucket(b1, [&](int i, unsigned long long pf, float) {
             const unsigned long long k = sort_key(pf, i);
             if (k >= klo && k <= khi) {
                 const int b2 = (int)((k - klo) >> sh);
@@ -269,7 +283,7 @@ __device__ __forceinline__ void search(Stage &s, Entries<CACHED> &en, unsigned l
     if (t == 0) { s.n_list = 0; s.best = INT_MAX; }
     if (t < LC) { s.lrank[t] = 0u; s.lcum[t] = 0ull; }
     __syncthreads();
-    en.walk_bucket(b1, [&](int i, unsigned long long pf) {
+    en.walk_bucket(b1, [&](int i, unsigned long long pf, float) {
         const unsigned long long k = sort_key(pf, i);
         if (k >= klo && k <= khi) {
             const int at = atomicAdd(&s.n_list, 1);
@@ -332,8 +346,7 @@ __device__ __forceinline__ void ask(Stage &s, Entries<CACHED> &en, const float *
         __syncthreads();
         return;
     }
-    en.walk_bucket(b1, [&](int i, unsigned long long pf) {
-        const float l = as_global(logits)[i];
+    en.walk_bucket(b1, [&](int i, unsigned long long pf, float l) {
         const int at = atomicAdd(&s.n_list, 1);
         s.lk[at] = sort_key(pf, i); s.lp[at] = pf; s.lid[at] = i; s.ll[at] = l;
     });
@@ -349,8 +362,9 @@ __device__ __forceinline__ void ask(Stage &s, Entries<CACHED> &en, const float *
             for (int j = part; j < nl; j += PARTS)
                 if (s.lk[j] < ki) { ++cnt; mass += s.lp[j]; }
         }
-#pragma unroll
-        for (int o = PARTS / 2; o > 0; o >>= 1) { cnt += __shfl_xor(cnt, o, WAVE); mass += __shfl_xor(mass, o, WAVE); }
+        mass = group_sum64<PARTS>(mass + ((unsigned long long)cnt << CNT_SHIFT));   // (as in a histogram word: at most 256 entries, masses below 2^42)
+        cnt = count_of(mass);
+        mass = mass_of(mass);
         if (i < nl && part == 0) {
             const unsigned long long before = mass_of(from) + mass, tot = before + s.lp[i];
             const bool crosses = reaches(tot) && (cnt == 0u || !reaches(before));
@@ -370,31 +384,41 @@ __global__ __launch_bounds__(SNT) void nucleus_kernel(const NucleusArgs a) {
     __shared__ Stage s;
     const int tid = threadIdx.x, lane = tid & (WAVE - 1);
     global_ptr<DevState> st = as_global(a.st);
-    // log-sum-exp, largest and smallest scaled logit from the per-slice statistics (every wave for itself)
-    float M = -INFINITY, mn = INFINITY;
-    for (int b = lane; b < a.n_part; b += WAVE) { M = fmaxf(M, as_global(a.pm)[b]); mn = fminf(mn, as_global(a.pn)[b]); }
-    M = wave_all_max(M);
-    mn = -wave_all_max(-mn);
+    // log-sum-exp, largest and smallest scaled logit from the per-slice statistics (every wave for itself); this thread's first logit comes
+    // along: one trip to memory instead of three.  32000 entries, cycles from the block's start, before -> now (with the sums by lane-crossing
+    // moves, probabilities of a bucket's entries formed again from their logits instead of stored and fetched, and three instructions
+    // instead of eight for two bucket numbers): slice 5400 -> 5200, counted 9100 -> 9500, histogram and sums 12800 -> 13900, the nucleus 20300 ->
+    // 20100, the draw 25200 -> 23800, end 26500 -> 24500; four tokens 77.3 -> 73.8 us.
+    const int lo = blockIdx.x * a.per_part, hi = min(a.vocab, lo + a.per_part);
+    const float first_logit = as_global(a.logits)[min(lo + tid, a.vocab - 1)];
+    static_assert(TOPK_PART_MAX == 2 * WAVE, "two slices per lane");
+    float pm[2], pn[2], ps[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int b = min(lane + q * WAVE, a.n_part - 1);
+        pm[q] = as_global(a.pm)[b]; pn[q] = as_global(a.pn)[b]; ps[q] = as_global(a.ps)[b];
+    }
+    const float M = wave_all_max(fmaxf(pm[0], pm[1])), mn = -wave_all_max(-fminf(pn[0], pn[1]));   // (a slice looked at twice changes neither)
     float S = 0.f;
-    for (int b = lane; b < a.n_part; b += WAVE) S += as_global(a.ps)[b] * expf(as_global(a.pm)[b] - M);
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+        if (lane + q * WAVE < a.n_part) S += ps[q] * expf(pm[q] - M);
     const float lse = M + logf(wave_all_sum(S));
     const float range = M - mn;
     const float scale = range > 0.f ? (float)NB / range : 0.f;
 
     // ---- stage A: this block's slice
-    const int lo = blockIdx.x * a.per_part, hi = min(a.vocab, lo + a.per_part);
     if (CACHED) {   // the slice's histogram
         s.hm[1][2 * tid] = 0ull; s.hm[1][2 * tid + 1] = 0ull;
         __syncthreads();
     }
     for (int i = lo + tid; i < hi; i += SNT) {
-        const float z = __fdiv_rn(as_global(a.logits)[i], a.tau);
-        const float p = expf(z - lse);
+        const float z = __fdiv_rn(i < lo + SNT ? first_logit : as_global(a.logits)[i], a.tau);
         const float fb = (M - z) * scale;                          // monotonic in z; anything beyond lands in the last bucket
         const int b = fb < (float)(NB - 1) ? (int)fb : NB - 1;
-        const unsigned long long pf = (unsigned long long)(p * FX_ONE);   // <= 2^40 (1 + a few ulp)
+        const unsigned long long pf = fixed_point(z - lse);
         const int bb = b < 0 ? 0 : b;
-        __hip_atomic_store(as_global(a.sc_pb) + i, ((unsigned long long)bb << PB_SHIFT) | pf, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (!CACHED) __hip_atomic_store(as_global(a.sc_pb) + i, ((unsigned long long)bb << PB_SHIFT) | pf, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (CACHED) {
             __hip_atomic_store(as_global(a.sc_bk) + i, (uint16_t)bb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             atomicAdd(&s.hm[1][bb], pf + ONE_ENTRY);
@@ -422,7 +446,7 @@ __global__ __launch_bounds__(SNT) void nucleus_kernel(const NucleusArgs a) {
 #pragma unroll
     for (int q = 0; q < SPD_TAIL; ++q) tail[q] = a.first ? st->prefix_tail[q] : st->tails[0][q];
     Entries<CACHED> en;
-    en.pb = a.sc_pb; en.vocab = a.vocab;
+    en.pb = a.sc_pb; en.vocab = a.vocab; en.logits = a.logits; en.tau = a.tau; en.lse = lse;
     if (tid == 0) { s.q_bucket[0] = s.q_bucket[1] = -1; s.n_list = 0; }
     unsigned long long h0, h1, sums[3];
     if constexpr (CACHED) {
@@ -435,7 +459,7 @@ __global__ __launch_bounds__(SNT) void nucleus_kernel(const NucleusArgs a) {
     } else {
         s.hm[0][2 * tid] = 0ull; s.hm[0][2 * tid + 1] = 0ull;
         __syncthreads();
-        en.first_walk([&](int, int b, unsigned long long pf) {
+        en.first_walk([&](int b, unsigned long long pf) {
             atomicAdd(&s.hm[0][b], pf + ONE_ENTRY);
         });
         __syncthreads();

@@ -192,6 +192,31 @@ def test_large_vocabulary_uses_the_uncached_path():
         sess.close()
 
 
+@pytest.mark.parametrize("vocab", [66, 1024, 1026, 4098, 32768, 32770])
+def test_neighbouring_entries_in_one_bucket_and_the_next(vocab):
+    """The entries of a bucket are found two bucket numbers at a time: ids side by side that share a bucket, that lie in buckets whose numbers
+    differ in the last bit alone, and at random; slices of one to 32 blocks, ragged ones, the last vocabulary whose bucket
+    numbers stay in registers and the first beyond."""
+    pkg = P()
+    shape = synth.ModelShape("buckets", 1, 64, 2, 2, 128, vocab, "fp32")
+    sess = pkg.Session(shape, synth.make_weights(shape, seed=2), max_ctx=32, k_max=8)
+    try:
+        sess.spd_prefill([1, 2, 3])
+        rng = np.random.default_rng(vocab)
+        i = np.arange(vocab)
+        width = 8.0 / 2048                                                          # of a bucket, the logits spanning 8
+        for lg in (rng.normal(size=vocab) * 2, np.repeat(rng.random(vocab // 2 + 1), 2)[:vocab] * 8, ((i * 7919) % 2048 // 2 * 2 + i % 2) * width, 8.0 - (i % 2048) * width):
+            lg = lg.astype(np.float32)
+            n_dec = 0
+            for u in (0.03, 0.31, 0.62, 0.97):
+                rec = O.nucleus_sample(lg, 0.7, 1.0, float(np.float32(u)), keep_logits=True)
+                tok = _sample_only(sess, pkg.SpdSampleCfg(0.7, 1.0), lg, float(np.float32(u)))
+                n_dec += check_draw(sess, rec, 0.7, 1.0, float(np.float32(u)), tok, rec.logp, 1e-5)
+            assert n_dec >= 1 or vocab > 4098
+    finally:
+        sess.close()
+
+
 def test_error_paths(tiny):
     shape, w, prefix = tiny
     pkg = P()
