@@ -21,18 +21,19 @@
 // activation, so they are requested while the block waits for its input, a slice at a time
 // between two looks at the input: the weight stream from HBM does not stop at phase boundaries.
 //
-// Phase GEMV ("row-contiguous"): the NW waves of a block read one matrix row side by side
+// Phase GEMV ("row-contiguous"): NW waves read one matrix row side by side
 // (wave w takes columns [(p*NW + w)*64*VEC, +64*VEC) of pass p), so the slice of x a lane
 // multiplies with is fixed and lives in registers; a tile is U rows, partial sums meet in LDS.
+// All 8 waves of a block where rows are that wide; narrow models have 8 / NW groups of NW waves side
+// by side, each with U rows of the tile (with 8, the waves past a row's end would request, await and add nothing).
 #include "spd_device.h"
 
 using namespace spdd;
 
 namespace {
 
-// One block per CU (few barrier participants).  With 512 threads: 8 waves that read one matrix
-// row side by side and have 256 vector registers each, i.e. room for a 16 KB weight tile in
-// flight per wave.  (1024 threads = two such row groups with half the registers.)
+// One block per CU (few barrier participants).  With 512 threads: 8 waves that have 256 vector registers each, i.e. room for a
+// 16 KB weight tile in flight per wave.
 constexpr int FUSED_UA = 16;          // rows per tile where one pass covers a row
 constexpr int FUSED_UO_EXTRA = 4;     // extra rows per tile of the O projection
 constexpr int FUSED_QD = 20;          // 16-byte pieces per lane of a phase's first tile requested while its input is awaited
@@ -49,18 +50,17 @@ constexpr int FUSED_ONE_CHUNK = 256;  // contexts up to this long are one attent
 static_assert(FUSED_ONE_CHUNK <= ATTN_CHUNK_MAX && FUSED_ONE_CHUNK_HALF <= ATTN_CHUNK_MAX, "one attention item must fit the score buffer");
 constexpr int INPUT_SLEEP = 2;        // s_sleep units (64 cycles) between two looks at an input that is not complete yet
 constexpr int NT = 512;               // threads per block
-constexpr int NW = 8;                 // waves side by side on one row
 constexpr int MAX_U = 32;
 constexpr int MAX_SLOTS = 128;       // partial sums (rows x passes) a tile may leave in LDS per row group
 constexpr int FUSED_UPM = 16;        // rows per tile (= pieces per lane in flight) of a pass-major phase
 constexpr bool FUSED_PM_CACHED = true;    // a pass-major phase reads all passes of its input but the last through the L2
-constexpr int NG = NT / WAVE / NW;   // row groups per block
+constexpr int row_groups(int NW) { return NT / WAVE / NW; }   // of a block whose rows take NW waves side by side
 constexpr unsigned SPIN_LIMIT = 1u << 22;
 
 constexpr int MAX_EPI = FUSED_MAX_EPI;   // residual values a block may need in one phase
 
-struct FusedShared {
-    float part[2][NG][MAX_SLOTS][NW]; // [buffer][row group][tile slot][wave]
+template <int NW> struct FusedShared {
+    float part[2][row_groups(NW)][MAX_SLOTS][NW]; // [buffer][row group][tile slot][wave]
     float epi[MAX_EPI];           // this block's slice of the residual, staged when the phase starts
     float2 rope[128];             // (cos, sin) of this step's position, all d_head / 2 <= 128 pairs
     float red[NT / WAVE];
@@ -161,7 +161,7 @@ struct Cursor { int j, lo, hi, u0; };
 
 // The input vector of a phase as its lanes await it: raw 16-byte pieces (XP per column pass),
 // which of them still read unset.
-template <int P, int VEC>
+template <int NW, int P, int VEC>
 struct LazyXT {
     static constexpr int XP = VEC / 4;
     static constexpr int PASS_COLS = NW * WAVE * VEC;
@@ -223,10 +223,10 @@ struct LazyXT {
 // What the predecessor phase sets up of a phase before its own last tile (see Gemv::tile, MODE
 // 2): where the block starts and, for a pass-major phase, the look at the first pass of its
 // input and the residual.
-template <int P, int VEC>
+template <int NW, int P, int VEC>
 struct PreT {
     Cursor cur;
-    LazyXT<P, VEC> lx;
+    LazyXT<NW, P, VEC> lx;
     float resid;  // this thread's element of the block's residual slice
     bool valid;   // the block owns units of this phase
 };
@@ -251,15 +251,17 @@ struct PreT {
 // pass 0 is complete and looks at the later passes, a tile's pass ahead each, while it streams.
 // With a producer that works in chunks of one pass width, only the last pass's chunk is still
 // being written when the phase starts, and it is needed a tile's (P - 1) / P later.
-template <typename WT, int P, int U, int EPI, int NBUF, int SL, bool PM = false, bool CHUNKS = false, int SL0 = SL, typename KT = float>
+template <typename WT, int NW, int P, int U, int EPI, int NBUF, int SL, bool PM = false, bool CHUNKS = false, int SL0 = SL, typename KT = float>
 struct Gemv {
+    static constexpr int NG = row_groups(NW);
+    using Shared = FusedShared<NW>;
     static constexpr int VEC = Store<WT>::VEC;
     static constexpr int XP = VEC / 4;   // 16-byte pieces of x per pass and lane
     static constexpr int UT = U / 2;     // units per tile
     static constexpr int NS = PM ? U : U * P;   // pieces per lane in flight
     static constexpr int PASS_COLS = NW * WAVE * VEC;   // columns of a row the block covers per pass
-    using LazyX = LazyXT<P, VEC>;
-    using Pre = PreT<P, VEC>;
+    using LazyX = LazyXT<NW, P, VEC>;
+    using Pre = PreT<NW, P, VEC>;
     static_assert(U % 2 == 0 && NS <= NBUF && U <= MAX_U && U * P <= MAX_SLOTS, "tile does not fit the register window");
     static_assert(NG * UT <= WAVE, "the epilogue threads must all sit in wave 0");
     static_assert(P * XP <= 32, "one bit per piece of x");
@@ -353,7 +355,7 @@ struct Gemv {
     // The block has met after a tile: the first NG * UT threads finish their units of the tile
     // at unit u0 (chunk range [lo, hi)); a unit's two sums are spread over NPART slots each.
     template <int NPART>
-    static __device__ __forceinline__ void finish(const GemvArgs &a, int u0, int lo, int hi, int pos, FusedShared &sh, int pb) {
+    static __device__ __forceinline__ void finish(const GemvArgs &a, int u0, int lo, int hi, int pos, Shared &sh, int pb) {
         const int tid = threadIdx.x;
         const int eu = min(u0 + tid, hi - 1);
         if (tid < NG * UT && u0 + tid < hi) {   // unit u0 + tid: row group tid / UT, pair tid % UT
@@ -393,7 +395,7 @@ struct Gemv {
     // by then.  MODE 0: not at all.
     template <int MODE, typename Nx, int NXQ = 0>
     static __device__ __forceinline__ void tile(const GemvArgs &a, const Cursor &c, const Cursor &n, int pos,
-                                                FusedShared &sh, u32x4 (&buf)[NBUF], const float (&xr)[P][VEC],
+                                                Shared &sh, u32x4 (&buf)[NBUF], const float (&xr)[P][VEC],
                                                 const uint32_t (&coff)[P], int pb, const GemvArgs &na) {
         const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = (tid / WAVE) % NW, g = tid / (WAVE * NW);
         if constexpr (MODE == 2) {   // registers the next phase's tile has beyond this one's
@@ -455,14 +457,14 @@ struct Gemv {
     // tile): takes the first pass of x and stages the residual.  Done there, in straight-line
     // code behind the requests, because the compiler counts outstanding loads per path: after
     // the merge with the path that requested nothing it would wait for every one of them.
-    static __device__ __forceinline__ void settle(const GemvArgs &a, Pre &pre, FusedShared &sh, int *err) {
+    static __device__ __forceinline__ void settle(const GemvArgs &a, Pre &pre, Shared &sh, int *err) {
         if (!PM) return;   // (others look at their input when they start)
         pre.lx.await(LazyX::pass_mask(0), err);
         stage_resid(a, pre.cur, pre.resid, sh, err);
     }
     // The block's slice of the residual goes to LDS for the epilogues (visible to them after
     // the tile's barrier; the last phase that read this buffer lies at least one barrier back).
-    static __device__ __forceinline__ void stage_resid(const GemvArgs &a, const Cursor &c, float r, FusedShared &sh, int *err) {
+    static __device__ __forceinline__ void stage_resid(const GemvArgs &a, const Cursor &c, float r, Shared &sh, int *err) {
         const int tid = threadIdx.x;
         if (EPI == EPI_RESID && tid < 2 * (c.hi - c.lo)) {
             for (unsigned spins = 0; __float_as_uint(r) == ACT_UNSET; ++spins) {   // (never taken unset)
@@ -483,7 +485,7 @@ struct Gemv {
     // a pass that is still incomplete then is waited for.
     template <int MODE, typename Nx, int NXQ = 0>
     static __device__ __forceinline__ void tile_pm(const GemvArgs &a, const Cursor &c, const Cursor &n, int pos,
-                                                   FusedShared &sh, u32x4 (&buf)[NBUF], float (&xr)[P][VEC], LazyX &lx, bool first,
+                                                   Shared &sh, u32x4 (&buf)[NBUF], float (&xr)[P][VEC], LazyX &lx, bool first,
                                                    int *err, const uint32_t (&coff)[P], int pb, const GemvArgs &na) {
         const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = (tid / WAVE) % NW, g = tid / (WAVE * NW);
 #pragma unroll
@@ -522,7 +524,7 @@ struct Gemv {
     // that way by its predecessor (`pre`), pieces [0, AH) of its first tile are on their way (a
     // pass-major phase: all of the tile, first pass of the input taken, residual staged).
     template <typename Nx, int NXQ, int AH>
-    static __device__ __forceinline__ void run(const GemvArgs &a_in, int pos, FusedShared &sh, u32x4 (&buf)[NBUF],
+    static __device__ __forceinline__ void run(const GemvArgs &a_in, int pos, Shared &sh, u32x4 (&buf)[NBUF],
                                                int &pb, bool ahead, int *err, const Prof &prof, unsigned point,
                                                const GemvArgs &na_in, bool hand, typename Nx::Pre *npre, Pre *pre) {
         constexpr bool PRE = PM && AH > 0;
@@ -687,32 +689,36 @@ __device__ __forceinline__ GemvArgs head_args(const FusedArgs &a, char *act) {
     return g;
 }
 
-// PA / PB: passes a block needs to cover d_model / d_ffn columns.  Rows per tile follow from
+// PA / PB: passes NW waves need to cover d_model / d_ffn columns.  Rows per tile follow from
 // them so that a tile stays at about 16 pieces (16 bytes each) per lane.
-constexpr int tile_rows(int passes) { return passes == 1 ? FUSED_UA : passes == 2 ? FUSED_UA / 2 : passes <= 4 ? 4 : 2; }
+// With fewer waves to a row (NW) they are the rows of one of the block's 8 / NW row groups.
+constexpr int tile_rows(int NW, int passes) {
+    if (NW == 8) return passes == 1 ? FUSED_UA : passes == 2 ? FUSED_UA / 2 : passes <= 4 ? 4 : 2;
+    return NW == 4 ? (passes == 1 ? 8 : 4) : 2;
+}
 
 // KT: element type of the key/value cache (float, or half_t for a bf16 model that asked for it).
-template <typename WT, typename KT, int PA, int PB>
+template <typename WT, typename KT, int NW, int PA, int PB>
 __global__ __launch_bounds__(NT) void fused_forward_kernel(const FusedArgs a) {
-    constexpr int UA = tile_rows(PA), UB = tile_rows(PB);
+    constexpr int UA = tile_rows(NW, PA), UB = tile_rows(NW, PB);
     // The O projection is one tile per block; its tile is a little taller so that it still is
     // when the blocks busy with attention items leave their rows to the others.
-    constexpr int UO = UA + FUSED_UO_EXTRA / PA;
+    constexpr int UO = NW == 8 ? UA + FUSED_UO_EXTRA / PA : UA;
     constexpr int NA = PA * UO;
     // The down projection walks its tiles pass by pass, and the gate/up phase before it works in
     // chunks of one such pass, where d_model is one block pass wide and d_ffn several.
-    constexpr bool PMD = PB >= 2 && PB <= 4;
+    constexpr bool PMD = NW == 8 && PB >= 2 && PB <= 4;
     // (rows per tile: 16, or 20 where a block's 20 rows -- the 13B shape -- would otherwise spill into a second tile)
     constexpr int UPM = (PA == 2 && PB == 4) ? 20 : FUSED_UPM;
     constexpr int ND = PMD ? UPM : PB * UB;
     constexpr int NBUF = (NA > ND) ? NA : ND;
     constexpr int SL = PA == 1 ? FUSED_SLICE : FUSED_SLICE_WIDE;
-    using Qkv = Gemv<WT, PA, UA, EPI_QKV, NBUF, SL, false, false, SL, KT>;
-    using Oproj = Gemv<WT, PA, UO, EPI_RESID, NBUF, SL>;
-    using GateUp = Gemv<WT, PA, UA, EPI_SWIGLU, NBUF, SL, false, PMD, FUSED_SLICE_GATE < SL ? FUSED_SLICE_GATE : SL>;
-    using Down = Gemv<WT, PB, PMD ? UPM : UB, EPI_RESID, NBUF, SL, PMD>;
-    using Head = Gemv<WT, PA, UA, EPI_PLAIN, NBUF, SL>;
-    __shared__ FusedShared sh;
+    using Qkv = Gemv<WT, NW, PA, UA, EPI_QKV, NBUF, SL, false, false, SL, KT>;
+    using Oproj = Gemv<WT, NW, PA, UO, EPI_RESID, NBUF, SL>;
+    using GateUp = Gemv<WT, NW, PA, UA, EPI_SWIGLU, NBUF, SL, false, PMD, FUSED_SLICE_GATE < SL ? FUSED_SLICE_GATE : SL>;
+    using Down = Gemv<WT, NW, PB, PMD ? UPM : UB, EPI_RESID, NBUF, SL, PMD>;
+    using Head = Gemv<WT, NW, PA, UA, EPI_PLAIN, NBUF, SL>;
+    __shared__ FusedShared<NW> sh;
     __shared__ __align__(16) float dyn[NT * Store<KT>::VEC];
 
     DevState *st = a.sup.st;
@@ -832,14 +838,14 @@ __global__ __launch_bounds__(NT) void fused_forward_kernel(const FusedArgs a) {
     }
 }
 
-template <typename WT, typename KT, int PA, int PB> struct Variant {
+template <typename WT, typename KT, int NW, int PA, int PB> struct Variant {
     static hipError_t launch(hipStream_t s, const FusedArgs &a, int blocks) {
-        hipLaunchKernelGGL((fused_forward_kernel<WT, KT, PA, PB>), dim3(blocks), dim3(NT), 0, s, a);
+        hipLaunchKernelGGL((fused_forward_kernel<WT, KT, NW, PA, PB>), dim3(blocks), dim3(NT), 0, s, a);
         return hipGetLastError();
     }
     static int blocks_per_cu() {
         int n = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (const void *)fused_forward_kernel<WT, KT, PA, PB>, NT, 0) != hipSuccess) {
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (const void *)fused_forward_kernel<WT, KT, NW, PA, PB>, NT, 0) != hipSuccess) {
             (void)hipGetLastError();
             return 0;
         }
@@ -847,32 +853,36 @@ template <typename WT, typename KT, int PA, int PB> struct Variant {
     }
 };
 
-// The instantiations that exist: passes needed to cover d_model and d_ffn with NW waves
-// (bf16: 4096 columns per pass).  (1,1) and (1,2): small models; (1,3): the Llama-2-7B shape;
-// (2,4): 13B; (2,7): 70B.  Calls f(Variant<...>{}) for the one that serves the shape.
+// The instantiations that exist, <waves side by side on a row, passes of theirs over d_model, over d_ffn>: (8, 2, 7) the 70B shape, (8, 2, 4)
+// 13B, (8, 1, 3) Llama-2-7B, (8, 1, 1) and (8, 1, 2) d_model up to 4096 in bf16.  Below that a row leaves most of eight waves idle: one
+// wave to a row where one wave's columns hold d_model (256 in fp32, 512 in bf16) and four of them d_ffn, four waves up to 1024 and
+// 2048.  The forward by events, us, eight waves -> this: one wave, fp32 256 x 1024, two layers 51.9 -> 46.1, six 134.5 -> 117.9; bf16 512 x
+// 1408 56.1 -> 48.5; four waves, fp32 512 x 2048 57.6 -> 49.2, 1024 x 2816 138 -> 116; bf16 1024 x 4096 143.5 -> 106, 2048 x 5504
+// (four layers) 172 -> 138, eight layers of 2048 x 6144 328 -> 268.  Tried: taller tiles (0 .. 10 % slower), two waves to a row (-4 .. +3 %), four
+// waves in three and seven passes for 13B (1 %).  PM and CHUNKS are for eight waves: their tiles would be one row.
 // The cache is fp32, or fp16 for a bf16 model that asked for it.
 template <typename F>
 bool with_variant(int dtype, int kv_half, int d_model, int d_ffn, F &&f) {
-    const int vec = dtype == SPD_DTYPE_BF16 ? 8 : 4;
-    const int span = NW * WAVE * vec;
-    const int pa = (d_model + span - 1) / span, pb = (d_ffn + span - 1) / span;
-    if (dtype == SPD_DTYPE_BF16 && kv_half) {
-        if (pa == 1 && pb == 1) return f(Variant<bf16_t, half_t, 1, 1>{}), true;
-        if (pa == 1 && pb == 2) return f(Variant<bf16_t, half_t, 1, 2>{}), true;
-        if (pa == 1 && pb == 3) return f(Variant<bf16_t, half_t, 1, 3>{}), true;
-        if (pa == 2 && pb == 4) return f(Variant<bf16_t, half_t, 2, 4>{}), true;
-        if (pa == 2 && pb == 7) return f(Variant<bf16_t, half_t, 2, 7>{}), true;
-    } else if (dtype == SPD_DTYPE_BF16) {
-        if (pa == 1 && pb == 1) return f(Variant<bf16_t, float, 1, 1>{}), true;
-        if (pa == 1 && pb == 2) return f(Variant<bf16_t, float, 1, 2>{}), true;
-        if (pa == 1 && pb == 3) return f(Variant<bf16_t, float, 1, 3>{}), true;
-        if (pa == 2 && pb == 4) return f(Variant<bf16_t, float, 2, 4>{}), true;
-        if (pa == 2 && pb == 7) return f(Variant<bf16_t, float, 2, 7>{}), true;
-    } else if (!kv_half) {
-        if (pa == 1 && pb == 1) return f(Variant<float, float, 1, 1>{}), true;
-        if (pa == 1 && pb == 2) return f(Variant<float, float, 1, 2>{}), true;
-        if (pa == 1 && pb == 3) return f(Variant<float, float, 1, 3>{}), true;
-    }
+    const int vec = dtype == SPD_DTYPE_BF16 ? 8 : 4, wave = WAVE * vec;
+    const bool one = d_model <= wave && d_ffn <= 4 * wave, four = d_model <= 4 * wave && d_ffn <= 12 * wave;
+    const int pa = (d_model + 8 * wave - 1) / (8 * wave), pb = (d_ffn + 8 * wave - 1) / (8 * wave);
+    auto serve = [&](auto wt, auto kt) {
+        using WT = decltype(wt);
+        using KT = decltype(kt);
+        if (one) return f(Variant<WT, KT, 1, 1, 4>{}), true;
+        if (four) return f(Variant<WT, KT, 4, 1, 3>{}), true;
+        if (pa == 1 && pb == 1) return f(Variant<WT, KT, 8, 1, 1>{}), true;
+        if (pa == 1 && pb == 2) return f(Variant<WT, KT, 8, 1, 2>{}), true;
+        if (pa == 1 && pb == 3) return f(Variant<WT, KT, 8, 1, 3>{}), true;
+        if constexpr (sizeof(WT) == 2) {
+            if (pa == 2 && pb == 4) return f(Variant<WT, KT, 8, 2, 4>{}), true;
+            if (pa == 2 && pb == 7) return f(Variant<WT, KT, 8, 2, 7>{}), true;
+        }
+        return false;
+    };
+    if (dtype == SPD_DTYPE_BF16 && kv_half) return serve(bf16_t{}, half_t{});
+    if (dtype == SPD_DTYPE_BF16) return serve(bf16_t{}, float{});
+    if (!kv_half) return serve(float{}, float{});
     return false;
 }
 

@@ -747,6 +747,40 @@ def test_fused_and_per_operator_forward_agree(tiny):
     np.testing.assert_allclose(out["fused"][0], out["per_operator"][0], rtol=0, atol=2e-5 * np.abs(out["fused"][0]).max())
 
 
+@pytest.mark.parametrize("dtype,d,heads,kv_heads,ffn", [
+    ("fp32", 32, 2, 1, 40), ("fp32", 256, 4, 2, 1024), ("fp32", 256, 4, 4, 1028), ("fp32", 272, 17, 17, 1024), ("fp32", 1024, 8, 8, 3072), ("fp32", 1024, 8, 2, 3076),
+    ("fp32", 1040, 65, 13, 3072), ("bf16", 512, 8, 8, 2048), ("bf16", 512, 8, 2, 2056), ("bf16", 528, 33, 33, 2048), ("bf16", 2048, 16, 4, 6144),
+    ("bf16", 2048, 16, 16, 6152), ("bf16", 2064, 129, 129, 6144)])
+def test_persistent_forward_of_one_four_and_eight_waves_to_a_row(dtype, d, heads, kv_heads, ffn):
+    """Either side of every line between one, four and eight waves to a row (the last widths that one and four waves hold, and the first
+    that they do not), rows far narrower than one wave, a vocabulary that leaves the last tiles ragged: prefix token by token, then
+    timesteps, against the forward of one kernel per product.  Both are fp32 sums of the same products in another order."""
+    pkg = P()
+    shape = synth.ModelShape("waves", 2, d, heads, kv_heads, ffn, 518, dtype)
+    w = synth.make_weights(shape, seed=d)
+    prefix = synth.make_prefix_uniform(shape.vocab, 5, seed=ffn)
+    dc = pkg.SpdDecodeCfg(3, 0.0, 1.0, 0.1)
+    for kv_dtype in ("fp32", "fp16")[:1 if dtype == "fp32" else 2]:
+        sess = session(shape, w, max_ctx=12, kv_dtype=kv_dtype)
+        try:
+            sess.spd_set_dense_prefill(False)
+            logits = []
+            for path in ("fused", "per_operator"):
+                select_path(sess, path)
+                sess.spd_prefill(prefix)
+                got = [sess.spd_read_logits()]
+                sess.spd_step(dc)
+                for t in range(3):
+                    sess.spd_set_state(np.resize(prefix + t, (3, 5)).astype(np.int32) % shape.vocab, np.array([-1.0, -2.0, -2.5], np.float32))
+                    sess.spd_step(dc)
+                    got.append(sess.spd_read_logits())
+                logits.append(got)
+            for x, y in zip(*logits):
+                np.testing.assert_allclose(x, y, rtol=0, atol=(2e-5 if kv_dtype == "fp32" else 1e-3) * np.abs(y).max())   # (1e-3: keys and values that round to the other fp16 neighbour)
+        finally:
+            sess.close()
+
+
 @pytest.mark.parametrize("max_ctx", [512, 513])
 def test_per_operator_attention_where_the_merge_begins(max_ctx):
     """Four query heads per cached head of 64 in fp16: up to 512 positions the longest context is one chunk and attention one
