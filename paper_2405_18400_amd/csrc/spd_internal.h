@@ -144,10 +144,9 @@ struct NucleusArgs {
     DevState *st;
     const float *pm, *ps, *pn;   // per-slice max, sum of exp and min of logit / tau (topk_partial)
     int32_t n_part, per_part;    // one block per slice of per_part entries
-    unsigned long long *sc_pb;   // scratch, [vocab]: first-level bucket above the probability in 40-bit fixed point
     unsigned *sc_count;          // blocks that have finished their slice; zero between calls
     unsigned long long *sc_hist; // scratch, [2048]: entry count above probability mass per first-level bucket; zero between calls
-    uint16_t *sc_bk;             // scratch, [32768]: first-level bucket per entry, 0xFFFF past the vocabulary (vocab <= 32768 only)
+    uint16_t *sc_bk;             // scratch, [vocab rounded up to eight]: first-level bucket + 1 per entry, 0 past the vocabulary
     float top_p, tau;
     float u;                     // the draw, or negative: it is in the state (a captured launch's arguments are fixed)
     int32_t first, advance;

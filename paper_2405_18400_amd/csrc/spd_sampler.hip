@@ -16,9 +16,7 @@
 //     smallest z (2048 buckets), stored per entry; mass and count per bucket of the slice (LDS
 //     atomics), added to the histogram in memory (one atomic per bucket the slice touches; sums
 //     of integers: the same in any order); the last block to finish goes on alone;
-//   stage B: that histogram (vocabularies beyond 32768 entries: built here from the entries'
-//     words instead), prefix sums over the buckets, the bucket
-//     in which the cumulative mass crosses x; should it hold more than a list's worth of
+//   stage B: that histogram, prefix sums over the buckets, the bucket in which the cumulative mass crosses x; should it hold more than a list's worth of
 //     entries it is cut again by key range (2048 sub-buckets per round: at most a few rounds
 //     even where thousands of entries tie); the bucket's entries are then ranked against one
 //     another (all pairs) and the first one whose cumulative mass crosses x is the answer.
@@ -36,7 +34,7 @@ constexpr int SNW = SNT / WAVE;
 constexpr int NB = 2 * SNT;        // buckets per level: two per thread in the prefix sums
 constexpr int LC = 256;            // entries that are ranked pairwise
 constexpr int ID_BITS = 23;        // token ids in a key (vocab <= 2^23)
-constexpr int ITEMS = 32;          // entries per thread that stage B keeps in registers (vocab <= 32768; else they are re-read)
+constexpr int PIECE = 8 * SNT;     // entries of one 16-byte piece of bucket numbers per thread
 constexpr float FX_ONE = 1099511627776.0f;   // 2^40: probability 1 in fixed point
 
 // exp(x) in fixed point, <= 2^40 (1 + a few ulp); the same bits wherever it is formed from an entry's logit.
@@ -136,102 +134,88 @@ __device__ __forceinline__ int crossing(Stage &s, int lv, unsigned long long x) 
     return b;
 }
 
-// Per entry, written by stage A where its bucket number does not stay in registers (not CACHED): one word with the first-level
-// bucket above the probability (x 2^40).  Written through to memory and read back coherently (the writers sit behind other
-// L2 caches; a device-wide fence would write back and invalidate whole caches -- tens of
-// microseconds -- where this is 8 bytes per entry).
-constexpr int PB_SHIFT = 48;
-constexpr unsigned long long P_MASK = (1ull << PB_SHIFT) - 1ull;
-constexpr unsigned long long NO_ENTRY = ~0ull;
-__device__ __forceinline__ unsigned long long load_pb(const unsigned long long *pb, int i) {
-    return __hip_atomic_load(as_global(pb) + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-// The entries i = tid, tid + SNT, ... that stage B walks several times.  The first walk reads
-// their words, CH at a time (one dependent trip to memory per CH entries: these walks are
-// chains of latencies, not bandwidth).  CACHED: the bucket numbers alone are stored, two to a
-// register here, and the walks -- which look for the entries of ONE bucket -- read only the
-// logits of those; otherwise every walk reads all words again.
-constexpr int CH = 16;
-template <bool CACHED>
+// The bucket numbers (one more, so that zero is no entry: past the vocabulary, where a load past the array's end returns zeros), 16 bits
+// per entry, written through to memory by stage A and read back coherently (the writers sit behind other L2 caches; a device-wide fence
+// would write back and invalidate whole caches -- tens of microseconds).  Stage B looks for the entries of ONE bucket at a time and reads
+// the logits of those.  A thread keeps PIECES pieces of eight numbers in registers; 0: the vocabulary has more, every walk reads them
+// again.  Beyond 32768 entries the last block used to build the histogram itself from eight bytes per entry, which every walk read again.
+// The kernel by events, top_p 0.9, 40000 / 50258 / 65536 / 100000 / 131072 / 262144 entries: 28.6 / 34.0 / 38.1 / 54.9 / 65.1 / 176 ->
+// 15.3 / 16.5 / 18.2 / 24.0 / 27.4 / 51 us; up to 32768 as before.
+constexpr int REREAD = 8;          // pieces per trip of a walk that reads the numbers again
+template <int PIECES>
 struct Entries {
-    const unsigned long long *pb;
+    static constexpr int HELD = PIECES ? PIECES : REREAD;
+    __amdgpu_buffer_rsrc_t ids;
     int vocab;
     const float *logits;
     float tau, lse;
-    unsigned bk[CACHED ? ITEMS / 2 : 1];
-    // CACHED: entry c of this thread is token 8 (tid + SNT (c / 8)) + c % 8 -- its bucket numbers are
-    // four 16-byte pieces of the per-entry bucket array (0xFFFF past the vocabulary)
-    static __device__ __forceinline__ int entry(int c) { return CACHED ? 8 * ((int)threadIdx.x + (c / 8) * SNT) + (c % 8) : (int)threadIdx.x + c * SNT; }
-    __device__ __forceinline__ void load_buckets(const uint16_t *ids) {
-        static_assert(!CACHED || ITEMS == 32, "four pieces of eight bucket numbers");
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(ids), 0, SNT * ITEMS * 2, 0x00020000);
+    unsigned bk[4 * HELD];
+    __device__ __forceinline__ void load(int first) {
 #pragma unroll
-        for (int r = 0; r < (CACHED ? 4 : 0); ++r) {
-            const u32x4 v = coherent_load16(rs, 16u * (threadIdx.x + (unsigned)(r * SNT)));
+        for (int r = 0; r < HELD; ++r) {
+            const u32x4 v = coherent_load16(ids, 16u * (threadIdx.x + (unsigned)((first + r) * SNT)));
             bk[4 * r] = v.x; bk[4 * r + 1] = v.y; bk[4 * r + 2] = v.z; bk[4 * r + 3] = v.w;
         }
     }
-    // f(an entry's bucket, its probability) for every entry of this thread
+    // entry c of this thread
+    static __device__ __forceinline__ int entry(int c) { return 8 * ((int)threadIdx.x + (c / 8) * SNT) + (c % 8); }
+    // f(i, its probability, its logit) for every entry of bucket b1 that this thread holds, its first one number 8 first
     template <typename F>
-    __device__ __forceinline__ void first_walk(F &&f) {
-        static_assert(!CACHED, "");
-        for (int i0 = threadIdx.x; i0 < vocab; i0 += SNT * CH) {
-            unsigned long long w[CH];
+    __device__ __forceinline__ void walk_held(int first, int b1, F &&f) {
+        constexpr int G = HELD / 4;
+        static_assert(HELD % 4 == 0, "a word of hits has one bit per entry of four pieces");
+        const unsigned both = (unsigned)(b1 + 1) | ((unsigned)(b1 + 1) << 16);
+        unsigned hits[G], any = 0u;
 #pragma unroll
-            for (int c = 0; c < CH; ++c) {
-                const int i = i0 + c * SNT;
-                w[c] = i < vocab ? load_pb(pb, i) : NO_ENTRY;
-            }
-#pragma unroll
-            for (int c = 0; c < CH; ++c)
-                if (w[c] != NO_ENTRY) f((int)(w[c] >> PB_SHIFT), w[c] & P_MASK);
-        }
-    }
-    // f(i, its probability, its logit) for every entry of this thread in bucket b1
-    template <typename F>
-    __device__ __forceinline__ void walk_bucket(int b1, F &&f) {
-        if (CACHED) {
-            static_assert(ITEMS == 32, "one bit per entry");
+        for (int g = 0; g < G; ++g) {
             unsigned others = 0u;                   // bit 15 - r: the lower number of register r is another; bit 31 - r: the upper one
-            const unsigned both = (unsigned)b1 | ((unsigned)b1 << 16);
 #pragma unroll
-            for (int r = 0; r < ITEMS / 2; ++r) {   // (three instructions for two bucket numbers: the block's waves share four SIMDs)
+            for (int r = 0; r < 16; ++r) {          // (three instructions for two bucket numbers: the block's waves share four SIMDs)
                 unsigned other;
-                asm("v_pk_min_u16 %0, %1, %2" : "=v"(other) : "v"(bk[r] ^ both), "v"(0x00010001u));
+                asm("v_pk_min_u16 %0, %1, %2" : "=v"(other) : "v"(bk[16 * g + r] ^ both), "v"(0x00010001u));
                 others = (others << 1) | other;
             }
-            unsigned hits = ~others;
-            while (hits) {   // (few: a bucket holds some dozens of the block's entries; two at a time)
-                const int c0 = __ffs(hits) - 1;
-                hits &= hits - 1u;
-                const bool two = hits != 0u;
-                const int c1 = two ? __ffs(hits) - 1 : c0;
-                hits &= hits - 1u;
-                const int i0 = entry(2 * (15 - c0 % 16) + c0 / 16), i1 = entry(2 * (15 - c1 % 16) + c1 / 16);
-                const float l0 = as_global(logits)[i0], l1 = as_global(logits)[i1];
-                f(i0, fixed_point(__fdiv_rn(l0, tau) - lse), l0);
-                if (two) f(i1, fixed_point(__fdiv_rn(l1, tau) - lse), l1);
-            }
-        } else {
-            for (int i0 = threadIdx.x; i0 < vocab; i0 += SNT * CH) {
-                unsigned long long w[CH];
+            hits[g] = ~others;
+            any |= hits[g];
+        }
+        auto next = [&]() {                         // (of the first word that has one, so that a lane's turns are as many as its entries)
+            unsigned word = hits[G - 1];
+            int at = G - 1;
 #pragma unroll
-                for (int c = 0; c < CH; ++c) {
-                    const int i = i0 + c * SNT;
-                    w[c] = i < vocab ? load_pb(pb, i) : NO_ENTRY;
-                }
+            for (int g = G - 2; g >= 0; --g)
+                if (hits[g]) { word = hits[g]; at = g; }
+            const int bit = __ffs(word) - 1;
+            word &= word - 1u;
+            any = 0u;
 #pragma unroll
-                for (int c = 0; c < CH; ++c)
-                    if ((int)(w[c] >> PB_SHIFT) == b1) f(i0 + c * SNT, w[c] & P_MASK, as_global(logits)[i0 + c * SNT]);
-            }
+            for (int g = 0; g < G; ++g) { hits[g] = g == at ? word : hits[g]; any |= hits[g]; }
+            return entry(8 * first + 32 * at + 2 * (15 - bit % 16) + bit / 16);
+        };
+        while (any) {   // (few: a bucket holds some dozens of the block's entries; two at a time)
+            const int i0 = next();
+            const bool two = any != 0u;
+            int i1 = i0;
+            if (two) i1 = next();
+            const float l0 = as_global(logits)[i0], l1 = as_global(logits)[i1];
+            f(i0, fixed_point(__fdiv_rn(l0, tau) - lse), l0);
+            if (two) f(i1, fixed_point(__fdiv_rn(l1, tau) - lse), l1);
+        }
+    }
+    // the same for every entry of the bucket among this thread's
+    template <typename F>
+    __device__ __forceinline__ void walk_bucket(int b1, F &&f) {
+        if (PIECES) { walk_held(0, b1, f); return; }
+        for (int first = 0; first * PIECE < vocab; first += REREAD) {
+            load(first);
+            walk_held(first, b1, f);
         }
     }
 };
 
 // The first entry in the order whose cumulative mass reaches (STRICT: exceeds) x; the last
 // entry if none does.  Level-1 prefix sums are in s.hm[0].  Result in s.r_*.
-template <bool STRICT, bool CACHED>
-__device__ __forceinline__ void search(Stage &s, Entries<CACHED> &en, unsigned long long x) {
+template <bool STRICT, int PIECES>
+__device__ __forceinline__ void search(Stage &s, Entries<PIECES> &en, unsigned long long x) {
     const int t = threadIdx.x;
     const int b1 = crossing<STRICT>(s, 0, x);
     unsigned long long base_m = mass_of(s.hm[0][b1]);
@@ -329,8 +313,8 @@ __device__ __forceinline__ void search(Stage &s, Entries<CACHED> &en, unsigned l
 // entry whose cumulative mass crosses x is the one that reaches it while the entry before does not, which each entry
 // knows by itself once it has its rank and mass.  Slots of Stage are per question, cleared beforehand.  32000 entries, the kernel:
 // 15.2 -> 13.2 us.
-template <bool STRICT, bool CACHED>
-__device__ __forceinline__ void ask(Stage &s, Entries<CACHED> &en, const float *logits, int which, unsigned long long x, const unsigned long long (&w)[3]) {
+template <bool STRICT, int PIECES>
+__device__ __forceinline__ void ask(Stage &s, Entries<PIECES> &en, const float *logits, int which, unsigned long long x, const unsigned long long (&w)[3]) {
     const int t = threadIdx.x;
     auto reaches = [&](unsigned long long m) { return STRICT ? m > x : m >= x; };
 #pragma unroll
@@ -341,7 +325,14 @@ __device__ __forceinline__ void ask(Stage &s, Entries<CACHED> &en, const float *
     const unsigned long long from = s.q_from[which];
     const unsigned base_c = count_of(from);
     if (b1 < 0 || count_of(s.q_to[which]) - base_c > (unsigned)LC) {   // (the same for every thread)
-        search<STRICT, CACHED>(s, en, x);
+        if constexpr (PIECES == 8) {   // (its own registers beside these would be more than there are: the numbers are read again)
+            Entries<0> again;
+            again.ids = en.ids; again.vocab = en.vocab; again.logits = en.logits; again.tau = en.tau; again.lse = en.lse;
+            search<STRICT, 0>(s, again, x);
+            if (!STRICT) en.load(0);
+        } else {
+            search<STRICT, PIECES>(s, en, x);
+        }
         if (t == 0) s.r_logit = as_global(logits)[s.r_id];
         __syncthreads();
         return;
@@ -379,7 +370,7 @@ __device__ __forceinline__ void ask(Stage &s, Entries<CACHED> &en, const float *
     __syncthreads();
 }
 
-template <bool CACHED>
+template <int PIECES>
 __global__ __launch_bounds__(SNT) void nucleus_kernel(const NucleusArgs a) {
     __shared__ Stage s;
     const int tid = threadIdx.x, lane = tid & (WAVE - 1);
@@ -408,29 +399,23 @@ __global__ __launch_bounds__(SNT) void nucleus_kernel(const NucleusArgs a) {
     const float scale = range > 0.f ? (float)NB / range : 0.f;
 
     // ---- stage A: this block's slice
-    if (CACHED) {   // the slice's histogram
-        s.hm[1][2 * tid] = 0ull; s.hm[1][2 * tid + 1] = 0ull;
-        __syncthreads();
-    }
-    for (int i = lo + tid; i < hi; i += SNT) {
+    s.hm[1][2 * tid] = 0ull; s.hm[1][2 * tid + 1] = 0ull;          // the slice's histogram
+    __syncthreads();
+    const int end = hi == a.vocab ? (hi + 7) & ~7 : hi;           // (a piece that the vocabulary ends in: no entries behind it)
+    for (int i = lo + tid; i < end; i += SNT) {
+        if (i >= hi) { __hip_atomic_store(as_global(a.sc_bk) + i, (uint16_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); continue; }
         const float z = __fdiv_rn(i < lo + SNT ? first_logit : as_global(a.logits)[i], a.tau);
         const float fb = (M - z) * scale;                          // monotonic in z; anything beyond lands in the last bucket
         const int b = fb < (float)(NB - 1) ? (int)fb : NB - 1;
-        const unsigned long long pf = fixed_point(z - lse);
         const int bb = b < 0 ? 0 : b;
-        if (!CACHED) __hip_atomic_store(as_global(a.sc_pb) + i, ((unsigned long long)bb << PB_SHIFT) | pf, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (CACHED) {
-            __hip_atomic_store(as_global(a.sc_bk) + i, (uint16_t)bb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            atomicAdd(&s.hm[1][bb], pf + ONE_ENTRY);
-        }
+        __hip_atomic_store(as_global(a.sc_bk) + i, (uint16_t)(bb + 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        atomicAdd(&s.hm[1][bb], fixed_point(z - lse) + ONE_ENTRY);
     }
-    if (CACHED) {
-        __syncthreads();
+    __syncthreads();
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const unsigned long long w = s.hm[1][2 * tid + q];
-            if (w) (void)__hip_atomic_fetch_add(as_global(a.sc_hist) + 2 * tid + q, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+    for (int q = 0; q < 2; ++q) {
+        const unsigned long long w = s.hm[1][2 * tid + q];
+        if (w) (void)__hip_atomic_fetch_add(as_global(a.sc_hist) + 2 * tid + q, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's write-through stores have been acknowledged
     __syncthreads();
@@ -445,31 +430,21 @@ __global__ __launch_bounds__(SNT) void nucleus_kernel(const NucleusArgs a) {
     int tail[SPD_TAIL];
 #pragma unroll
     for (int q = 0; q < SPD_TAIL; ++q) tail[q] = a.first ? st->prefix_tail[q] : st->tails[0][q];
-    Entries<CACHED> en;
-    en.pb = a.sc_pb; en.vocab = a.vocab; en.logits = a.logits; en.tau = a.tau; en.lse = lse;
+    Entries<PIECES> en;
+    en.ids = __builtin_amdgcn_make_buffer_rsrc(a.sc_bk, 0, ((a.vocab + 7) & ~7) * 2, 0x00020000);
+    en.vocab = a.vocab; en.logits = a.logits; en.tau = a.tau; en.lse = lse;
     if (tid == 0) { s.q_bucket[0] = s.q_bucket[1] = -1; s.n_list = 0; }
-    unsigned long long h0, h1, sums[3];
-    if constexpr (CACHED) {
-        // the histogram all blocks have added to (left at zero for the next call), and this thread's bucket numbers
-        const __amdgpu_buffer_rsrc_t hrs = __builtin_amdgcn_make_buffer_rsrc(a.sc_hist, 0, NB * 8, 0x00020000);
-        const u32x4 v = coherent_load16(hrs, 16u * (unsigned)tid);   // one 16-byte piece: this thread's two words
-        en.load_buckets(a.sc_bk);
-        h0 = ((unsigned long long)v.y << 32) | v.x;
-        h1 = ((unsigned long long)v.w << 32) | v.z;
-    } else {
-        s.hm[0][2 * tid] = 0ull; s.hm[0][2 * tid + 1] = 0ull;
-        __syncthreads();
-        en.first_walk([&](int b, unsigned long long pf) {
-            atomicAdd(&s.hm[0][b], pf + ONE_ENTRY);
-        });
-        __syncthreads();
-        h0 = s.hm[0][2 * tid]; h1 = s.hm[0][2 * tid + 1];
-    }
+    // the histogram all blocks have added to (left at zero for the next call), and this thread's bucket numbers
+    const __amdgpu_buffer_rsrc_t hrs = __builtin_amdgcn_make_buffer_rsrc(a.sc_hist, 0, NB * 8, 0x00020000);
+    const u32x4 v = coherent_load16(hrs, 16u * (unsigned)tid);   // one 16-byte piece: this thread's two words
+    if (PIECES) en.load(0);
+    const unsigned long long h0 = ((unsigned long long)v.y << 32) | v.x, h1 = ((unsigned long long)v.w << 32) | v.z;
+    unsigned long long sums[3];
     prefix_sums(s, 0, h0, h1, sums);
 
     // 1. the nucleus: the first entry whose cumulative probability reaches top_p, and all before it
     const unsigned long long x_p = (unsigned long long)((double)a.top_p * (double)FX_ONE);
-    ask<false, CACHED>(s, en, a.logits, 0, x_p, sums);
+    ask<false, PIECES>(s, en, a.logits, 0, x_p, sums);
     const unsigned long long mass_fx = s.r_mass, key_T = s.r_key;
     const unsigned size = s.r_index + 1u;
     const int id_T = s.r_id;
@@ -477,15 +452,13 @@ __global__ __launch_bounds__(SNT) void nucleus_kernel(const NucleusArgs a) {
     if (tid == 0) s.n_list = 0;     // (everybody has read it; the next barrier stands before its next use)
     // 2. the draw: the first entry whose cumulative probability exceeds u * mass (within the nucleus)
     const unsigned long long x_u = (unsigned long long)((double)u * (double)mass_fx);
-    ask<true, CACHED>(s, en, a.logits, 1, x_u, sums);
+    ask<true, PIECES>(s, en, a.logits, 1, x_u, sums);
     int tok = s.r_id;
     float logit = s.r_logit;
     if (s.r_key > key_T) { tok = id_T; logit = logit_T; }   // (only rounding could take it past the nucleus)
 
-    if (CACHED) {
-        __hip_atomic_store(as_global(a.sc_hist) + 2 * tid, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(as_global(a.sc_hist) + 2 * tid + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    __hip_atomic_store(as_global(a.sc_hist) + 2 * tid, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(as_global(a.sc_hist) + 2 * tid + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (tid == 0) {   // the pass's state: one draft (k = 1, gamma = 1)
         const float logp = __fdiv_rn(logit, a.tau) - lse;
 #pragma unroll
@@ -511,9 +484,13 @@ __global__ __launch_bounds__(SNT) void nucleus_kernel(const NucleusArgs a) {
 
 namespace spdk {
 
+// As many pieces of bucket numbers per thread as hold the vocabulary, up to eight: 40000 and 65536 entries, kernel by events: eight held 14.2 and
+// 15.7 us, read again 16.8 and 18.5; 65538 and 131072 entries, sixteen held 18.7 and 22.2 (and four registers spilled), read again 17.7 and 21.8.
 hipError_t nucleus(hipStream_t s, const NucleusArgs &a) {
-    if (a.vocab <= SNT * ITEMS) hipLaunchKernelGGL(nucleus_kernel<true>, dim3(a.n_part), dim3(SNT), 0, s, a);
-    else hipLaunchKernelGGL(nucleus_kernel<false>, dim3(a.n_part), dim3(SNT), 0, s, a);
+    const dim3 grid(a.n_part), block(SNT);
+    if (a.vocab <= 4 * PIECE) hipLaunchKernelGGL(nucleus_kernel<4>, grid, block, 0, s, a);
+    else if (a.vocab <= 8 * PIECE) hipLaunchKernelGGL(nucleus_kernel<8>, grid, block, 0, s, a);
+    else hipLaunchKernelGGL(nucleus_kernel<0>, grid, block, 0, s, a);
     return hipGetLastError();
 }
 

@@ -217,6 +217,31 @@ def test_neighbouring_entries_in_one_bucket_and_the_next(vocab):
         sess.close()
 
 
+@pytest.mark.parametrize("vocab", [32766, 32770, 65534, 65536, 65538, 131072, 140002])
+def test_vocabularies_around_the_bucket_numbers_a_thread_holds(vocab):
+    """Four pieces of eight bucket numbers per thread, eight, or all read again per walk; a last piece that the vocabulary ends in; slices of
+    1024 entries and longer ones; buckets that fit the list, and ties by the thousand that do not (cut again by key)."""
+    pkg = P()
+    shape = synth.ModelShape("pieces", 1, 64, 2, 2, 128, vocab, "fp32")
+    sess = pkg.Session(shape, synth.make_weights(shape, seed=2), max_ctx=32, k_max=8)
+    try:
+        sess.spd_prefill([1, 2, 3])
+        rng = np.random.default_rng(vocab)
+        ends = np.full(vocab, -12.0)
+        ends[[0, 7, 8, vocab // 2, vocab - 2, vocab - 1]] = [0.5, 1.0, 0.2, 0.7, 0.9, 1.1]      # the mass at the array's ends
+        for lg in (rng.normal(size=vocab) * 3, rng.integers(0, 6, vocab) * 1.5, ends, np.zeros(vocab)):
+            lg = lg.astype(np.float32)
+            for u in (0.0, 0.35, 0.8, 0.995):
+                u = float(np.float32(u))
+                rec = O.nucleus_sample(lg, 0.93, 1.0, u, keep_logits=True)
+                tok = _sample_only(sess, pkg.SpdSampleCfg(0.93, 1.0), lg, u)
+                check_draw(sess, rec, 0.93, 1.0, u, tok, rec.logp, 1e-5)
+                if rec.margin_nucleus > 1e-5:
+                    assert sess.spd_get_nucleus_info()[0] == rec.nucleus_size
+    finally:
+        sess.close()
+
+
 def test_error_paths(tiny):
     shape, w, prefix = tiny
     pkg = P()
