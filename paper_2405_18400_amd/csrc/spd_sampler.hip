@@ -140,7 +140,7 @@ __device__ __forceinline__ int crossing(Stage &s, int lv, unsigned long long x) 
 // the logits of those.  A thread keeps PIECES pieces of eight numbers in registers; 0: the vocabulary has more, every walk reads them
 // again.  Beyond 32768 entries the last block used to build the histogram itself from eight bytes per entry, which every walk read again.
 // The kernel by events, top_p 0.9, 40000 / 50258 / 65536 / 100000 / 131072 / 262144 entries: 28.6 / 34.0 / 38.1 / 54.9 / 65.1 / 176 ->
-// 15.3 / 16.5 / 18.2 / 24.0 / 27.4 / 51 us; up to 32768 as before.
+// 15.3 / 15.9 / 17.4 / 23.0 / 25.8 / 50 us; up to 32768 as before.
 constexpr int REREAD = 8;          // pieces per trip of a walk that reads the numbers again
 template <int PIECES>
 struct Entries {
@@ -350,8 +350,15 @@ __device__ __forceinline__ void ask(Stage &s, Entries<PIECES> &en, const float *
         unsigned long long mass = 0ull;
         if (i < nl) {
             const unsigned long long ki = s.lk[i];
-            for (int j = part; j < nl; j += PARTS)
-                if (s.lk[j] < ki) { ++cnt; mass += s.lp[j]; }
+            constexpr int SIDE = 4;    // pairs side by side: their reads of the list are one trip to LDS (one by one: 65536 entries, top_p 0.98 19.5 -> 18.0 us)
+            for (int j0 = part; j0 < nl; j0 += SIDE * PARTS) {
+                unsigned long long kj[SIDE], pj[SIDE];
+#pragma unroll
+                for (int q = 0; q < SIDE; ++q) { const int j = min(j0 + q * PARTS, LC - 1); kj[q] = s.lk[j]; pj[q] = s.lp[j]; }
+#pragma unroll
+                for (int q = 0; q < SIDE; ++q)
+                    if (j0 + q * PARTS < nl && kj[q] < ki) { ++cnt; mass += pj[q]; }
+            }
         }
         mass = group_sum64<PARTS>(mass + ((unsigned long long)cnt << CNT_SHIFT));   // (as in a histogram word: at most 256 entries, masses below 2^42)
         cnt = count_of(mass);
