@@ -13,13 +13,14 @@
 //
 //   stage A (one block per slice of the vocabulary, all compute units in parallel): scaled
 //     logit z, probability, and a bucket number that is linear in z between the largest and the
-//     smallest z (2048 buckets), stored per entry; mass and count per bucket of the slice (LDS
+//     smallest z (2048 buckets), which is stored; mass and count per bucket of the slice (LDS
 //     atomics), added to the histogram in memory (one atomic per bucket the slice touches; sums
 //     of integers: the same in any order); the last block to finish goes on alone;
-//   stage B: that histogram, prefix sums over the buckets, the bucket in which the cumulative mass crosses x; should it hold more than a list's worth of
-//     entries it is cut again by key range (2048 sub-buckets per round: at most a few rounds
-//     even where thousands of entries tie); the bucket's entries are then ranked against one
-//     another (all pairs) and the first one whose cumulative mass crosses x is the answer.
+//   stage B: that histogram, prefix sums over the buckets, the bucket in which the cumulative
+//     mass crosses x; should it hold more than a list's worth of entries it is cut again by key
+//     range (2048 sub-buckets per round: at most a few rounds even where thousands of entries
+//     tie); the bucket's entries are then ranked against one another (all pairs) and the first
+//     one whose cumulative mass crosses x is the answer.
 //   The first-level histogram serves both questions.
 #include "spd_device.h"
 

@@ -195,8 +195,8 @@ def test_large_vocabulary_uses_the_uncached_path():
 @pytest.mark.parametrize("vocab", [66, 1024, 1026, 4098, 32768, 32770])
 def test_neighbouring_entries_in_one_bucket_and_the_next(vocab):
     """The entries of a bucket are found two bucket numbers at a time: ids side by side that share a bucket, that lie in buckets whose numbers
-    differ in the last bit alone, and at random; slices of one to 32 blocks, ragged ones, the last vocabulary whose bucket
-    numbers stay in registers and the first beyond."""
+    differ in the last bit alone, and at random; slices of one to 32 blocks, ragged ones, the last vocabulary of four
+    pieces of bucket numbers per thread and the first beyond."""
     pkg = P()
     shape = synth.ModelShape("buckets", 1, 64, 2, 2, 128, vocab, "fp32")
     sess = pkg.Session(shape, synth.make_weights(shape, seed=2), max_ctx=32, k_max=8)
