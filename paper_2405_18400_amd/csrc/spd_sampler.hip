@@ -258,10 +258,9 @@ __device__ __forceinline__ void search(Stage &s, Entries<PIECES> &en, unsigned l
         base_m += mass_of(s.hm[1][b2]);
         base_c += count_of(s.hm[1][b2]);
         n = count_of(s.hm[1][b2 + 1]) - count_of(s.hm[1][b2]);
-        const unsigned long long lo2 = klo + ((unsigned long long)b2 << sh);
-        const unsigned long long hi2 = lo2 + ((1ull << sh) - 1ull);
-        klo = lo2;
-        khi = hi2 < khi ? hi2 : khi;
+        klo += (unsigned long long)b2 << sh;
+        const unsigned long long span = (1ull << sh) - 1ull;       // (klo + span itself may pass 2^64: keys of probabilities near zero end there)
+        khi = khi - klo > span ? klo + span : khi;
         __syncthreads();
     }
     // the candidates into the list (in any order: they are ranked below)

@@ -242,6 +242,46 @@ def test_vocabularies_around_the_bucket_numbers_a_thread_holds(vocab):
         sess.close()
 
 
+@pytest.mark.parametrize("vocab", [2050, 32000, 40000, 65538])
+def test_masked_logits(vocab):
+    """Tokens excluded with -inf, the type's lowest value or a large negative one, next to live entries from the likeliest down to
+    probabilities of 1e-9: many more entries between two keys than are ranked pairwise, keys up to the last one that a
+    64-bit word holds (a range of keys that ends there used to come out empty, its answer an entry that nothing had written)."""
+    pkg = P()
+    shape = synth.ModelShape("masked", 1, 64, 2, 2, 128, vocab, "fp32")
+    sess = pkg.Session(shape, synth.make_weights(shape, seed=2), max_ctx=32, k_max=8)
+    try:
+        sess.spd_prefill([1, 2, 3])
+        rng = np.random.default_rng(vocab)
+        few = 1200.0 / vocab
+        for mask in (-np.inf, float(np.finfo(np.float32).min), -1e9):
+            tail = np.full(vocab, mask)
+            tail[rng.permutation(vocab)[:1000]] = -9.0 - rng.random(1000)      # one likely entry, the rest of the mass spread thin
+            tail[vocab // 3] = 0.0
+            vectors = [tail, np.full(vocab, mask)]
+            vectors[1][vocab - 1] = 1.0                                        # a single live entry
+            for live in (0.5, few):
+                lg = rng.normal(size=vocab) * 3
+                lg[rng.random(vocab) >= live] = mask
+                vectors.append(lg)
+            lg = np.full(vocab, mask)
+            lg[:700] = rng.normal(size=700) * 3                               # whole slices without an entry
+            vectors.append(lg)
+            for lg in vectors:
+                lg, n_dec = lg.astype(np.float32), 0
+                for top_p, u in ((0.5, 0.3), (0.9, 0.05), (0.9, 0.97), (0.98, 0.6), (0.9999, 0.93), (1.0, 0.02), (1.0, 0.875), (1.0, 0.99)):
+                    u = float(np.float32(u))
+                    rec = O.nucleus_sample(lg, top_p, 1.0, u, keep_logits=True)
+                    tok = _sample_only(sess, pkg.SpdSampleCfg(top_p, 1.0), lg, u)
+                    assert lg[tok] > -1e8
+                    n_dec += check_draw(sess, rec, top_p, 1.0, u, tok, rec.logp, 1e-5)
+                    if rec.margin_nucleus > 1e-5:
+                        assert sess.spd_get_nucleus_info()[0] == rec.nucleus_size
+                assert n_dec >= 4
+    finally:
+        sess.close()
+
+
 def test_error_paths(tiny):
     shape, w, prefix = tiny
     pkg = P()
