@@ -13,7 +13,7 @@
 //
 //   stage A (one block per slice of the vocabulary, all compute units in parallel): scaled
 //     logit z, probability, and a bucket number that is linear in z between the largest and the
-//     smallest z (2048 buckets), which is stored; mass and count per bucket of the slice (LDS
+//     smallest z with a probability above zero (2048 buckets), which is stored; mass and count per bucket of the slice (LDS
 //     atomics), added to the histogram in memory (one atomic per bucket the slice touches; sums
 //     of integers: the same in any order); the last block to finish goes on alone;
 //   stage B: that histogram, prefix sums over the buckets, the bucket in which the cumulative
@@ -211,6 +211,19 @@ struct Entries {
             walk_held(first, b1, f);
         }
     }
+    // the highest token of the bucket among this thread's, -1: none
+    __device__ __forceinline__ int last_of_bucket(int b1) {
+        int last = -1;
+        for (int first = 0; PIECES ? first == 0 : first * PIECE < vocab; first += REREAD) {
+            if (!PIECES) load(first);
+#pragma unroll
+            for (int r = 0; r < 4 * HELD; ++r) {    // (a thread's tokens ascend)
+                if ((bk[r] & 0xFFFFu) == (unsigned)(b1 + 1)) last = entry(8 * first + 2 * r);
+                if (bk[r] >> 16 == (unsigned)(b1 + 1)) last = entry(8 * first + 2 * r + 1);
+            }
+        }
+        return last;
+    }
 };
 
 // The first entry in the order whose cumulative mass reaches (STRICT: exceeds) x; the last
@@ -222,6 +235,17 @@ __device__ __forceinline__ void search(Stage &s, Entries<PIECES> &en, unsigned l
     unsigned long long base_m = mass_of(s.hm[0][b1]);
     unsigned base_c = count_of(s.hm[0][b1]);
     unsigned n = count_of(s.hm[0][b1 + 1]) - base_c;
+    if (mass_of(s.hm[0][b1 + 1]) == base_m) {   // (the same for every thread) nothing reaches x and the last bucket has no mass: its entries stand by id.
+                                                // (a bucket that does not come here has mass; 50258 entries, 97 % -inf, top_p 1: 548 -> 15 us)
+        if (t == 0) s.best = -1;
+        __syncthreads();
+        const int last = (int)wave_all_max((float)en.last_of_bucket(b1));   // (ids are exact in a float)
+        if ((t & (WAVE - 1)) == 0) atomicMax(&s.best, last);
+        __syncthreads();
+        if (t == 0) { s.r_id = s.best; s.r_key = sort_key(0ull, s.best); s.r_mass = base_m; s.r_index = base_c + n - 1u; }
+        __syncthreads();
+        return;
+    }
     // the candidates: level-1 bucket b1, and within it the key range [klo, khi] once it has been cut
     unsigned long long klo = 0ull, khi = ~0ull;
     bool cut = false;
@@ -402,7 +426,10 @@ __global__ __launch_bounds__(SNT) void nucleus_kernel(const NucleusArgs a) {
     for (int q = 0; q < 2; ++q)
         if (lane + q * WAVE < a.n_part) S += ps[q] * expf(pm[q] - M);
     const float lse = M + logf(wave_all_sum(S));
-    const float range = M - mn;
+    // The buckets end where the fixed-point probabilities do (exp(-29) 2^40 < 1), the rest shares the last one: masked logits (-inf, -FLT_MAX, -1e9)
+    // would stretch them until all live entries fell into one.  Half of the entries -inf, top_p 0.9,
+    // 32000 / 50258 / 131072 entries, the kernel by events: 382 / 603 / 1482 -> 12.9 / 14.7 / 20.9 us.
+    const float range = M - fmaxf(mn, lse - 29.f);
     const float scale = range > 0.f ? (float)NB / range : 0.f;
 
     // ---- stage A: this block's slice

@@ -267,6 +267,7 @@ def test_masked_logits(vocab):
             lg = np.full(vocab, mask)
             lg[:700] = rng.normal(size=700) * 3                               # whole slices without an entry
             vectors.append(lg)
+            vectors.append(rng.normal(size=vocab) * 30)                        # no mask, most probabilities zero in 40 bits all the same
             for lg in vectors:
                 lg, n_dec = lg.astype(np.float32), 0
                 for top_p, u in ((0.5, 0.3), (0.9, 0.05), (0.9, 0.97), (0.98, 0.6), (0.9999, 0.93), (1.0, 0.02), (1.0, 0.875), (1.0, 0.99)):
@@ -275,8 +276,10 @@ def test_masked_logits(vocab):
                     tok = _sample_only(sess, pkg.SpdSampleCfg(top_p, 1.0), lg, u)
                     assert lg[tok] > -1e8
                     n_dec += check_draw(sess, rec, top_p, 1.0, u, tok, rec.logp, 1e-5)
+                    size, mass, _ = sess.spd_get_nucleus_info()
+                    assert abs(mass - rec.nucleus_mass) <= 1e-5 + rec.p_edge * (rec.margin_nucleus <= 1e-5) and size <= vocab
                     if rec.margin_nucleus > 1e-5:
-                        assert sess.spd_get_nucleus_info()[0] == rec.nucleus_size
+                        assert size == rec.nucleus_size
                 assert n_dec >= 4
     finally:
         sess.close()
