@@ -484,7 +484,8 @@ __global__ __launch_bounds__(SNT) void nucleus_kernel(const NucleusArgs a) {
     prefix_sums(s, 0, h0, h1, sums);
 
     // 1. the nucleus: the first entry whose cumulative probability reaches top_p, and all before it
-    const unsigned long long x_p = (unsigned long long)((double)a.top_p * (double)FX_ONE);
+    // (at least one unit: a top_p below 2^-40 is the likeliest entry alone, not a mass that nothing has to reach)
+    const unsigned long long x_p = max(1ull, (unsigned long long)((double)a.top_p * (double)FX_ONE));
     ask<false, PIECES>(s, en, a.logits, 0, x_p, sums);
     const unsigned long long mass_fx = s.r_mass, key_T = s.r_key;
     const unsigned size = s.r_index + 1u;

@@ -135,7 +135,9 @@ def test_sampler_on_scripted_logits_ties_and_limits(tiny):
         # tiny top_p: greedy whatever the draw
         rng = np.random.default_rng(5)
         rl = (rng.normal(size=V) * 3).astype(np.float32)
-        assert all(_sample_only(sess, pkg.SpdSampleCfg(1e-6, 1.0), rl, u) == int(np.argmax(rl)) for u in (0.0, 0.5, 0.999))
+        for p in (1e-6, 2.0 ** -40, 1e-13, 1e-30):      # (down to masses below the sampler's unit, 2^-40)
+            assert all(_sample_only(sess, pkg.SpdSampleCfg(p, 1.0), rl, u) == int(np.argmax(rl)) for u in (0.0, 0.5, 0.999))
+            assert sess.spd_get_nucleus_info()[0] == 1
         # random logits, many draws, both temperatures: equal to the oracle wherever it is decisive
         for tau in (1.0, 0.4):
             n_dec = 0
