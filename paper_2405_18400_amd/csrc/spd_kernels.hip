@@ -385,6 +385,12 @@ __global__ __launch_bounds__(BLOCK) void topk_partial_kernel(const TopkArgs a) {
 // lane goes on by itself (no shuffles), an 8-lane mask is cut from half a ballot, the keys come from where they were hashed, and a group
 // takes only as many probes as its wave has.  Cycles for the counts of k = 5, 8, 10 and five orders: 13600, 14500, 16400 -> 3900, 7100, 11300.
 constexpr int PROBE_LANES = 8;
+// Between a result's zero, stored by one lane, and its count, stored by the lane of the same wave that hits: a wave's LDS stores stay in program
+// order, and this keeps the compiler from changing that order.
+__device__ __forceinline__ void cleared_before_probes() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
 // `home`: the key's home slot, NO_HOME: not wanted (its 64-bit multiplications are dear: one lane's work, not eight's).
 constexpr uint64_t NO_HOME = ~0ull;
 template <int N, typename F>
@@ -515,6 +521,7 @@ __global__ __launch_bounds__(ENT) void expand_prune_kernel(const TopkArgs slice,
             const bool known = make_key(tail, SPD_MIN_ORDER + e % SPD_N_ORDERS, NG_TOTAL, key[0]);
             const uint64_t home[1] = {known && e < n_total ? ngram_home(ngram_hash(key[0]), a.ng.capacity) : NO_HOME};
             if (e < n_total && u % PROBE_LANES == 0) s_tot[e] = 0ull;
+            cleared_before_probes();
             ngram_probes<1>(a.ng, key, home, [&](int, unsigned long long total) { s_tot[e] = total; });
         }
     }
@@ -630,6 +637,7 @@ __global__ __launch_bounds__(ENT) void expand_prune_kernel(const TopkArgs slice,
                         else s_tot[e - n_count] = count;
                     };
                     if (e < n_probe && tid % PROBE_LANES == 0) put(0ull);
+                    cleared_before_probes();
                     ngram_probes<1>(a.ng, key, home, [&](int, unsigned long long count) { put(count); });
                 }
             } else {
