@@ -87,21 +87,25 @@ def test_pass_teacher_forced(tiny, top_p, tau):
 
 
 def test_free_running_pass_and_graph_replay_agree(tiny):
+    """Replayed from a graph (the forward of one kernel per product; the persistent one is launched plainly whatever the switch says) and
+    plainly launched: the same tokens and log-probabilities."""
     shape, w, prefix = tiny
     pkg = P()
     us = np.random.default_rng(12).random(10).astype(np.float32)
-    out = []
-    for graph in (True, False):
-        sess = pkg.Session(shape, w, max_ctx=64, k_max=8)
-        try:
-            sess.spd_set_graph(graph)
-            sc = pkg.SpdSampleCfg(0.9, 1.0)
-            sess.spd_prefill(prefix)
-            out.append([sess.spd_nucleus_step(sc, float(u)) for u in us])
-            assert abs(sess.spd_get_nucleus_info()[2] - sum(lp for _, lp in out[-1])) < 1e-3
-        finally:
-            sess.close()
-    assert out[0] == out[1]
+    for fused in (False, True):
+        out = []
+        for graph in (True, False, True):
+            sess = pkg.Session(shape, w, max_ctx=64, k_max=8)
+            try:
+                sess.spd_set_fused(fused)
+                sess.spd_set_graph(graph)
+                sc = pkg.SpdSampleCfg(0.9, 1.0)
+                sess.spd_prefill(prefix)
+                out.append([sess.spd_nucleus_step(sc, float(u)) for u in us])
+                assert abs(sess.spd_get_nucleus_info()[2] - sum(lp for _, lp in out[-1])) < 1e-3
+            finally:
+                sess.close()
+        assert out[0] == out[1] == out[2]
 
 
 def _sample_only(sess, sc, logits, u, first=True):

@@ -622,10 +622,10 @@ def test_fp16_cache_head_width_32_plain_prefix_attention():
     assert max(s["logit_err"] for s in stats if "logit_err" in s) < FP16_CACHE_LOGIT_ERR
 
 
-def test_fp16_cache_graph_replay_is_bit_exact_across_the_switch_of_reading_widths():
-    """A free-running generation whose context passes 160 positions (where the persistent kernel
-    goes from 8-byte to 16-byte pieces of the fp16 cache): graph replay, plain launches and a
-    second replayed generation give the same bits; the per-operator forward agrees to rounding."""
+def test_fp16_cache_generation_repeats_its_bits_across_the_switch_of_reading_widths():
+    """A free-running generation of the persistent forward whose context passes 160 positions (where it goes from 8-byte to
+    16-byte pieces of the fp16 cache) gives the same bits each time, whatever the graph switch says; the per-operator
+    forward agrees to rounding."""
     pkg = P()
     shape = synth.ModelShape("small-bf16", 3, 512, 8, 2, 1408, 2048, "bf16")
     w = synth.make_weights(shape, seed=5)
@@ -633,15 +633,14 @@ def test_fp16_cache_graph_replay_is_bit_exact_across_the_switch_of_reading_width
     dc = pkg.SpdDecodeCfg(3, 0.0, 1.0, 0.1)
     sess = session(shape, w, max_ctx=200, kv_dtype="fp16")
     try:
+        select_path(sess, "fused")
         drafts, scores = sess.spd_generate(prefix, dc, 24)
         logits = sess.spd_read_logits()
-        sess.spd_set_graph(False)
-        drafts2, scores2 = sess.spd_generate(prefix, dc, 24)
-        assert np.array_equal(drafts, drafts2) and np.array_equal(scores, scores2)
-        assert np.array_equal(logits, sess.spd_read_logits())
-        sess.spd_set_graph(True)
-        drafts3, scores3 = sess.spd_generate(prefix, dc, 24)
-        assert np.array_equal(drafts, drafts3) and np.array_equal(scores, scores3)
+        for graph in (False, True):
+            sess.spd_set_graph(graph)
+            drafts2, scores2 = sess.spd_generate(prefix, dc, 24)
+            assert np.array_equal(drafts, drafts2) and np.array_equal(scores, scores2)
+            assert np.array_equal(logits, sess.spd_read_logits())
         # the same prefix and the same first timesteps through one kernel per operator
         sess.spd_prefill(prefix)
         sess.spd_step(dc)
@@ -653,6 +652,31 @@ def test_fp16_cache_graph_replay_is_bit_exact_across_the_switch_of_reading_width
         sess.spd_step(dc)
         per_op = sess.spd_read_logits()
         np.testing.assert_allclose(fused, per_op, rtol=0, atol=2e-5 * np.abs(per_op).max())
+    finally:
+        sess.close()
+
+
+@pytest.mark.parametrize("n_prefix", [150, 500])
+def test_fp16_cache_graph_replay_of_the_per_operator_forward(n_prefix):
+    """bf16 weights, an fp16 cache, four query heads per cached head of 64: one captured timestep is replayed while the context grows, from
+    500 tokens on past the 512 positions that are one attention chunk.  Each generation has the bits of plain launches."""
+    pkg = P()
+    shape = synth.ModelShape("small-bf16", 3, 512, 8, 2, 1408, 2048, "bf16")
+    w = synth.make_weights(shape, seed=5)
+    prefix = synth.make_prefix_zipf(shape.vocab, n_prefix, seed=9)
+    dc, sc = pkg.SpdDecodeCfg(3, 0.0, 1.0, 0.1), pkg.SpdSampleCfg(0.9, 1.0)
+    sess = session(shape, w, max_ctx=n_prefix + 30, kv_dtype="fp16")
+    try:
+        select_path(sess, "per_operator")
+        runs = []
+        for graph in (False, True, True, False, True):
+            sess.spd_set_graph(graph)
+            drafts, scores = sess.spd_generate(prefix, dc, 24)
+            logits = sess.spd_read_logits()
+            sess.spd_prefill(prefix)
+            sampled = [sess.spd_nucleus_step(sc, float(u)) for u in np.linspace(0.05, 0.95, 20)]
+            runs.append((drafts.tolist(), scores.tolist(), logits.tolist(), sampled, sess.spd_read_logits().tolist()))
+        assert all(r == runs[0] for r in runs)
     finally:
         sess.close()
 
@@ -833,14 +857,16 @@ def test_generate_free_running_matches_until_first_undecided_step(tiny, dense):
             # GPU kept later descends from that set
             upto = {tuple(d) for d in recs[decided].state_in.drafts}
             assert {tuple(d[:decided]) for d in drafts.tolist()} <= upto
-        # graph replay and plain launches agree bit for bit
-        sess.spd_set_graph(False)
-        drafts2, scores2 = sess.spd_generate(prefix, dc, 10)
-        assert np.array_equal(drafts, drafts2) and np.array_equal(scores, scores2)
-        # and so does a second replayed generation (determinism, counters reset, state reset)
-        sess.spd_set_graph(True)
-        drafts3, scores3 = sess.spd_generate(prefix, dc, 10)
-        assert np.array_equal(drafts, drafts3) and np.array_equal(scores, scores3)
+        # and so does a second generation (determinism, counters reset, state reset), plainly launched and, with one kernel
+        # per product, replayed from a graph
+        for fused in (True, False):
+            sess.spd_set_fused(fused)
+            runs = [(drafts.tolist(), scores.tolist())] if fused else []
+            for graph in (False, True, True):
+                sess.spd_set_graph(graph)
+                again, scores2 = sess.spd_generate(prefix, dc, 10)
+                runs.append((again.tolist(), scores2.tolist()))
+            assert all(r == runs[0] for r in runs)
     finally:
         sess.close()
 
@@ -1057,7 +1083,7 @@ def test_error_paths(tiny):
 @pytest.mark.parametrize("kv_dtype", ["fp16", "fp32"])
 def test_full_size_7b_shape_teacher_forced(kv_dtype):
     """The headline workload at its real size and in the launch configuration the benchmark times
-    (fused forward, graph replay, fp16 cache; and with the fp32 cache): Llama-2-7B shape, bf16,
+    (persistent forward, fp16 cache; and with the fp32 cache): Llama-2-7B shape, bf16,
     64-token Zipf prefix, k = 3, alpha = 0.54, synthetic n = 2..6 tables.  The oracle runs the
     full model on the host (a few seconds per step), so three timesteps are compared,
     teacher-forced."""
