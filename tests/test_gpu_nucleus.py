@@ -178,10 +178,11 @@ def test_draws_on_a_grid_follow_the_renormalised_distribution(tiny):
         sess.close()
 
 
-def test_large_vocabulary_uses_the_uncached_path():
-    """More than 32768 entries: the sampler recomputes probabilities instead of holding them."""
+@pytest.mark.parametrize("vocab", [40000, 70000])
+def test_draws_from_large_vocabularies(vocab):
+    """More than 32768 entries: eight pieces of bucket numbers per thread, and beyond 65536 all of them read again for each question."""
     pkg = P()
-    shape = synth.ModelShape("bigvocab", 1, 64, 2, 2, 128, 40000, "fp32")
+    shape = synth.ModelShape("bigvocab", 1, 64, 2, 2, 128, vocab, "fp32")
     w = synth.make_weights(shape, seed=2)
     sess = pkg.Session(shape, w, max_ctx=32, k_max=8)
     try:
