@@ -368,16 +368,20 @@ const char *check_dc(const spd_ctx *c, const spd_decode_cfg *dc) {
 }
 
 constexpr int DENSE_PREFILL_MIN = 8;   // shorter prefixes go token by token
-// The same for fp32 models: three, whose chunk takes 0.37 .. 0.75 times what they take one by one (up to six layers).  Two tokens, 80 models, as a chunk against one by
-// one: 0.54 .. 0.98 times up to three layers (1.01 at worst), and beyond where no wave's share of a product's k is long against the tiles
-// there are.  The persistent forward is the faster way from 1280 wide with a feed-forward past 4096 (four layers 0.95 .. 1.05, 12 and more
-// 1.07 .. 1.18: 24 layers of 2048 wide, 2170 us as a chunk, 1836 one by one); a kernel per product, the way of wider rows, only
-// with a feed-forward beyond eight times the width (1.02 .. 1.27).
+// The same for fp32 models: three, whose chunk takes 0.42 .. 0.80 times what they take one by one (up to 24 layers).  Two tokens, some 400 models
+// of 256 .. 2304 wide and 1 .. 24 layers, as a chunk against one by one:
+//   persistent forward, from 1152 wide with a feed-forward past 4096: 0.69 .. 0.99 times up to three layers; 0.95 .. 1.05 with four, 1.07 ..
+//     1.18 with 12 and more (24 layers of 2048 wide: 2170 us as a chunk, 1836 one by one);
+//   from 1152 wide, feed-forward up to 2048: 0.91 .. 1.04 up to four layers, 1.04 .. 1.12 with eight, 1.10 .. 1.18 with 24;
+//   640 .. 1024 wide, feed-forward up to 3072 (four waves to a row): 0.83 .. 1.00 up to four layers (1.07 with heads of 128, 1.09 with six),
+//     0.96 .. 1.16 with eight, 0.98 .. 1.19 with 12, 1.05 .. 1.23 with 24;
+//   other widths of it 0.61 .. 1.06; a kernel per product 0.62 .. 1.06, beyond eight times the width 1.02 .. 1.27 from four layers on.
 int chunk32_min(const spd_ctx *c) {
     const spd_model_cfg &m = c->cfg;
-    const bool persistent = c->use_fused && c->fused_blocks > 0;
-    const bool slow = persistent ? m.d_model > 1024 && m.d_ffn > 4096 : m.d_model <= 2048 && m.d_ffn > 8 * m.d_model;
-    return m.n_layers > 3 && slow ? 3 : 2;
+    const bool persistent = c->use_fused && c->fused_blocks > 0, wide = m.d_model > 1024;
+    const bool four = persistent ? wide && m.d_ffn > 4096 : m.d_model <= 2048 && m.d_ffn > 8 * m.d_model;        // slow from four layers on
+    const bool eight = persistent && (wide ? m.d_ffn <= 2048 : m.d_model >= 640 && m.d_ffn <= 3072);              // from eight
+    return (m.n_layers > 3 && four) || (m.n_layers > 7 && eight) ? 3 : 2;
 }
 
 // A graph is for the forward of one kernel per product (a dozen launches and more).  With the persistent forward a timestep is two or

@@ -391,7 +391,9 @@ def test_fp32_prefix_pass_matches_the_token_by_token_pass(shape, m):
 
 @pytest.mark.parametrize("layers,d,heads,ffn,fused,chunk", [
     (4, 1152, 9, 4112, True, False), (3, 1152, 9, 4112, True, True), (4, 1024, 8, 4112, True, True), (4, 1152, 9, 4096, True, True), (4, 1152, 9, 4112, False, True),
-    (4, 128, 2, 6160, False, False), (3, 128, 2, 6160, False, True), (4, 256, 4, 2048, False, True)])
+    (4, 128, 2, 6160, False, False), (3, 128, 2, 6160, False, True), (4, 256, 4, 2048, False, True),
+    (8, 640, 10, 3072, True, False), (7, 640, 10, 3072, True, True), (8, 640, 10, 3088, True, True), (8, 576, 9, 3072, True, True), (8, 1024, 8, 256, True, False),
+    (8, 1152, 9, 2048, True, False), (7, 1152, 9, 2048, True, True), (8, 1152, 9, 2064, True, True), (8, 640, 10, 1024, False, True)])
 def test_fp32_prefix_of_two_tokens_goes_the_faster_way(layers, d, heads, ffn, fused, chunk):
     """Either side of every line of the rule, with the persistent forward and with a kernel per product (feed-forwards past 6144 have no
     other): two tokens are one chunk, which makes no launch of the forward, or two forwards; three are always a chunk."""
