@@ -744,8 +744,9 @@ __global__ __launch_bounds__(ENT) void expand_prune_kernel(const TopkArgs slice,
 
 __global__ void advance_kernel(DevState *st) { st->pos += 1; }
 
-// The drafts and their scores come as arguments, 384 bytes: two copies to the device, a wait for them and one for a kernel of one
-// thread took the call 19.7 us, this 6.3.  (Results the other way: a kernel that stores them into pinned memory takes as long as the copy.)
+// The drafts and their scores come as arguments, 388 bytes: with two copies to the device, a wait for them and one for a kernel of one
+// thread the whole call took 17.4 us, with this 12.5 (through the Python entry 20.4 and 13.4).  (Results the other way: a kernel that
+// stores them into pinned memory takes as long as the copy.)
 __global__ __launch_bounds__(WAVE) void set_drafts_kernel(DevState *st, const DraftArgs a) {
     const int i = threadIdx.x;
     for (int e = i; e < SPD_K_MAX * SPD_TAIL; e += WAVE) (&st->tails[0][0])[e] = (&a.tails[0][0])[e];

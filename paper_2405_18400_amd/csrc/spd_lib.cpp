@@ -386,10 +386,10 @@ int chunk32_min(const spd_ctx *c) {
 
 // A graph is for the forward of one kernel per product (a dozen launches and more).  With the persistent forward a timestep is two or
 // three launches, a prefix token two, and the graph's own start costs more than they do.  us per timestep, graph -> plain launches, enqueued
-// one behind the other | with results fetched: tiny fp32 model 64.1 -> 59.0 | 78.1 -> 72.2, four layers of the 1B widths 183.9 -> 179.2 |
-// 198.4 -> 191.7, 7B 2234 -> 2224 | 2246 -> 2238; the host's share 15 -> 8, and the first timestep captures nothing.  One kernel per
-// product: 54.4 -> 50.4, 168.5 -> 165.2, 2730 -> 2725, but the host's share 15 -> 36, 28 -> 59, 72 -> 478 (16 layers of the 1B widths,
-// 551 -> 556 in all): the graph stays.
+// one behind the other | with results fetched: tiny fp32 model 58.2 -> 53.0 | 73.9 -> 66.0, four layers of the 1B widths 151 -> 147 |
+// 168 -> 160, 7B 2235 -> 2227 | 2249 -> 2241; the host's share 20 -> 9, and the first timestep captures nothing.  One kernel per
+// product: 54.3 -> 51.4 | 68.6 -> 94.5, 167 -> 166 | 183 -> 192, 2727 -> 2725 | 2749 -> 2746, the host's share 23 -> 40, 33 -> 68, 69 -> 465 (16 layers of the
+// 1B widths 557 -> 559 | 575 -> 598): the graph stays.
 bool graphs_usable(const spd_ctx *c) { return c->use_graph && !c->timing && c->stream != nullptr && !(c->use_fused && c->fused_blocks > 0); }
 
 }  // namespace

@@ -140,8 +140,8 @@ __device__ __forceinline__ int crossing(Stage &s, int lv, unsigned long long x) 
 // would write back and invalidate whole caches -- tens of microseconds).  Stage B looks for the entries of ONE bucket at a time and reads
 // the logits of those.  A thread keeps PIECES pieces of eight numbers in registers; 0: the vocabulary has more, every walk reads them
 // again.  Beyond 32768 entries the last block used to build the histogram itself from eight bytes per entry, which every walk read again.
-// The kernel by events, top_p 0.9, 40000 / 50258 / 65536 / 100000 / 131072 / 262144 entries: 28.6 / 34.0 / 38.1 / 54.9 / 65.1 / 176 ->
-// 15.3 / 15.9 / 17.4 / 23.0 / 25.8 / 50 us; up to 32768 as before.
+// The kernel by events, top_p 0.9, 32000 / 40000 / 50258 / 65536 / 100000 / 131072 / 262144 entries: 14.4 / 28.7 / 33.5 / 38.2 / 54.9 / 64.6 / 175 ->
+// 13.7 / 15.2 / 16.3 / 17.6 / 22.9 / 26.0 / 47.6 us.
 constexpr int REREAD = 8;          // pieces per trip of a walk that reads the numbers again
 template <int PIECES>
 struct Entries {
@@ -526,8 +526,9 @@ __global__ __launch_bounds__(SNT) void nucleus_kernel(const NucleusArgs a) {
 
 namespace spdk {
 
-// As many pieces of bucket numbers per thread as hold the vocabulary, up to eight: 40000 and 65536 entries, kernel by events: eight held 14.2 and
-// 15.7 us, read again 16.8 and 18.5; 65538 and 131072 entries, sixteen held 18.7 and 22.2 (and four registers spilled), read again 17.7 and 21.8.
+// As many pieces of bucket numbers per thread as hold the vocabulary, up to eight.  The kernel by events, 40000 and 65536 entries, eight held
+// 14.2 and 15.8 us at top_p 0.5, 15.2 and 17.6 at 0.9; read again 14.4 and 15.9, 15.4 and 17.7.  65538 and 131072 entries, top_p 0.5, sixteen held 18.7
+// and 22.2 (and four registers spilled), read again 17.7 and 21.6.
 hipError_t nucleus(hipStream_t s, const NucleusArgs &a) {
     const dim3 grid(a.n_part), block(SNT);
     if (a.vocab <= 4 * PIECE) hipLaunchKernelGGL(nucleus_kernel<4>, grid, block, 0, s, a);
