@@ -592,9 +592,10 @@ __global__ __launch_bounds__(ENT) void expand_prune_kernel(const TopkArgs slice,
         const int rank = rank_among<PARTS>(entry, MERGE_WAVES * k), t = tid / PARTS;
         if (t < MERGE_WAVES * k && rank < k && tid % PARTS == 0) {
             const float logp = __fdiv_rn(sv[t], a.tau) - s_lse;
-            s_top[rank] = si[t];
+            const int id = si[t] == INT_MAX ? 0 : si[t];     // (fewer than k logits are numbers: the next forward still looks up a token there is)
+            s_top[rank] = id;
             s_logp[rank] = logp;
-            st->top_ids[rank] = si[t];
+            st->top_ids[rank] = id;
             st->top_logp[rank] = logp;
         }
     }

@@ -898,6 +898,39 @@ def test_graph_replay_of_the_per_operator_forward_equals_plain_launches(tiny):
         sess.close()
 
 
+@pytest.mark.parametrize("fused", [True, False])
+def test_logits_that_are_no_numbers_give_tokens_that_exist(tiny, fused):
+    """Fewer numbers among the logits than drafts are kept: the numbers first, in their order, and for the rest ids of the vocabulary
+    (they were 2^31 - 1, which the next forward looked up in the embeddings); scores are NaN, and stay so through the timesteps."""
+    shape, w, _, prefix = tiny
+    pkg = P()
+    dc = pkg.SpdDecodeCfg(4, 0.0, 1.0, 0.1)
+    sess = session(shape, w)
+    try:
+        sess.spd_set_fused(fused)
+        for numbers in ([], [5], [9, 3, shape.vocab - 1]):
+            z = torch.full((shape.vocab,), float("nan"))
+            z[numbers] = torch.arange(len(numbers), 0, -1, dtype=torch.float32)
+            z = z.cuda()
+            sess.spd_prefill(prefix)
+            for t in range(2):
+                sess.spd_expand_prune(dc, z, t == 0)
+                ids = sess.spd_get_step_info(4)[0]
+                tails, scores, _ = sess.spd_get_state()
+                assert ids[:len(numbers)].tolist() == numbers and np.all((ids >= 0) & (ids < shape.vocab))
+                assert np.all((tails[:, -1] >= 0) & (tails[:, -1] < shape.vocab)) and np.isnan(scores).all()
+            for _ in range(2):
+                tok, _, sc = sess.spd_step(dc)
+                assert np.all((tok >= 0) & (tok < shape.vocab)) and np.isnan(sc).all()
+            sess.spd_prefill(prefix)
+            sess.spd_nucleus_sample(pkg.SpdSampleCfg(0.9, 1.0), 0.5, z, True)
+            assert 0 <= sess.spd_get_state()[0][0, -1] < shape.vocab
+        sess.spd_prefill(prefix)                   # and a prefix pass starts from numbers again
+        assert np.isfinite(sess.spd_step(dc)[2]).all()
+    finally:
+        sess.close()
+
+
 def test_k1_is_greedy_on_the_gpu(tiny):
     shape, w, _, prefix = tiny
     pkg = P()
