@@ -583,7 +583,8 @@ __global__ __launch_bounds__(ENT) void expand_prune_kernel(const TopkArgs slice,
         else select(std::integral_constant<int, 1>());
         if (lane < k) {
             const int at = (tid / WAVE) * k + lane;
-            sv[at] = kv; si[at] = ki; entry[at] = ki == INT_MAX ? 0ull : entry_key(kv, ki);
+            sv[at] = kv; entry[at] = ki == INT_MAX ? 0ull : entry_key(kv, ki);
+            si[at] = ki == INT_MAX ? 0 : ki;     // (fewer than k logits are numbers: the next forward still looks up a token there is)
         }
     }
     __syncthreads();
@@ -592,10 +593,9 @@ __global__ __launch_bounds__(ENT) void expand_prune_kernel(const TopkArgs slice,
         const int rank = rank_among<PARTS>(entry, MERGE_WAVES * k), t = tid / PARTS;
         if (t < MERGE_WAVES * k && rank < k && tid % PARTS == 0) {
             const float logp = __fdiv_rn(sv[t], a.tau) - s_lse;
-            const int id = si[t] == INT_MAX ? 0 : si[t];     // (fewer than k logits are numbers: the next forward still looks up a token there is)
-            s_top[rank] = id;
+            s_top[rank] = si[t];
             s_logp[rank] = logp;
-            st->top_ids[rank] = id;
+            st->top_ids[rank] = si[t];
             st->top_logp[rank] = logp;
         }
     }
